@@ -59,7 +59,7 @@ typedef enum { PAEP_ACT_NONE = 0, PAEP_ACT_SILU = 1, PAEP_ACT_GELU = 2 } paep_ac
  * PAEP_ERR_UNSUPPORTED when the shape does not fit it. */
 typedef enum {
     PAEP_PATH_AUTO = 0,
-    PAEP_PATH_SIMPLE = 1,     /* any dtype and shape; plain vector arithmetic */
+    PAEP_PATH_SIMPLE = 1,     /* any dtype and shape; fp32: fp32 matrix instructions, bf16: plain vector arithmetic */
     PAEP_PATH_DECODE = 2,     /* bf16, T <= 64: weight-streaming, r split over workgroups */
     PAEP_PATH_PREFILL = 3     /* bf16, large T: fused back-to-back matrix-core tiles */
 } paep_path;

@@ -76,7 +76,8 @@ int resolve(const paep_predict_desc* d, const paep::PredictArgs& a)
     // an empty call runs nothing; report the family the shape would use at T = 1
     paep::PredictArgs b = a;
     if (b.T == 0) b.T = 1;
-    const bool dec = paep::decode_supported(b), pre = paep::prefill_supported(b), sim = paep::simple_supported(b);
+    const bool dec = paep::decode_supported(b), pre = paep::prefill_supported(b),
+               sim = paep::f32_supported(b) || paep::simple_supported(b);
     switch (d->path) {
     case PAEP_PATH_SIMPLE: return sim ? PAEP_PATH_SIMPLE : 0;
     case PAEP_PATH_DECODE: return dec ? PAEP_PATH_DECODE : 0;
@@ -117,14 +118,22 @@ int paep_predict_resolve_path(const paep_predict_desc* desc)
     return p ? p : -1;
 }
 
+// device workspace of the family `path` for this call
+static size_t path_workspace_bytes(int path, const paep::PredictArgs& a)
+{
+    switch (path) {
+    case PAEP_PATH_DECODE: return paep::decode_workspace_bytes(a);
+    case PAEP_PATH_PREFILL: return paep::prefill_workspace_bytes(a);
+    case PAEP_PATH_SIMPLE: return a.dtype == PAEP_F32 ? paep::f32_workspace_bytes(a) : 0;
+    default: return 0;
+    }
+}
+
 size_t paep_predict_workspace_bytes(const paep_predict_desc* desc)
 {
     if (check_desc(desc) != PAEP_OK) return 0;
     const paep::PredictArgs a = to_args(desc);
-    const int path = resolve(desc, a);
-    if (path == PAEP_PATH_DECODE) return paep::decode_workspace_bytes(a);
-    if (path == PAEP_PATH_PREFILL) return paep::prefill_workspace_bytes(a);
-    return 0;
+    return path_workspace_bytes(resolve(desc, a), a);
 }
 
 static paep_status predict_common(const paep_predict_desc* desc,
@@ -143,8 +152,7 @@ static paep_status predict_common(const paep_predict_desc* desc,
     a.margin = margin_dev;                                   // the families differ in how many candidates they can keep
     const int path = resolve(desc, a);
     if (!path) return PAEP_ERR_UNSUPPORTED;
-    const size_t need = (path == PAEP_PATH_DECODE) ? paep::decode_workspace_bytes(a)
-                      : (path == PAEP_PATH_PREFILL) ? paep::prefill_workspace_bytes(a) : 0;
+    const size_t need = path_workspace_bytes(path, a);
     if (need > 0 && (!workspace_dev || !aligned16(workspace_dev) || workspace_bytes < need)) return PAEP_ERR_WORKSPACE;
     if (desc->T == 0) return PAEP_OK;
 
@@ -156,7 +164,7 @@ static paep_status predict_common(const paep_predict_desc* desc,
     switch (path) {
     case PAEP_PATH_DECODE: err = paep::launch_predict_decode(a); break;
     case PAEP_PATH_PREFILL: err = paep::launch_predict_prefill(a); break;
-    default: err = paep::launch_predict_simple(a); break;
+    default: err = a.dtype == PAEP_F32 ? paep::launch_predict_f32(a) : paep::launch_predict_simple(a); break;
     }
     return err == hipSuccess ? PAEP_OK : PAEP_ERR_HIP;
 }

@@ -46,7 +46,17 @@ inline hipError_t ensure_lds_limit(LdsLimit& st, const void* kern, size_t lds)
     return err;
 }
 
-// plain vector-ALU kernel, any dtype / shape
+// adds `S` slices of partial scores, laid out [tile][slice][BM][E] from tile `tile0` on, and finishes their rows
+// (softmax, top-k); decode, fp32 and prefill calls that cut r over workgroups end with it
+hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, int tiles, int BM, int tile0,
+                           int tiles_per_layer);
+
+// fp32 storage, any shape: fp32 matrix instructions
+bool f32_supported(const PredictArgs& a);
+size_t f32_workspace_bytes(const PredictArgs& a);
+hipError_t launch_predict_f32(const PredictArgs& a);
+
+// bf16 storage, shapes that the matrix-core kernels do not take: plain vector arithmetic
 bool simple_supported(const PredictArgs& a);
 hipError_t launch_predict_simple(const PredictArgs& a);
 

@@ -24,9 +24,8 @@
 // 64 contiguous bytes, and a lane permutation puts the fragment into the
 // A-operand layout.
 //
-// Kernel 2 (finalize): one wave per token adds the slices in ascending order
-// (fixed order, so the result is reproducible; up to 32 loads in flight), adds b2, and runs softmax and
-// top-k (eq. 1 and eq. 4) in registers with wave shuffles.
+// Kernel 2 (finalize.hip): one wave per token adds the slices in ascending order
+// and runs softmax and top-k.
 #include <type_traits>
 
 #include "paep_device.h"
@@ -467,55 +466,7 @@ __global__ __launch_bounds__(RW_WAVES * 64, 4) void decode_rows_kernel(
     }
 }
 
-// One wave per token row: lane l owns experts l, l+64, ...  The slice partials
-// are summed in ascending slice order, 32 loads in flight at a time.
-static constexpr int FIN_NV = 8;                          // experts per lane at most: E <= 512
-
-template <int NV>                                         // experts per lane: E <= 64 * NV
-__global__ __launch_bounds__(DEC_THREADS) void decode_finalize_kernel(
-    int T, int E, int k, int S, int rows_total, const float* __restrict__ partial,
-    const uint16_t* __restrict__ b2, int32_t* __restrict__ idx, float* __restrict__ probs,
-    float* __restrict__ logits, int32_t* __restrict__ counts, int prob_mode, float* __restrict__ margin)
-{
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * (DEC_THREADS / 64) + (threadIdx.x >> 6);
-    if (row >= rows_total) return;
-    const int layer = row / T, t = row - layer * T;
-    const long long sstride = (long long)T * E;
-    const float* src = partial + ((long long)layer * S * T + t) * E;
-    // all of a row's experts at once, CH slices per round: NV * CH loads in flight, added in ascending slice order
-    constexpr int CH = (NV >= 8) ? 4 : 32 / NV;
-    float z[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) z[v] = 0.0f;
-    for (int s0 = 0; s0 < S; s0 += CH) {
-        float p[NV][CH];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int e = lane + 64 * v;
-#pragma unroll
-            for (int u = 0; u < CH; ++u) p[v][u] = (e < E && s0 + u < S) ? src[(long long)(s0 + u) * sstride + e] : 0.0f;
-        }
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-            for (int u = 0; u < CH; ++u)
-                if (s0 + u < S) z[v] += p[v][u];          // uniform; a skipped slice adds nothing, not even +0
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int e = lane + 64 * v;
-        if (e < E) {
-            if (b2) z[v] += bf16_bits_to_f32(b2[(long long)layer * E + e]);
-            if (logits) logits[(long long)row * E + e] = z[v];
-        }
-    }
-    const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr, counts ? counts + (long long)layer * E : nullptr};
-    // one expert per lane: rank counting; more: k rounds of a wave-wide maximum (measured at 128 experts, k = 8:
-    // 6.8 us against 9.6 us for rank counting at 48 rows, 11.6 against 17.7 at 3072 rows)
-    if constexpr (NV == 1) wave_softmax_topk_rank<NV>(z, E, k, lane, idx + (long long)row * k, probs + (long long)row * k, eo);
-    else                   wave_softmax_topk<NV>(z, E, k, lane, idx + (long long)row * k, probs + (long long)row * k, eo);
-}
+static constexpr int FIN_NV = 8;                          // experts per lane of the finalize kernel at most: E <= 512
 
 bool decode_supported(const PredictArgs& a)
 {
@@ -574,20 +525,9 @@ hipError_t launch_predict_decode(const PredictArgs& a)
     }
 #undef PAEP_LAUNCH_DEC
     }
-    hipError_t err = hipGetLastError();
+    const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int rows = a.L * a.T;
-    const int rows_per_wg = DEC_THREADS / 64;
-#define PAEP_LAUNCH_FIN(NVV)                                                                                \
-    hipLaunchKernelGGL(decode_finalize_kernel<NVV>, dim3((rows + rows_per_wg - 1) / rows_per_wg), dim3(DEC_THREADS), \
-                       0, a.stream, a.T, a.E, a.k, S, rows, partial, (const uint16_t*)a.b2, a.idx, a.probs,          \
-                       a.logits, a.counts, a.prob_mode, a.margin)
-    if (a.E <= 64)       PAEP_LAUNCH_FIN(1);
-    else if (a.E <= 128) PAEP_LAUNCH_FIN(2);
-    else if (a.E <= 256) PAEP_LAUNCH_FIN(4);
-    else                 PAEP_LAUNCH_FIN(8);
-#undef PAEP_LAUNCH_FIN
-    return hipGetLastError();
+    return launch_finalize(a, partial, S, a.L, a.T, 0, 1);
 }
 
 }  // namespace paep

@@ -1,0 +1,316 @@
+// Predictor for fp32 storage, any shape: both linear layers (paper section 4.3,
+// eq. 3) on the fp32 matrix instruction v_mfma_f32_32x32x2_f32, whose products
+// and sums are fp32 like the vector unit's fma.
+//
+// What bounds it: that instruction, 256 flops per clock and CU (157 TFLOP/s on
+// the chip).  It is 16 times slower than the bf16 one while the operands are
+// only twice as wide, so small tiles are enough to keep it fed -- a 64 x 64
+// tile asks LDS for 16 bytes per clock of the 128 it can deliver -- and the
+// tiles are kept small so that a few hundred tokens of one layer already
+// spread over every CU.
+//
+// A workgroup owns BM tokens of one layer and a range of chunks of BN
+// hidden units.  Per chunk it forms h^T[BN, BM] = W1[chunk, :] . x^T over stages of
+// 32 columns, which travel global -> LDS by direct copies through a ring of NS
+// stages (row of 128 bytes = 8 chunks of 16 bytes, chunk c in slot c ^ (row % 8),
+// chosen on the global side; rows past T, r and columns past d lie outside the
+// buffer resource and arrive as zeros).  A lane takes its fragment as one
+// ds_read_b128, four k-steps of the instruction: the order in which k is walked is
+// free as long as both operands agree.  Then h gets bias and activation, goes to
+// LDS as [token][unit], and is multiplied by the chunk's columns of W2 into scores that stay
+// in accumulators over the chunks.
+//   BM = BN = 64   eight waves, two to each 32 x 32 block of h
+//   BM = BN = 32   (T <= 32) four waves, all on one block: four times as many workgroups to stream the weights
+// Waves that share a block split the columns of each stage and their sums meet in LDS in
+// wave order: a second wave on every SIMD covers the other's barriers and LDS reads even where a
+// CU has one workgroup (512 tokens of one 2048-wide layer: 48 us with one wave to a block, 46 with two).
+// Sums over d are carried in stretches of 256 columns that are added up, so their rounding
+// error stays below that of one long chain of additions.
+// Few token tiles: r is cut over several workgroups per tile, their scores meet in the
+// workspace and finalize_kernel adds them; otherwise softmax and top-k follow here.
+// Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for the vector kernel
+// that served this before, 52 us here (46 in this kernel: 96 TFLOP/s).
+#include "paep_device.h"
+#include "paep_internal.h"
+
+namespace paep {
+
+static constexpr int F32_BK = 32;                          // columns of d per stage
+static constexpr int F32_FOLD = 8;                         // stages per stretch of the sum over d
+static constexpr size_t F32_WORKSPACE_MAX = 16u << 20;     // what predict_static can offer
+
+typedef void __attribute__((address_space(3)))* f32_lds_ptr_t;
+#define PAEP_F32_VMCNT(n) ((((n) & 0xF) | (((n) >> 4) << 14)) | 0x0F70)
+
+// EBW: 32 x 32 score blocks per wave
+template <int B_, int NS, int EBW>
+__global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predict_f32_kernel(
+    int T, int d, int r, int E, int k, int act, int tiles_per_layer, int groups, int nchunks,
+    long long xs, long long w1s, long long w2s, const float* __restrict__ x, const float* __restrict__ W1,
+    const float* __restrict__ W2, const float* __restrict__ b1, const float* __restrict__ b2,
+    int32_t* __restrict__ idx, float* __restrict__ probs, float* __restrict__ logits, int32_t* __restrict__ counts,
+    int prob_mode, float* __restrict__ margin, float* __restrict__ partial)
+{
+    constexpr int BM = B_, BN = B_;
+    constexpr int WAVES = B_ == 64 ? 8 : 4, THREADS = 64 * WAVES;
+    constexpr int TBN = BM / 32, NBLK = TBN * TBN;         // 32-token blocks, blocks of h
+    constexpr int KPARTS = WAVES / NBLK;                   // waves that share a block
+    constexpr int NP = (BM + BN) / 8 / WAVES;              // copy instructions per wave and stage, 8 rows each
+    constexpr int STAGE = (BM + BN) * F32_BK * 4;          // bytes
+    constexpr int HP = BN + 4;                             // pitch of h: 16 lanes of a fragment read hit all 64 banks
+    extern __shared__ __attribute__((aligned(16))) unsigned char fsmem[];
+    float* red = (float*)fsmem;                            // the waves' sums, 4 KB each; reuses the ring
+    float* ht = (float*)(fsmem + WAVES * 4096);            // h of the chunk; reuses the ring
+    static_assert(WAVES * 4096 + BM * HP * 4 <= NS * STAGE, "sums and h fit in the ring");
+    float* zs = (float*)fsmem;                             // 32 rows of scores; reuses everything
+
+    const int grp = blockIdx.x % groups, tile_id = blockIdx.x / groups;
+    const int layer = tile_id / tiles_per_layer, t0 = (tile_id - layer * tiles_per_layer) * BM;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const float* xl = x + layer * xs + (long long)t0 * d;
+    const float* W1l = W1 + layer * w1s;
+    const float* W2l = W2 + layer * w2s;
+
+    // copies: instruction wave * NP + j moves rows 8 * that .. + 7 of the stage; the first half of the waves moves
+    // rows of W1, the second half token rows
+    const bool moves_w = wave < WAVES / 2;
+    const int xrows = T - t0 < BM ? T - t0 : BM;
+    uint32_t src_off[NP];
+    int lcol[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int row = ((wave % (WAVES / 2)) * NP + j) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ (row & 7);
+        src_off[j] = (uint32_t)(row * d + c * 4) * 4u;
+        lcol[j] = c * 4;
+    }
+    const int NKT = (d + F32_BK - 1) / F32_BK;
+
+    f32x16 zacc[EBW];
+#pragma unroll
+    for (int j = 0; j < EBW; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zacc[j][i] = 0.0f;
+
+    const int n_begin = (int)((long long)grp * nchunks / groups), n_end = (int)((long long)(grp + 1) * nchunks / groups);
+#pragma unroll 1
+    for (int n = n_begin; n < n_end; ++n) {
+        const int u0 = n * BN;
+        const int wrows = r - u0 < BN ? r - u0 : BN;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(moves_w ? W1l + (long long)u0 * d : xl), 0, (moves_w ? wrows : xrows) * d * 4, 0x00020000);
+        auto issue = [&](int kt, int slot) {
+            if (kt >= NKT) kt = NKT - 1;                   // past the end: the last stage again, into a slot nobody reads
+            const int left = d - kt * F32_BK;              // columns past d: an offset outside the resource
+#pragma unroll
+            for (int j = 0; j < NP; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rsrc, (f32_lds_ptr_t)(fsmem + slot * STAGE + (wave * NP + j) * 1024), 16,
+                    (int)(lcol[j] < left ? src_off[j] : 0x70000000u), kt * (F32_BK * 4), 0, 0);
+        };
+        f32x16 acc, tot;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { acc[i] = 0.0f; tot[i] = 0.0f; }
+        const int blk = wave % NBLK, kpart = wave / NBLK;  // block of h: units (blk / TBN) * 32.., tokens (blk % TBN) * 32..
+        const int arow = (blk / TBN) * 32 + l32;
+        const int brow = BN + (blk % TBN) * 32 + l32;
+        for (int s = 0; s < NS - 1; ++s) issue(s, s);
+        int slot = 0;
+#pragma unroll 1
+        for (int kt = 0; kt < NKT; ++kt) {
+            __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(NP * (NS - 2)));   // this wave's part of stage kt has landed
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();                  // everyone's has, and everyone is done with stage kt - 1
+            asm volatile("" ::: "memory");
+            issue(kt + NS - 1, slot == 0 ? NS - 1 : slot - 1);
+            const float* st = (const float*)(fsmem + slot * STAGE);
+            auto step = [&](int q) {
+                const int c = ((2 * q + g) ^ (l32 & 7)) * 4;
+                const f32x4 a = *(const f32x4*)(st + arow * F32_BK + c);
+                const f32x4 b = *(const f32x4*)(st + brow * F32_BK + c);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+            };
+#pragma unroll
+            for (int q = 0; q < 4 / KPARTS; ++q) step(kpart * (4 / KPARTS) + q);
+            if ((kt & (F32_FOLD - 1)) == F32_FOLD - 1) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) { tot[i] += acc[i]; acc[i] = 0.0f; }
+            }
+            slot = slot + 1 == NS ? 0 : slot + 1;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] += tot[i];
+        __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(0));     // no copy may land in the ring once it holds h
+        __syncthreads();
+
+        // acc[4q + i] = this wave's part of h[unit (blk / TBN) * 32 + 8q + 4g + i][token (blk % TBN) * 32 + l32]
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(f32x4*)(red + ((wave * 4 + q) * 64 + lane) * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int it = tid; it < NBLK * 256; it += THREADS) {
+            const int hb = it >> 8, q = (it >> 6) & 3;     // lane and g are this thread's own
+            f32x4 v = *(const f32x4*)(red + ((hb * 4 + q) * 64 + lane) * 4);
+#pragma unroll
+            for (int p = 1; p < KPARTS; ++p) v += *(const f32x4*)(red + (((p * NBLK + hb) * 4 + q) * 64 + lane) * 4);
+            const int unit = (hb / TBN) * 32 + 8 * q + 4 * g, tok = (hb % TBN) * 32 + l32;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (b1 && u0 + unit + i < r) v[i] += b1[(long long)layer * r + u0 + unit + i];
+                v[i] = apply_act(v[i], act);
+            }
+            *(f32x4*)(ht + tok * HP + unit) = v;
+        }
+        __syncthreads();
+        // z^T[E, tokens] += W2[:, chunk] . h^T; score block b = wave + WAVES * j is expert block b / TBN, token block b % TBN
+#pragma unroll
+        for (int j = 0; j < EBW; ++j) {
+            const int b = wave + WAVES * j;
+            const int e = (b / TBN) * 32 + l32, tok = (b % TBN) * 32 + l32;
+            if ((b / TBN) * 32 < E) {                      // wave-uniform
+                f32x4 w[BN / 8];
+#pragma unroll
+                for (int q = 0; q < BN / 8; ++q) {
+                    w[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (e < E && u0 + 8 * q < r) w[q] = *(const f32x4*)(W2l + (long long)e * r + u0 + 8 * q + 4 * g);
+                }
+#pragma unroll
+                for (int q = 0; q < BN / 8; ++q) {
+                    const f32x4 h = *(const f32x4*)(ht + tok * HP + 8 * q + 4 * g);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        zacc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q][i], h[i], zacc[j], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);             // one block's fetches at a time in registers
+        }
+        __syncthreads();                                   // h has been read; the ring may be filled again
+    }
+
+    // zacc[j][4q + i] = score of expert (b / TBN) * 32 + 8q + 4g + i, token (b % TBN) * 32 + l32
+    if (groups > 1) {
+#pragma unroll
+        for (int j = 0; j < EBW; ++j) {
+            const int b = wave + WAVES * j;
+            const int t = t0 + (b % TBN) * 32 + l32;
+            if (t < T) {
+                float* dst = partial + (((long long)layer * groups + grp) * T + t) * E;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int e = (b / TBN) * 32 + 8 * q + 4 * g;
+                    if (e + 3 < E) {
+                        *(f32x4*)(dst + e) = f32x4{zacc[j][4 * q], zacc[j][4 * q + 1], zacc[j][4 * q + 2], zacc[j][4 * q + 3]};
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (e + i < E) dst[e + i] = zacc[j][4 * q + i];
+                    }
+                }
+            }
+        }
+        return;
+    }
+    const int ZP = E + 1;
+#pragma unroll 1
+    for (int tb = 0; tb < TBN; ++tb) {
+#pragma unroll
+        for (int j = 0; j < EBW; ++j) {
+            const int b = wave + WAVES * j;
+            if (b % TBN == tb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int e = (b / TBN) * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
+                    if (e < E) zs[l32 * ZP + e] = zacc[j][i] + (b2 ? b2[(long long)layer * E + e] : 0.0f);
+                }
+        }
+        __syncthreads();
+        for (int rr = wave; rr < 32; rr += WAVES) {            // one wave per row
+            const int t = t0 + tb * 32 + rr;
+            if (t < T) {
+                constexpr int NV = EBW * WAVES / TBN / 2;      // experts per lane
+                const long long row = (long long)layer * T + t;
+                float z[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int e = lane + 64 * v;
+                    z[v] = e < E ? zs[rr * ZP + e] : 0.0f;
+                    if (logits && e < E) logits[row * E + e] = z[v];
+                }
+                const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr,
+                                     counts ? counts + (long long)layer * E : nullptr};
+                wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// tokens (and hidden units) per tile: the small tile while it holds all tokens of a layer
+static int f32_tile(const PredictArgs& a) { return a.T <= 32 ? 32 : 64; }
+
+// Workgroups per token tile: up to two per CU (512 in all), which keep the matrix pipe fed between one's chunks;
+// more would only add score tiles to add up.
+static int f32_groups(const PredictArgs& a)
+{
+    const int B = f32_tile(a), nchunks = (a.r + B - 1) / B;
+    const long long tiles = (long long)((a.T + B - 1) / B) * a.L;
+    long long g = (512 + tiles - 1) / tiles;
+    if (g > nchunks) g = nchunks;
+    const long long per_group = (long long)a.L * a.T * a.E * 4;
+    if (g * per_group > (long long)F32_WORKSPACE_MAX) g = (long long)F32_WORKSPACE_MAX / per_group;
+    return g < 1 ? 1 : (int)g;
+}
+
+// byte offsets inside a tile's rows are 32-bit
+bool f32_supported(const PredictArgs& a) { return a.dtype == 0 && a.d <= (1 << 21); }
+
+size_t f32_workspace_bytes(const PredictArgs& a)
+{
+    if (a.T == 0) return 0;
+    const int g = f32_groups(a);
+    return g == 1 ? 0 : sizeof(float) * (size_t)g * (size_t)a.L * (size_t)a.T * (size_t)a.E;
+}
+
+hipError_t launch_predict_f32(const PredictArgs& a)
+{
+    if (a.T == 0) return hipSuccess;
+    const int B = f32_tile(a), tiles = (a.T + B - 1) / B, nchunks = (a.r + B - 1) / B, groups = f32_groups(a);
+    const size_t epilogue = groups == 1 ? sizeof(float) * 32 * (size_t)(a.E + 1) : 0;
+    const int eblocks = (a.E + 31) / 32, waves = B == 64 ? 8 : 4,
+              ebw = (eblocks * (B / 32) + waves - 1) / waves;
+    hipError_t err;
+#define PAEP_LAUNCH_F32(BV, NSV, EBV)                                                                              \
+    do {                                                                                                           \
+        const size_t ring = (size_t)NSV * 2 * BV * F32_BK * 4, lds = ring > epilogue ? ring : epilogue;            \
+        auto kern = predict_f32_kernel<BV, NSV, EBV>;                                                              \
+        static LdsLimit limit;                                                                                     \
+        err = ensure_lds_limit(limit, (const void*)kern, lds);                                                     \
+        if (err != hipSuccess) return err;                                                                         \
+        hipLaunchKernelGGL(kern, dim3(tiles * a.L * groups), dim3(64 * waves), lds, a.stream, a.T, a.d, a.r, a.E, \
+                           a.k, a.act, tiles, groups, nchunks, a.x_stride, a.w1_stride, a.w2_stride,               \
+                           (const float*)a.x, (const float*)a.W1, (const float*)a.W2, (const float*)a.b1,          \
+                           (const float*)a.b2, a.idx, a.probs, a.logits, a.counts, a.prob_mode, a.margin,          \
+                           (float*)a.workspace);                                                                   \
+    } while (0)
+    // score blocks per wave the kernel is compiled for
+    if (B == 64) {
+        if (ebw <= 1)      PAEP_LAUNCH_F32(64, 4, 1);
+        else if (ebw <= 2) PAEP_LAUNCH_F32(64, 4, 2);
+        else if (ebw <= 4) PAEP_LAUNCH_F32(64, 4, 4);
+        else               PAEP_LAUNCH_F32(64, 4, 8);
+    } else {
+        if (ebw <= 1)      PAEP_LAUNCH_F32(32, 8, 1);
+        else if (ebw <= 2) PAEP_LAUNCH_F32(32, 8, 2);
+        else               PAEP_LAUNCH_F32(32, 8, 8);
+    }
+#undef PAEP_LAUNCH_F32
+    err = hipGetLastError();
+    if (err != hipSuccess || groups == 1) return err;
+    return launch_finalize(a, (const float*)a.workspace, groups, a.L, a.T, 0, 1);
+}
+
+}  // namespace paep

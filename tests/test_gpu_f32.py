@@ -1,0 +1,48 @@
+"""The fp32 matrix-instruction kernel against the oracle, every row, at the sizes where its tiling can go wrong:
+token counts around the two tile heights (32 and 64), widths that are no multiple of a stage (32 columns) or of a
+chunk (32 or 64 units), every count of score blocks per wave, one workgroup per token tile (r of one chunk: softmax
+and top-k inside the kernel) and several (scores through the workspace).  Tolerance: 1e-5 of the row's score scale,
+the checker's bound for fp32 storage."""
+import pytest
+
+from test_gpu_predict import _run_and_check, _rand_layers
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,r,E,k,L,act,bias", [
+    (1, 8, 8, 1, 1, 1, "none", False),
+    (1, 2048, 256, 64, 6, 2, "none", True),
+    (31, 264, 72, 130, 9, 2, "silu", True),                # small tile, remainders of d and r, 2 blocks per wave
+    (32, 1000, 40, 1000, 32, 1, "gelu", True),             # small tile, 8 blocks per wave
+    (32, 96, 32, 300, 7, 3, "none", False),                # small tile, one chunk: epilogue in the kernel
+    (33, 264, 72, 64, 6, 2, "silu", True),                 # large tile, one row in its second block
+    (65, 544, 200, 128, 8, 2, "gelu", True),               # 2 blocks per wave
+    (130, 256, 64, 16, 2, 3, "none", True),                # one chunk: epilogue in the kernel
+    (150, 72, 40, 256, 12, 2, "none", True),               # 4 blocks per wave
+    (70, 520, 136, 1000, 32, 1, "silu", True),             # 16 blocks per wave
+    (70, 40, 64, 1000, 17, 2, "none", False),              # ... and the epilogue in the kernel
+    (8193, 32, 128, 40, 3, 4, "none", True),               # more tiles than workgroups wanted: two chunks per workgroup
+])
+def test_f32_kernel_edges(T, d, r, E, k, L, act, bias):
+    x, W1, W2, b1, b2 = _rand_layers(900 + T + d, L=L, T=T, d=d, r=r, E=E, dtype="f32", bias=bias)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "f32", act=act, what=f"f32 T={T} d={d} r={r} E={E}")
+    assert out.path == "simple"
+
+
+def test_f32_shared_tokens_margin_and_counts():
+    import torch
+    import oracle
+    from paper_2511_10676_amd import binding as B
+    from test_gpu_predict import _dev
+    x, W1, W2, b1, b2 = _rand_layers(77, L=3, T=45, d=320, r=136, E=48, dtype="f32", bias=True)
+    counts = torch.zeros((3, 48), dtype=torch.int32, device="cuda")
+    o = B.predict(_dev(x[:1], "f32"), _dev(W1, "f32"), _dev(W2, "f32"), 5, b1=_dev(b1, "f32"), b2=_dev(b2, "f32"),
+                  want_logits=True, want_margin=True, counts=counts)
+    torch.cuda.synchronize()
+    z = o.logits.sort(dim=2, descending=True).values
+    assert torch.equal(o.margin, z[:, :, 4] - z[:, :, 5])
+    idx = o.idx.cpu().numpy()
+    for l in range(3):
+        ref = oracle.group_by_expert(idx[l], 48)[0]
+        assert counts[l].cpu().numpy().tolist() == ref.tolist()
