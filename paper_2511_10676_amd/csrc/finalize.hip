@@ -1,9 +1,15 @@
 // Last step of every predict call whose inner width r was cut into slices that
 // different workgroups worked on: each slice left its contribution to the
-// scores in the workspace (fp32), and here one wave per token row adds the
-// slices in ascending order (a fixed order, so the result is reproducible),
-// adds b2, and runs softmax and top-k (eq. 1 and eq. 4) in registers with wave
-// shuffles.  Lane l owns experts l, l + 64, ...
+// scores in the workspace (fp32); here a row's slices are added in ascending
+// order (a fixed order, so the result is reproducible), b2 is added, and softmax
+// and top-k (eq. 1 and eq. 4) follow in registers.  Two forms:
+//   finalize_kernel       one wave per row, lane l owns experts l, l + 64, ...: the shortest path for
+//                         one row, for calls of few rows
+//   finalize_rows_kernel  4 to 16 lanes per row, up to 16 scores each as float4 loads, sorted lists merged
+//                         between the lanes: fewer instructions per row, for calls of many.  Both move few
+//                         bytes; what bounds them at many rows is instructions: 262144 rows of 16 experts
+//                         in 2 slices 463 us with a wave per row, 14 us here; 7826 rows of 64 in 8 slices
+//                         20 -> 15 us; 1952 rows of 16 in 8 slices 7.7 -> 5.8 us; 512 rows equal.
 //
 // The partial scores are laid out [tile][slice][BM][E]: a tile is BM token rows
 // of one layer, tiles_per_layer of them to a layer (BM = T and one tile per
@@ -68,10 +74,100 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(
     else                   wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
 }
 
+// G lanes per row; lane g owns experts 4 * (j * G + g) + i, j < NJ, i < 4.  E a multiple of 4, lists of KMAX.
+template <int NJ, int G, int KMAX>
+__global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
+    int T, int E, int k, int S, int rows, int BM, int tile0, int tiles_per_layer, const float* __restrict__ partial,
+    const void* __restrict__ b2, int b2_f32, int32_t* __restrict__ idx, float* __restrict__ probs,
+    float* __restrict__ logits, int32_t* __restrict__ counts, int prob_mode, float* __restrict__ margin)
+{
+    const int slot = (blockIdx.x * FIN_THREADS + threadIdx.x) / G, g = threadIdx.x % G;
+    if (slot >= rows) return;                             // the lanes of a row leave together
+    const int tile = slot / BM, tl = slot - tile * BM;
+    const int layer = (tile + tile0) / tiles_per_layer;
+    const int t = (tile + tile0 - layer * tiles_per_layer) * BM + tl;
+    if (t >= T) return;
+    const long long row = (long long)layer * T + t;
+    const long long sstride = (long long)BM * E;
+    const float* src = partial + ((long long)tile * S * BM + tl) * E + 4 * g;
+    f32x4 z[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) z[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int CH = 4;                                 // slices in flight
+    for (int s0 = 0; s0 < S; s0 += CH) {
+        f32x4 p[CH][NJ];
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (s0 + u < S && 4 * (j * G + g) < E) p[u][j] = *(const f32x4*)(src + (s0 + u) * sstride + 4 * j * G);
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (s0 + u < S && 4 * (j * G + g) < E) z[j] += p[u][j];
+    }
+    TopList<KMAX> top;
+    top.clear();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int e = 4 * (j * G + g);
+        if (e < E) {
+            if (b2) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const long long c = (long long)layer * E + e + i;
+                    z[j][i] += b2_f32 ? ((const float*)b2)[c] : bf16_bits_to_f32(((const uint16_t*)b2)[c]);
+                }
+            }
+            if (logits)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) logits[row * E + e + i] = z[j][i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) top.insert(make_key(z[j][i], e + i));
+        }
+    }
+    top.template merge_group<G>();
+    const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr, counts ? counts + (long long)layer * E : nullptr};
+    write_selection<KMAX, G>(top, E, k, g, idx + row * k, probs + row * k, eo, [&](float m) {
+        float s = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (4 * (j * G + g) < E && z[j][i] == z[j][i]) s += __expf(z[j][i] - m);
+        return s;
+    });
+}
+
+// From this many rows on, finalize_rows_kernel: a chip of waves holds 8192 rows at a time as one wave each, and at a
+// thousand the two forms take the same 6 us.
+static constexpr int FIN_MANY_ROWS = 1024;
+
 hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, int tiles, int BM, int tile0,
                            int tiles_per_layer)
 {
     const int rows = tiles * BM;
+    const int need = a.k + ((a.margin && a.k < a.E) ? 1 : 0);     // sorted keys per row
+    if (rows >= FIN_MANY_ROWS && a.E % 4 == 0 && a.E <= 256 && need <= 16) {
+#define PAEP_LAUNCH_FINR(NJV, GV, KV)                                                                            \
+    hipLaunchKernelGGL((finalize_rows_kernel<NJV, GV, KV>), dim3((rows + FIN_THREADS / GV - 1) / (FIN_THREADS / GV)), \
+                       dim3(FIN_THREADS), 0, a.stream, a.T, a.E, a.k, S, rows, BM, tile0, tiles_per_layer, partial, \
+                       a.b2, a.dtype == 0 ? 1 : 0, a.idx, a.probs, a.logits, a.counts, a.prob_mode, a.margin)
+#define PAEP_LAUNCH_FINR_K(NJV, GV)                                                                              \
+    do {                                                                                                         \
+        if (need <= 2)      PAEP_LAUNCH_FINR(NJV, GV, 2);                                                        \
+        else if (need <= 8) PAEP_LAUNCH_FINR(NJV, GV, 8);                                                        \
+        else                PAEP_LAUNCH_FINR(NJV, GV, 16);                                                       \
+    } while (0)
+        if (a.E <= 16)       PAEP_LAUNCH_FINR_K(1, 4);
+        else if (a.E <= 64)  PAEP_LAUNCH_FINR_K(4, 4);
+        else if (a.E <= 128) PAEP_LAUNCH_FINR_K(4, 8);
+        else                 PAEP_LAUNCH_FINR_K(4, 16);
+#undef PAEP_LAUNCH_FINR_K
+#undef PAEP_LAUNCH_FINR
+        return hipGetLastError();
+    }
     const int rows_per_wg = FIN_THREADS / 64;
 #define PAEP_LAUNCH_FIN(NVV)                                                                                     \
     hipLaunchKernelGGL(finalize_kernel<NVV>, dim3((rows + rows_per_wg - 1) / rows_per_wg), dim3(FIN_THREADS), 0, \

@@ -99,6 +99,39 @@ struct TopList {
             key[j] = hi;
         }
     }
+    // The KMAX best of this list and another one (both sorted).  For a power of two: max of the j-th best here and
+    // the j-th worst there is a bitonic sequence of the KMAX best, which log2(KMAX) rounds of compare-exchanges
+    // sort -- 8 + 12 exchanges for 8 keys where inserting one key after the other takes 64.
+    __device__ __forceinline__ void merge(const uint64_t (&other)[KMAX])
+    {
+        if constexpr ((KMAX & (KMAX - 1)) == 0) {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) key[j] = other[KMAX - 1 - j] > key[j] ? other[KMAX - 1 - j] : key[j];
+#pragma unroll
+            for (int st = KMAX / 2; st > 0; st >>= 1)
+#pragma unroll
+                for (int j = 0; j < KMAX; ++j)
+                    if ((j & st) == 0) {
+                        const uint64_t a = key[j], b = key[j + st];
+                        key[j] = a > b ? a : b;
+                        key[j + st] = a > b ? b : a;
+                    }
+        } else {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) insert(other[j]);
+        }
+    }
+    // every lane of an aligned group of G ends with the group's list
+    template <int G> __device__ __forceinline__ void merge_group()
+    {
+#pragma unroll
+        for (int mask = 1; mask < G; mask <<= 1) {
+            uint64_t other[KMAX];
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) other[j] = __shfl_xor((unsigned long long)key[j], mask, 64);
+            merge(other);
+        }
+    }
 };
 
 // What the epilogue writes besides idx.
@@ -116,34 +149,17 @@ struct EpilogueOut {
 
 __device__ __forceinline__ float sigmoidf_(float v) { return 1.0f / (1.0f + __expf(-v)); }
 
-// Softmax + top-k of one row of E scores held in LDS, computed by G
-// consecutive lanes (G a power of two, the group aligned to G).  Lane g of
-// the group scans e = g, g+G, ...; the per-lane lists are merged with
-// xor-shuffles so that every lane ends with the row's list; lane g writes
-// outputs j = g, g+G, ... < k.  KMAX >= k, and >= k + 1 when the margin is
-// wanted and k < E.
-template <int KMAX, int G>
-__device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k, int g,
-                                                 int32_t* idx_row, float* probs_row, const EpilogueOut& o)
+// The outputs of one row from its merged list `top`, by the G lanes that share it: lane g writes outputs
+// j = g, g + G, ... < k.  KMAX >= k, and >= k + 1 when the margin is wanted and k < E.  exp_sum(m) is this lane's
+// share of sum(exp(z - m)) over the row's scores.
+template <int KMAX, int G, class F>
+__device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E, int k, int g, int32_t* idx_row,
+                                                float* probs_row, const EpilogueOut& o, F&& exp_sum)
 {
-    TopList<KMAX> top;
-    top.clear();
-    for (int e = g; e < E; e += G) top.insert(make_key(zrow[e], e));
-#pragma unroll
-    for (int mask = 1; mask < G; mask <<= 1) {
-        uint64_t other[KMAX];
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) other[j] = __shfl_xor((unsigned long long)top.key[j], mask, 64);
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) top.insert(other[j]);
-    }
     const float m = key_score(top.key[0]);       // row maximum (NaNs order last)
     float s = 0.0f;
     if (o.prob_mode == 0) {
-        for (int e = g; e < E; e += G) {
-            const float v = zrow[e];
-            if (v == v) s += __expf(v - m);
-        }
+        s = exp_sum(m);
 #pragma unroll
         for (int mask = 1; mask < G; mask <<= 1) s += __shfl_xor(s, mask, 64);
     } else if (o.prob_mode == 1) {
@@ -168,6 +184,28 @@ __device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k
             if (j == k && k < E) mg = key_score(top.key[j - 1]) - key_score(top.key[j]);
         *o.margin_row = mg;
     }
+}
+
+// Softmax + top-k of one row of E scores held in LDS, computed by G
+// consecutive lanes (G a power of two, the group aligned to G).  Lane g of
+// the group scans e = g, g+G, ...; the per-lane lists are merged with
+// xor-shuffles so that every lane ends with the row's list.
+template <int KMAX, int G>
+__device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k, int g,
+                                                 int32_t* idx_row, float* probs_row, const EpilogueOut& o)
+{
+    TopList<KMAX> top;
+    top.clear();
+    for (int e = g; e < E; e += G) top.insert(make_key(zrow[e], e));
+    top.template merge_group<G>();
+    write_selection<KMAX, G>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
+        float s = 0.0f;
+        for (int e = g; e < E; e += G) {
+            const float v = zrow[e];
+            if (v == v) s += __expf(v - m);
+        }
+        return s;
+    });
 }
 
 // Dispatch on the smallest list length that holds k (and the runner-up, when the margin is wanted).

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ W1, const uint16_t* __restrict__ W2,
     const uint16_t* __restrict__ b1, const uint16_t* __restrict__ b2,
     int32_t* __restrict__ idx, float* __restrict__ probs, float* __restrict__ logits,
-    float* __restrict__ zpart, int* __restrict__ tickets, int32_t* __restrict__ counts,
+    float* __restrict__ zpart, int32_t* __restrict__ counts,
     int prob_mode, float* __restrict__ margin)
 {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NS = C::NS, WR = C::WR, WT = C::WT;
@@ -578,10 +578,10 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         return;
     }
 
-    // r is split over `groups` workgroups: park this group's score tile in the
-    // workspace as zpart[tile][group][token][expert]; the workgroup that arrives
-    // last (ticket counter, release/acquire fences) adds the groups in ascending
-    // order -- a fixed order, whoever is last -- and finishes the rows.
+    // r is split over `groups` workgroups: park this group's score tile in the workspace as
+    // zpart[tile][group][token][expert]; finalize_kernel adds the groups in ascending order and finishes the rows.
+    // (The workgroup that arrived last used to do that here: it went through groups x BM x E scores by itself, 8 loads
+    // at a time, while the rest of the chip was done -- 512 tokens of a 2048 x 2048 layer in 16 groups 75 -> 36 us.)
     float* zmine = zpart + ((long long)(tile_id - split_tile0) * groups + cg) * BM * E;
 #pragma unroll 1
     for (int zp = 0; zp < BM / ZROWS; ++zp) {
@@ -592,51 +592,6 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         }
         __syncthreads();
     }
-    // One thread publishes for the workgroup: the barrier orders every thread's
-    // stores before its device-scope release fence, and its acquire fence before
-    // every thread's later loads (one L2 write-back / invalidate per workgroup,
-    // not one per thread).
-    __syncthreads();
-    int* flag = (int*)smem_raw;
-    if (tid == 0) {
-        __threadfence();
-        const int ticket = atomicAdd(&tickets[tile_id - split_tile0], 1);
-        if (ticket == groups - 1) __threadfence();
-        *flag = ticket;
-    }
-    __syncthreads();
-    const bool last = (*flag == groups - 1);
-    __syncthreads();
-    if (!last) return;
-    const float* zall = zpart + (long long)(tile_id - split_tile0) * groups * BM * E;
-#pragma unroll 1
-    for (int zp = 0; zp < BM / ZROWS; ++zp) {
-        if (t0 + zp * ZROWS >= T) break;                      // no tokens left in this tile (uniform)
-        for (int i = tid; i < ZROWS * E; i += C::THREADS) {
-            const int tl = i / E, e = i - tl * E;
-            if (t0 + zp * ZROWS + tl >= T) continue;
-            const float* src = zall + (long long)(zp * ZROWS + tl) * E + e;
-            float v = 0.0f;
-            for (int q0 = 0; q0 < groups; q0 += 8) {          // eight loads in flight, added in ascending order
-                float part[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) part[u] = (q0 + u < groups) ? src[(long long)(q0 + u) * BM * E] : 0.0f;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v += part[u];
-            }
-            if (b2) v += bf16_bits_to_f32(b2[(long long)layer * E + e]);
-            zs[tl * ZP + e] = v;
-        }
-        __syncthreads();
-        finish_rows(zp);
-    }
-    flush_counts();
-}
-
-__global__ void prefill_clear_tickets(int* tickets, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) tickets[i] = 0;
 }
 
 // Configurations (all 8 waves and one workgroup per CU except Small).  The 160 KB of
@@ -760,6 +715,7 @@ static size_t cfg_workspace_bytes(const PredictArgs& a)
 {
     const PfLayout f = cfg_layout<C>(a);
     if (f.split_tiles == 0) return 0;
+    // score tiles, and a word per tile that nothing uses any more: callers know this size
     return (size_t)f.split_tiles * f.split_groups * C::BM * a.E * sizeof(float) +
            (((size_t)f.split_tiles * sizeof(int) + 15) / 16) * 16;
 }
@@ -771,14 +727,7 @@ static hipError_t launch_cfg(const PredictArgs& a)
     const PfLayout f = cfg_layout<C>(a);
     const int main_wgs = f.main_tiles * f.main_groups, tail_wgs = f.tail_tiles * f.tail_groups;
     const size_t lds = cfg_lds_bytes<C, EB32>(a.E);
-    float* zpart = nullptr;
-    int* tickets = nullptr;
-    if (f.split_tiles > 0) {
-        zpart = (float*)a.workspace;
-        tickets = (int*)((char*)a.workspace + (size_t)f.split_tiles * f.split_groups * C::BM * a.E * sizeof(float));
-        hipLaunchKernelGGL(prefill_clear_tickets, dim3((f.split_tiles + 255) / 256), dim3(256), 0, a.stream, tickets,
-                           f.split_tiles);
-    }
+    float* zpart = (float*)a.workspace;
     auto kern = prefill_kernel<C, EB32>;
     static LdsLimit limit;
     hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
@@ -787,9 +736,11 @@ static hipError_t launch_cfg(const PredictArgs& a)
                        tiles, main_wgs, f.main_groups, tail_wgs, f.tail_groups, f.split_tile0, a.r / C::BN,
                        a.x_stride, a.w1_stride, a.w2_stride, (const uint16_t*)a.x,
                        (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
-                       (const uint16_t*)a.b2, a.idx, a.probs, a.logits, zpart, tickets, a.counts, a.prob_mode,
+                       (const uint16_t*)a.b2, a.idx, a.probs, a.logits, zpart, a.counts, a.prob_mode,
                        a.margin);
-    return hipGetLastError();
+    err = hipGetLastError();
+    if (err != hipSuccess || f.split_tiles == 0) return err;
+    return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
 }
 
 // The large tiles pay off once they fill a good part of the 256 CUs; below

@@ -478,3 +478,23 @@ def test_fold_batchnorm_matches_the_oracle_and_feeds_predict(dtype):
     # Architecture 1 end to end: folded weights + exact GELU through the predictor, against the oracle on the same weights
     Wh, bh = W1f.float().cpu().numpy(), b1f.float().cpu().numpy()
     _run_and_check(x, Wh, W2, bh, None, k, dtype, act="gelu", path="simple", what=f"arch-1 folded {dtype}")
+
+
+@pytest.mark.parametrize("E,k,margin", [(4, 4, True), (12, 2, False), (16, 7, True), (20, 16, False), (64, 8, False),
+                                        (64, 15, True), (100, 8, True), (128, 1, True), (132, 12, False), (256, 8, True),
+                                        (130, 6, True), (64, 20, False)])
+def test_finalize_many_rows(E, k, margin):
+    """1040 rows whose slices of r meet in the workspace: several lanes per row with 4, 16, 8 x 16 and 16 x 16
+    scores between them and lists of 2, 8 and 16; the last two shapes (E no multiple of 4, k above 16) take a wave
+    per row.  Every row against the oracle; the margin equals the difference of the two exported scores."""
+    x, W1, W2, b1, b2 = _rand_layers(700 + E + k, L=16, T=65, d=128, r=256, E=E, dtype="bf16", bias=True)
+    path = "auto" if k <= 16 else "decode"
+    T = 65 if k <= 16 else 64
+    x = x[:, :T]
+    _run_and_check(x, W1, W2, b1, b2, k, "bf16", path=path, what=f"finalize E={E} k={k}")
+    if margin:
+        o = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, b1=_dev(b1, "bf16"), b2=_dev(b2, "bf16"),
+                      path=path, want_logits=True, want_margin=True)
+        z = o.logits.sort(dim=2, descending=True).values
+        want = z[:, :, k - 1] - z[:, :, k] if k < E else torch.full_like(o.margin, float("inf"))
+        assert torch.equal(o.margin, want)
