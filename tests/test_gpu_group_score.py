@@ -222,6 +222,23 @@ def test_confidence_select_group_and_score_match_oracle(L, T, E, kp, kb, kr, rat
         assert sc[l].cpu().numpy().tolist() == oracle.score(idx_out, ref[l], E, k_row=k_row).tolist()
 
 
+@pytest.mark.parametrize("T,kp,kb", [(255, 2, 1), (257, 31, 30), (513, 32, 7), (1, 5, 2)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_confidence_select_copies_whole_workgroups_and_remainders(T, kp, kb, shift):
+    """Rows around a workgroup's 256, and arrays that do not start on 16 bytes."""
+    g = np.random.default_rng(T + kp)
+    idx, probs = _sorted_softmax(g, 2, T, kp, 64, temp=1.5)
+    buf = torch.zeros(idx.size + 1, dtype=torch.int32, device="cuda")
+    dev = buf[shift:shift + idx.size].view(2, T, kp)
+    dev.copy_(torch.from_numpy(idx))
+    got = B.confidence_select(dev, torch.from_numpy(probs).cuda(), kb, 1.1)
+    for l in range(2):
+        k_row, idx_out, n_wide = oracle.confidence_select(idx[l], probs[l], kb, 1.1)
+        assert np.array_equal(got.k_row[l].cpu().numpy(), k_row)
+        assert np.array_equal(got.idx[l].cpu().numpy(), idx_out)
+        assert int(got.n_wide[l]) == n_wide
+
+
 def test_score_rows_with_arbitrary_widths():
     g = np.random.default_rng(77)
     L, T, E, kp, kr = 2, 5000, 64, 9, 4
