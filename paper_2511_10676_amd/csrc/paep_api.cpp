@@ -153,7 +153,12 @@ static paep_status predict_common(const paep_predict_desc* desc,
     const int path = resolve(desc, a);
     if (!path) return PAEP_ERR_UNSUPPORTED;
     const size_t need = path_workspace_bytes(path, a);
-    if (need > 0 && (!workspace_dev || !aligned16(workspace_dev) || workspace_bytes < need)) return PAEP_ERR_WORKSPACE;
+    // the fp32 kernel can do without: r then stays with one workgroup per token tile
+    const bool optional = path == PAEP_PATH_SIMPLE;
+    if (need > 0 && (!workspace_dev || !aligned16(workspace_dev) || workspace_bytes < need)) {
+        if (!optional) return PAEP_ERR_WORKSPACE;
+        workspace_dev = nullptr;
+    }
     if (desc->T == 0) return PAEP_OK;
 
     a.x = x_dev; a.W1 = W1_dev; a.W2 = W2_dev; a.b1 = b1_dev; a.b2 = b2_dev;

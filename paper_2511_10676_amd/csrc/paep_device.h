@@ -99,27 +99,23 @@ struct TopList {
             key[j] = hi;
         }
     }
-    // The KMAX best of this list and another one (both sorted).  For a power of two: max of the j-th best here and
+    // The KMAX best of this list and another one (both sorted): max of the j-th best here and
     // the j-th worst there is a bitonic sequence of the KMAX best, which log2(KMAX) rounds of compare-exchanges
     // sort -- 8 + 12 exchanges for 8 keys where inserting one key after the other takes 64.
     __device__ __forceinline__ void merge(const uint64_t (&other)[KMAX])
     {
-        if constexpr ((KMAX & (KMAX - 1)) == 0) {
+        static_assert((KMAX & (KMAX - 1)) == 0, "a power of two");
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j) key[j] = other[KMAX - 1 - j] > key[j] ? other[KMAX - 1 - j] : key[j];
+        for (int j = 0; j < KMAX; ++j) key[j] = other[KMAX - 1 - j] > key[j] ? other[KMAX - 1 - j] : key[j];
 #pragma unroll
-            for (int st = KMAX / 2; st > 0; st >>= 1)
+        for (int st = KMAX / 2; st > 0; st >>= 1)
 #pragma unroll
-                for (int j = 0; j < KMAX; ++j)
-                    if ((j & st) == 0) {
-                        const uint64_t a = key[j], b = key[j + st];
-                        key[j] = a > b ? a : b;
-                        key[j + st] = a > b ? b : a;
-                    }
-        } else {
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j) insert(other[j]);
-        }
+            for (int j = 0; j < KMAX; ++j)
+                if ((j & st) == 0) {
+                    const uint64_t a = key[j], b = key[j + st];
+                    key[j] = a > b ? a : b;
+                    key[j + st] = a > b ? b : a;
+                }
     }
     // every lane of an aligned group of G ends with the group's list
     template <int G> __device__ __forceinline__ void merge_group()
@@ -206,18 +202,6 @@ __device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k
         }
         return s;
     });
-}
-
-// Dispatch on the smallest list length that holds k (and the runner-up, when the margin is wanted).
-template <int G>
-__device__ __forceinline__ void row_softmax_topk_any(const float* zrow, int E, int k, int g,
-                                                     int32_t* idx_row, float* probs_row, const EpilogueOut& o)
-{
-    const int need = k + ((o.margin_row && k < E) ? 1 : 0);
-    if (need <= 2)       row_softmax_topk<2, G>(zrow, E, k, g, idx_row, probs_row, o);
-    else if (need <= 8)  row_softmax_topk<8, G>(zrow, E, k, g, idx_row, probs_row, o);
-    else if (need <= 16) row_softmax_topk<16, G>(zrow, E, k, g, idx_row, probs_row, o);
-    else                 row_softmax_topk<33, G>(zrow, E, k, g, idx_row, probs_row, o);
 }
 
 // Softmax + top-k of one row held in registers by a whole wave: lane l owns
@@ -356,7 +340,7 @@ __device__ __forceinline__ void wave_softmax_topk_rank(const float (&z)[NV], int
     }
 }
 
-// Same, for kernels that only accept lists of up to 16 (keeps their register budget small):
+// row_softmax_topk with the smallest list length that holds k (and the runner-up, when the margin is wanted):
 // k <= 16, and k <= 15 when the margin is wanted and k < E.
 template <int G>
 __device__ __forceinline__ void row_softmax_topk_upto16(const float* zrow, int E, int k, int g,

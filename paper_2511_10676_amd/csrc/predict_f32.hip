@@ -265,8 +265,12 @@ static int f32_groups(const PredictArgs& a)
     return g < 1 ? 1 : (int)g;
 }
 
-// byte offsets inside a tile's rows are 32-bit
-bool f32_supported(const PredictArgs& a) { return a.dtype == 0 && a.d <= (1 << 21); }
+// The sizes that fp32 storage has always taken (four rows of tokens, hidden units and scores in 160 KB); byte offsets
+// inside a tile's rows stay far below 32 bits.
+bool f32_supported(const PredictArgs& a)
+{
+    return a.dtype == 0 && (long long)a.d + a.r + a.E <= 160 * 1024 / 16;
+}
 
 size_t f32_workspace_bytes(const PredictArgs& a)
 {
@@ -278,7 +282,8 @@ size_t f32_workspace_bytes(const PredictArgs& a)
 hipError_t launch_predict_f32(const PredictArgs& a)
 {
     if (a.T == 0) return hipSuccess;
-    const int B = f32_tile(a), tiles = (a.T + B - 1) / B, nchunks = (a.r + B - 1) / B, groups = f32_groups(a);
+    const int B = f32_tile(a), tiles = (a.T + B - 1) / B, nchunks = (a.r + B - 1) / B,
+              groups = a.workspace ? f32_groups(a) : 1;
     const size_t epilogue = groups == 1 ? sizeof(float) * 32 * (size_t)(a.E + 1) : 0;
     const int eblocks = (a.E + 31) / 32, waves = B == 64 ? 8 : 4,
               ebw = (eblocks * (B / 32) + waves - 1) / waves;

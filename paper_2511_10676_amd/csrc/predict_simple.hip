@@ -95,7 +95,10 @@ __global__ __launch_bounds__(SIMPLE_THREADS) void predict_simple_kernel(
         const long long row = (long long)layer * Tn + t;
         const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr,
                              counts ? counts + (long long)layer * E : nullptr};
-        row_softmax_topk_any<64>(zt + wave * E, E, k, lane, idx + row * k, probs + row * k, eo);
+        float z[16];                                        // E <= 1024
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z[v] = lane + 64 * v < E ? zt[wave * E + lane + 64 * v] : 0.0f;
+        wave_softmax_topk<16>(z, E, k, lane, idx + row * k, probs + row * k, eo);
     }
 }
 

@@ -88,6 +88,8 @@ def test_path_resolution_by_shape():
     assert B.resolve_path(_desc(T=65, **ds)) == "prefill"
     assert B.resolve_path(_desc(T=4096, **ds)) == "prefill"
     assert B.resolve_path(_desc(T=512)) == "simple"
+    assert B.resolve_path(_desc(T=512, d=8192, r=2032)) == "simple"       # fp32: d + r + E up to 10240
+    assert B.resolve_path(_desc(T=512, d=8192, r=2040)) == "invalid"
     assert B.resolve_path(_desc(T=4096, dtype=B.BF16, d=72, r=40, E=13, k=5)) == "simple"
     assert B.resolve_path(_desc(T=4096, dtype=B.BF16, d=2048, r=4096, E=256, k=8)) == "prefill"
     assert B.resolve_path(_desc(k=0)) == "invalid"

@@ -46,3 +46,20 @@ def test_f32_shared_tokens_margin_and_counts():
     for l in range(3):
         ref = oracle.group_by_expert(idx[l], 48)[0]
         assert counts[l].cpu().numpy().tolist() == ref.tolist()
+
+
+@pytest.mark.parametrize("T", [20, 100])
+def test_f32_without_a_workspace_keeps_r_in_one_workgroup(T):
+    """fp32 calls never needed a workspace: a missing one costs the split of r, not the call.  The two runs add the
+    same products in another order: 1e-5 of the row's score scale, the bound for fp32 storage."""
+    import torch
+    from paper_2511_10676_amd import binding as B
+    from test_gpu_predict import _dev
+    x, W1, W2, _, _ = _rand_layers(5, L=2, T=T, d=264, r=520, E=64, dtype="f32", bias=False)
+    args = _dev(x, "f32"), _dev(W1, "f32"), _dev(W2, "f32"), 6
+    a = B.predict(*args, want_logits=True)
+    b = B.predict(*args, want_logits=True, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    scale = a.logits.abs().amax(dim=2, keepdim=True)
+    assert ((a.logits - b.logits).abs() <= 2e-5 * scale).all()
+    assert torch.equal(b.idx.long(), torch.sort(b.logits, dim=2, descending=True, stable=True).indices[:, :, :6])
