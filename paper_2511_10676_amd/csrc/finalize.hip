@@ -21,40 +21,55 @@ namespace paep {
 
 static constexpr int FIN_THREADS = 256;
 
-template <int NV>                                         // experts per lane: E <= 64 * NV
+// NV: experts per lane, E <= 64 * NV.  WPR: waves per row, 1 or the whole workgroup.
+template <int NV, int WPR>
 __global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(
     int T, int E, int k, int S, int rows, int BM, int tile0, int tiles_per_layer, const float* __restrict__ partial,
     const void* __restrict__ b2, int b2_f32, int32_t* __restrict__ idx, float* __restrict__ probs,
     float* __restrict__ logits, int32_t* __restrict__ counts, int prob_mode, float* __restrict__ margin)
 {
     const int lane = threadIdx.x & 63;
-    const int slot = blockIdx.x * (FIN_THREADS / 64) + (threadIdx.x >> 6);
+    const int wave = threadIdx.x >> 6;
+    const int slot = WPR == 1 ? blockIdx.x * (FIN_THREADS / 64) + wave : blockIdx.x;
     if (slot >= rows) return;
     const int tile = slot / BM, tl = slot - tile * BM;
     const int layer = (tile + tile0) / tiles_per_layer;
     const int t = (tile + tile0 - layer * tiles_per_layer) * BM + tl;
-    if (t >= T) return;
+    if (t >= T) return;                                   // the waves of a row leave together
     const long long row = (long long)layer * T + t;
     const long long sstride = (long long)BM * E;
     const float* src = partial + ((long long)tile * S * BM + tl) * E;
+    // this wave's slices
+    const int s_begin = WPR == 1 ? 0 : wave * S / WPR, s_end = WPR == 1 ? S : (wave + 1) * S / WPR;
     // all of a row's experts at once, CH slices per round: NV * CH loads in flight, added in ascending slice order
     constexpr int CH = (NV >= 8) ? 4 : 32 / NV;
     float z[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) z[v] = 0.0f;
-    for (int s0 = 0; s0 < S; s0 += CH) {
+    for (int s0 = s_begin; s0 < s_end; s0 += CH) {
         float p[NV][CH];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int e = lane + 64 * v;
 #pragma unroll
-            for (int u = 0; u < CH; ++u) p[v][u] = (e < E && s0 + u < S) ? src[(long long)(s0 + u) * sstride + e] : 0.0f;
+            for (int u = 0; u < CH; ++u) p[v][u] = (e < E && s0 + u < s_end) ? src[(long long)(s0 + u) * sstride + e] : 0.0f;
         }
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int u = 0; u < CH; ++u)
-                if (s0 + u < S) z[v] += p[v][u];          // uniform; a skipped slice adds nothing, not even +0
+                if (s0 + u < s_end) z[v] += p[v][u];      // uniform; a skipped slice adds nothing, not even +0
+    }
+    if constexpr (WPR > 1) {                              // the waves' sums, added in wave order
+        __shared__ float part[WPR][64 * NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) part[wave][lane + 64 * v] = z[v];
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int w = 1; w < WPR; ++w) z[v] += part[w][lane + 64 * v];
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -168,11 +183,15 @@ hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, in
 #undef PAEP_LAUNCH_FINR
         return hipGetLastError();
     }
-    const int rows_per_wg = FIN_THREADS / 64;
+    // many slices and few rows: four waves share a row's slices (a wave alone takes them in rounds of 32 loads, one
+    // memory round trip each)
+    const bool wide = S >= 64 && rows <= 256;
+    const int rows_per_wg = wide ? 1 : FIN_THREADS / 64;
 #define PAEP_LAUNCH_FIN(NVV)                                                                                     \
-    hipLaunchKernelGGL(finalize_kernel<NVV>, dim3((rows + rows_per_wg - 1) / rows_per_wg), dim3(FIN_THREADS), 0, \
-                       a.stream, a.T, a.E, a.k, S, rows, BM, tile0, tiles_per_layer, partial, a.b2,              \
-                       a.dtype == 0 ? 1 : 0, a.idx, a.probs, a.logits, a.counts, a.prob_mode, a.margin)
+    hipLaunchKernelGGL((wide ? finalize_kernel<NVV, 4> : finalize_kernel<NVV, 1>),                              \
+                       dim3((rows + rows_per_wg - 1) / rows_per_wg), dim3(FIN_THREADS), 0, a.stream, a.T, a.E,  \
+                       a.k, S, rows, BM, tile0, tiles_per_layer, partial, a.b2, a.dtype == 0 ? 1 : 0, a.idx,     \
+                       a.probs, a.logits, a.counts, a.prob_mode, a.margin)
     if (a.E <= 64)       PAEP_LAUNCH_FIN(1);
     else if (a.E <= 128) PAEP_LAUNCH_FIN(2);
     else if (a.E <= 256) PAEP_LAUNCH_FIN(4);

@@ -20,7 +20,9 @@
 //   d-split  slices of 64 hidden units, four waves that split d into quarters,
 //          weights and tokens both straight into registers, the four partial
 //          sums added in LDS wave after wave (decode_partial_kernel).
-// In both a lane reads 16 contiguous bytes of one row, four neighbouring lanes
+//   thin   (one layer or a few) slices of 16 or 32 hidden units, eight waves that split d, so that the slices of
+//          a single layer already occupy half the chip (decode_thin_kernel).
+// In all of them a lane reads 16 contiguous bytes of one row, four neighbouring lanes
 // 64 contiguous bytes, and a lane permutation puts the fragment into the
 // A-operand layout.
 //
@@ -466,6 +468,185 @@ __global__ __launch_bounds__(RW_WAVES * 64, 4) void decode_rows_kernel(
     }
 }
 
+// The form for calls with few hidden units in all (one layer, a decode step): slices of 128 units would leave most
+// CUs without a workgroup, and each of the few would stream its half megabyte alone, which takes as long as 26 layers
+// on a full chip.  Here a slice is 16 * RB units and the columns of d are dealt out to the eight waves of a workgroup,
+// each wave's share (up to SPW stages of 128 columns) requested at once and held in registers, so that the weights of
+// a 2048-wide layer are all in flight together.  What remains is latency: one memory round trip, the chain of matrix
+// instructions, the launch of the finalize kernel.
+// The chain is walked in the row-split kernel's order -- the same stages, starting at the same column, one accumulator
+// handed from wave to wave through LDS -- so that h is the same to the bit: a hidden unit whose sum falls on the other
+// side of a bf16 rounding boundary moves a score by 1e-4 of its scale, and with one row nothing averages that out.
+// (The hand-overs cost 1 us against waves that add their sums up: 12.5 -> 13.4 us for one 2048-wide layer and one
+// token, weights from memory; the row-split kernel takes 20.3.)
+static constexpr int TH_WAVES = 8;
+
+template <int TB, int RB, int SPW>
+__global__ __launch_bounds__(TH_WAVES * 64) void decode_thin_kernel(
+    int T, int d, int r, int E, int act, int S, int total_wgs, long long xs_, long long w1s, long long w2s,
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ W1, const uint16_t* __restrict__ W2,
+    const uint16_t* __restrict__ b1, float* __restrict__ partial)
+{
+    constexpr int US = 16 * RB, TP = 16 * TB, KS = RW_KST / 32;
+    __shared__ __attribute__((aligned(16))) float hand[RB * TB][64 * 4];           // the accumulators on their way
+    __shared__ __attribute__((aligned(16))) uint16_t ht[TP * (US + HPAD)];
+
+    int item = blockIdx.x;
+    {
+        const int per = total_wgs / 8, rem = total_wgs % 8;
+        const int xcd = item % 8, slot = item / 8;
+        item = xcd * per + (xcd < rem ? xcd : rem) + slot;
+    }
+    const int layer = item / S, slice = item - layer * S;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, kg = lane >> 4;
+    const uint16_t* xl = x + (long long)layer * xs_;
+    const uint16_t* W1l = W1 + (long long)layer * w1s;
+    const uint16_t* W2l = W2 + (long long)layer * w2s;
+
+    // fragments are fetched as in the kernels above (lane l: row l / 4, bytes 16 * (l % 4) of a 64-byte k-step)
+    const int lrow = lane >> 2, lchunk = lane & 3;
+    const int perm_src = (4 * m + kg) * 4;
+    const uint16_t* arow = W1l + (long long)(slice * US + lrow) * d + lchunk * 8;
+    const uint16_t* brow = xl + (long long)lrow * d + lchunk * 8;
+    const int NST = d / RW_KST;
+    const int rot = (layer * (r / RW_RS) + slice * US / RW_RS) % NST;              // where the row-split kernel starts
+    const int s_begin = wave * NST / TH_WAVES, s_end = (wave + 1) * NST / TH_WAVES;   // at most SPW stages
+    u32x4 fa[SPW][KS][RB], fb[SPW][KS][TB];
+#pragma unroll
+    for (int b = 0; b < SPW; ++b) {
+        const int s = s_begin + b;
+        const bool live = s < s_end;                          // wave-uniform
+        const int st = s + rot < NST ? s + rot : s + rot - NST;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int off = st * RW_KST + ks * 32;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                fa[b][ks][rb] = u32x4{0u, 0u, 0u, 0u};
+                if (live) fa[b][ks][rb] = *(const u32x4*)(arow + (long long)rb * 16 * d + off);
+            }
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) {
+                fb[b][ks][tb] = u32x4{0u, 0u, 0u, 0u};
+                if (live && tb * 16 + lrow < T) fb[b][ks][tb] = *(const u32x4*)(brow + (long long)tb * 16 * d + off);
+            }
+        }
+    }
+    // W2 columns of this wave's first expert block: lane (m, kg) holds expert m, units 4 * kg .. + 3 of each 16
+    const int EB = (E + 15) / 16;
+    u32x2 w2pf[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int e_row = wave * 16 + m;
+        w2pf[rb] = u32x2{0u, 0u};
+        if (e_row < E) w2pf[rb] = *(const u32x2*)(W2l + (long long)e_row * r + slice * US + rb * 16 + kg * 4);
+    }
+    // into the operand layout, before the wave's turn
+    auto to_mfma_layout = [&](u32x4& f) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(perm_src, (int)f[i]);
+    };
+#pragma unroll
+    for (int b = 0; b < SPW; ++b)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) to_mfma_layout(fa[b][ks][rb]);
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) to_mfma_layout(fb[b][ks][tb]);
+        }
+
+#pragma unroll 1
+    for (int w = 0; w < TH_WAVES; ++w) {
+        if (wave == w) {
+            f32x4 acc[RB][TB];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) {
+                    acc[rb][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (w > 0) acc[rb][tb] = *(const f32x4*)(&hand[rb * TB + tb][lane * 4]);
+                }
+#pragma unroll
+            for (int b = 0; b < SPW; ++b)
+                if (s_begin + b < s_end) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                            for (int tb = 0; tb < TB; ++tb)
+                                acc[rb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, fa[b][ks][rb]), __builtin_bit_cast(bf16x8, fb[b][ks][tb]),
+                                    acc[rb][tb], 0, 0, 0);
+                }
+            if (w + 1 < TH_WAVES) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) *(f32x4*)(&hand[rb * TB + tb][lane * 4]) = acc[rb][tb];
+            } else {
+                // acc[rb][tb][i] = h[token tb*16 + m][unit slice*US + rb*16 + 4*kg + i]
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) {
+                        const int unit = rb * 16 + 4 * kg, tok = tb * 16 + m;
+                        float h[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float t = acc[rb][tb][i];
+                            if (b1) t += bf16_bits_to_f32(b1[(long long)layer * r + slice * US + unit + i]);
+                            t = round_to_bf16(t);
+                            if (act != 0) t = round_to_bf16(apply_act(t, act));
+                            h[i] = t;
+                        }
+                        *(u32x2*)(ht + tok * (US + HPAD) + unit) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
+                    }
+            }
+        }
+        __syncthreads();
+    }
+
+    // scores of this slice: z^T[e, t] = W2[e, slice] . h^T[slice, t]; expert blocks dealt to the waves
+    auto score_block = [&](int eb, const u32x2 (&wfrag)[RB]) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+            f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const u32x2 hv = *(const u32x2*)(ht + (tb * 16 + m) * (US + HPAD) + rb * 16 + kg * 4);
+                z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, wfrag[rb]),
+                                                              __builtin_bit_cast(short4v, hv), z, 0, 0, 0);
+            }
+            const int t = tb * 16 + m;
+            if (t < T) {
+                float* dst = partial + (((long long)layer * S + slice) * T + t) * E + eb * 16 + 4 * kg;
+                if (eb * 16 + 4 * kg + 3 < E) {
+                    *(f32x4*)dst = z;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (eb * 16 + 4 * kg + i < E) dst[i] = z[i];
+                }
+            }
+        }
+    };
+    if (wave < EB) score_block(wave, w2pf);
+    for (int eb = wave + TH_WAVES; eb < EB; eb += TH_WAVES) {
+        const int e_row = eb * 16 + m;
+        u32x2 wfrag[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            wfrag[rb] = u32x2{0u, 0u};
+            if (e_row < E) wfrag[rb] = *(const u32x2*)(W2l + (long long)e_row * r + slice * US + rb * 16 + kg * 4);
+        }
+        score_block(eb, wfrag);
+    }
+}
+
 static constexpr int FIN_NV = 8;                          // experts per lane of the finalize kernel at most: E <= 512
 
 bool decode_supported(const PredictArgs& a)
@@ -475,9 +656,42 @@ bool decode_supported(const PredictArgs& a)
            a.k <= 32;
 }
 
+// Units per slice of the thin kernel, or 0 where one of the others runs.  It is the faster one while its slices still
+// find a CU each (256 of them); the price of thin slices is that every one fetches all tokens and leaves a score per
+// token and expert to be added up, which limits T and E.  Measured with the weights out of the caches, us for the
+// row-split kernel / 16 / 32 units a slice:
+//   2048 x 2048, 64 experts: 1 layer, 1 token 20.3 / 13.4 / 16.2; 2 layers, 64 tokens 26.4 / 23.2 / -; 4 layers, 1 token
+//   21.2 / 17.1 / 18.3, 16 tokens 22.3 / 19.6 / 19.4, 32 tokens 23.3 / 27.3 / 22.9; 6 layers, 16 tokens 23.4 / 24.2 / 25.3
+//   1024 x 4096, 16 experts: 1 layer, 1 token 29.8 / 16.0 / 20.6; 8 layers, 16 tokens 33.4 / 32.0 / 27.1
+//   4096 x 2048, 256 experts: 1 layer, 1 token 26.6 / 25.3 / 22.7; 2 layers, 16 tokens 29.2 / 32.3 / 26.2
+static int decode_thin_units(const PredictArgs& a)
+{
+    if (a.r % RW_RS != 0) return 0;                           // the order of sums that it keeps is the row-split kernel's
+    const long long units = (long long)a.L * a.r;
+    // stages of 128 columns a wave can hold in registers, by token blocks
+    const int stages = (a.d / RW_KST + TH_WAVES - 1) / TH_WAVES, tb = (a.T + 15) / 16;
+    if (units <= 256 * 16 && a.E <= 128 && stages <= (tb == 1 ? 6 : tb == 2 ? 4 : 2)) return 16;
+    if (units <= 256 * 32 && a.E <= 256 && tb == 1 && stages <= 4) return 32;
+    return 0;
+}
+
+static size_t decode_partial_bytes(const PredictArgs& a)
+{
+    const int thin = decode_thin_units(a), rs = thin ? thin : RS;
+    return sizeof(float) * (size_t)a.L * (size_t)(a.r / rs) * (size_t)a.T * (size_t)a.E;
+}
+
+// never less for more tokens, so that a workspace for the longest batch serves the shorter ones
 size_t decode_workspace_bytes(const PredictArgs& a)
 {
-    return sizeof(float) * (size_t)a.L * (size_t)(a.r / RS) * (size_t)a.T * (size_t)a.E;
+    size_t need = decode_partial_bytes(a);
+    for (int t = 16; t < a.T; t += 16) {                      // the token counts at which the kernel may change
+        PredictArgs b = a;
+        b.T = t;
+        const size_t n = decode_partial_bytes(b);
+        if (n > need) need = n;
+    }
+    return need;
 }
 
 // r in whole slices of 128: the row-split kernel (measured against the d-split kernel at 1 token: 26 layers of
@@ -488,11 +702,27 @@ static bool decode_by_rows(const PredictArgs& a) { return a.r % RW_RS == 0; }
 hipError_t launch_predict_decode(const PredictArgs& a)
 {
     const bool rows_kernel = decode_by_rows(a);
-    const int S = a.r / (rows_kernel ? RW_RS : RS);
+    const int thin = decode_thin_units(a);
+    const int S = a.r / (thin ? thin : (rows_kernel ? RW_RS : RS));
     const int total = S * a.L;
     float* partial = (float*)a.workspace;
     const int TB = (a.T + 15) / 16;
-    if (rows_kernel) {
+    if (thin) {
+#define PAEP_LAUNCH_THIN(TBV, RBV, SPWV)                                                                        \
+    hipLaunchKernelGGL((decode_thin_kernel<TBV, RBV, SPWV>), dim3(total), dim3(TH_WAVES * 64), 0, a.stream, a.T, \
+                       a.d, a.r, a.E, a.act, S, total, a.x_stride, a.w1_stride, a.w2_stride,                    \
+                       (const uint16_t*)a.x, (const uint16_t*)a.W1, (const uint16_t*)a.W2,                      \
+                       (const uint16_t*)a.b1, partial)
+        const bool narrow = a.d <= 2 * 8 * RW_KST;            // two stages a wave
+        if (thin == 16) {
+            if (TB == 1)      { if (narrow) PAEP_LAUNCH_THIN(1, 1, 2); else if (a.d <= 4 * 8 * RW_KST) PAEP_LAUNCH_THIN(1, 1, 4); else PAEP_LAUNCH_THIN(1, 1, 6); }
+            else if (TB == 2) { if (narrow) PAEP_LAUNCH_THIN(2, 1, 2); else PAEP_LAUNCH_THIN(2, 1, 4); }
+            else              PAEP_LAUNCH_THIN(4, 1, 2);
+        } else {
+            if (narrow) PAEP_LAUNCH_THIN(1, 2, 2); else PAEP_LAUNCH_THIN(1, 2, 4);
+        }
+#undef PAEP_LAUNCH_THIN
+    } else if (rows_kernel) {
 #define PAEP_LAUNCH_ROWS(TBV, NSV)                                                                          \
         {                                                                                                   \
             constexpr size_t lds = (size_t)NSV * 16 * TBV * RW_KST * 2;                                     \

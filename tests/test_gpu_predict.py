@@ -130,6 +130,40 @@ def test_decode_shared_tokens_across_layers():
         _run_and_check(x[:1], W1, W2, None, None, 4, "bf16", path="decode", what=f"decode rows shared x T={T}")
 
 
+# Few hidden units in all (L * r <= 4096, or 8192 up to 16 tokens, r a multiple of 128): slices of 16 or 32 units, the
+# stages of 128 columns dealt to eight waves.  Fewer stages than waves, ragged shares, two, four and six stages a wave,
+# token counts around a block of 16, expert counts around a block of 16 and 8 blocks, both slice widths.
+@pytest.mark.parametrize("T,d,r,E,k,act,L", [
+    (1, 128, 128, 1, 1, "none", 1), (16, 384, 128, 16, 3, "silu", 4), (17, 1152, 256, 17, 4, "none", 2),
+    (32, 2048, 256, 128, 8, "gelu", 1), (33, 2048, 128, 120, 6, "none", 3), (64, 640, 384, 65, 16, "silu", 2),
+    (1, 5120, 128, 64, 6, "none", 1), (31, 4096, 128, 64, 6, "none", 1), (9, 2176, 128, 33, 6, "none", 2),
+    (1, 640, 128, 129, 5, "none", 3), (16, 4096, 128, 255, 32, "silu", 1), (15, 512, 2048, 64, 6, "none", 3),
+    (2, 256, 1152, 250, 9, "gelu", 2), (16, 128, 8192, 16, 2, "none", 1),
+])
+def test_decode_thin_slices(T, d, r, E, k, act, L):
+    x, W1, W2, b1, b2 = _rand_layers(400 + T + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, path="decode", what=f"decode thin T={T} d={d} r={r} E={E}")
+    assert out.path == "decode"
+
+
+# The other two kernels, in calls with more hidden units than those: r in slices of 128 and r in slices of 64.
+@pytest.mark.parametrize("T,d,r,E,k,L", [
+    (1, 128, 128, 64, 6, 65), (33, 256, 256, 130, 5, 33), (64, 128, 128, 16, 2, 66),
+    (1, 128, 192, 64, 6, 43), (16, 256, 64, 17, 3, 129), (33, 128, 320, 40, 4, 26), (64, 384, 192, 64, 6, 43),
+])
+def test_decode_many_layers(T, d, r, E, k, L):
+    x, W1, W2, b1, b2 = _rand_layers(500 + T + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", path="decode", what=f"decode T={T} d={d} r={r} E={E} L={L}")
+    assert out.path == "decode"
+
+
+@pytest.mark.parametrize("L,r,E", [(1, 2048, 64), (2, 2048, 128), (4, 2048, 64), (2, 4096, 256), (1, 192, 130)])
+@pytest.mark.parametrize("d", [2048, 4096])
+def test_decode_workspace_for_more_tokens_serves_fewer(L, r, E, d):
+    sizes = [B.predict_workspace_bytes(B.make_desc(T, d, r, E, 1, L, B.BF16)) for T in range(1, 65)]
+    assert sizes == sorted(sizes)
+
+
 def test_decode_row_split_many_experts_and_wide_k():
     # 512 experts (eight per lane in the finalize kernel, four expert blocks per wave in the slices kernel) and k = 32
     x, W1, W2, b1, b2 = _rand_layers(57, L=2, T=40, d=256, r=256, E=512, dtype="bf16", bias=True)
