@@ -54,6 +54,44 @@ __device__ __forceinline__ float apply_act(float v, int act)
     return v;
 }
 
+// The same two functions for a v on the bf16 grid whose result is rounded to bf16 again, one instruction stream per
+// activation (ACT: 0 identity, 1 SiLU, 2 GELU).  The general forms above spend some 50 vector instructions on a hidden
+// unit (erff: both of its ranges; the division: its scaling and correction steps), more than the matrix work of that
+// unit leaves idle (26 layers 2048 x 2048, 301 tokens with SiLU: 174 -> 165 us with these and one kernel per activation).
+//   SiLU  v / (1 + e^-v) by the hardware reciprocal; 1 + e^-v is scaled by 2^-32 so that neither it nor its
+//         reciprocal leaves the normal range before the result does.
+//   GELU  v Phi(v), with Phi(-u) = e^(-u^2 / 2) t P(t), t = 1 / (1 + 0.21 u), u = |v| (the form of Abramowitz and
+//         Stegun 26.2.17): P of degree 8 fitted to e^(u^2 / 2) Phi(-u) / t over 0 <= u <= 14, relative error 1.6e-8.
+// Over all finite bf16 inputs both give the correctly rounded bf16 result (SiLU down to v = -88, where e^-v overflows);
+// 0.5 v (1 + erff) does not below v = -4.4, where 1 + erff cancels.
+template <int ACT> __device__ __forceinline__ float act_bf16(float v)
+{
+    if constexpr (ACT == 1) {
+        const float e = __builtin_amdgcn_exp2f(v * -1.44269504088896341f);
+        return v * (__builtin_amdgcn_rcpf(fmaf(e, 0x1p-32f, 0x1p-32f)) * 0x1p-32f);
+    } else if constexpr (ACT == 2) {
+        const float u = fabsf(v);
+        const float t = __builtin_amdgcn_rcpf(fmaf(u, 0.21f, 1.0f));
+        float p = -0.0716562569141388f;
+        p = fmaf(p, t, 0.28358834981918335f);
+        p = fmaf(p, t, -0.330253005027771f);
+        p = fmaf(p, t, 0.3494006395339966f);
+        p = fmaf(p, t, -0.09392499178647995f);
+        p = fmaf(p, t, 0.12487264722585678f);
+        p = fmaf(p, t, 0.06919218599796295f);
+        p = fmaf(p, t, 0.08506885915994644f);
+        p = fmaf(p, t, 0.08371157944202423f);
+        const float tail = (p * t) * __builtin_amdgcn_exp2f(u * u * -0.72134752044448170f);
+        return v * (v < 0.0f ? tail : 1.0f - tail);
+    } else {
+        return v;
+    }
+}
+__device__ __forceinline__ float apply_act_bf16(float v, int act)
+{
+    return act == 1 ? act_bf16<1>(v) : act == 2 ? act_bf16<2>(v) : v;
+}
+
 // ---------------------------------------------------------------------------
 // (score, expert) -> 64-bit key.  Larger key = better candidate.
 // ---------------------------------------------------------------------------

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_partial_kernel(
             float t = v[i];
             if (b1) t += bf16_bits_to_f32(b1[(long long)layer * r + slice * RS + unit + i]);
             t = round_to_bf16(t);
-            if (act != 0) t = round_to_bf16(apply_act(t, act));
+            if (act != 0) t = round_to_bf16(apply_act_bf16(t, act));
             h[i] = t;
         }
         *(u32x2*)(ht + tok * (RS + HPAD) + unit) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(RW_WAVES * 64, 4) void decode_rows_kernel(
             float t = acc[tb][i];
             if (b1) t += bf16_bits_to_f32(b1[(long long)layer * r + slice * RW_RS + unit + i]);
             t = round_to_bf16(t);
-            if (act != 0) t = round_to_bf16(apply_act(t, act));
+            if (act != 0) t = round_to_bf16(apply_act_bf16(t, act));
             h[i] = t;
         }
         *(u32x2*)(ht + tok * (RW_RS + HPAD) + unit) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(TH_WAVES * 64) void decode_thin_kernel(
                             float t = acc[rb][tb][i];
                             if (b1) t += bf16_bits_to_f32(b1[(long long)layer * r + slice * US + unit + i]);
                             t = round_to_bf16(t);
-                            if (act != 0) t = round_to_bf16(apply_act(t, act));
+                            if (act != 0) t = round_to_bf16(apply_act_bf16(t, act));
                             h[i] = t;
                         }
                         *(u32x2*)(ht + tok * (US + HPAD) + unit) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};

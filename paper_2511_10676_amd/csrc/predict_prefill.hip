@@ -88,10 +88,13 @@ struct PfZRows {
     static constexpr int value = (C::BM * (EB32 * 32 + 1) * 4 > 128 * 1024) ? C::BM / 2 : C::BM;
 };
 
-// EB32: 32-expert blocks (E <= 32 * EB32).
-template <class C, int EB32>
+// EB32: 32-expert blocks (E <= 32 * EB32).  MODE: 0 neither bias b1 nor activation, else act + 1 with an optional b1:
+// one kernel for each, because the registers of a form that a call does not use are spilled by the one it does (22
+// spills with all forms in one kernel, none without: 26 layers 2048 x 2048, 4096 tokens 932 -> 899 us; 48 layers
+// 4096 x 2048, 256 experts 39.6 -> 36.1 ms, both with the late fragments below).
+template <class C, int EB32, int MODE>
 __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
-    int T, int d, int r, int E, int k, int act, int tiles_per_layer, int main_wgs, int main_groups, int tail_wgs,
+    int T, int d, int r, int E, int k, int tiles_per_layer, int main_wgs, int main_groups, int tail_wgs,
     int tail_groups, int split_tile0, int nchunks,
     long long xs_, long long w1s, long long w2s,
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ W1, const uint16_t* __restrict__ W2,
@@ -308,8 +311,16 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         const u32x2 hi = *(const u32x2*)(row + (((c0 + 1) ^ sw) << 4));
         return u32x4{lo[0], lo[1], hi[0], hi[1]};
     };
+    // b1 of the layer as 32-bit words in the constant address space (scalar loads); where it starts in the middle of
+    // a word, two units are put together from two words
+    typedef const __attribute__((address_space(4))) uint32_t* const_words;
+    const uintptr_t b1_addr = (uintptr_t)(b1 + (long long)layer * r);
+    const const_words b1_words = (const_words)(b1_addr & ~(uintptr_t)3);
+    const int b1_odd = (int)(b1_addr >> 1) & 1;
+    auto word_pair = [&](const_words w, int i) {
+        return (uint32_t)((((uint64_t)w[i + b1_odd] << 32) | w[i]) >> (16 * b1_odd));
+    };
     auto second_layer = [&](int n) {
-        const bool plain = (act == 0) && (b1 == nullptr);     // uniform: no bias, identity activation
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
@@ -321,7 +332,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                     for (int eb = 0; eb < EB32; ++eb) wv[eb] = w2_fragment(eb, unit0);
                 }
                 bf16x8 hb[NI];
-                if (plain) {
+                if constexpr (MODE == 0) {
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni) {
                         const f32x16& a = acc1[mi][ni];
@@ -330,25 +341,33 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                         hb[ni] = __builtin_bit_cast(bf16x8, pk);
                     }
                 } else {
-                    float bias[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) bias[i] = 0.f;
+                    uint32_t bias[4] = {0u, 0u, 0u, 0u};                         // pairs of bf16: units +0, +2, +8, +10
                     if (b1) {
+                        // the 16 units of this step by scalar loads; the upper half of the wave has units 4 further on
+                        // (the offset is opaque so that all steps' loads are not gathered in one place, in registers)
+                        int first = (n * BN + wr * WM + mi * 32 + 16 * s) >> 1;
+                        asm volatile("" : "+s"(first));
+                        const const_words w = b1_words + first;
 #pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            bias[i] = bf16_bits_to_f32(b1[(long long)layer * r + unit0 + (i & 3) + 8 * (i >> 2)]);
+                        for (int p = 0; p < 4; ++p) {
+                            const int i = (p & 1) + 4 * (p >> 1);
+                            bias[p] = g ? word_pair(w, i + 2) : word_pair(w, i);
+                        }
                     }
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni) {
-                        float v[8];
+                        u32x4 pk;
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            float h = acc1[mi][ni][8 * s + i] + bias[i];
-                            if (act != 0) h = apply_act(round_to_bf16(h), act);   // h is stored as bf16 before the activation
-                            v[i] = h;                                            // rounded to bf16 by the packing below
+                        for (int p = 0; p < 4; ++p) {
+                            float lo = acc1[mi][ni][8 * s + 2 * p] + __uint_as_float(bias[p] << 16);
+                            float hi = acc1[mi][ni][8 * s + 2 * p + 1] + __uint_as_float(bias[p] & 0xFFFF0000u);
+                            pk[p] = pack_bf16x2(lo, hi);                 // h is stored as bf16 before the activation
+                            if constexpr (MODE > 1) {
+                                lo = act_bf16<MODE - 1>(__uint_as_float(pk[p] << 16));
+                                hi = act_bf16<MODE - 1>(__uint_as_float(pk[p] & 0xFFFF0000u));
+                                pk[p] = pack_bf16x2(lo, hi);
+                            }
                         }
-                        u32x4 pk = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                                         pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
                         hb[ni] = __builtin_bit_cast(bf16x8, pk);
                     }
                 }
@@ -394,7 +413,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     // With fewer stages the current tile's own stage is refilled, which requires
     // this wave's last fragment reads to have completed first.
     constexpr bool LAG = (NS >= 4);
-    constexpr bool LATE_FRAGS = (EB32 >= 8);
+    constexpr bool LATE_FRAGS = (MI + EB32) * NI * 16 >= 192;
     constexpr bool DEFER = (NS >= 3) && (NP % 2 == 0) && (NP / 2 <= MI);
     constexpr int HALF = NP / 2;
     constexpr int PRO = LAG ? NS - 1 : NS;                        // tiles requested before the loop
@@ -463,8 +482,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                     // be replaced by this chunk's; it is read at the end of the chunk, NK - 1 tiles later.
                     if (C::W2L && kt == 0 && n > n_begin) issue_w2(n);
                     if constexpr (!DEFER) issue_tile(free_slot);
-                    // With many experts the score accumulators leave no room to carry the next
-                    // tile's first fragments across the second layer: fetch them after it instead.
+                    // With 192 accumulators there is no room to carry the next tile's first fragments
+                    // across the second layer: fetch them after it instead.
                     const bool prefetch = !(LATE_FRAGS && kt == NK - 1);
                     if (prefetch) read_b(stn, IC<0>{}, IC<nxt>{});
                     __builtin_amdgcn_sched_barrier(0);
@@ -720,19 +739,19 @@ static size_t cfg_workspace_bytes(const PredictArgs& a)
            (((size_t)f.split_tiles * sizeof(int) + 15) / 16) * 16;
 }
 
-template <class C, int EB32>
-static hipError_t launch_cfg(const PredictArgs& a)
+template <class C, int EB32, int MODE>
+static hipError_t launch_mode(const PredictArgs& a)
 {
     const int tiles = (a.T + C::BM - 1) / C::BM;
     const PfLayout f = cfg_layout<C>(a);
     const int main_wgs = f.main_tiles * f.main_groups, tail_wgs = f.tail_tiles * f.tail_groups;
     const size_t lds = cfg_lds_bytes<C, EB32>(a.E);
     float* zpart = (float*)a.workspace;
-    auto kern = prefill_kernel<C, EB32>;
+    auto kern = prefill_kernel<C, EB32, MODE>;
     static LdsLimit limit;
     hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kern, dim3(main_wgs + tail_wgs), dim3(C::THREADS), lds, a.stream, a.T, a.d, a.r, a.E, a.k, a.act,
+    hipLaunchKernelGGL(kern, dim3(main_wgs + tail_wgs), dim3(C::THREADS), lds, a.stream, a.T, a.d, a.r, a.E, a.k,
                        tiles, main_wgs, f.main_groups, tail_wgs, f.tail_groups, f.split_tile0, a.r / C::BN,
                        a.x_stride, a.w1_stride, a.w2_stride, (const uint16_t*)a.x,
                        (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
@@ -741,6 +760,16 @@ static hipError_t launch_cfg(const PredictArgs& a)
     err = hipGetLastError();
     if (err != hipSuccess || f.split_tiles == 0) return err;
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
+}
+
+template <class C, int EB32>
+static hipError_t launch_cfg(const PredictArgs& a)
+{
+    switch (a.act) {
+    case 0: return a.b1 ? launch_mode<C, EB32, 1>(a) : launch_mode<C, EB32, 0>(a);
+    case 1: return launch_mode<C, EB32, 2>(a);
+    default: return launch_mode<C, EB32, 3>(a);
+    }
 }
 
 // The large tiles pay off once they fill a good part of the 256 CUs; below

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(SIMPLE_THREADS) void predict_simple_kernel(
             if (lane == 0) {
                 if (b1) v += bf16_at(b1, (long long)layer * r + j);
                 v = round_to_bf16(v);
-                v = apply_act(v, act);
+                v = apply_act_bf16(v, act);
                 if (act != 0) v = round_to_bf16(v);
                 ht[t * r + j] = v;
             }

@@ -532,3 +532,39 @@ def test_finalize_many_rows(E, k, margin):
         z = o.logits.sort(dim=2, descending=True).values
         want = z[:, :, k - 1] - z[:, :, k] if k < E else torch.full_like(o.margin, float("inf"))
         assert torch.equal(o.margin, want)
+
+
+# ------------------------------------------------------------------ activations on the bf16 grid
+@pytest.mark.parametrize("act", ["silu", "gelu"])
+@pytest.mark.parametrize("path,T,d,r", [("prefill", 4096, 32, 128), ("decode", 64, 128, 64), ("decode", 64, 128, 128)])
+def test_activation_of_every_bf16_value(path, T, d, r, act):
+    """One hidden unit per token holds a bf16 value v (x[t, 0] = v, W1 = 1), the score of expert 0 is act(v): it must be
+    act(v) in float64 rounded to bf16, to the bit, for every v of magnitude 2^-60 .. 64 whose result is a normal number.
+    A value within 1e-6 of a rounding boundary may go either way (the float32 arithmetic's own bound)."""
+    from scipy.special import log_ndtr
+    bits = np.arange(65536, dtype=np.uint32) << 16
+    v = bits.view(np.float32)
+    v = v[np.isfinite(v) & (np.abs(v) >= 2.0 ** -60) & (np.abs(v) <= 64)].astype(np.float64)
+    exact = v * np.exp(log_ndtr(v)) if act == "gelu" else v * np.exp(-np.logaddexp(0.0, -v))
+    keep = np.abs(exact) >= 2.0 ** -125
+    v, exact = v[keep], exact[keep]
+    L = -(-v.size // T)
+    x = torch.zeros((L, T, d), dtype=torch.bfloat16, device="cuda")
+    flat = torch.zeros(L * T, dtype=torch.float64)
+    flat[:v.size] = torch.from_numpy(v)
+    x[:, :, 0] = flat.view(L, T).to(torch.bfloat16).cuda()
+    W1 = torch.zeros((L, r, d), dtype=torch.bfloat16, device="cuda")
+    W1[:, :, 0] = 1.0
+    W2 = torch.zeros((L, 2, r), dtype=torch.bfloat16, device="cuda")
+    W2[:, 0, r - 3] = 1.0
+    out = B.predict(x, W1, W2, 1, act=act, path=path, want_logits=True)
+    torch.cuda.synchronize()
+    got = out.logits[:, :, 0].reshape(-1)[:v.size].double().cpu().numpy()
+
+    def to_bf16(a):
+        m, e = np.frexp(a)
+        return np.ldexp(np.rint(m * 256) / 256, e)
+    lo, hi = to_bf16(exact * (1 - 1e-6)), to_bf16(exact * (1 + 1e-6))
+    bad = (got != lo) & (got != hi)
+    assert not bad.any(), (v[bad][:5], got[bad][:5], exact[bad][:5])
+    print(f"{path} {act}: {v.size} values, {(got != to_bf16(exact)).sum()} not correctly rounded", flush=True)
