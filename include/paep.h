@@ -99,8 +99,10 @@ typedef struct {
     int64_t w2_layer_stride;
 } paep_predict_desc;
 
-/* Bytes of device workspace paep_predict needs for this shape (0 is possible).
- * Returns 0 for an invalid descriptor; paep_predict reports the reason. */
+/* Bytes of device workspace paep_predict runs fastest with for this shape (0 is
+ * possible).  Calls with less run on where the work can be laid out without it
+ * (large bf16 calls of more than 64 experts: the hidden vectors then stay on
+ * chip; fp32), else they return PAEP_ERR_WORKSPACE.  Returns 0 for an invalid descriptor; paep_predict reports the reason. */
 size_t paep_predict_workspace_bytes(const paep_predict_desc *desc);
 
 /* Which kernel family AUTO resolves to for this shape (a paep_path value),
@@ -117,16 +119,16 @@ int paep_predict_resolve_path(const paep_predict_desc *desc);
  *     probs[l,t,j] = softmax(s)[idx[l,t,j]]      over all E scores (desc->prob = 0;
  *                    see paep_prob for the other two confidence scores)
  * Selection is done on the raw scores: softmax preserves ranking
- * (sections 1 and 3.1).  h and s never go to memory unless logits_dev is
- * given.
+ * (sections 1 and 3.1).  Outside the workspace h and s go to memory only if
+ * logits_dev is given (s).
  *
  *   x_dev   [L or 1][T, d]   W1_dev [L][r, d]   W2_dev [L][E, r]
  *   b1_dev  [L][r] or NULL   b2_dev [L][E] or NULL   (dense, layer stride r / E)
  *   idx_dev [L][T, k] int32  probs_dev [L][T, k] float
  *   logits_dev [L][T, E] float or NULL: the scores s, for checking only
  *   workspace_dev: at least paep_predict_workspace_bytes(desc) bytes,
- *                  16-byte aligned; may be NULL when that is 0, and with
- *                  fp32 storage (which then runs slower).  Contents on
+ *                  16-byte aligned; may be NULL when that is 0 (less: see
+ *                  there).  Contents on
  *                  entry do not matter; calls that may run at the same time
  *                  (different streams) need a workspace each.
  * x, W1, W2 and their layer strides must be 16-byte aligned.  With T = 0 the
@@ -183,8 +185,8 @@ paep_status paep_predict_confidence(const paep_predict_desc *desc,
  * PAEP_STATIC_SCRATCH_BYTES that lives inside the library's code object, one
  * copy per GPU, held until the process ends.  The call allocates and frees
  * nothing (no hipMalloc, no hipFree, no allocating library routine).
- *   - Shapes whose paep_predict_workspace_bytes exceeds
- *     PAEP_STATIC_SCRATCH_BYTES return PAEP_ERR_WORKSPACE (16 MiB covers the
+ *   - Shapes that cannot do with PAEP_STATIC_SCRATCH_BYTES of workspace
+ *     return PAEP_ERR_WORKSPACE (16 MiB covers the
  *     decode path of a DeepSeek-V2-Lite-sized bank up to 64 tokens and every
  *     prefill shape that needs no r split); nothing is launched then.
  *   - Every call on a GPU uses that GPU's one buffer, which keeps whatever the

@@ -155,6 +155,29 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
     });
 }
 
+// Activation counts of the rows first_row .. L * T - 1 of a call, from their selections: counted in LDS, COUNT_ROWS rows
+// of one layer at a time, and added to the layer's counters once.  (One global atomic per selection, as the rows'
+// lanes do it in calls of few rows, meets the others of a popular expert on one address.)
+static constexpr int COUNT_ROWS = 2048;
+__global__ __launch_bounds__(FIN_THREADS) void count_selected_kernel(int T, int E, int k, long long first_row,
+                                                                     const int32_t* __restrict__ idx,
+                                                                     int32_t* __restrict__ counts)
+{
+    extern __shared__ int32_t cnt[];                      // E
+    const long long layer = first_row / T + blockIdx.y;
+    const long long first = layer * T > first_row ? layer * T : first_row;
+    const long long row0 = first + (long long)blockIdx.x * COUNT_ROWS, end = (layer + 1) * T;
+    if (row0 >= end) return;
+    for (int e = threadIdx.x; e < E; e += FIN_THREADS) cnt[e] = 0;
+    __syncthreads();
+    const int rows = end - row0 < COUNT_ROWS ? (int)(end - row0) : COUNT_ROWS;
+    const int32_t* src = idx + row0 * k;
+    for (int i = threadIdx.x; i < rows * k; i += FIN_THREADS) atomicAdd(&cnt[src[i]], 1);
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += FIN_THREADS)
+        if (cnt[e]) atomicAdd(&counts[layer * E + e], cnt[e]);
+}
+
 // From this many rows on, finalize_rows_kernel: a chip of waves holds 8192 rows at a time as one wave each, and at a
 // thousand the two forms take the same 6 us.
 static constexpr int FIN_MANY_ROWS = 1024;
@@ -163,6 +186,18 @@ hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, in
                            int tiles_per_layer)
 {
     const int rows = tiles * BM;
+    if (a.counts && rows >= FIN_MANY_ROWS) {
+        PredictArgs b = a;
+        b.counts = nullptr;
+        const hipError_t err = launch_finalize(b, partial, S, tiles, BM, tile0, tiles_per_layer);
+        if (err != hipSuccess) return err;
+        // the tiles are the call's last ones
+        const int layer0 = tile0 / tiles_per_layer;
+        const long long first_row = (long long)layer0 * a.T + (long long)(tile0 - layer0 * tiles_per_layer) * BM;
+        hipLaunchKernelGGL(count_selected_kernel, dim3((a.T + COUNT_ROWS - 1) / COUNT_ROWS, a.L - layer0),
+                           dim3(FIN_THREADS), sizeof(int32_t) * a.E, a.stream, a.T, a.E, a.k, first_row, a.idx, a.counts);
+        return hipGetLastError();
+    }
     const int need = a.k + ((a.margin && a.k < a.E) ? 1 : 0);     // sorted keys per row
     if (rows >= FIN_MANY_ROWS && a.E % 4 == 0 && a.E <= 256 && need <= 16) {
 #define PAEP_LAUNCH_FINR(NJV, GV, KV)                                                                            \

@@ -118,7 +118,7 @@ int paep_predict_resolve_path(const paep_predict_desc* desc)
     return p ? p : -1;
 }
 
-// device workspace of the family `path` for this call
+// device workspace of the family `path` for this call: what it runs fastest with
 static size_t path_workspace_bytes(int path, const paep::PredictArgs& a)
 {
     switch (path) {
@@ -126,6 +126,16 @@ static size_t path_workspace_bytes(int path, const paep::PredictArgs& a)
     case PAEP_PATH_PREFILL: return paep::prefill_workspace_bytes(a);
     case PAEP_PATH_SIMPLE: return a.dtype == PAEP_F32 ? paep::f32_workspace_bytes(a) : 0;
     default: return 0;
+    }
+}
+
+// ... and what it cannot do without
+static size_t path_workspace_min(int path, const paep::PredictArgs& a)
+{
+    switch (path) {
+    case PAEP_PATH_DECODE: return paep::decode_workspace_bytes(a);
+    case PAEP_PATH_PREFILL: return paep::prefill_workspace_min(a);
+    default: return 0;                                       // the fp32 kernel: r stays with one workgroup per token tile
     }
 }
 
@@ -152,18 +162,15 @@ static paep_status predict_common(const paep_predict_desc* desc,
     a.margin = margin_dev;                                   // the families differ in how many candidates they can keep
     const int path = resolve(desc, a);
     if (!path) return PAEP_ERR_UNSUPPORTED;
-    const size_t need = path_workspace_bytes(path, a);
-    // the fp32 kernel can do without: r then stays with one workgroup per token tile
-    const bool optional = path == PAEP_PATH_SIMPLE;
-    if (need > 0 && (!workspace_dev || !aligned16(workspace_dev) || workspace_bytes < need)) {
-        if (!optional) return PAEP_ERR_WORKSPACE;
-        workspace_dev = nullptr;
-    }
+    const size_t need = path_workspace_min(path, a);
+    const bool usable = workspace_dev && aligned16(workspace_dev);
+    if (need > 0 && (!usable || workspace_bytes < need)) return PAEP_ERR_WORKSPACE;
     if (desc->T == 0) return PAEP_OK;
 
     a.x = x_dev; a.W1 = W1_dev; a.W2 = W2_dev; a.b1 = b1_dev; a.b2 = b2_dev;
     a.idx = idx_dev; a.probs = probs_dev; a.logits = logits_dev; a.counts = counts_dev;
-    a.workspace = workspace_dev;
+    a.workspace = usable ? workspace_dev : nullptr;
+    a.workspace_bytes = usable ? workspace_bytes : 0;
     a.stream = static_cast<hipStream_t>(stream);
     hipError_t err;
     switch (path) {
@@ -219,7 +226,8 @@ paep_status paep_predict_static(const paep_predict_desc* desc,
 {
     const paep_status st = check_desc(desc);
     if (st != PAEP_OK) return st;
-    const size_t need = paep_predict_workspace_bytes(desc);
+    const paep::PredictArgs a = to_args(desc);
+    const size_t need = path_workspace_min(resolve(desc, a), a);
     if (need > (size_t)PAEP_STATIC_SCRATCH_BYTES) return PAEP_ERR_WORKSPACE;
     void* ws = nullptr;
     if (scratch_for_current_device(&ws) != hipSuccess) return PAEP_ERR_HIP;

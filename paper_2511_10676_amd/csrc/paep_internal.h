@@ -25,7 +25,8 @@ struct PredictArgs {
     int32_t* counts;    // nullable: [L][E] activation counts, added to
     int prob_mode;      // 0 softmax over all E, 1 softmax over the k selected, 2 sigmoid
     float* margin;      // nullable: [L][T] last selected score minus the best score left out
-    void* workspace;
+    void* workspace;    // null: the call does without
+    size_t workspace_bytes;
     hipStream_t stream;
 };
 
@@ -68,6 +69,7 @@ hipError_t launch_predict_decode(const PredictArgs& a);
 // bf16 fused matrix-core kernel for large T
 bool prefill_supported(const PredictArgs& a);
 size_t prefill_workspace_bytes(const PredictArgs& a);
+size_t prefill_workspace_min(const PredictArgs& a);      // with less than this the call is refused
 hipError_t launch_predict_prefill(const PredictArgs& a);
 // tile configuration id, workgroups per token tile, chunks of r per workgroup (what the launcher will use)
 void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_group);

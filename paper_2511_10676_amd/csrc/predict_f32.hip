@@ -283,7 +283,7 @@ hipError_t launch_predict_f32(const PredictArgs& a)
 {
     if (a.T == 0) return hipSuccess;
     const int B = f32_tile(a), tiles = (a.T + B - 1) / B, nchunks = (a.r + B - 1) / B,
-              groups = a.workspace ? f32_groups(a) : 1;
+              groups = a.workspace && a.workspace_bytes >= f32_workspace_bytes(a) ? f32_groups(a) : 1;
     const size_t epilogue = groups == 1 ? sizeof(float) * 32 * (size_t)(a.E + 1) : 0;
     const int eblocks = (a.E + 31) / 32, waves = B == 64 ? 8 : 4,
               ebw = (eblocks * (B / 32) + waves - 1) / waves;

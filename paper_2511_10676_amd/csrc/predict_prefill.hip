@@ -92,6 +92,8 @@ struct PfZRows {
 // one kernel for each, because the registers of a form that a call does not use are spilled by the one it does (22
 // spills with all forms in one kernel, none without: 26 layers 2048 x 2048, 4096 tokens 932 -> 899 us; 48 layers
 // 4096 x 2048, 256 experts 39.6 -> 36.1 ms, both with the late fragments below).
+// EB32 = 0: the first layer alone; h goes to memory (`hout`, bf16, laid out in fragments: block of 32 tokens, step of 16
+// units, then 16 bytes for every lane of the wave that will multiply it) and scores_of_h_kernel takes it from there.
 template <class C, int EB32, int MODE>
 __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     int T, int d, int r, int E, int k, int tiles_per_layer, int main_wgs, int main_groups, int tail_wgs,
@@ -101,7 +103,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     const uint16_t* __restrict__ b1, const uint16_t* __restrict__ b2,
     int32_t* __restrict__ idx, float* __restrict__ probs, float* __restrict__ logits,
     float* __restrict__ zpart, int32_t* __restrict__ counts,
-    int prob_mode, float* __restrict__ margin)
+    int prob_mode, float* __restrict__ margin, u32x4* __restrict__ hout)
 {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NS = C::NS, WR = C::WR, WT = C::WT;
     constexpr int WM = C::WM, WN = C::WN, MI = C::MI, NI = C::NI, CPR = C::CPR, RPI = C::RPI;
@@ -166,7 +168,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     const char* xtile = (const char*)(xl + (long long)t0 * d);
 
     f32x16 acc1[MI][NI];
-    f32x16 acc2[EB32][NI];
+    constexpr int EBA = EB32 > 0 ? EB32 : 1;
+    f32x16 acc2[EBA][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const int unit0 = n * BN + wr * WM + mi * 32 + 16 * s + 4 * g;   // units unit0+0..3, unit0+8..11
-                u32x4 wv[EB32];
+                u32x4 wv[EBA];
                 if constexpr (EARLY_W2) {
 #pragma unroll
                     for (int eb = 0; eb < EB32; ++eb) wv[eb] = w2_fragment(eb, unit0);
@@ -371,7 +374,15 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                         hb[ni] = __builtin_bit_cast(bf16x8, pk);
                     }
                 }
-                if constexpr (C::W2L) {
+                if constexpr (EB32 == 0) {
+                    const long long steps = (long long)nchunks * (BN / 16);
+                    const int us = (n * BN + wr * WM + mi * 32 + 16 * s) / 16;
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) {
+                        const long long blk = (long long)tile_id * (BM / 32) + wt * NI + ni;
+                        hout[(blk * steps + us) * 64 + lane] = __builtin_bit_cast(u32x4, hb[ni]);
+                    }
+                } else if constexpr (C::W2L) {
                     // fragments from LDS, the next one requested before the current one is multiplied
                     const int ubase = wr * WM + mi * 32 + 16 * s;
                     u32x4 cur = w2_fragment_lds(0, ubase);
@@ -513,6 +524,10 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
             read_b(stc, IC<0>{}, IC<(((KS - 1) & 1) ^ 1)>{});
         }
         __builtin_amdgcn_s_waitcnt(WAIT_LDS);                     // next tile's first fragments have landed
+    }
+    if constexpr (EB32 == 0) {
+        __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));         // the copies of the pipeline's end land in this workgroup's LDS
+        return;
     }
     __syncthreads();                                       // all tile reads done before LDS is reused
 
@@ -756,7 +771,7 @@ static hipError_t launch_mode(const PredictArgs& a)
                        a.x_stride, a.w1_stride, a.w2_stride, (const uint16_t*)a.x,
                        (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
                        (const uint16_t*)a.b2, a.idx, a.probs, a.logits, zpart, a.counts, a.prob_mode,
-                       a.margin);
+                       a.margin, nullptr);
     err = hipGetLastError();
     if (err != hipSuccess || f.split_tiles == 0) return err;
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
@@ -770,6 +785,233 @@ static hipError_t launch_cfg(const PredictArgs& a)
     case 1: return launch_mode<C, EB32, 2>(a);
     default: return launch_mode<C, EB32, 3>(a);
     }
+}
+
+// ---------------------------------------------------------------------------
+// Two passes for many experts.  The fused kernel keeps E scores per token in accumulators beside the chunk of h, and
+// with more than 64 experts that costs it the tile shape: 256 x 128 tiles (E up to 256) need half as many bytes again
+// per flop through the CU's copy path as 256 x 256 ones, which is what the loop waits for, and waves side by side along
+// tokens read 1.1-1.25 LDS fragments per matrix instruction instead of 0.75.  Here the first layer runs by itself in the
+// 2 x 4 layout with five stages, h takes a round trip through memory (2 r bytes per token each way, 0.1-0.2 of the
+// layer's bytes at 2048-wide rows), and a second kernel forms the scores.
+//
+// scores_of_h_kernel: a workgroup owns 256 tokens, eight waves with 32 tokens and all experts each.  h arrives in the
+// layout of the matrix instruction, straight into registers, two stages of 64 units ahead; W2's columns of a stage are
+// copied to LDS for all waves (swizzled like the slices above), a ring of three stages.  What bounds it is the reading
+// of h.  The scores go to memory as [tile][slice][256][E], finalize.hip does the rest.
+// ---------------------------------------------------------------------------
+static constexpr int SH_BM = 256, SH_BN = 64, SH_NST = 3;
+
+template <int EB32>
+__global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
+    int T, int r, int E, int tiles_per_layer, int slices, long long w2s, const u32x4* __restrict__ h,
+    const uint16_t* __restrict__ W2, float* __restrict__ zpart)
+{
+    constexpr int ROWS = EB32 * 32, STAGE_BYTES = ROWS * SH_BN * 2;
+    constexpr int W2J = ROWS / 8 / 8;                       // copy instructions per wave and stage, 8 rows each
+    constexpr int KS = SH_BN / 16;
+    static_assert(W2J * 64 == ROWS, "rows divide among the waves");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+
+    const int slice = blockIdx.x % slices, tile_id = blockIdx.x / slices;
+    const int layer = tile_id / tiles_per_layer, t0 = (tile_id - layer * tiles_per_layer) * SH_BM;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int nst = r / SH_BN;
+    const int s_begin = (int)((long long)slice * nst / slices), s_end = (int)((long long)(slice + 1) * nst / slices);
+    const u32x4* hw = h + ((long long)(tile_id * (SH_BM / 32) + wave) * (r / 16)) * 64 + lane;
+
+    const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(W2 + (long long)layer * w2s), 0, (int)((long long)E * r * 2), 0x00020000);
+    uint32_t w2lane[W2J];
+#pragma unroll
+    for (int j = 0; j < W2J; ++j) {
+        const int e = (wave * W2J + j) * 8 + (lane >> 3);
+        w2lane[j] = (uint32_t)(e * r + (((lane & 7) ^ (e & 7)) * 8)) * 2u;   // rows past E lie outside the resource: zeros
+    }
+    auto issue_w2 = [&](int st, int slot) {
+#pragma unroll
+        for (int j = 0; j < W2J; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w2, (lptr_t)(smem_raw + slot * STAGE_BYTES + (wave * W2J + j) * 1024),
+                                                     16, (int)w2lane[j], st * SH_BN * 2, 0, 0);
+    };
+    u32x4 hb[SH_NST][KS];
+    auto load_h = [&](auto buf_c, int st) {
+        constexpr int buf = decltype(buf_c)::value;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) hb[buf][ks] = hw[(long long)(st * KS + ks) * 64];
+    };
+    f32x16 acc[EB32];
+#pragma unroll
+    for (int eb = 0; eb < EB32; ++eb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[eb][i] = 0.f;
+
+    // Stage s is requested two stages ahead, W2 first; past the end the last stage is requested again, into a slot
+    // nobody reads any more, so that the count of requests in flight stays the same.
+    constexpr int WAIT_STAGE = PAEP_VMCNT((SH_NST - 2) * (W2J + KS));
+    static_for<SH_NST - 1>([&](auto b_c) {
+        constexpr int b = decltype(b_c)::value;
+        const int st = s_begin + b < s_end ? s_begin + b : s_end - 1;
+        issue_w2(st, b);
+        __builtin_amdgcn_sched_barrier(0);
+        load_h(b_c, st);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    for (int s0 = s_begin; s0 < s_end; s0 += SH_NST) {
+        static_for<SH_NST>([&](auto b_c) {
+            constexpr int b = decltype(b_c)::value, nb = (b + SH_NST - 1) % SH_NST;
+            const int st = s0 + b;
+            if (st < s_end) {                               // uniform over the workgroup
+                __builtin_amdgcn_s_waitcnt(WAIT_STAGE);     // this wave's part of the stage has landed
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();               // everyone's has; and everyone is done with the stage before
+                asm volatile("" ::: "memory");
+                const int sn = st + SH_NST - 1 < s_end ? st + SH_NST - 1 : s_end - 1;
+                issue_w2(sn, nb);
+                __builtin_amdgcn_sched_barrier(0);
+                load_h(IC<nb>{}, sn);
+                __builtin_amdgcn_sched_barrier(0);
+                const unsigned char* stage = smem_raw + b * STAGE_BYTES;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 hv = __builtin_bit_cast(bf16x8, hb[b][ks]);
+#pragma unroll
+                    for (int eb = 0; eb < EB32; ++eb) {
+                        const int e = eb * 32 + l32;
+                        const unsigned char* row = stage + e * (SH_BN * 2) + 8 * g;
+                        const u32x2 lo = *(const u32x2*)(row + (((2 * ks) ^ (l32 & 7)) << 4));
+                        const u32x2 hi = *(const u32x2*)(row + (((2 * ks + 1) ^ (l32 & 7)) << 4));
+                        const u32x4 w = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                        acc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), hv, acc[eb], 0, 0, 0);
+                    }
+                }
+            }
+        });
+    }
+    __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));              // no copy may land in this LDS once it belongs to another workgroup
+    const int tl = wave * 32 + l32;
+    if (t0 + tl < T) {
+        float* dst = zpart + (((long long)tile_id * slices + slice) * SH_BM + tl) * E;
+#pragma unroll
+        for (int eb = 0; eb < EB32; ++eb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = eb * 32 + 8 * q + 4 * g;
+                if (e + 3 < E) {
+                    *(f32x4*)(dst + e) = f32x4{acc[eb][4 * q], acc[eb][4 * q + 1], acc[eb][4 * q + 2], acc[eb][4 * q + 3]};
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (e + i < E) dst[e + i] = acc[eb][4 * q + i];
+                }
+            }
+    }
+}
+
+typedef PfCfg<256, 256, 32, 5, 2, 4, 1, false> CfgFirst;
+
+// Layers go through the two kernels in batches whose h takes up to TWO_PASS_BYTES: enough workgroups that the launches'
+// ends do not show, no more memory than that buys (48 layers 2048 x 2048, 128 experts, 6011 tokens, in batches of 150 /
+// 300 / 600 / 1300 MB 3.33 / 3.13 / 3.04 / 2.95 ms; 4096 x 2048, 256 experts, 32768 tokens 300 / 600 / 1300 MB 27.9 / 27.1 / 27.9).
+static constexpr long long TWO_PASS_BYTES = 600ll * 1000 * 1000;
+// Workgroups per token tile of the first kernel, each with its share of r: 4 of them and 8 tiles run on an XCD together and
+// share their rows of W1 and x through its L2 (2 / 4 / 8: 28.1 / 27.1 / 27.4 ms on the larger shape).
+static constexpr int TWO_PASS_GROUPS = 4;
+
+// Layers per batch and slices of r in the second kernel.
+struct TwoPass { int batch, slices; size_t h_bytes, z_bytes; };
+static TwoPass two_pass_layout(const PredictArgs& a)
+{
+    const long long tiles = (a.T + SH_BM - 1) / SH_BM;
+    const long long per_layer = tiles * SH_BM * a.r * 2;
+    long long batch = TWO_PASS_BYTES / per_layer;
+    if (batch < 1) batch = 1;
+    if (batch > a.L) batch = a.L;
+    batch = (a.L + (a.L + batch - 1) / batch - 1) / ((a.L + batch - 1) / batch);      // batches of even size
+    TwoPass p{(int)batch, 1, (size_t)(batch * per_layer), 0};
+    while (tiles * batch * p.slices < 192 && p.slices < 4) p.slices *= 2;
+    p.z_bytes = (size_t)(batch * tiles) * p.slices * SH_BM * a.E * sizeof(float);
+    return p;
+}
+
+// Where the fused kernel is the slower one.  Fused against two passes, us: 256 experts, 16 layers x 8192 tokens 2048 x 2048
+// 1602 / 1234, 2048 x 4096 2863 / 2154; 200 experts, 32 layers x 8192 1024 x 2048 1667 / 1353; 128 experts, 2048 x 2048
+// 16 layers x 4096 tokens 599 / 610, 48 x 2048 tokens 948 / 921, 48 x 6011 with GELU 3373 / 3040; 64 experts, 32 x 4096
+// 1030 / 1101, 26 x 8192 1621 / 1850.
+static bool two_pass_wanted(const PredictArgs& a)
+{
+    const long long tiles = (long long)((a.T + 255) / 256) * a.L;
+    return a.r % CfgFirst::BN == 0 && (a.E > 128 ? tiles >= 128 : a.E > 64 && tiles >= 384);
+}
+
+template <int MODE>
+static hipError_t launch_first_layer(const PredictArgs& a, int tiles, int groups, u32x4* h)
+{
+    auto kern = prefill_kernel<CfgFirst, 0, MODE>;
+    const size_t lds = CfgFirst::TILE_BYTES;
+    static LdsLimit limit;
+    const hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(tiles * a.L * groups), dim3(CfgFirst::THREADS), lds, a.stream, a.T, a.d, a.r, a.E, a.k,
+                       tiles, tiles * a.L * groups, groups, 0, 1, 0, a.r / CfgFirst::BN, a.x_stride, a.w1_stride,
+                       a.w2_stride, (const uint16_t*)a.x, (const uint16_t*)a.W1, (const uint16_t*)a.W2,
+                       (const uint16_t*)a.b1, (const uint16_t*)nullptr, (int32_t*)nullptr, (float*)nullptr, (float*)nullptr,
+                       (float*)nullptr, (int32_t*)nullptr, 0, (float*)nullptr, h);
+    return hipGetLastError();
+}
+
+template <int EB32>
+static hipError_t launch_scores_of_h(const PredictArgs& a, int tiles, int slices, const u32x4* h, float* z)
+{
+    auto kern = scores_of_h_kernel<EB32>;
+    const size_t lds = (size_t)SH_NST * EB32 * 32 * SH_BN * 2;
+    static LdsLimit limit;
+    const hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(tiles * a.L * slices), dim3(512), lds, a.stream, a.T, a.r, a.E, tiles, slices,
+                       a.w2_stride, h, (const uint16_t*)a.W2, z);
+    return hipGetLastError();
+}
+
+static hipError_t launch_two_pass(const PredictArgs& a)
+{
+    const TwoPass p = two_pass_layout(a);
+    const int tiles = (a.T + SH_BM - 1) / SH_BM, NC = a.r / CfgFirst::BN;
+    int groups = TWO_PASS_GROUPS;
+    while (NC % groups != 0) groups /= 2;
+    u32x4* h = (u32x4*)a.workspace;
+    float* z = (float*)((char*)a.workspace + p.h_bytes);
+    for (int l0 = 0; l0 < a.L; l0 += p.batch) {
+        PredictArgs b = a;                                  // layers l0 .. of the call
+        b.L = a.L - l0 < p.batch ? a.L - l0 : p.batch;
+        b.x = (const uint16_t*)a.x + l0 * a.x_stride;
+        b.W1 = (const uint16_t*)a.W1 + l0 * a.w1_stride;
+        b.W2 = (const uint16_t*)a.W2 + l0 * a.w2_stride;
+        if (a.b1) b.b1 = (const uint16_t*)a.b1 + (long long)l0 * a.r;
+        if (a.b2) b.b2 = (const uint16_t*)a.b2 + (long long)l0 * a.E;
+        const long long rows = (long long)l0 * a.T;
+        b.idx = a.idx + rows * a.k;
+        b.probs = a.probs + rows * a.k;
+        if (a.logits) b.logits = a.logits + rows * a.E;
+        if (a.margin) b.margin = a.margin + rows;
+        if (a.counts) b.counts = a.counts + (long long)l0 * a.E;
+        hipError_t err;
+        switch (a.act) {
+        case 0: err = a.b1 ? launch_first_layer<1>(b, tiles, groups, h) : launch_first_layer<0>(b, tiles, groups, h); break;
+        case 1: err = launch_first_layer<2>(b, tiles, groups, h); break;
+        default: err = launch_first_layer<3>(b, tiles, groups, h); break;
+        }
+        if (err != hipSuccess) return err;
+        if (a.E <= 64)       err = launch_scores_of_h<2>(b, tiles, p.slices, h, z);
+        else if (a.E <= 128) err = launch_scores_of_h<4>(b, tiles, p.slices, h, z);
+        else                 err = launch_scores_of_h<8>(b, tiles, p.slices, h, z);
+        if (err != hipSuccess) return err;
+        err = launch_finalize(b, z, p.slices, tiles * b.L, SH_BM, 0, tiles);
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
 }
 
 // The large tiles pay off once they fill a good part of the 256 CUs; below
@@ -805,7 +1047,8 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
     }
 }
 
-size_t prefill_workspace_bytes(const PredictArgs& a)
+// what a call cannot do without
+size_t prefill_workspace_min(const PredictArgs& a)
 {
     switch (pick_cfg(a)) {
     case 2: return cfg_workspace_bytes<CfgBig>(a);
@@ -816,8 +1059,18 @@ size_t prefill_workspace_bytes(const PredictArgs& a)
     }
 }
 
+// what it runs fastest with; calls with less, down to the above, run without the second pass
+size_t prefill_workspace_bytes(const PredictArgs& a)
+{
+    const size_t fused = prefill_workspace_min(a);
+    if (!two_pass_wanted(a)) return fused;
+    const TwoPass p = two_pass_layout(a);
+    return p.h_bytes + p.z_bytes > fused ? p.h_bytes + p.z_bytes : fused;
+}
+
 hipError_t launch_predict_prefill(const PredictArgs& a)
 {
+    if (two_pass_wanted(a) && a.workspace && a.workspace_bytes >= prefill_workspace_bytes(a)) return launch_two_pass(a);
     switch (pick_cfg(a)) {
     case 2:
         if (a.d >= 4096 && a.d % 64 == 0) return a.E <= 32 ? launch_cfg<CfgBigDeep, 1>(a) : launch_cfg<CfgBigDeep, 2>(a);

@@ -568,3 +568,46 @@ def test_activation_of_every_bf16_value(path, T, d, r, act):
     bad = (got != lo) & (got != hi)
     assert not bad.any(), (v[bad][:5], got[bad][:5], exact[bad][:5])
     print(f"{path} {act}: {v.size} values, {(got != to_bf16(exact)).sum()} not correctly rounded", flush=True)
+
+
+# ------------------------------------------------------------------ two passes for many experts
+@pytest.mark.parametrize("T,d,r,E,k,L,act,bias", [
+    (4097, 64, 256, 129, 8, 8, "none", False),             # 17 tiles a layer, one row in the last; one chunk of r
+    (8191, 96, 768, 256, 15, 4, "silu", True),             # three chunks: one workgroup per tile takes them all
+    (1000, 64, 1024, 200, 3, 33, "gelu", True),            # four chunks, four workgroups per tile; 132 tiles
+    (4100, 32, 512, 250, 8, 16, "none", True),             # scores that are no multiple of 4 apart
+    (12300, 64, 256, 100, 6, 8, "none", True),             # up to 128 experts: from 384 tiles on
+])
+def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
+    """First layer and scores as two kernels, against the oracle, and the fused kernel that runs with a smaller
+    workspace: the hidden vector is the same to the bit, the scores add the same products in another order (2e-6 of the
+    row's scale: r products of 2^-24 each, as a random walk, four times over)."""
+    x, W1, W2, b1, b2 = _rand_layers(700 + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"two passes T={T} d={d} r={r} E={E}",
+                             rows=np.unique(np.concatenate([np.arange(0, T, 9), np.arange(T - 300, T)])))
+    need = B.predict_workspace_bytes(B.make_desc(T, d, r, E, k, L, B.BF16))
+    assert need >= 2 * T * r                               # h of a layer at least
+    counts = torch.zeros((L, E), dtype=torch.int32, device="cuda")
+    args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k
+    opts = dict(b1=None if b1 is None else _dev(b1, "bf16"), b2=None if b2 is None else _dev(b2, "bf16"), act=act,
+                want_logits=True)
+    two = B.predict(*args, counts=counts, **opts)
+    one = B.predict(*args, workspace=torch.empty(need - 1, dtype=torch.uint8, device="cuda"), **opts)
+    torch.cuda.synchronize()
+    assert torch.equal(two.idx, out.idx) and torch.equal(two.probs, out.probs)
+    scale = one.logits.abs().amax(dim=2, keepdim=True)
+    assert ((two.logits - one.logits).abs() <= 2e-6 * scale).all()
+    ref = torch.stack([torch.bincount(two.idx[l].flatten().long(), minlength=E) for l in range(L)])
+    assert torch.equal(counts.long(), ref)
+
+
+def test_counts_of_rows_finished_outside_the_prefill_kernel():
+    """More than 1024 rows whose r is split: the counts come from the selections, whole layers and the last tiles of a call
+    (33 x 9 tiles: the 41 beyond the full round of 256 are cut along r)."""
+    for T, d, r, E, L in ((500, 64, 512, 64, 3), (8229, 64, 1024, 64, 9)):
+        x, W1, W2, _, _ = _rand_layers(T, L=L, T=T, d=d, r=r, E=E, dtype="bf16")
+        counts = torch.full((L, E), 7, dtype=torch.int32, device="cuda")
+        out = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), 6, counts=counts)
+        torch.cuda.synchronize()
+        ref = torch.stack([torch.bincount(out.idx[l].flatten().long(), minlength=E) for l in range(L)])
+        assert torch.equal(counts.long() - 7, ref)
