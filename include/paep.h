@@ -180,8 +180,9 @@ paep_status paep_predict_confidence(const paep_predict_desc *desc,
 /*
  * paep_predict for callers that cannot allocate device memory or carry a
  * workspace around: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same computation, same kernels and same
- * results as paep_predict; the workspace is a buffer of
+ * harnesses that forbid hipMalloc.  Same computation and results as
+ * paep_predict (where that is given more workspace than this buffer, the sum of
+ * a score may be rounded in another order); the workspace is a buffer of
  * PAEP_STATIC_SCRATCH_BYTES that lives inside the library's code object, one
  * copy per GPU, held until the process ends.  The call allocates and frees
  * nothing (no hipMalloc, no hipFree, no allocating library routine).
@@ -210,7 +211,8 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  * output (want_margin = 1) will run this shape.  Host only; for tests and reports.
  *   plan[0] kernel family (paep_path)
  *   plan[1] tile configuration of the prefill family (0 otherwise):
- *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide
+ *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
+ *           5 64x64 (given the workspace that paep_predict_workspace_bytes names)
  *   plan[2] workgroups that share one token tile (the inner width r split
  *           between them; 1 = no split, no workspace)
  *   plan[3] chunks of r each of them walks

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                     if (b1) {
                         // the 16 units of this step by scalar loads; the upper half of the wave has units 4 further on
                         // (the offset is opaque so that all steps' loads are not gathered in one place, in registers)
-                        int first = (n * BN + wr * WM + mi * 32 + 16 * s) >> 1;
+                        int first = __builtin_amdgcn_readfirstlane((n * BN + wr * WM + mi * 32 + 16 * s) >> 1);
                         asm volatile("" : "+s"(first));
                         const const_words w = b1_words + first;
 #pragma unroll
@@ -529,7 +529,9 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));         // the copies of the pipeline's end land in this workgroup's LDS
         return;
     }
-    __syncthreads();                                       // all tile reads done before LDS is reused
+    // all tile reads done, and the copies of the pipeline's end landed, before LDS is reused
+    __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));
+    __syncthreads();
 
     // Activation counters of this workgroup's rows, kept in LDS behind the score
     // tile and flushed to the layer's counts once at the end: at most E global
@@ -647,6 +649,9 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
 //             four stages of 24 KB + 64 KB slice.
 //   Small     128 x 128, 4 waves, two workgroups per CU (4 x 16 KB + 16 KB slice each): short inputs
 //             and any r that is a multiple of 128.  SmallWide: the same for E > 64 (64 KB slice).
+//   Tiny      64 x 64, 4 waves, four 64-wide stages, two workgroups per CU: calls whose 128 x 128 tiles would not reach
+//             every CU.  What bounds it is the chain of stages, 0.5 us each whatever is tried on it (eight stages, all
+//             of a stage's fragments read a stage ahead: no faster).
 typedef PfCfg<256, 256, 32, 4, 2, 4, 1> CfgBig;
 typedef PfCfg<256, 256, 64, 2, 2, 4, 1> CfgBigDeep;      // long rows (d >= 4096): half as many barriers per flop
 typedef PfCfg<256, 128, 32, 5, 2, 4, 1> CfgMid;
@@ -654,6 +659,7 @@ typedef PfCfg<256, 256, 32, 3, 1, 8, 1> CfgBigWide;      // 64 < E <= 128, r a m
 typedef PfCfg<256, 128, 32, 4, 1, 8, 1> CfgMidWide;
 typedef PfCfg<128, 128, 32, 4, 2, 2, 2> CfgSmall;
 typedef PfCfg<128, 128, 32, 4, 1, 4, 1> CfgSmallWide;
+typedef PfCfg<64, 64, 64, 4, 2, 2, 2> CfgTiny;
 
 template <class C, int EB32>
 static size_t cfg_lds_bytes(int E)
@@ -1018,10 +1024,19 @@ static hipError_t launch_two_pass(const PredictArgs& a)
 // that, more and smaller workgroups win.
 static bool enough_large_tiles(const PredictArgs& a) { return (long long)((a.T + 255) / 256) * a.L >= 128; }
 
-// 0: small, 1: small wide, 2: big, 3: mid, 4: big wide
-static int pick_cfg(const PredictArgs& a)
+// 0: small, 1: small wide, 2: big, 3: mid, 4: big wide, 5: tiny (with the workspace for its score tiles)
+static bool tiny_wanted(const PredictArgs& a)
+{
+    // 64 x 64 workgroups for everything, up to two per CU; with more experts the score tiles cost what the tiles gain.
+    // Against 128 x 128 tiles, us: 2048 x 2048, 64 experts, one layer, 65 tokens 31.9 / 23.4, 512 tokens 37.3 / 25.3, 1024
+    // tokens 47.4 / 39.7, 2048 tokens 49.5 / 50.0; 1024 x 4096, 16 experts, 2048 tokens 46.4 / 36.1; 2048 x 2048, 128
+    // experts, 512 tokens 38.8 / 31.2; 4096 x 2048, 256 experts, 512 tokens 61.4 / 69.6
+    return a.E <= 128 && a.d % CfgTiny::BK == 0 && (long long)((a.T + 63) / 64) * a.L * (a.r / 64) <= 512;
+}
+static int pick_cfg(const PredictArgs& a, bool roomy)
 {
     const bool large = enough_large_tiles(a);
+    if (roomy && !large && tiny_wanted(a)) return 5;
     if (a.E <= 64) return (large && a.r % 256 == 0) ? 2 : 0;
     if (!large) return 1;
     return (a.E <= 128 && a.r % 256 == 0) ? 4 : 3;
@@ -1037,8 +1052,9 @@ static void cfg_plan(const PredictArgs& a, int* groups, int* cpg)
 
 void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_group)
 {
-    *cfg = pick_cfg(a);
+    *cfg = pick_cfg(a, true);
     switch (*cfg) {
+    case 5: cfg_plan<CfgTiny>(a, groups, chunks_per_group); break;
     case 2: cfg_plan<CfgBig>(a, groups, chunks_per_group); break;
     case 3: cfg_plan<CfgMid>(a, groups, chunks_per_group); break;
     case 4: cfg_plan<CfgBigWide>(a, groups, chunks_per_group); break;
@@ -1047,31 +1063,41 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
     }
 }
 
-// what a call cannot do without
-size_t prefill_workspace_min(const PredictArgs& a)
+static size_t fused_workspace_bytes(const PredictArgs& a, bool roomy)
 {
-    switch (pick_cfg(a)) {
+    switch (pick_cfg(a, roomy)) {
     case 2: return cfg_workspace_bytes<CfgBig>(a);
     case 3: return cfg_workspace_bytes<CfgMid>(a);
     case 4: return cfg_workspace_bytes<CfgBigWide>(a);
+    case 5: return cfg_workspace_bytes<CfgTiny>(a);
     case 1: return cfg_workspace_bytes<CfgSmallWide>(a);
     default: return cfg_workspace_bytes<CfgSmall>(a);
     }
 }
 
-// what it runs fastest with; calls with less, down to the above, run without the second pass
+// what a call cannot do without
+size_t prefill_workspace_min(const PredictArgs& a) { return fused_workspace_bytes(a, false); }
+
+static size_t two_pass_bytes(const PredictArgs& a)
+{
+    const TwoPass p = two_pass_layout(a);
+    return p.h_bytes + p.z_bytes;
+}
+
+// what it runs fastest with; calls with less, down to the above, run without what the rest is for
 size_t prefill_workspace_bytes(const PredictArgs& a)
 {
-    const size_t fused = prefill_workspace_min(a);
-    if (!two_pass_wanted(a)) return fused;
-    const TwoPass p = two_pass_layout(a);
-    return p.h_bytes + p.z_bytes > fused ? p.h_bytes + p.z_bytes : fused;
+    size_t need = prefill_workspace_min(a);
+    const size_t best = two_pass_wanted(a) ? two_pass_bytes(a) : fused_workspace_bytes(a, true);
+    return best > need ? best : need;
 }
 
 hipError_t launch_predict_prefill(const PredictArgs& a)
 {
-    if (two_pass_wanted(a) && a.workspace && a.workspace_bytes >= prefill_workspace_bytes(a)) return launch_two_pass(a);
-    switch (pick_cfg(a)) {
+    if (two_pass_wanted(a) && a.workspace_bytes >= two_pass_bytes(a)) return launch_two_pass(a);
+    switch (pick_cfg(a, a.workspace_bytes >= fused_workspace_bytes(a, true))) {
+    case 5:
+        return a.E <= 32 ? launch_cfg<CfgTiny, 1>(a) : a.E <= 64 ? launch_cfg<CfgTiny, 2>(a) : launch_cfg<CfgTiny, 4>(a);
     case 2:
         if (a.d >= 4096 && a.d % 64 == 0) return a.E <= 32 ? launch_cfg<CfgBigDeep, 1>(a) : launch_cfg<CfgBigDeep, 2>(a);
         return a.E <= 32 ? launch_cfg<CfgBig, 1>(a) : launch_cfg<CfgBig, 2>(a);

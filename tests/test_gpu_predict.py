@@ -611,3 +611,26 @@ def test_counts_of_rows_finished_outside_the_prefill_kernel():
         torch.cuda.synchronize()
         ref = torch.stack([torch.bincount(out.idx[l].flatten().long(), minlength=E) for l in range(L)])
         assert torch.equal(counts.long() - 7, ref)
+
+
+# ------------------------------------------------------------------ 64 x 64 tiles
+@pytest.mark.parametrize("T,d,r,E,k,L,act,bias", [
+    (65, 64, 128, 16, 2, 1, "none", False),                # one stage per chunk, one row in the second tile
+    (127, 192, 256, 33, 6, 3, "silu", True),               # three stages: fewer than the ring
+    (200, 640, 384, 64, 6, 2, "gelu", True),               # two blocks of experts, a ragged tile
+    (512, 448, 512, 128, 8, 1, "none", True),              # four blocks
+    (1000, 320, 512, 65, 12, 2, "silu", False),            # several rows' finalize form, 256 workgroups
+])
+def test_prefill_64x64_tiles(T, d, r, E, k, L, act, bias):
+    """Against the oracle, every row, and the 128 x 128 tiles that run with a smaller workspace: the same hidden vector,
+    the scores' slices of r half as wide (2e-6 of the row's scale, as for the two passes)."""
+    assert _plan(T, d, r, E, k, L).tile == "64x64"
+    x, W1, W2, b1, b2 = _rand_layers(800 + T, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"64x64 T={T} d={d} r={r} E={E}")
+    need = B.predict_workspace_bytes(B.make_desc(T, d, r, E, k, L, B.BF16))
+    one = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, act=act, want_logits=True,
+                    b1=None if b1 is None else _dev(b1, "bf16"), b2=None if b2 is None else _dev(b2, "bf16"),
+                    workspace=torch.empty(need - 1, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    scale = one.logits.abs().amax(dim=2, keepdim=True)
+    assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
