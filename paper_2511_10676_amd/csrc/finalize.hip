@@ -124,6 +124,9 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
     }
     TopList<KMAX> top;
     top.clear();
+    constexpr bool SORTED = KMAX > 2 && NJ * 4 >= KMAX;   // whole lists of keys at a time
+    constexpr int JB = SORTED ? KMAX / 4 : 1;
+    uint64_t more[JB * 4];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int e = 4 * (j * G + g);
@@ -138,8 +141,15 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
             if (logits)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) logits[row * E + e + i] = z[j][i];
+            if constexpr (!SORTED) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) top.insert(make_key(z[j][i], e + i));
+                for (int i = 0; i < 4; ++i) top.insert(make_key(z[j][i], e + i));
+            }
+        }
+        if constexpr (SORTED) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) more[(j % JB) * 4 + i] = e < E ? make_key(z[j][i], e + i) : 0;
+            if (j % JB == JB - 1) top.add(more, j < JB);
         }
     }
     top.template merge_group<G>();

@@ -155,6 +155,34 @@ struct TopList {
                     key[j + st] = a > b ? b : a;
                 }
     }
+    // descending order of KMAX keys by Batcher's odd-even merge sort: 19 compare-exchanges for 8 keys, 63 for 16
+    static __device__ __forceinline__ void sort(uint64_t (&k)[KMAX])
+    {
+#pragma unroll
+        for (int p = 1; p < KMAX; p <<= 1)
+#pragma unroll
+            for (int q = p; q >= 1; q >>= 1)
+#pragma unroll
+                for (int j = q % p; j + q < KMAX; j += 2 * q)
+#pragma unroll
+                    for (int i = 0; i < q; ++i)
+                        if (i + j + q < KMAX && (i + j) / (2 * p) == (i + j + q) / (2 * p)) {
+                            const uint64_t a = k[i + j], b = k[i + j + q];
+                            k[i + j] = a > b ? a : b;
+                            k[i + j + q] = a > b ? b : a;
+                        }
+    }
+    // KMAX more keys (0: none): sorted by themselves and merged, 39 compare-exchanges where inserting 8 takes 64
+    __device__ __forceinline__ void add(uint64_t (&more)[KMAX], bool first)
+    {
+        sort(more);
+        if (first) {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) key[j] = more[j];
+        } else {
+            merge(more);
+        }
+    }
     // every lane of an aligned group of G ends with the group's list
     template <int G> __device__ __forceinline__ void merge_group()
     {
@@ -224,13 +252,24 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
 // consecutive lanes (G a power of two, the group aligned to G).  Lane g of
 // the group scans e = g, g+G, ...; the per-lane lists are merged with
 // xor-shuffles so that every lane ends with the row's list.
-template <int KMAX, int G>
+// SORTED: KMAX scores at a time, sorted and merged; else one inserted after the other (fewer registers).
+template <int KMAX, int G, bool SORTED>
 __device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k, int g,
                                                  int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     TopList<KMAX> top;
     top.clear();
-    for (int e = g; e < E; e += G) top.insert(make_key(zrow[e], e));
+    if constexpr (!SORTED) {
+        for (int e = g; e < E; e += G) top.insert(make_key(zrow[e], e));
+    } else {
+#pragma unroll 1
+        for (int e0 = g; e0 < E; e0 += G * KMAX) {
+            uint64_t more[KMAX];
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) more[j] = e0 + G * j < E ? make_key(zrow[e0 + G * j], e0 + G * j) : 0;
+            top.add(more, false);
+        }
+    }
     top.template merge_group<G>();
     write_selection<KMAX, G>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
         float s = 0.0f;
@@ -380,14 +419,15 @@ __device__ __forceinline__ void wave_softmax_topk_rank(const float (&z)[NV], int
 
 // row_softmax_topk with the smallest list length that holds k (and the runner-up, when the margin is wanted):
 // k <= 16, and k <= 15 when the margin is wanted and k < E.
-template <int G>
+// LEAN: the caller's registers are full (lists of 16 by insertion).
+template <int G, bool LEAN>
 __device__ __forceinline__ void row_softmax_topk_upto16(const float* zrow, int E, int k, int g,
                                                         int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     const int need = k + ((o.margin_row && k < E) ? 1 : 0);
-    if (need <= 2)      row_softmax_topk<2, G>(zrow, E, k, g, idx_row, probs_row, o);
-    else if (need <= 8) row_softmax_topk<8, G>(zrow, E, k, g, idx_row, probs_row, o);
-    else                row_softmax_topk<16, G>(zrow, E, k, g, idx_row, probs_row, o);
+    if (need <= 2)      row_softmax_topk<2, G, false>(zrow, E, k, g, idx_row, probs_row, o);
+    else if (need <= 8) row_softmax_topk<8, G, true>(zrow, E, k, g, idx_row, probs_row, o);
+    else                row_softmax_topk<16, G, !LEAN>(zrow, E, k, g, idx_row, probs_row, o);
 }
 
 }  // namespace paep

@@ -599,7 +599,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         if (tbase + tl < T) {
             const long long row = (long long)layer * T + tbase + tl;
             const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr, counts ? cnt_lds : nullptr};
-            row_softmax_topk_upto16<ZG>(zs + tl * ZP, E, k, gg, idx + row * k, probs + row * k, eo);
+            row_softmax_topk_upto16<ZG, (EB32 > 2)>(zs + tl * ZP, E, k, gg, idx + row * k, probs + row * k, eo);
         }
         __syncthreads();
     };
