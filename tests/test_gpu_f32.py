@@ -2,7 +2,7 @@
 token counts around the two tile heights (32 and 64), widths that are no multiple of a stage (32 columns) or of a
 chunk (32 or 64 units), every count of score blocks per wave, one workgroup per token tile (r of one chunk: softmax
 and top-k inside the kernel) and several (scores through the workspace).  Tolerance: 1e-5 of the row's score scale,
-the checker's bound for fp32 storage."""
+the bound of tests/parity.py for fp32 storage."""
 import pytest
 
 from test_gpu_predict import _run_and_check, _rand_layers
