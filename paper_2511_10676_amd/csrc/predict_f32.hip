@@ -24,22 +24,34 @@
 // Waves that share a block split the columns of each stage and their sums meet in LDS in
 // wave order: a second wave on every SIMD covers the other's barriers and LDS reads even where a
 // CU has one workgroup (512 tokens of one 2048-wide layer: 48 us with one wave to a block, 46 with two).
-// Sums over d are carried in stretches of 256 columns that are added up, so their rounding
-// error stays below that of one long chain of additions.
+// Rounding: the instruction rounds after every product, so a chain of n additions errs like
+// sqrt(n / 2) roundings.  Sums over d are therefore chains of 8 to 32 columns (by d, below) that are
+// added up in double, sums over r chains of 8 units added up per chunk; with that the scores are no further from
+// float64 than those of a lane-split dot product with a butterfly (relative error of the scores, that / chains of 128
+// and 64 / here: 512 tokens 2048 x 2048 1.76e-7 / 2.85e-7 / 1.72e-7, 4 x 8192 tokens 1.77e-7 / 8.4e-7 / 1.72e-7, 256 x 64
+// 1.06e-7 / 2.9e-7 / 1.05e-7).  A chain is folded behind the next stage's LDS reads, when its last product is through the
+// pipe (at the end of its own stage: 64.5 against 61.2 us for the first of these; the long chains: 57.9).
 // Few token tiles: r is cut over several workgroups per tile, their scores meet in the
 // workspace and finalize_kernel adds them; otherwise softmax and top-k follow here.
-// Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for the vector kernel
-// that served this before, 52 us here (46 in this kernel: 96 TFLOP/s).
+// Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for a kernel of vector
+// instructions (a wave per hidden unit), 61 us here.
 #include "paep_device.h"
 #include "paep_internal.h"
 
 namespace paep {
 
 static constexpr int F32_BK = 32;                          // columns of d per stage
-static constexpr int F32_FOLD = 8;                         // stages per stretch of the sum over d
 static constexpr size_t F32_WORKSPACE_MAX = 16u << 20;     // what predict_static can offer
 
 typedef void __attribute__((address_space(3)))* f32_lds_ptr_t;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+__device__ __forceinline__ f32x16 zero16()
+{
+    f32x16 v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+    return v;
+}
 #define PAEP_F32_VMCNT(n) ((((n) & 0xF) | (((n) >> 4) << 14)) | 0x0F70)
 
 // EBW: 32 x 32 score blocks per wave
@@ -59,9 +71,11 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
     constexpr int STAGE = (BM + BN) * F32_BK * 4;          // bytes
     constexpr int HP = BN + 4;                             // pitch of h: 16 lanes of a fragment read hit all 64 banks
     extern __shared__ __attribute__((aligned(16))) unsigned char fsmem[];
-    float* red = (float*)fsmem;                            // the waves' sums, 4 KB each; reuses the ring
-    float* ht = (float*)(fsmem + WAVES * 4096);            // h of the chunk; reuses the ring
-    static_assert(WAVES * 4096 + BM * HP * 4 <= NS * STAGE, "sums and h fit in the ring");
+    constexpr int QPW = 4 / KPARTS;                        // quarters of a block that a wave finishes (of a stage: that it multiplies)
+    constexpr int RED = (KPARTS - 1) * NBLK * 1024 * 8;    // bytes
+    double* red = (double*)fsmem;                          // the waves' sums for one another; reuses the ring
+    float* ht = (float*)(fsmem + RED);                     // h of the chunk; reuses the ring
+    static_assert(RED + BM * HP * 4 <= NS * STAGE, "sums and h fit in the ring");
     float* zs = (float*)fsmem;                             // 32 rows of scores; reuses everything
 
     const int grp = blockIdx.x % groups, tile_id = blockIdx.x / groups;
@@ -87,6 +101,8 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
         lcol[j] = c * 4;
     }
     const int NKT = (d + F32_BK - 1) / F32_BK;
+    const int chain = d < 768 ? 8 : d < 2048 ? 16 : 32;    // columns; shorter ones where d leaves fewer roundings to hide among
+    const int fold_every = chain > 8 * QPW ? chain / (8 * QPW) : 1;      // stages
 
     f32x16 zacc[EBW];
 #pragma unroll
@@ -110,10 +126,17 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
                     rsrc, (f32_lds_ptr_t)(fsmem + slot * STAGE + (wave * NP + j) * 1024), 16,
                     (int)(lcol[j] < left ? src_off[j] : 0x70000000u), kt * (F32_BK * 4), 0, 0);
         };
-        f32x16 acc, tot;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { acc[i] = 0.0f; tot[i] = 0.0f; }
         const int blk = wave % NBLK, kpart = wave / NBLK;  // block of h: units (blk / TBN) * 32.., tokens (blk % TBN) * 32..
+        f32x16 acc = zero16();
+        int fold_in = fold_every + 1;                      // stages until the chain is as long as it may get
+        double tot[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tot[i] = 0.0;             // 29 more bits: the order of these sums no longer matters
+        auto fold = [&]() {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) tot[i] += (double)acc[i];
+            acc = zero16();
+        };
         const int arow = (blk / TBN) * 32 + l32;
         const int brow = BN + (blk % TBN) * 32 + l32;
         for (int s = 0; s < NS - 1; ++s) issue(s, s);
@@ -126,44 +149,50 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
             asm volatile("" ::: "memory");
             issue(kt + NS - 1, slot == 0 ? NS - 1 : slot - 1);
             const float* st = (const float*)(fsmem + slot * STAGE);
-            auto step = [&](int q) {
-                const int c = ((2 * q + g) ^ (l32 & 7)) * 4;
-                const f32x4 a = *(const f32x4*)(st + arow * F32_BK + c);
-                const f32x4 b = *(const f32x4*)(st + brow * F32_BK + c);
+            f32x4 fa[QPW], fb[QPW];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
-            };
+            for (int q = 0; q < QPW; ++q) {
+                const int c = ((2 * (kpart * QPW + q) + g) ^ (l32 & 7)) * 4;
+                fa[q] = *(const f32x4*)(st + arow * F32_BK + c);
+                fb[q] = *(const f32x4*)(st + brow * F32_BK + c);
+            }
+            if (--fold_in == 0) { fold(); fold_in = fold_every; }
 #pragma unroll
-            for (int q = 0; q < 4 / KPARTS; ++q) step(kpart * (4 / KPARTS) + q);
-            if ((kt & (F32_FOLD - 1)) == F32_FOLD - 1) {
+            for (int q = 0; q < QPW; ++q) {
+                if (q > 0 && chain == 8) fold();
 #pragma unroll
-                for (int i = 0; i < 16; ++i) { tot[i] += acc[i]; acc[i] = 0.0f; }
+                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q][i], fb[q][i], acc, 0, 0, 0);
             }
             slot = slot + 1 == NS ? 0 : slot + 1;
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] += tot[i];
+        fold();
         __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(0));     // no copy may land in the ring once it holds h
         __syncthreads();
 
-        // acc[4q + i] = this wave's part of h[unit (blk / TBN) * 32 + 8q + 4g + i][token (blk % TBN) * 32 + l32]
+        // tot[4q + i] = this wave's part of h[unit (blk / TBN) * 32 + 8q + 4g + i][token (blk % TBN) * 32 + l32]: the waves
+        // of a block finish QPW of the four q each, with the others' parts from LDS
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *(f32x4*)(red + ((wave * 4 + q) * 64 + lane) * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        for (int q = 0; q < 4; ++q) {
+            const int owner = q / QPW, part = kpart < owner ? kpart : kpart - 1;
+            if (kpart != owner)
+                *(f64x4*)(red + (((part * NBLK + blk) * 4 + q) * 64 + lane) * 4) = f64x4{tot[4 * q], tot[4 * q + 1], tot[4 * q + 2], tot[4 * q + 3]};
+        }
         __syncthreads();
 #pragma unroll
-        for (int it = tid; it < NBLK * 256; it += THREADS) {
-            const int hb = it >> 8, q = (it >> 6) & 3;     // lane and g are this thread's own
-            f32x4 v = *(const f32x4*)(red + ((hb * 4 + q) * 64 + lane) * 4);
+        for (int q = 0; q < 4; ++q) {
+            if (kpart == q / QPW) {
+                f64x4 v = f64x4{tot[4 * q], tot[4 * q + 1], tot[4 * q + 2], tot[4 * q + 3]};
 #pragma unroll
-            for (int p = 1; p < KPARTS; ++p) v += *(const f32x4*)(red + (((p * NBLK + hb) * 4 + q) * 64 + lane) * 4);
-            const int unit = (hb / TBN) * 32 + 8 * q + 4 * g, tok = (hb % TBN) * 32 + l32;
+                for (int p = 0; p < KPARTS - 1; ++p) v += *(const f64x4*)(red + (((p * NBLK + blk) * 4 + q) * 64 + lane) * 4);
+                const int unit = (blk / TBN) * 32 + 8 * q + 4 * g, tok = (blk % TBN) * 32 + l32;
+                f32x4 hv;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (b1 && u0 + unit + i < r) v[i] += b1[(long long)layer * r + u0 + unit + i];
-                v[i] = apply_act(v[i], act);
+                for (int i = 0; i < 4; ++i) {
+                    if (b1 && u0 + unit + i < r) v[i] += (double)b1[(long long)layer * r + u0 + unit + i];
+                    hv[i] = apply_act((float)v[i], act);
+                }
+                *(f32x4*)(ht + tok * HP + unit) = hv;
             }
-            *(f32x4*)(ht + tok * HP + unit) = v;
         }
         __syncthreads();
         // z^T[E, tokens] += W2[:, chunk] . h^T; score block b = wave + WAVES * j is expert block b / TBN, token block b % TBN
@@ -178,13 +207,16 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
                     w[q] = f32x4{0.f, 0.f, 0.f, 0.f};
                     if (e < E && u0 + 8 * q < r) w[q] = *(const f32x4*)(W2l + (long long)e * r + u0 + 8 * q + 4 * g);
                 }
+                f32x16 zc = zero16();
 #pragma unroll
                 for (int q = 0; q < BN / 8; ++q) {
                     const f32x4 h = *(const f32x4*)(ht + tok * HP + 8 * q + 4 * g);
+                    f32x16 zq = zero16();
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        zacc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q][i], h[i], zacc[j], 0, 0, 0);
+                    for (int i = 0; i < 4; ++i) zq = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q][i], h[i], zq, 0, 0, 0);
+                    zc += zq;
                 }
+                zacc[j] += zc;
             }
             __builtin_amdgcn_sched_barrier(0);             // one block's fetches at a time in registers
         }

@@ -63,3 +63,23 @@ def test_f32_without_a_workspace_keeps_r_in_one_workgroup(T):
     scale = a.logits.abs().amax(dim=2, keepdim=True)
     assert ((a.logits - b.logits).abs() <= 2e-5 * scale).all()
     assert torch.equal(b.idx.long(), torch.sort(b.logits, dim=2, descending=True, stable=True).indices[:, :, :6])
+
+
+@pytest.mark.parametrize("L,T,d,r,E", [(1, 16, 2048, 2048, 64), (1, 512, 2048, 2048, 64), (4, 8192, 2048, 2048, 64),
+                                       (2, 64, 256, 64, 16), (2, 300, 4096, 1024, 64), (1, 33, 768, 512, 8)])
+def test_f32_scores_are_as_close_to_float64_as_a_lane_split_sum(L, T, d, r, E):
+    """A dot product of n terms split over 64 lanes and added up by a butterfly rounds n / 64 times in a lane, on sums
+    that grow towards their end (n / 128 full roundings in the variance), and 6 times between the lanes; a rounding errs
+    by up to 2^-24 of the value, half of that as a standard deviation.  Both layers together:
+    2^-25 * sqrt((d + r) / 128 + 12) of the scores' norm."""
+    import torch
+    from paper_2511_10676_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(d + T)
+    x = torch.randn((L, T, d), device="cuda", generator=g)
+    W1 = torch.randn((L, r, d), device="cuda", generator=g) / d ** 0.5
+    W2 = torch.randn((L, E, r), device="cuda", generator=g) / r ** 0.5
+    z = B.predict(x, W1, W2, min(6, E), want_logits=True).logits.double()
+    exact = torch.stack([(x[l].double() @ W1[l].double().T) @ W2[l].double().T for l in range(L)])
+    err = float((z - exact).norm() / exact.norm())
+    print(f"f32 {L} x {T} x ({d}, {r}, {E}): {err:.2e}", flush=True)
+    assert err <= 2.0 ** -25 * ((d + r) / 128 + 12) ** 0.5
