@@ -189,7 +189,7 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (b1 && u0 + unit + i < r) v[i] += (double)b1[(long long)layer * r + u0 + unit + i];
-                    hv[i] = apply_act((float)v[i], act);
+                    hv[i] = u0 + unit + i < r ? apply_act((float)v[i], act) : 0.0f;   // rows past r: 0 x infinity in a token is no 0
                 }
                 *(f32x4*)(ht + tok * HP + unit) = hv;
             }

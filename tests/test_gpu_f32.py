@@ -83,3 +83,19 @@ def test_f32_scores_are_as_close_to_float64_as_a_lane_split_sum(L, T, d, r, E):
     err = float((z - exact).norm() / exact.norm())
     print(f"f32 {L} x {T} x ({d}, {r}, {E}): {err:.2e}", flush=True)
     assert err <= 2.0 ** -25 * ((d + r) / 128 + 12) ** 0.5
+
+
+@pytest.mark.parametrize("T,r", [(3, 40), (70, 40), (70, 200)])
+def test_f32_infinite_token_does_not_meet_the_padding_of_r(T, r):
+    """Positive weights and one token with an infinity: its scores are infinities, not NaN, although r is no multiple of
+    a chunk; the other tokens' scores are what they are without it."""
+    import torch
+    from paper_2511_10676_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x, W1, W2 = (torch.rand(s, device="cuda", generator=g) + 0.1 for s in ((1, T, 48), (1, r, 48), (1, 20, r)))
+    plain = B.predict(x, W1, W2, 3, want_logits=True).logits
+    x[0, 1, 7] = float("inf")
+    z = B.predict(x, W1, W2, 3, want_logits=True).logits
+    assert bool((z[0, 1] == float("inf")).all())
+    keep = torch.arange(T, device="cuda") != 1
+    assert torch.equal(z[0, keep], plain[0, keep])
