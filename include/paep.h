@@ -102,7 +102,9 @@ typedef struct {
 /* Bytes of device workspace paep_predict runs fastest with for this shape (0 is
  * possible).  Calls with less run on where the work can be laid out without it
  * (large bf16 calls of more than 64 experts: the hidden vectors then stay on
- * chip; fp32), else they return PAEP_ERR_WORKSPACE.  Returns 0 for an invalid descriptor; paep_predict reports the reason. */
+ * chip; T <= 64 with few layers: wider slices of r, L * (r / 64) * T * E * 4
+ * bytes; fp32), else they return PAEP_ERR_WORKSPACE.  Returns 0 for an invalid
+ * descriptor; paep_predict reports the reason. */
 size_t paep_predict_workspace_bytes(const paep_predict_desc *desc);
 
 /* Which kernel family AUTO resolves to for this shape (a paep_path value),

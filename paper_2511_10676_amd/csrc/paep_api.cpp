@@ -133,7 +133,7 @@ static size_t path_workspace_bytes(int path, const paep::PredictArgs& a)
 static size_t path_workspace_min(int path, const paep::PredictArgs& a)
 {
     switch (path) {
-    case PAEP_PATH_DECODE: return paep::decode_workspace_bytes(a);
+    case PAEP_PATH_DECODE: return paep::decode_workspace_min(a);
     case PAEP_PATH_PREFILL: return paep::prefill_workspace_min(a);
     default: return 0;                                       // the fp32 kernel: r stays with one workgroup per token tile
     }

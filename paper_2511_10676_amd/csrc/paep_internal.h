@@ -64,6 +64,7 @@ hipError_t launch_predict_simple(const PredictArgs& a);
 // bf16 weight-streaming kernel for T <= 64
 bool decode_supported(const PredictArgs& a);
 size_t decode_workspace_bytes(const PredictArgs& a);
+size_t decode_workspace_min(const PredictArgs& a);       // with less than this the call is refused
 hipError_t launch_predict_decode(const PredictArgs& a);
 
 // bf16 fused matrix-core kernel for large T

@@ -675,21 +675,27 @@ static int decode_thin_units(const PredictArgs& a)
     return 0;
 }
 
-static size_t decode_partial_bytes(const PredictArgs& a)
+// the slices' scores in the workspace: of the d-split and the row-split kernel (sized for slices of 64 for both: callers
+// know this size), and of the thin one
+size_t decode_workspace_min(const PredictArgs& a)
 {
-    const int thin = decode_thin_units(a), rs = thin ? thin : RS;
-    return sizeof(float) * (size_t)a.L * (size_t)(a.r / rs) * (size_t)a.T * (size_t)a.E;
+    return sizeof(float) * (size_t)a.L * (size_t)(a.r / RS) * (size_t)a.T * (size_t)a.E;
+}
+static size_t decode_thin_bytes(const PredictArgs& a, int units)
+{
+    return sizeof(float) * (size_t)a.L * (size_t)(a.r / units) * (size_t)a.T * (size_t)a.E;
 }
 
-// never less for more tokens, so that a workspace for the longest batch serves the shorter ones
+// What a call runs fastest with; with less, down to the minimum, the thin kernel's calls go to the row-split one.
+// Never less for more tokens, so that a workspace for the longest batch serves the shorter ones as well as it can.
 size_t decode_workspace_bytes(const PredictArgs& a)
 {
-    size_t need = decode_partial_bytes(a);
-    for (int t = 16; t < a.T; t += 16) {                      // the token counts at which the kernel may change
-        PredictArgs b = a;
-        b.T = t;
-        const size_t n = decode_partial_bytes(b);
-        if (n > need) need = n;
+    size_t need = decode_workspace_min(a);
+    PredictArgs b = a;
+    for (int t = 16; t < a.T + 16; t += 16) {                 // the token counts at which the kernel may change
+        b.T = t < a.T ? t : a.T;
+        const int units = decode_thin_units(b);
+        if (units && decode_thin_bytes(b, units) > need) need = decode_thin_bytes(b, units);
     }
     return need;
 }
@@ -702,7 +708,8 @@ static bool decode_by_rows(const PredictArgs& a) { return a.r % RW_RS == 0; }
 hipError_t launch_predict_decode(const PredictArgs& a)
 {
     const bool rows_kernel = decode_by_rows(a);
-    const int thin = decode_thin_units(a);
+    int thin = decode_thin_units(a);
+    if (thin && a.workspace_bytes < decode_thin_bytes(a, thin)) thin = 0;
     const int S = a.r / (thin ? thin : (rows_kernel ? RW_RS : RS));
     const int total = S * a.L;
     float* partial = (float*)a.workspace;

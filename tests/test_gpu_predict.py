@@ -164,6 +164,27 @@ def test_decode_workspace_for_more_tokens_serves_fewer(L, r, E, d):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("L,T,d,r,E,act", [(2, 64, 512, 2048, 64, "none"), (1, 1, 2048, 1024, 128, "silu"),
+                                           (4, 16, 256, 2048, 200, "gelu"), (1, 33, 384, 128, 60, "none")])
+def test_decode_runs_in_the_scores_of_64_wide_slices(L, T, d, r, E, act):
+    """The workspace that every decode call can do with: L * (r / 64) * T * E floats, never more for fewer layers.  Thin
+    slices want more and are left out then: the same hidden vector to the bit, the scores in wider slices (2e-6 of the
+    row's scale: r products of 2^-24 each, as a random walk, four times over).  One byte less is refused."""
+    x, W1, W2, b1, b2 = _rand_layers(450 + T, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), 5
+    opts = dict(b1=_dev(b1, "bf16"), b2=_dev(b2, "bf16"), act=act, want_logits=True, path="decode")
+    need = 4 * L * (r // 64) * T * E
+    assert B.predict_workspace_bytes(B.make_desc(T, d, r, E, 5, L, B.BF16)) > need
+    best = B.predict(*args, **opts)
+    least = B.predict(*args, workspace=torch.empty(need, dtype=torch.uint8, device="cuda"), **opts)
+    torch.cuda.synchronize()
+    scale = best.logits.abs().amax(dim=2, keepdim=True)
+    assert ((best.logits - least.logits).abs() <= 2e-6 * scale).all()
+    assert torch.equal(least.idx.long(), torch.sort(least.logits, dim=2, descending=True, stable=True).indices[:, :, :5])
+    with pytest.raises(B.PaepError, match="WORKSPACE"):
+        B.predict(*args, workspace=torch.empty(need - 1, dtype=torch.uint8, device="cuda"), **opts)
+
+
 def test_decode_row_split_many_experts_and_wide_k():
     # 512 experts (eight per lane in the finalize kernel, four expert blocks per wave in the slices kernel) and k = 32
     x, W1, W2, b1, b2 = _rand_layers(57, L=2, T=40, d=256, r=256, E=512, dtype="bf16", bias=True)
