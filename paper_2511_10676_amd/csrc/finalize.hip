@@ -8,12 +8,14 @@
 //   finalize_rows_kernel  4 to 16 lanes per row, up to 16 scores each as float4 loads, sorted lists merged
 //                         between the lanes: fewer instructions per row, for calls of many.  Both move few
 //                         bytes; what bounds them at many rows is instructions: 262144 rows of 16 experts
-//                         in 2 slices 463 us with a wave per row, 14 us here; 7826 rows of 64 in 8 slices
-//                         20 -> 15 us; 1952 rows of 16 in 8 slices 7.7 -> 5.8 us; 512 rows equal.
+//                         in 2 slices 463 us with a wave per row, 14 us here; 16384 rows of 64 in 8 slices
+//                         30 -> 9 us (where the line lies: finalize_rows_from)
 //
 // The partial scores are laid out [tile][slice][BM][E]: a tile is BM token rows
 // of one layer, tiles_per_layer of them to a layer (BM = T and one tile per
 // layer where the producer does not tile the tokens).
+#include <limits.h>
+
 #include "paep_device.h"
 #include "paep_internal.h"
 
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
 
 // Activation counts of the rows first_row .. L * T - 1 of a call, from their selections: counted in LDS, COUNT_ROWS rows
 // of one layer at a time, and added to the layer's counters once.  (One global atomic per selection, as the rows'
-// lanes do it in calls of few rows, meets the others of a popular expert on one address.)
+// lanes do it where a layer has few rows, meets the others of a popular expert on one address.)
 static constexpr int COUNT_ROWS = 2048;
 __global__ __launch_bounds__(FIN_THREADS) void count_selected_kernel(int T, int E, int k, long long first_row,
                                                                      const int32_t* __restrict__ idx,
@@ -188,15 +190,36 @@ __global__ __launch_bounds__(FIN_THREADS) void count_selected_kernel(int T, int 
         if (cnt[e]) atomicAdd(&counts[layer * E + e], cnt[e]);
 }
 
-// From this many rows on, finalize_rows_kernel: a chip of waves holds 8192 rows at a time as one wave each, and at a
-// thousand the two forms take the same 6 us.
-static constexpr int FIN_MANY_ROWS = 1024;
+// Rows from which on finalize_rows_kernel is the faster form; `need` keys are kept per row.  It takes a row's S slices in
+// rounds of four and fewer waves for the same rows, so it wants more of them the more slices there are and the longer the
+// lists; the other form takes a row per wave, up to 32 slices at once, and 8192 rows at a time.  us, wave per row /
+// several lanes per row:
+//   16 experts, k = 2 or 6   1024 rows, 16 slices 6.2 / 4.3-5.7; 32 slices 1024 rows 6.3 / 7.1, 1536 rows 7.4 / 7.1
+//   64, k = 6     2 slices: 1536 rows 7.3 / 6.9; 8: 2048 rows 7.4 / 7.9, 3072 rows 8.6 / 7.9; 16: 1664 rows 7.4 / 9.4,
+//                 4096 rows 9.7 / 9.5; 32: 4096 rows 10.1 / 13.3, 8192 rows 19.9 / 17.8
+//   64, k = 12    2 slices: 4096 rows 9.7 / 9.9; 8: 5120 rows 12.2 / 10.9; 16: 6144 rows 13.8 / 13.0
+//   128, k = 8    2 slices: 2048 rows 7.8 / 8.0; 8: 3072 rows 9.0 / 8.9; 16: 4096 rows 10.1 / 11.0, 8192 rows 17.4 / 17.0
+//   256, k = 8    2 slices: 2048 rows 8.0 / 8.8, 4096 rows 10.1 / 8.8; 8: 4096 rows 10.4 / 10.2; 16: 8192 rows 25.9 / 26.4,
+//                 16384 rows 43.9 / 44.9
+static int finalize_rows_from(int E, int S, int need)
+{
+    if (E <= 16) return S * 48 > (need <= 8 ? 1024 : 2048) ? S * 48 : need <= 8 ? 1024 : 2048;
+    if (E > 128 && S >= 16) return INT_MAX;
+    return (need <= 8 ? 1024 : 4096) + 192 * S + (E > 64 ? 8 * E : 0);
+}
+
+// Rows from which on the counts are taken from the selections, in calls whose layers have more rows than a decode batch
+// (or where every row selects most of the experts): one launch more, 2 us, where atomics from the rows' lanes cost
+// 0.2 to 1 us for 16 x 64 rows, 12 us for 16 x 512 of 64 experts.
+static constexpr int FIN_COUNT_ROWS = 1024;
 
 hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, int tiles, int BM, int tile0,
                            int tiles_per_layer)
 {
     const int rows = tiles * BM;
-    if (a.counts && rows >= FIN_MANY_ROWS) {
+    const int need = a.k + ((a.margin && a.k < a.E) ? 1 : 0);     // sorted keys per row
+    const bool many = a.E % 4 == 0 && a.E <= 256 && need <= 16 && rows >= finalize_rows_from(a.E, S, need);
+    if (a.counts && rows >= FIN_COUNT_ROWS && (a.T > 64 || (many && 2 * a.k > a.E))) {
         PredictArgs b = a;
         b.counts = nullptr;
         const hipError_t err = launch_finalize(b, partial, S, tiles, BM, tile0, tiles_per_layer);
@@ -208,8 +231,7 @@ hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, in
                            dim3(FIN_THREADS), sizeof(int32_t) * a.E, a.stream, a.T, a.E, a.k, first_row, a.idx, a.counts);
         return hipGetLastError();
     }
-    const int need = a.k + ((a.margin && a.k < a.E) ? 1 : 0);     // sorted keys per row
-    if (rows >= FIN_MANY_ROWS && a.E % 4 == 0 && a.E <= 256 && need <= 16) {
+    if (many) {
 #define PAEP_LAUNCH_FINR(NJV, GV, KV)                                                                            \
     hipLaunchKernelGGL((finalize_rows_kernel<NJV, GV, KV>), dim3((rows + FIN_THREADS / GV - 1) / (FIN_THREADS / GV)), \
                        dim3(FIN_THREADS), 0, a.stream, a.T, a.E, a.k, S, rows, BM, tile0, tiles_per_layer, partial, \

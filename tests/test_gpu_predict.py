@@ -539,13 +539,12 @@ def test_fold_batchnorm_matches_the_oracle_and_feeds_predict(dtype):
                                         (64, 15, True), (100, 8, True), (128, 1, True), (132, 12, False), (256, 8, True),
                                         (130, 6, True), (64, 20, False)])
 def test_finalize_many_rows(E, k, margin):
-    """1040 rows whose slices of r meet in the workspace: several lanes per row with 4, 16, 8 x 16 and 16 x 16
-    scores between them and lists of 2, 8 and 16; the last two shapes (E no multiple of 4, k above 16) take a wave
-    per row.  Every row against the oracle; the margin equals the difference of the two exported scores."""
-    x, W1, W2, b1, b2 = _rand_layers(700 + E + k, L=16, T=65, d=128, r=256, E=E, dtype="bf16", bias=True)
+    """6400 rows whose slices of r (two or four) meet in the workspace: several lanes per row with 4, 16, 8 x 16 and
+    16 x 16 scores between them and lists of 2, 8 and 16; the last two shapes (E no multiple of 4, k above 16) take a
+    wave per row.  Every row against the oracle; the margin equals the difference of the two exported scores."""
+    T = 400 if k <= 16 else 64
+    x, W1, W2, b1, b2 = _rand_layers(700 + E + k, L=16, T=T, d=128, r=256, E=E, dtype="bf16", bias=True)
     path = "auto" if k <= 16 else "decode"
-    T = 65 if k <= 16 else 64
-    x = x[:, :T]
     _run_and_check(x, W1, W2, b1, b2, k, "bf16", path=path, what=f"finalize E={E} k={k}")
     if margin:
         o = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, b1=_dev(b1, "bf16"), b2=_dev(b2, "bf16"),
@@ -620,6 +619,18 @@ def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     assert ((two.logits - one.logits).abs() <= 2e-6 * scale).all()
     ref = torch.stack([torch.bincount(two.idx[l].flatten().long(), minlength=E) for l in range(L)])
     assert torch.equal(counts.long(), ref)
+
+
+@pytest.mark.parametrize("T,E,k", [(64, 64, 6), (63, 16, 2), (64, 16, 12), (33, 16, 12)])
+def test_counts_of_a_decode_batch(T, E, k):
+    """33 layers, 1089 to 2112 rows: counted by a wave per row, by several lanes per row, from the selections of those."""
+    x, W1, W2, _, _ = _rand_layers(T + k, L=33, T=T, d=128, r=256, E=E, dtype="bf16")
+    counts = torch.full((33, E), 7, dtype=torch.int32, device="cuda")
+    out = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, counts=counts)
+    torch.cuda.synchronize()
+    assert out.path == "decode"
+    ref = torch.stack([torch.bincount(out.idx[l].flatten().long(), minlength=E) for l in range(33)])
+    assert torch.equal(counts.long() - 7, ref)
 
 
 def test_counts_of_rows_finished_outside_the_prefill_kernel():
