@@ -91,8 +91,11 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(
     else                   wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
 }
 
-// G lanes per row; lane g owns experts 4 * (j * G + g) + i, j < NJ, i < 4.  E a multiple of 4, lists of KMAX.
-template <int NJ, int G, int KMAX>
+typedef f32x4 __attribute__((aligned(4))) f32x4_words;
+
+// G lanes per row; lane g owns experts 4 * (j * G + g) + i, j < NJ, i < 4.  Lists of KMAX.  RAGGED: E is no multiple of
+// 4; the loads are then aligned to words only, and the last lane's scores past E are left out one by one.
+template <int NJ, int G, int KMAX, bool RAGGED>
 __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
     int T, int E, int k, int S, int rows, int BM, int tile0, int tiles_per_layer, const float* __restrict__ partial,
     const void* __restrict__ b2, int b2_f32, int32_t* __restrict__ idx, float* __restrict__ probs,
@@ -117,7 +120,17 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
         for (int u = 0; u < CH; ++u)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                if (s0 + u < S && 4 * (j * G + g) < E) p[u][j] = *(const f32x4*)(src + (s0 + u) * sstride + 4 * j * G);
+                if (s0 + u < S && 4 * (j * G + g) < E) {
+                    const float* at = src + (s0 + u) * sstride + 4 * j * G;
+                    if (!RAGGED) {
+                        p[u][j] = *(const f32x4*)at;
+                    } else if (4 * (j * G + g) + 3 < E) {
+                        p[u][j] = *(const f32x4_words*)at;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) p[u][j][i] = 4 * (j * G + g) + i < E ? at[i] : 0.f;
+                    }
+                }
 #pragma unroll
         for (int u = 0; u < CH; ++u)
 #pragma unroll
@@ -136,21 +149,24 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
             if (b2) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
+                    if (RAGGED && e + i >= E) continue;
                     const long long c = (long long)layer * E + e + i;
                     z[j][i] += b2_f32 ? ((const float*)b2)[c] : bf16_bits_to_f32(((const uint16_t*)b2)[c]);
                 }
             }
             if (logits)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) logits[row * E + e + i] = z[j][i];
+                for (int i = 0; i < 4; ++i)
+                    if (!RAGGED || e + i < E) logits[row * E + e + i] = z[j][i];
             if constexpr (!SORTED) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) top.insert(make_key(z[j][i], e + i));
+                for (int i = 0; i < 4; ++i)
+                    if (!RAGGED || e + i < E) top.insert(make_key(z[j][i], e + i));
             }
         }
         if constexpr (SORTED) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) more[(j % JB) * 4 + i] = e < E ? make_key(z[j][i], e + i) : 0;
+            for (int i = 0; i < 4; ++i) more[(j % JB) * 4 + i] = (RAGGED ? e + i : e) < E ? make_key(z[j][i], e + i) : 0;
             if (j % JB == JB - 1) top.add(more, j < JB);
         }
     }
@@ -162,7 +178,7 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (4 * (j * G + g) < E && z[j][i] == z[j][i]) s += __expf(z[j][i] - m);
+                if (4 * (j * G + g) + (RAGGED ? i : 0) < E && z[j][i] == z[j][i]) s += __expf(z[j][i] - m);
         return s;
     });
 }
@@ -201,11 +217,15 @@ __global__ __launch_bounds__(FIN_THREADS) void count_selected_kernel(int T, int 
 //   128, k = 8    2 slices: 2048 rows 7.8 / 8.0; 8: 3072 rows 9.0 / 8.9; 16: 4096 rows 10.1 / 11.0, 8192 rows 17.4 / 17.0
 //   256, k = 8    2 slices: 2048 rows 8.0 / 8.8, 4096 rows 10.1 / 8.8; 8: 4096 rows 10.4 / 10.2; 16: 8192 rows 25.9 / 26.4,
 //                 16384 rows 43.9 / 44.9
+// The scores past E of the last lane cost E that is no multiple of 4 a third more rows (62, k = 6: 8 slices 3072 rows
+// 8.7 / 9.3, 4096 rows 9.8 / 9.3; 16: 5120 rows 12.4 / 11.9).
 static int finalize_rows_from(int E, int S, int need)
 {
-    if (E <= 16) return S * 48 > (need <= 8 ? 1024 : 2048) ? S * 48 : need <= 8 ? 1024 : 2048;
+    int from = need <= 8 ? 1024 : E <= 16 ? 2048 : 4096;
     if (E > 128 && S >= 16) return INT_MAX;
-    return (need <= 8 ? 1024 : 4096) + 192 * S + (E > 64 ? 8 * E : 0);
+    if (E > 16) from += 192 * S + (E > 64 ? 8 * E : 0);
+    else if (S * 48 > from) from = S * 48;
+    return E % 4 == 0 ? from : from / 3 * 4;
 }
 
 // Rows from which on the counts are taken from the selections, in calls whose layers have more rows than a decode batch
@@ -218,7 +238,7 @@ hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, in
 {
     const int rows = tiles * BM;
     const int need = a.k + ((a.margin && a.k < a.E) ? 1 : 0);     // sorted keys per row
-    const bool many = a.E % 4 == 0 && a.E <= 256 && need <= 16 && rows >= finalize_rows_from(a.E, S, need);
+    const bool many = a.E <= 256 && need <= 16 && rows >= finalize_rows_from(a.E, S, need);
     if (a.counts && rows >= FIN_COUNT_ROWS && (a.T > 64 || (many && 2 * a.k > a.E))) {
         PredictArgs b = a;
         b.counts = nullptr;
@@ -233,8 +253,8 @@ hipError_t launch_finalize(const PredictArgs& a, const float* partial, int S, in
     }
     if (many) {
 #define PAEP_LAUNCH_FINR(NJV, GV, KV)                                                                            \
-    hipLaunchKernelGGL((finalize_rows_kernel<NJV, GV, KV>), dim3((rows + FIN_THREADS / GV - 1) / (FIN_THREADS / GV)), \
-                       dim3(FIN_THREADS), 0, a.stream, a.T, a.E, a.k, S, rows, BM, tile0, tiles_per_layer, partial, \
+    hipLaunchKernelGGL((a.E % 4 == 0 ? finalize_rows_kernel<NJV, GV, KV, false> : finalize_rows_kernel<NJV, GV, KV, true>), \
+                       dim3((rows + FIN_THREADS / GV - 1) / (FIN_THREADS / GV)), dim3(FIN_THREADS), 0, a.stream, a.T, a.E, a.k, S, rows, BM, tile0, tiles_per_layer, partial, \
                        a.b2, a.dtype == 0 ? 1 : 0, a.idx, a.probs, a.logits, a.counts, a.prob_mode, a.margin)
 #define PAEP_LAUNCH_FINR_K(NJV, GV)                                                                              \
     do {                                                                                                         \

@@ -537,11 +537,12 @@ def test_fold_batchnorm_matches_the_oracle_and_feeds_predict(dtype):
 
 @pytest.mark.parametrize("E,k,margin", [(4, 4, True), (12, 2, False), (16, 7, True), (20, 16, False), (64, 8, False),
                                         (64, 15, True), (100, 8, True), (128, 1, True), (132, 12, False), (256, 8, True),
-                                        (130, 6, True), (64, 20, False)])
+                                        (130, 6, True), (64, 20, False), (13, 8, True),
+                                        (15, 15, False), (62, 6, False), (63, 12, True), (250, 2, False), (255, 15, True)])
 def test_finalize_many_rows(E, k, margin):
     """6400 rows whose slices of r (two or four) meet in the workspace: several lanes per row with 4, 16, 8 x 16 and
-    16 x 16 scores between them and lists of 2, 8 and 16; the last two shapes (E no multiple of 4, k above 16) take a
-    wave per row.  Every row against the oracle; the margin equals the difference of the two exported scores."""
+    16 x 16 scores between them and lists of 2, 8 and 16, E a multiple of 4 and not; k above 16 takes a wave per row.
+    Every row against the oracle; the margin equals the difference of the two exported scores."""
     T = 400 if k <= 16 else 64
     x, W1, W2, b1, b2 = _rand_layers(700 + E + k, L=16, T=T, d=128, r=256, E=E, dtype="bf16", bias=True)
     path = "auto" if k <= 16 else "decode"
@@ -552,6 +553,23 @@ def test_finalize_many_rows(E, k, margin):
         z = o.logits.sort(dim=2, descending=True).values
         want = z[:, :, k - 1] - z[:, :, k] if k < E else torch.full_like(o.margin, float("inf"))
         assert torch.equal(o.margin, want)
+
+
+@pytest.mark.parametrize("E,k", [(1, 1), (2, 2), (3, 1), (5, 5), (7, 3)])
+def test_finalize_many_rows_of_few_experts(E, k):
+    """The same with so few experts that a row's largest score can be close to 0, which the oracle check's scale (that
+    score) does not fit: scores within 0.02 of the scores' norm over the batch (bf16 rounding of h, the bound of the
+    oracle check), selection, probabilities and margin from the exported scores."""
+    x, W1, W2, _, b2 = _rand_layers(750 + E, L=16, T=400, d=128, r=256, E=E, dtype="bf16", bias=True)
+    xs, a, b, c = (_dev(v, "bf16") for v in (x, W1, W2, b2))
+    o = B.predict(xs, a, b, k, b2=c, want_logits=True, want_margin=True)
+    z = torch.matmul(torch.matmul(xs.double(), a.double().transpose(1, 2)), b.double().transpose(1, 2)) + c.double()[:, None]
+    assert float((o.logits - z).abs().max()) <= 0.02 * float(z.square().mean().sqrt()) * 5     # 5: the largest of 6400 E
+    srt, order = torch.sort(o.logits, dim=2, descending=True, stable=True)
+    assert torch.equal(o.idx.long(), order[:, :, :k])
+    want = torch.softmax(o.logits.double(), dim=2).gather(2, order[:, :, :k])
+    assert float(((o.probs - want) / want).abs().max()) <= parity.PROB_TOL_OWN
+    assert torch.equal(o.margin, srt[:, :, k - 1] - srt[:, :, k] if k < E else torch.full_like(o.margin, float("inf")))
 
 
 # ------------------------------------------------------------------ activations on the bf16 grid
