@@ -944,14 +944,22 @@ static TwoPass two_pass_layout(const PredictArgs& a)
     return p;
 }
 
-// Where the fused kernel is the slower one.  Fused against two passes, us: 256 experts, 16 layers x 8192 tokens 2048 x 2048
-// 1602 / 1234, 2048 x 4096 2863 / 2154; 200 experts, 32 layers x 8192 1024 x 2048 1667 / 1353; 128 experts, 2048 x 2048
-// 16 layers x 4096 tokens 599 / 610, 48 x 2048 tokens 948 / 921, 48 x 6011 with GELU 3373 / 3040; 64 experts, 32 x 4096
-// 1030 / 1101, 26 x 8192 1621 / 1850.
+// Where the fused kernel is the slower one.  What two passes cost goes with r (h written and read again), what they save
+// with d, more of it where the fused kernel has to be 128 units wide (E > 128) and where GELU meets 192 accumulators in
+// it (64 < E <= 128).  Two passes / fused:
+//   256 experts  d = 512 0.94-1.18, 768 0.82-1.03, 1024 0.80-0.99, 2048 0.74-0.89, 4096 0.66-0.77 (from 256 tiles on, 320 to
+//                640 of them, r = 1024 to 4096); 192 tiles: 0.91 or less at any d
+//   130 experts  d = 768 0.84-1.11, 1024 0.81-1.01, 2048 0.75-0.90
+//   128 experts  d = 1024 1.06-1.29, 1536 1.01-1.22, 2048 0.96-1.08, 2304 0.91-1.03, 2560 0.89-1.02, 4096 0.92-1.04
+//                (384 to 1568 tiles); with SiLU 2048 0.97-1.06, 2560 0.88-1.00; with GELU 1024 0.91-1.07, 1536 0.86-1.03,
+//                2048 0.82-0.92
+//   64 experts   slower: 2048 x 2048, 32 layers x 4096 tokens 1030 / 1101 us, 26 x 8192 1621 / 1850 us
 static bool two_pass_wanted(const PredictArgs& a)
 {
     const long long tiles = (long long)((a.T + 255) / 256) * a.L;
-    return a.r % CfgFirst::BN == 0 && (a.E > 128 ? tiles >= 128 : a.E > 64 && tiles >= 384);
+    if (a.r % CfgFirst::BN != 0) return false;
+    if (a.E > 128) return tiles >= 128 && (tiles < 256 || a.d >= (a.E < 192 ? 1024 : 768));
+    return a.E > 64 && tiles >= 384 && a.d >= (a.act == 2 ? 1536 : 2560);
 }
 
 template <int MODE>

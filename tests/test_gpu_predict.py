@@ -609,12 +609,26 @@ def test_activation_of_every_bf16_value(path, T, d, r, act):
 
 
 # ------------------------------------------------------------------ two passes for many experts
+@pytest.mark.parametrize("T,d,r,E,L,act,two", [
+    (8192, 512, 4096, 256, 16, "none", False), (8192, 768, 4096, 256, 16, "none", True),
+    (8192, 768, 2048, 140, 16, "none", False), (8192, 1024, 2048, 140, 16, "none", True),
+    (2048, 64, 1024, 200, 24, "none", True), (8192, 2048, 4096, 128, 16, "none", False),
+    (8192, 2560, 4096, 128, 16, "none", True), (8192, 1024, 2048, 128, 16, "gelu", False),
+    (8192, 1536, 2048, 128, 16, "gelu", True), (8192, 2048, 2048, 64, 16, "none", False),
+])
+def test_two_passes_are_chosen_where_d_pays_for_h(T, d, r, E, L, act, two):
+    """The workspace holds the hidden vectors of a layer at least, or not.  (With 128 experts and d = 256 two passes take 1.5
+    times as long as the fused kernel.)"""
+    assert (B.predict_workspace_bytes(B.make_desc(T, d, r, E, 8, L, B.BF16, act=act)) >= 2 * T * r) == two
+
+
 @pytest.mark.parametrize("T,d,r,E,k,L,act,bias", [
     (4097, 64, 256, 129, 8, 8, "none", False),             # 17 tiles a layer, one row in the last; one chunk of r
     (8191, 96, 768, 256, 15, 4, "silu", True),             # three chunks: one workgroup per tile takes them all
     (1000, 64, 1024, 200, 3, 33, "gelu", True),            # four chunks, four workgroups per tile; 132 tiles
-    (4100, 32, 512, 250, 8, 16, "none", True),             # scores that are no multiple of 4 apart
-    (12300, 64, 256, 100, 6, 8, "none", True),             # up to 128 experts: from 384 tiles on
+    (4100, 768, 512, 250, 8, 16, "none", True),            # scores that are no multiple of 4 apart
+    (6000, 1024, 256, 140, 8, 11, "none", True),           # 264 tiles: from 256 on not with narrower tokens
+    (12300, 1536, 256, 100, 6, 8, "gelu", True),           # up to 128 experts: from 384 tiles on
 ])
 def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     """First layer and scores as two kernels, against the oracle, and the fused kernel that runs with a smaller
@@ -623,7 +637,7 @@ def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     x, W1, W2, b1, b2 = _rand_layers(700 + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"two passes T={T} d={d} r={r} E={E}",
                              rows=np.unique(np.concatenate([np.arange(0, T, 9), np.arange(T - 300, T)])))
-    need = B.predict_workspace_bytes(B.make_desc(T, d, r, E, k, L, B.BF16))
+    need = B.predict_workspace_bytes(B.make_desc(T, d, r, E, k, L, B.BF16, act=act))
     assert need >= 2 * T * r                               # h of a layer at least
     counts = torch.zeros((L, E), dtype=torch.int32, device="cuda")
     args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k
