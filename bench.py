@@ -221,12 +221,13 @@ class Runner:
             ach = flops * w.L / (predict_ms * 1e-3) / 1e12
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": measured_traffic("prefill", w.name, T),
-                    "kernel": "prefill_kernel", "kernel_ms": round(predict_ms, 4)}
+                    "kernel": ("prefill_kernel+scores_of_h_kernel+finalize" if self.plan.tile.endswith("two passes")
+                               else "prefill_kernel"), "kernel_ms": round(predict_ms, 4)}
         else:
             ach = nbytes * w.L / (predict_ms * 1e-3) / 1e9
             roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": measured_traffic("decode", w.name, T),
-                    "kernel": ("decode_rows_kernel" if w.r % 128 == 0 else "decode_partial_kernel") + "+decode_finalize_kernel",
+                    "kernel": ("decode_rows_kernel" if w.r % 128 == 0 else "decode_partial_kernel") + "+finalize",
                     "kernel_ms": round(predict_ms, 4)}
         self.i = 0                       # one untimed step on bank 0, whose weights the labels were drawn for
         self.step()

@@ -214,9 +214,11 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  *   plan[0] kernel family (paep_path)
  *   plan[1] tile configuration of the prefill family (0 otherwise):
  *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
- *           5 64x64 (given the workspace that paep_predict_workspace_bytes names)
+ *           5 64x64, 6 256x256 for the first layer and the scores as a second
+ *           kernel (5 and 6 given the workspace that
+ *           paep_predict_workspace_bytes names; with less, one of the others)
  *   plan[2] workgroups that share one token tile (the inner width r split
- *           between them; 1 = no split, no workspace)
+ *           between them; 1 = no split, and but for tile 6 no workspace)
  *   plan[3] chunks of r each of them walks
  * Returns PAEP_OK, or the status paep_predict would give for the descriptor.
  */

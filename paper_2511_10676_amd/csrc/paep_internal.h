@@ -72,7 +72,8 @@ bool prefill_supported(const PredictArgs& a);
 size_t prefill_workspace_bytes(const PredictArgs& a);
 size_t prefill_workspace_min(const PredictArgs& a);      // with less than this the call is refused
 hipError_t launch_predict_prefill(const PredictArgs& a);
-// tile configuration id, workgroups per token tile, chunks of r per workgroup (what the launcher will use)
+// tile configuration id, workgroups per token tile, chunks of r per workgroup (what the launcher will use, given the
+// workspace of prefill_workspace_bytes)
 void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_group);
 
 size_t group_workspace_bytes(int L, int T, int k, int E);

@@ -927,6 +927,12 @@ static constexpr long long TWO_PASS_BYTES = 600ll * 1000 * 1000;
 // Workgroups per token tile of the first kernel, each with its share of r: 4 of them and 8 tiles run on an XCD together and
 // share their rows of W1 and x through its L2 (2 / 4 / 8: 28.1 / 27.1 / 27.4 ms on the larger shape).
 static constexpr int TWO_PASS_GROUPS = 4;
+static int two_pass_groups(const PredictArgs& a)
+{
+    int groups = TWO_PASS_GROUPS;
+    while ((a.r / CfgFirst::BN) % groups != 0) groups /= 2;
+    return groups;
+}
 
 // Layers per batch and slices of r in the second kernel.
 struct TwoPass { int batch, slices; size_t h_bytes, z_bytes; };
@@ -994,9 +1000,7 @@ static hipError_t launch_scores_of_h(const PredictArgs& a, int tiles, int slices
 static hipError_t launch_two_pass(const PredictArgs& a)
 {
     const TwoPass p = two_pass_layout(a);
-    const int tiles = (a.T + SH_BM - 1) / SH_BM, NC = a.r / CfgFirst::BN;
-    int groups = TWO_PASS_GROUPS;
-    while (NC % groups != 0) groups /= 2;
+    const int tiles = (a.T + SH_BM - 1) / SH_BM, groups = two_pass_groups(a);
     u32x4* h = (u32x4*)a.workspace;
     float* z = (float*)((char*)a.workspace + p.h_bytes);
     for (int l0 = 0; l0 < a.L; l0 += p.batch) {
@@ -1034,7 +1038,6 @@ static hipError_t launch_two_pass(const PredictArgs& a)
 // that, more and smaller workgroups win.
 static bool enough_large_tiles(const PredictArgs& a) { return (long long)((a.T + 255) / 256) * a.L >= 128; }
 
-// 0: small, 1: small wide, 2: big, 3: mid, 4: big wide, 5: tiny (with the workspace for its score tiles)
 static bool tiny_wanted(const PredictArgs& a)
 {
     // 64 x 64 workgroups for everything, up to two per CU; with more experts the score tiles cost what the tiles gain.
@@ -1043,6 +1046,7 @@ static bool tiny_wanted(const PredictArgs& a)
     // experts, 512 tokens 38.8 / 31.2; 4096 x 2048, 256 experts, 512 tokens 61.4 / 69.6
     return a.E <= 128 && a.d % CfgTiny::BK == 0 && (long long)((a.T + 63) / 64) * a.L * (a.r / 64) <= 512;
 }
+// the fused kernel's tile: 0 small, 1 small wide, 2 big, 3 mid, 4 big wide, 5 tiny (with the workspace for its score tiles)
 static int pick_cfg(const PredictArgs& a, bool roomy)
 {
     const bool large = enough_large_tiles(a);
@@ -1062,6 +1066,12 @@ static void cfg_plan(const PredictArgs& a, int* groups, int* cpg)
 
 void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_group)
 {
+    if (two_pass_wanted(a)) {
+        *cfg = 6;
+        *groups = two_pass_groups(a);
+        *chunks_per_group = a.r / CfgFirst::BN / *groups;
+        return;
+    }
     *cfg = pick_cfg(a, true);
     switch (*cfg) {
     case 5: cfg_plan<CfgTiny>(a, groups, chunks_per_group); break;

@@ -193,6 +193,14 @@ def test_plan_reports_the_family_and_the_tile_choice():
     assert p1.path == "prefill" and p1.groups > 1 and p1.groups * p1.chunks_per_group * 128 in (2048, 4096)
     assert B.predict_plan(B.make_desc(8, 2048, 2048, 64, 6, 26, B.BF16)).path == "decode"
     assert B.predict_plan(B.make_desc(512, 256, 64, 16, 2, 1, B.F32)) == B.Plan("simple", "", 1, 0)
+    # many experts and wide tokens: the first layer in 256 x 256 tiles, four workgroups to each, the scores by a second
+    # kernel; narrow tokens, up to 128 experts without GELU: one kernel
+    stress = dict(d=2048, r=4096, E=256, k=8, L=48, dtype=B.BF16)
+    assert B.predict_plan(B.make_desc(32768, **stress)) == B.Plan("prefill", "256x256 two passes", 4, 4)
+    assert B.predict_plan(B.make_desc(32768, **dict(stress, d=256))) == B.Plan("prefill", "256x128", 1, 32)
+    qwen = dict(d=2048, r=2048, E=128, k=8, L=48, dtype=B.BF16)
+    assert B.predict_plan(B.make_desc(8192, **qwen)) == B.Plan("prefill", "256x256 wide", 1, 8)
+    assert B.predict_plan(B.make_desc(8192, **qwen, act="gelu")) == B.Plan("prefill", "256x256 two passes", 4, 2)
     # a margin output makes the matrix-core family keep one more candidate: k = 16 no longer fits there
     d16 = B.make_desc(4096, 2048, 2048, 64, 16, 26, B.BF16)
     assert B.predict_plan(d16).path == "prefill" and B.predict_plan(d16, want_margin=True).path == "simple"
@@ -200,6 +208,21 @@ def test_plan_reports_the_family_and_the_tile_choice():
     out = (ctypes.c_int32 * 4)()
     assert B.lib().paep_predict_plan(ctypes.byref(bad), 0, ctypes.byref(out)) == E_K
     assert B.lib().paep_predict_plan(ctypes.byref(d16), 0, None) == E_NULL
+
+
+@pytest.mark.parametrize("T,d,r,E,L,act,two", [
+    (8192, 512, 4096, 256, 16, "none", False), (8192, 768, 4096, 256, 16, "none", True),
+    (8192, 768, 2048, 140, 16, "none", False), (8192, 1024, 2048, 140, 16, "none", True),
+    (2048, 64, 1024, 200, 24, "none", True), (8192, 2048, 4096, 128, 16, "none", False),
+    (8192, 2560, 4096, 128, 16, "none", True), (8192, 1024, 2048, 128, 16, "gelu", False),
+    (8192, 1536, 2048, 128, 16, "gelu", True), (8192, 2048, 2048, 64, 16, "none", False),
+])
+def test_two_passes_are_chosen_where_d_pays_for_h(T, d, r, E, L, act, two):
+    """... and the workspace then holds the hidden vectors of a layer at least.  (With 128 experts and d = 256 two passes
+    take 1.5 times as long as the fused kernel.)"""
+    desc = B.make_desc(T, d, r, E, 8, L, B.BF16, act=act)
+    assert (B.predict_plan(desc).tile == "256x256 two passes") == two
+    assert (B.predict_workspace_bytes(desc) >= 2 * T * r) == two
 
 
 def test_confidence_predict_and_fold_reject_bad_arguments():
