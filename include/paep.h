@@ -107,6 +107,10 @@ typedef struct {
  * descriptor; paep_predict reports the reason. */
 size_t paep_predict_workspace_bytes(const paep_predict_desc *desc);
 
+/* ... and the bytes it cannot do without: with less, paep_predict returns
+ * PAEP_ERR_WORKSPACE.  Never more than the above. */
+size_t paep_predict_workspace_min_bytes(const paep_predict_desc *desc);
+
 /* Which kernel family AUTO resolves to for this shape (a paep_path value),
  * or -1 for an invalid descriptor.  Host only. */
 int paep_predict_resolve_path(const paep_predict_desc *desc);

@@ -32,7 +32,7 @@ STATUS_NAMES = ["PAEP_OK", "PAEP_ERR_NULL", "PAEP_ERR_SHAPE", "PAEP_ERR_K", "PAE
 
 STATIC_SCRATCH_BYTES = 16 << 20
 
-EXPORTS = ["paep_predict_workspace_bytes", "paep_predict_resolve_path", "paep_predict_plan", "paep_predict",
+EXPORTS = ["paep_predict_workspace_bytes", "paep_predict_workspace_min_bytes", "paep_predict_resolve_path", "paep_predict_plan", "paep_predict",
            "paep_static_init", "paep_predict_static",
            "paep_predict_counted", "paep_predict_confidence", "paep_fold_batchnorm",
            "paep_group_workspace_bytes", "paep_group_by_expert", "paep_score",
@@ -76,6 +76,8 @@ def lib() -> ctypes.CDLL:
         dp = ctypes.POINTER(PredictDesc)
         L.paep_predict_workspace_bytes.argtypes = [dp]
         L.paep_predict_workspace_bytes.restype = sz
+        L.paep_predict_workspace_min_bytes.argtypes = [dp]
+        L.paep_predict_workspace_min_bytes.restype = sz
         L.paep_predict_resolve_path.argtypes = [dp]
         L.paep_predict_resolve_path.restype = ctypes.c_int
         L.paep_predict.argtypes = [dp] + [vp] * 9 + [sz, vp]
@@ -191,6 +193,10 @@ def predict_workspace_bytes(desc: PredictDesc) -> int:
     return int(lib().paep_predict_workspace_bytes(ctypes.byref(desc)))
 
 
+def predict_workspace_min_bytes(desc: PredictDesc) -> int:
+    return int(lib().paep_predict_workspace_min_bytes(ctypes.byref(desc)))
+
+
 def resolve_path(desc: PredictDesc) -> str:
     p = int(lib().paep_predict_resolve_path(ctypes.byref(desc)))
     return PATH_NAME.get(p, "invalid")
@@ -258,7 +264,15 @@ def prepare_predict(x: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor, k: int,
             raise ValueError("logits buffer has the wrong shape or dtype")
     need = predict_workspace_bytes(desc)
     if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        try:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            # the hidden vectors of two passes, say: the call runs without them, in one kernel
+            least = predict_workspace_min_bytes(desc)
+            if least == need:
+                raise
+            if least > 0:
+                workspace = torch.empty(least, dtype=torch.uint8, device=dev)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if counts is not None:
         _need_device(counts)

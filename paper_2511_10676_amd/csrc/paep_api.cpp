@@ -146,6 +146,13 @@ size_t paep_predict_workspace_bytes(const paep_predict_desc* desc)
     return path_workspace_bytes(resolve(desc, a), a);
 }
 
+size_t paep_predict_workspace_min_bytes(const paep_predict_desc* desc)
+{
+    if (check_desc(desc) != PAEP_OK) return 0;
+    const paep::PredictArgs a = to_args(desc);
+    return path_workspace_min(resolve(desc, a), a);
+}
+
 static paep_status predict_common(const paep_predict_desc* desc,
                                   const void* x_dev, const void* W1_dev, const void* W2_dev,
                                   const void* b1_dev, const void* b2_dev,

@@ -109,6 +109,25 @@ def test_path_resolution_by_shape():
     assert B.predict_workspace_bytes(_desc(k=0)) == 0
 
 
+def test_workspace_a_call_cannot_do_without():
+    least = lambda *a, **kw: B.predict_workspace_min_bytes(B.make_desc(*a, **kw))
+    # T, d, r, E, k, L: two passes run as one kernel, thin slices as 64-wide ones, fp32 without a split of r
+    assert least(32768, 2048, 4096, 256, 8, 48, B.BF16) == 0
+    assert least(8, 2048, 2048, 64, 6, 1, B.BF16) == 4 * (2048 // 64) * 8 * 64
+    assert least(512, 2048, 2048, 64, 6, 1, B.F32) == 0
+    assert least(4096, 2048, 2048, 64, 6, 20, B.BF16) == B.predict_workspace_bytes(B.make_desc(4096, 2048, 2048, 64, 6, 20, B.BF16))
+    assert least(8, 2048, 2048, 64, 0, 1, B.BF16) == 0                     # invalid
+    for T in (0, 1, 20, 64, 65, 300, 5000):
+        for L in (1, 3, 40):
+            for E in (16, 100, 200):
+                for dt in (B.F32, B.BF16):
+                    desc = B.make_desc(T, 1536, 1024, E, 4, L, dt, act="gelu")
+                    assert B.predict_workspace_min_bytes(desc) <= B.predict_workspace_bytes(desc)
+                    need = B.predict_workspace_min_bytes(desc)
+                    if need:
+                        assert _predict(desc, ws=FAKE, ws_bytes=need - 1) == E_WS
+
+
 def _group(idx=FAKE, L=1, T=0, k=2, E=16, outs=(FAKE,) * 6, ws=FAKE, ws_bytes=1 << 20):
     return B.lib().paep_group_by_expert(idx, L, T, k, E, *outs, ws, ws_bytes, None)
 

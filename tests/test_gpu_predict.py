@@ -640,6 +640,30 @@ def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     assert torch.equal(counts.long(), ref)
 
 
+def test_predict_runs_where_its_best_workspace_does_not_fit(monkeypatch):
+    """The allocation of h for two passes fails: the call goes on in the least workspace instead of raising."""
+    T, d, r, E, k, L = 1000, 64, 1024, 200, 3, 33
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16)
+    least, best = B.predict_workspace_min_bytes(desc), B.predict_workspace_bytes(desc)
+    assert B.predict_plan(desc).tile == "256x256 two passes" and least < best
+    x, W1, W2, _, _ = _rand_layers(3, L=L, T=T, d=d, r=r, E=E, dtype="bf16")
+    args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k
+    one = B.predict(*args, want_logits=True, workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
+    empty, sizes = torch.empty, []
+
+    def full_device(*size, **kw):
+        if kw.get("dtype") == torch.uint8:
+            sizes.append(size[0])
+            if size[0] > least:
+                raise torch.OutOfMemoryError("planted")
+        return empty(*size, **kw)
+    monkeypatch.setattr(torch, "empty", full_device)
+    out = B.predict(*args, want_logits=True)
+    monkeypatch.undo()
+    assert sizes[0] == best
+    assert torch.equal(out.logits, one.logits) and torch.equal(out.idx, one.idx) and torch.equal(out.probs, one.probs)
+
+
 @pytest.mark.parametrize("T,E,k", [(64, 64, 6), (63, 16, 2), (64, 16, 12), (33, 16, 12)])
 def test_counts_of_a_decode_batch(T, E, k):
     """33 layers, 1089 to 2112 rows: counted by a wave per row, by several lanes per row, from the selections of those."""
