@@ -640,6 +640,46 @@ def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     assert torch.equal(counts.long(), ref)
 
 
+@pytest.mark.parametrize("T,d,r,E,k,L,act,shared,batches", [
+    (5000, 768, 4096, 200, 8, 32, "none", False, (11, 11, 10)),
+    (5000, 768, 4096, 256, 15, 32, "silu", True, (11, 11, 10)),
+    (8100, 2048, 2048, 128, 8, 21, "gelu", False, (11, 10)),
+])
+def test_two_passes_in_batches_of_layers(T, d, r, E, k, L, act, shared, batches):
+    """More layers than 600 MB of hidden vectors hold: batches of them, the last one shorter, each with its own part of
+    every operand and output; a ragged last tile.  Both biases, scores, margin and counts; layers that share their
+    tokens.  Rows of every layer against the oracle, every row against the fused kernel (2e-6 of the row's scale, as
+    above)."""
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
+    assert B.predict_plan(desc, want_margin=True).tile == "256x256 two passes"
+    need, tiles = B.predict_workspace_bytes(desc), -(-T // 256)
+    assert sum(batches) == L and batches[0] * tiles * 256 * (r * 2 + E * 4) == need
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=g)
+    x = torch.stack([rnd(T, d).to(torch.bfloat16) for _ in range(1 if shared else L)])
+    W1 = torch.stack([(rnd(r, d) / d ** 0.5).to(torch.bfloat16) for _ in range(L)])
+    W2 = (rnd(L, E, r) / r ** 0.5).to(torch.bfloat16)
+    b1, b2 = (0.3 * rnd(L, r)).to(torch.bfloat16), (0.5 * rnd(L, E)).to(torch.bfloat16)
+    opts = dict(b1=b1, b2=b2, act=act, want_logits=True, want_margin=True)
+    counts = torch.full((L, E), 5, dtype=torch.int32, device="cuda")
+    out = B.predict(x, W1, W2, k, counts=counts, **opts)
+    one = B.predict(x, W1, W2, k, workspace=torch.empty(need - 1, dtype=torch.uint8, device="cuda"), **opts)
+    torch.cuda.synchronize()
+    scale = one.logits.abs().amax(dim=2, keepdim=True)
+    assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+    srt, order = torch.sort(out.logits, dim=2, descending=True, stable=True)
+    assert torch.equal(out.idx.long(), order[:, :, :k])
+    assert torch.equal(out.margin, srt[:, :, k - 1] - srt[:, :, k])
+    ref = torch.stack([torch.bincount(out.idx[l].flatten().long(), minlength=E) for l in range(L)])
+    assert torch.equal(counts.long() - 5, ref)
+    rows = np.unique(np.concatenate([np.arange(7, T, T // 6), [0, T - 1]]))
+    cpu = lambda t: t.float().cpu().numpy()
+    for l in range(L):
+        parity.check_layer(cpu(x[0 if shared else l][rows]), cpu(W1[l]), cpu(W2[l]), cpu(b1[l]), cpu(b2[l]), ACT_ID[act], k,
+                           "bf16", out.idx[l].cpu().numpy()[rows], out.probs[l].cpu().numpy()[rows],
+                           out.logits[l].cpu().numpy()[rows], what=f"batches layer {l}")
+
+
 def test_predict_runs_where_its_best_workspace_does_not_fit(monkeypatch):
     """The allocation of h for two passes fails: the call goes on in the least workspace instead of raising."""
     T, d, r, E, k, L = 1000, 64, 1024, 200, 3, 33
