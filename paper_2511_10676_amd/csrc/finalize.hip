@@ -87,7 +87,7 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(
     const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr, counts ? counts + (long long)layer * E : nullptr};
     // one expert per lane: rank counting; more: k rounds of a wave-wide maximum (measured at 128 experts, k = 8:
     // 6.8 us against 9.6 us for rank counting at 48 rows, 11.6 against 17.7 at 3072 rows)
-    if constexpr (NV == 1) wave_softmax_topk_rank<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
+    if constexpr (NV == 1) wave_softmax_topk_rank(z[0], E, k, lane, idx + row * k, probs + row * k, eo);
     else                   wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
 }
 

@@ -293,20 +293,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     // second layer straight from the accumulator registers, then clear acc1.
     // acc1[mi][ni][i] = h[token wt*WN + ni*32 + l32]
     //                    [unit n*BN + wr*WM + mi*32 + 8*(i/4) + 4*g + i%4]
-    // W2 fragments are requested first (with few enough experts that they fit in
-    // registers beside the conversion's temporaries), so that their latency runs
-    // under the rounding arithmetic; rows past E are clamped for the address and
-    // zeroed by a select, which keeps the loads free of branches.
-    constexpr bool EARLY_W2 = !C::W2L && (EB32 <= 4) && (MI * NI + EB32 * NI < 12);    // accumulators leave room for the fragments
-    auto w2_fragment = [&](int eb, int unit0) {
-        const int e = eb * 32 + l32;
-        const uint16_t* wp = W2l + (long long)(e < E ? e : E - 1) * r + unit0;
-        const u32x2 lo = *(const u32x2*)wp;
-        const u32x2 hi = *(const u32x2*)(wp + 8);
-        const bool ok = e < E;
-        return u32x4{ok ? lo[0] : 0u, ok ? lo[1] : 0u, ok ? hi[0] : 0u, ok ? hi[1] : 0u};
-    };
-    // the same fragment out of the LDS copy of the slice; ubase = first hidden unit of the 16-unit step inside the chunk
+    // W2 fragment out of the LDS copy of the slice; ubase = first hidden unit of the 16-unit step inside the chunk
     auto w2_fragment_lds = [&](int eb, int ubase) {
         const int e = eb * 32 + l32;
         const char* row = (const char*)w2lds + e * (BN * 2) + 8 * g;
@@ -329,12 +316,6 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                const int unit0 = n * BN + wr * WM + mi * 32 + 16 * s + 4 * g;   // units unit0+0..3, unit0+8..11
-                u32x4 wv[EBA];
-                if constexpr (EARLY_W2) {
-#pragma unroll
-                    for (int eb = 0; eb < EB32; ++eb) wv[eb] = w2_fragment(eb, unit0);
-                }
                 bf16x8 hb[NI];
                 if constexpr (MODE == 0) {
 #pragma unroll
@@ -383,7 +364,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                         const long long blk = (long long)tile_id * (BM / 32) + wt * NI + ni;
                         hout[(blk * steps + us) * 64 + lane] = __builtin_bit_cast(u32x4, hb[ni]);
                     }
-                } else if constexpr (C::W2L) {
+                } else {
                     // fragments from LDS, the next one requested before the current one is multiplied
                     const int ubase = wr * WM + mi * 32 + 16 * s;
                     u32x4 cur = w2_fragment_lds(0, ubase);
@@ -396,15 +377,6 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                         for (int ni = 0; ni < NI; ++ni)
                             acc2[eb][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hb[ni], acc2[eb][ni], 0, 0, 0);
                         cur = nxt;
-                    }
-                } else {
-#pragma unroll
-                    for (int eb = 0; eb < EB32; ++eb) {
-                        if constexpr (!EARLY_W2) wv[eb] = w2_fragment(eb, unit0);
-                        const bf16x8 wa = __builtin_bit_cast(bf16x8, wv[eb]);
-#pragma unroll
-                        for (int ni = 0; ni < NI; ++ni)
-                            acc2[eb][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hb[ni], acc2[eb][ni], 0, 0, 0);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);          // keep the W2 fetches of later steps from piling up in registers
@@ -1024,9 +996,7 @@ static hipError_t launch_two_pass(const PredictArgs& a)
         default: err = launch_first_layer<3>(b, tiles, groups, h); break;
         }
         if (err != hipSuccess) return err;
-        if (a.E <= 64)       err = launch_scores_of_h<2>(b, tiles, p.slices, h, z);
-        else if (a.E <= 128) err = launch_scores_of_h<4>(b, tiles, p.slices, h, z);
-        else                 err = launch_scores_of_h<8>(b, tiles, p.slices, h, z);
+        err = a.E <= 128 ? launch_scores_of_h<4>(b, tiles, p.slices, h, z) : launch_scores_of_h<8>(b, tiles, p.slices, h, z);
         if (err != hipSuccess) return err;
         err = launch_finalize(b, z, p.slices, tiles * b.L, SH_BM, 0, tiles);
         if (err != hipSuccess) return err;
