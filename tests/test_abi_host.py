@@ -98,7 +98,7 @@ def test_path_resolution_by_shape():
     assert B.predict_workspace_bytes(_desc(T=4096, **dict(ds, L=32))) == 0
     assert B.predict_workspace_bytes(_desc(T=4096, **ds)) == 0
     # ... otherwise those tiles (20 x 16 = 256 + 64) are cut along r into 4 pieces each, whose score tiles of
-    # 256 x E fp32 meet in the workspace, plus a ticket per tile ...
+    # 256 x E fp32 meet in the workspace, plus a word per tile (unused; callers know the size) ...
     assert B.predict_workspace_bytes(_desc(T=4096, **dict(ds, L=20))) == 64 * 4 * 256 * 64 * 4 + 64 * 4
     # ... and with long rows (d >= 4096) r is split over two co-scheduled workgroups for every tile
     phi = dict(dtype=B.BF16, d=4096, r=1024, E=16, k=2, L=32)

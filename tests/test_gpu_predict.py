@@ -39,11 +39,11 @@ def _rand_layers(seed, L, T, d, r, E, dtype, bias=False, outliers=True):
     return rs(x), rs(W1), rs(W2), rs(b1), rs(b2)
 
 
-def _run_and_check(x, W1, W2, b1, b2, k, dtype, act="none", path="auto", rows=None, what=""):
+def _run_and_check(x, W1, W2, b1, b2, k, dtype, act="none", path="auto", rows=None, what="", workspace=None):
     L = W1.shape[0]
     out = B.predict(_dev(x, dtype), _dev(W1, dtype), _dev(W2, dtype), k,
                     b1=None if b1 is None else _dev(b1, dtype), b2=None if b2 is None else _dev(b2, dtype),
-                    act=act, path=path, want_logits=True)
+                    act=act, path=path, want_logits=True, workspace=workspace)
     torch.cuda.synchronize()
     idx, probs, z = out.idx.cpu().numpy(), out.probs.cpu().numpy(), out.logits.cpu().numpy()
     tot, tot_m = parity.RowReport(), parity.RowReport()
@@ -250,7 +250,7 @@ def test_empty_call():
 @pytest.mark.parametrize("E,k,r,d,L,T", [
     (64, 6, 256, 64, 4, 8229), (128, 8, 128, 64, 4, 8229), (256, 8, 384, 64, 4, 8229), (24, 2, 512, 64, 4, 8229),
     # d = 4096: the token tile is large enough that r is split over two workgroups per tile
-    # (score tiles through the workspace, ticketed last-arriver reduction); so it is, further, in
+    # (score tiles through the workspace, added by the finalize kernels); so it is, further, in
     # every case here with fewer than 256 tiles
     (64, 6, 512, 4096, 4, 8300), (200, 8, 256, 4096, 4, 8300),
     # several chunks of r per tile, many layers, a single layer with many tiles
@@ -263,9 +263,12 @@ def test_empty_call():
 ])
 def test_prefill_large_tile_configs_with_ragged_tail(E, k, r, d, L, T):
     """Enough tokens that the large-tile kernels are chosen, a token count that
-    is not a multiple of any tile, every row checked."""
+    is not a multiple of any tile, every row checked; with the least workspace, so that
+    the fused kernel runs where two passes would."""
     x, W1, W2, b1, b2 = _rand_layers(70 + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
-    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", path="prefill", what=f"prefill large tiles E={E} r={r} d={d}")
+    least = B.predict_workspace_min_bytes(B.make_desc(T, d, r, E, k, L, B.BF16, path="prefill"))
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", path="prefill", what=f"prefill large tiles E={E} r={r} d={d}",
+                             workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
     assert out.path == "prefill"
 
 
@@ -282,7 +285,7 @@ def test_prefill_large_tile_configs_with_ragged_tail(E, k, r, d, L, T):
     (128, 8, 1024, 64, 9, 8229, "256x256 wide", 1, 4),
     (256, 8, 512, 64, 9, 8229, "256x128", 1, 4),
     # ... and with long rows (d = 4096) r split over two workgroups per tile, again at >= 256 tiles:
-    # score tiles through the workspace, last arriver adds them (release/acquire through one thread's fences)
+    # score tiles through the workspace, added by the finalize kernels
     (64, 6, 512, 4096, 8, 8300, "256x256", 2, 1),
 ])
 def test_prefill_many_tiles_every_row(E, k, r, d, L, T, tile, groups, cpg):
@@ -575,7 +578,7 @@ def test_finalize_many_rows_of_few_experts(E, k):
 # ------------------------------------------------------------------ activations on the bf16 grid
 @pytest.mark.parametrize("act", ["silu", "gelu"])
 @pytest.mark.parametrize("path,T,d,r", [("prefill", 4096, 32, 128), ("decode", 64, 128, 64), ("decode", 64, 128, 128)])
-def test_activation_of_every_bf16_value(path, T, d, r, act):
+def test_activation_over_the_bf16_grid(path, T, d, r, act):
     """One hidden unit per token holds a bf16 value v (x[t, 0] = v, W1 = 1), the score of expert 0 is act(v): it must be
     act(v) in float64 rounded to bf16, to the bit, for every v of magnitude 2^-60 .. 64 whose result is a normal number.
     A value within 1e-6 of a rounding boundary may go either way (the float32 arithmetic's own bound)."""
@@ -606,6 +609,23 @@ def test_activation_of_every_bf16_value(path, T, d, r, act):
     bad = (got != lo) & (got != hi)
     assert not bad.any(), (v[bad][:5], got[bad][:5], exact[bad][:5])
     print(f"{path} {act}: {v.size} values, {(got != to_bf16(exact)).sum()} not correctly rounded", flush=True)
+
+
+# ------------------------------------------------------------------ biases that start anywhere
+@pytest.mark.parametrize("T,d,r,E,L,act", [(300, 64, 256, 40, 2, "none"), (8200, 64, 512, 64, 8, "gelu"),
+                                           (1000, 64, 1024, 200, 33, "silu"), (5, 128, 128, 20, 3, "none"),
+                                           (40, 128, 192, 20, 3, "silu")])
+def test_biases_that_start_in_the_middle_of_a_word(T, d, r, E, L, act):
+    """b1 and b2 need no alignment beyond their own: shifted by one element they give the same bits."""
+    x, W1, W2, b1, b2 = _rand_layers(60 + T, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), 4
+    a1, a2 = _dev(b1, "bf16"), _dev(b2, "bf16")
+    shift = lambda t: torch.cat([t.new_full((1,), 99.0), t.flatten()])[1:].view(t.shape)
+    s1, s2 = shift(a1), shift(a2)
+    assert s1.data_ptr() % 4 == 2 and s2.data_ptr() % 4 == 2
+    a = B.predict(*args, b1=a1, b2=a2, act=act, want_logits=True)
+    b = B.predict(*args, b1=s1, b2=s2, act=act, want_logits=True)
+    assert torch.equal(a.logits, b.logits) and torch.equal(a.idx, b.idx) and torch.equal(a.probs, b.probs)
 
 
 # ------------------------------------------------------------------ two passes for many experts

@@ -53,7 +53,7 @@ def _both_ways(x, W1, W2, k):
 @pytest.mark.parametrize("first,second", [
     # decode path: fp32 partial scores of every slice of r go through the scratch buffer
     (dict(L=6, T=64, d=512, r=512, E=64, k=6), dict(L=3, T=5, d=512, r=256, E=48, k=4)),
-    # prefill path with r split over workgroups: score tiles and tickets go through it
+    # prefill path with r split over workgroups: score tiles go through it
     (dict(L=2, T=700, d=256, r=1024, E=128, k=8), dict(L=1, T=130, d=256, r=512, E=40, k=8)),
     # one after the other across the two families
     (dict(L=2, T=300, d=256, r=512, E=64, k=6), dict(L=26, T=1, d=256, r=128, E=64, k=6)),
