@@ -269,9 +269,9 @@ __global__ __launch_bounds__(SCORE_THREADS) void confidence_select_kernel(
     float ratio, int32_t* __restrict__ idx_out, int32_t* __restrict__ k_row, int32_t* __restrict__ n_wide)
 {
     __shared__ int32_t width[SCORE_THREADS];
-    __shared__ int32_t n_first;                             // wide rows of the layer the workgroup starts in
+    __shared__ int32_t n_of[SCORE_THREADS];                 // wide rows of the layers the workgroup's rows belong to
     const long long row0 = (long long)blockIdx.x * SCORE_THREADS, row = row0 + threadIdx.x;
-    if (threadIdx.x == 0) n_first = 0;
+    n_of[threadIdx.x] = 0;
     __syncthreads();
     const int first_layer = (int)(row0 / T);
     if (row < rows) {
@@ -280,14 +280,10 @@ __global__ __launch_bounds__(SCORE_THREADS) void confidence_select_kernel(
         const int w = confident ? k_base : k_pred;
         k_row[row] = w;
         width[threadIdx.x] = w;
-        if (!confident) {
-            const int layer = (int)(row / T);
-            if (layer == first_layer) atomicAdd(&n_first, 1);
-            else atomicAdd(&n_wide[layer], 1);              // the workgroup crosses into another layer
-        }
+        if (!confident) atomicAdd(&n_of[(int)(row / T) - first_layer], 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && n_first) atomicAdd(&n_wide[first_layer], n_first);
+    if (n_of[threadIdx.x]) atomicAdd(&n_wide[first_layer + threadIdx.x], n_of[threadIdx.x]);
     const int n = (int)((rows - row0 < SCORE_THREADS ? rows - row0 : SCORE_THREADS)) * k_pred;   // <= 256 * 32
     const int32_t* src = idx + row0 * k_pred;
     int32_t* dst = idx_out + row0 * k_pred;

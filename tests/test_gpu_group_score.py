@@ -239,6 +239,18 @@ def test_confidence_select_copies_whole_workgroups_and_remainders(T, kp, kb, shi
         assert int(got.n_wide[l]) == n_wide
 
 
+@pytest.mark.parametrize("L,T", [(300, 1), (200, 3), (9, 61), (5, 255), (5, 257), (3, 600)])
+def test_confidence_select_counts_wide_rows_of_every_layer(L, T):
+    """Workgroups of 256 rows that span up to 256 layers, parts of two, and one."""
+    g = np.random.default_rng(L)
+    idx, probs = _sorted_softmax(g, L, T, 6, 64, temp=1.5)
+    got = B.confidence_select(torch.from_numpy(idx).cuda(), torch.from_numpy(probs).cuda(), 3, 1.1)
+    for l in range(L):
+        k_row, idx_out, n_wide = oracle.confidence_select(idx[l], probs[l], 3, 1.1)
+        assert int(got.n_wide[l]) == n_wide and np.array_equal(got.k_row[l].cpu().numpy(), k_row)
+        assert np.array_equal(got.idx[l].cpu().numpy(), idx_out)
+
+
 def test_score_rows_with_arbitrary_widths():
     g = np.random.default_rng(77)
     L, T, E, kp, kr = 2, 5000, 64, 9, 4
