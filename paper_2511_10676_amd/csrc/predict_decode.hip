@@ -658,21 +658,38 @@ bool decode_supported(const PredictArgs& a)
 
 // Units per slice of the thin kernel, or 0 where one of the others runs.  It is the faster one while its slices still
 // find a CU each (256 of them); the price of thin slices is that every one fetches all tokens and leaves a score per
-// token and expert to be added up, which limits T and E.  Measured with the weights out of the caches, us for the
-// row-split kernel / 16 / 32 units a slice:
+// token and expert to be added up, which limits T and E, and that the waves wait for one another, which takes rows
+// long enough to make up for.  us for the row-split kernel / 16 / 32 units a slice, weights out of the caches:
 //   2048 x 2048, 64 experts: 1 layer, 1 token 20.3 / 13.4 / 16.2; 2 layers, 64 tokens 26.4 / 23.2 / -; 4 layers, 1 token
 //   21.2 / 17.1 / 18.3, 16 tokens 22.3 / 19.6 / 19.4, 32 tokens 23.3 / 27.3 / 22.9; 6 layers, 16 tokens 23.4 / 24.2 / 25.3
 //   1024 x 4096, 16 experts: 1 layer, 1 token 29.8 / 16.0 / 20.6; 8 layers, 16 tokens 33.4 / 32.0 / 27.1
 //   4096 x 2048, 256 experts: 1 layer, 1 token 26.6 / 25.3 / 22.7; 2 layers, 16 tokens 29.2 / 32.3 / 26.2
+// and over d (r = 2048, 64 experts unless said; row-split / 16 units):
+//   1 token     d = 256 11.1 / 11.2, 512 12.4 / 11.6, 1024 14.9 / 12.2; r = 4096: 512 12.7 / 13.3, 1024 15.4 / 14.2;
+//               128 experts: 512 12.9 / 12.8, 768 14.2 / 13.0
+//   32 tokens   d = 512 13.5 / 13.8, 1024 16.2 / 14.7; r = 4096: 1024 16.7 / 17.0, 1536 19.8 / 18.2; 128 experts, 2 layers:
+//               1024 17.2 / 17.7, 1536 20.3 / 19.0
+//   64 tokens   d = 512 15.3 / 17.0, 1024 18.7 / 18.6, 1536 22.6 / 19.7; 128 experts, 2 layers: 1536 23.6 / 24.6, 2048
+//               27.1 / 26.9; r = 4096: 2048 28.3 / 29.9
+// weights in the caches, row-split / 32 units, 1 token: 256 experts, r = 2048 x 4 layers, d = 1024 1.17 times as long, 2048
+// 0.98; r = 8192, d = 2048 1.21, 4096 1.05; 64 experts d = 768 1.02, 1024 0.94
 static int decode_thin_units(const PredictArgs& a)
 {
     if (a.r % RW_RS != 0) return 0;                           // the order of sums that it keeps is the row-split kernel's
     const long long units = (long long)a.L * a.r;
     // stages of 128 columns a wave can hold in registers, by token blocks
     const int stages = (a.d / RW_KST + TH_WAVES - 1) / TH_WAVES, tb = (a.T + 15) / 16;
-    if (units <= 256 * 16 && a.E <= 128 && stages <= (tb == 1 ? 6 : tb == 2 ? 4 : 2)) return 16;
-    if (units <= 256 * 32 && a.E <= 256 && tb == 1 && stages <= 4) return 32;
-    return 0;
+    int us = 0;
+    if (units <= 256 * 16 && a.E <= 128 && stages <= (tb == 1 ? 6 : tb == 2 ? 4 : 2)) us = 16;
+    else if (units <= 256 * 32 && a.E <= 256 && tb == 1 && stages <= 4) us = 32;
+    if (us == 0) return 0;
+    const bool long_sum = a.r / us >= 256;                    // slices that the finalize kernel adds up for a row
+    if (long_sum && a.E > 128) return 0;
+    int from = us == 32 || tb == 2 ? 1024 : tb == 1 ? 512 : 1536;
+    if (long_sum) from += 512;
+    if (a.E > 64) from += us == 16 && tb == 1 ? 256 : 512;
+    if (a.E > 128) from += 512;
+    return a.d >= from ? us : 0;
 }
 
 // the slices' scores in the workspace: of the d-split and the row-split kernel (sized for slices of 64 for both: callers

@@ -128,6 +128,20 @@ def test_workspace_a_call_cannot_do_without():
                         assert _predict(desc, ws=FAKE, ws_bytes=need - 1) == E_WS
 
 
+@pytest.mark.parametrize("T,d,r,E,L,units", [
+    (1, 384, 2048, 64, 1, 64), (1, 512, 2048, 64, 1, 16), (1, 896, 4096, 64, 1, 64), (1, 1024, 4096, 64, 1, 16),
+    (16, 640, 2048, 100, 2, 64), (16, 768, 2048, 100, 2, 16), (9, 896, 2048, 64, 4, 64), (9, 1024, 2048, 64, 4, 32),
+    (32, 1024, 2048, 64, 1, 16), (32, 1536, 2048, 100, 2, 16), (64, 1536, 128, 64, 4, 16),
+    (16, 1920, 128, 256, 1, 64), (16, 2048, 128, 256, 1, 32), (1, 4096, 8192, 256, 1, 64),
+])
+def test_thin_slices_are_chosen_where_d_pays_for_them(T, d, r, E, L, units):
+    """The workspace holds the scores of slices of 16, 32 or 64 units.  (64 tokens of a 512 x 512 layer: 13.7 us in slices of
+    128, which have 64's workspace, 15.7 in slices of 16.)"""
+    desc = B.make_desc(T, d, r, E, 1, L, B.BF16)
+    assert B.resolve_path(desc) == "decode"
+    assert B.predict_workspace_bytes(desc) == 4 * L * (r // units) * T * E
+
+
 def _group(idx=FAKE, L=1, T=0, k=2, E=16, outs=(FAKE,) * 6, ws=FAKE, ws_bytes=1 << 20):
     return B.lib().paep_group_by_expert(idx, L, T, k, E, *outs, ws, ws_bytes, None)
 

@@ -130,17 +130,20 @@ def test_decode_shared_tokens_across_layers():
         _run_and_check(x[:1], W1, W2, None, None, 4, "bf16", path="decode", what=f"decode rows shared x T={T}")
 
 
-# Few hidden units in all (L * r <= 4096, or 8192 up to 16 tokens, r a multiple of 128): slices of 16 or 32 units, the
-# stages of 128 columns dealt to eight waves.  Fewer stages than waves, ragged shares, two, four and six stages a wave,
-# token counts around a block of 16, expert counts around a block of 16 and 8 blocks, both slice widths.
+# Few hidden units in all (L * r <= 4096, or 8192 up to 16 tokens, r a multiple of 128) and d long enough: slices of 16 or
+# 32 units, the stages of 128 columns dealt to eight waves.  Fewer stages than waves, ragged shares, two, four and six
+# stages a wave, token counts around a block of 16, expert counts around a block of 16 and 8 blocks, both slice widths.
 @pytest.mark.parametrize("T,d,r,E,k,act,L", [
-    (1, 128, 128, 1, 1, "none", 1), (16, 384, 128, 16, 3, "silu", 4), (17, 1152, 256, 17, 4, "none", 2),
-    (32, 2048, 256, 128, 8, "gelu", 1), (33, 2048, 128, 120, 6, "none", 3), (64, 640, 384, 65, 16, "silu", 2),
+    (1, 512, 128, 1, 1, "none", 1), (16, 640, 128, 16, 3, "silu", 4), (17, 1152, 256, 17, 4, "none", 2),
+    (32, 2048, 256, 128, 8, "gelu", 1), (33, 2048, 128, 120, 6, "none", 2), (64, 1664, 384, 64, 16, "silu", 2),
     (1, 5120, 128, 64, 6, "none", 1), (31, 4096, 128, 64, 6, "none", 1), (9, 2176, 128, 33, 6, "none", 2),
-    (1, 640, 128, 129, 5, "none", 3), (16, 4096, 128, 255, 32, "silu", 1), (15, 512, 2048, 64, 6, "none", 3),
-    (2, 256, 1152, 250, 9, "gelu", 2), (16, 128, 8192, 16, 2, "none", 1),
+    (1, 2176, 128, 129, 5, "none", 3), (16, 4096, 128, 255, 32, "silu", 1), (15, 1152, 2048, 64, 6, "none", 3),
+    (2, 2304, 1152, 250, 9, "gelu", 2), (16, 1536, 8192, 16, 2, "none", 1), (1, 1920, 4096, 16, 2, "none", 1),
 ])
 def test_decode_thin_slices(T, d, r, E, k, act, L):
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16)
+    units = 16 if E <= 128 and L * r <= 4096 else 32
+    assert B.predict_workspace_bytes(desc) == 4 * L * (r // units) * T * E             # thin slices are chosen
     x, W1, W2, b1, b2 = _rand_layers(400 + T + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, path="decode", what=f"decode thin T={T} d={d} r={r} E={E}")
     assert out.path == "decode"
@@ -164,8 +167,8 @@ def test_decode_workspace_for_more_tokens_serves_fewer(L, r, E, d):
     assert sizes == sorted(sizes)
 
 
-@pytest.mark.parametrize("L,T,d,r,E,act", [(2, 64, 512, 2048, 64, "none"), (1, 1, 2048, 1024, 128, "silu"),
-                                           (4, 16, 256, 2048, 200, "gelu"), (1, 33, 384, 128, 60, "none")])
+@pytest.mark.parametrize("L,T,d,r,E,act", [(2, 64, 1536, 2048, 64, "none"), (1, 1, 2048, 1024, 128, "silu"),
+                                           (4, 16, 2048, 2048, 200, "gelu"), (1, 33, 1664, 128, 60, "none")])
 def test_decode_runs_in_the_scores_of_64_wide_slices(L, T, d, r, E, act):
     """The workspace that every decode call can do with: L * (r / 64) * T * E floats, never more for fewer layers.  Thin
     slices want more and are left out then: the same hidden vector to the bit, the scores in wider slices (2e-6 of the
