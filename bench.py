@@ -44,22 +44,22 @@ MALL_BYTES = 256 << 20
 # once a kernel's code changes, the figure no longer describes it and the
 # report says null.
 TRAFFIC_BYTES = {
-    ("prefill", "be865277bf0be11a"): {("deepseek_v2_lite", 4096): 3.891e+09,
-                                      ("qwen3_30b_a3b", 8192): 1.457e+10,
-                                      ("phi_mini_moe", 8192): 4.91e+09,
-                                      ("stress", 32768): 2.41e+11},
-    ("decode", "d527a095cb363a51"): {("deepseek_v2_lite", 1): 2.259e+08,
-                                     ("deepseek_v2_lite", 64): 2.588e+08},
+    ("prefill", "7784f760d70e1124"): {("deepseek_v2_lite", 4096): 3.838e+09,
+                                      ("qwen3_30b_a3b", 8192): 1.43e+10,
+                                      ("phi_mini_moe", 8192): 4.908e+09,
+                                      ("stress", 32768): 6.887e+10},
+    ("decode", "ab79da61901cf2e7"): {("deepseek_v2_lite", 1): 2.257e+08,
+                                     ("deepseek_v2_lite", 64): 2.587e+08},
 }
 
 
 def _code_hash(path):
-    """Hash of the kernel's source with // comments and blank space removed, so that
+    """Hash of the kernels' sources with // comments and blank space removed, so that
     rewording a comment does not retire a measurement but any change to code does."""
     import hashlib
     import re
     m = hashlib.sha256()
-    for f in ("predict_%s.hip" % path, "paep_device.h"):
+    for f in ("predict_%s.hip" % path, "finalize.hip", "paep_device.h"):
         try:
             with open(os.path.join(ROOT, "paper_2511_10676_amd", "csrc", f), "r") as fh:
                 text = fh.read()
@@ -221,7 +221,7 @@ class Runner:
             ach = flops * w.L / (predict_ms * 1e-3) / 1e12
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": measured_traffic("prefill", w.name, T),
-                    "kernel": ("prefill_kernel+scores_of_h_kernel+finalize" if self.plan.tile.endswith("two passes")
+                    "kernel": ("prefill_kernel+scores_of_h_kernel+finalize" if self.plan.tile.startswith("two-pass")
                                else "prefill_kernel"), "kernel_ms": round(predict_ms, 4)}
         else:
             ach = nbytes * w.L / (predict_ms * 1e-3) / 1e9

@@ -30,11 +30,11 @@
 // float64 than those of a lane-split dot product with a butterfly (relative error of the scores, that / chains of 128
 // and 64 / here: 512 tokens 2048 x 2048 1.76e-7 / 2.85e-7 / 1.72e-7, 4 x 8192 tokens 1.77e-7 / 8.4e-7 / 1.72e-7, 256 x 64
 // 1.06e-7 / 2.9e-7 / 1.05e-7).  A chain is folded behind the next stage's LDS reads, when its last product is through the
-// pipe (at the end of its own stage: 64.5 against 61.2 us for the first of these; the long chains: 57.9).
+// pipe (the first of these in one run: 61.2 us, folded at the end of its own stage 64.5; the long chains 57.9).
 // Few token tiles: r is cut over several workgroups per tile, their scores meet in the
 // workspace and finalize_kernel adds them; otherwise softmax and top-k follow here.
 // Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for a kernel of vector
-// instructions (a wave per hidden unit), 61 us here.
+// instructions (a wave per hidden unit), 55 us here.
 #include "paep_device.h"
 #include "paep_internal.h"
 

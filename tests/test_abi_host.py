@@ -229,11 +229,11 @@ def test_plan_reports_the_family_and_the_tile_choice():
     # many experts and wide tokens: the first layer in 256 x 256 tiles, four workgroups to each, the scores by a second
     # kernel; narrow tokens, up to 128 experts without GELU: one kernel
     stress = dict(d=2048, r=4096, E=256, k=8, L=48, dtype=B.BF16)
-    assert B.predict_plan(B.make_desc(32768, **stress)) == B.Plan("prefill", "256x256 two passes", 4, 4)
+    assert B.predict_plan(B.make_desc(32768, **stress)) == B.Plan("prefill", "two-pass 256x256", 4, 4)
     assert B.predict_plan(B.make_desc(32768, **dict(stress, d=256))) == B.Plan("prefill", "256x128", 1, 32)
     qwen = dict(d=2048, r=2048, E=128, k=8, L=48, dtype=B.BF16)
     assert B.predict_plan(B.make_desc(8192, **qwen)) == B.Plan("prefill", "256x256 wide", 1, 8)
-    assert B.predict_plan(B.make_desc(8192, **qwen, act="gelu")) == B.Plan("prefill", "256x256 two passes", 4, 2)
+    assert B.predict_plan(B.make_desc(8192, **qwen, act="gelu")) == B.Plan("prefill", "two-pass 256x256", 4, 2)
     # a margin output makes the matrix-core family keep one more candidate: k = 16 no longer fits there
     d16 = B.make_desc(4096, 2048, 2048, 64, 16, 26, B.BF16)
     assert B.predict_plan(d16).path == "prefill" and B.predict_plan(d16, want_margin=True).path == "simple"
@@ -254,7 +254,7 @@ def test_two_passes_are_chosen_where_d_pays_for_h(T, d, r, E, L, act, two):
     """... and the workspace then holds the hidden vectors of a layer at least.  (With 128 experts and d = 256 two passes
     take 1.5 times as long as the fused kernel.)"""
     desc = B.make_desc(T, d, r, E, 8, L, B.BF16, act=act)
-    assert (B.predict_plan(desc).tile == "256x256 two passes") == two
+    assert (B.predict_plan(desc).tile == "two-pass 256x256") == two
     assert (B.predict_workspace_bytes(desc) >= 2 * T * r) == two
 
 

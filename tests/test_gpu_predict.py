@@ -362,7 +362,7 @@ def test_stress_shaped_prefill_sampled_with_near_ties():
     """Two layers of 32768 tokens: 256 token tiles, the launcher's choice for all 48 layers."""
     w = configs.get("stress")
     full, part = _plan(32768, w.d, w.r, w.E, w.k, w.L), _plan(32768, w.d, w.r, w.E, w.k, 2)
-    assert full == part and (part.tile, part.groups, part.chunks_per_group) == ("256x256 two passes", 4, 4), (full, part)
+    assert full == part and (part.tile, part.groups, part.chunks_per_group) == ("two-pass 256x256", 4, 4), (full, part)
     out, tot, tot_m, lays = _paper_shaped("stress", 32768, [0, 47], 64, "prefill")
     assert lays[0].tie_rows.size == 328
     # the planted rows sit inside the tolerance band; they must still be valid selections
@@ -674,7 +674,7 @@ def test_two_passes_in_batches_of_layers(T, d, r, E, k, L, act, shared, batches)
     tokens.  Rows of every layer against the oracle, every row against the fused kernel (2e-6 of the row's scale, as
     above)."""
     desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
-    assert B.predict_plan(desc, want_margin=True).tile == "256x256 two passes"
+    assert B.predict_plan(desc, want_margin=True).tile == "two-pass 256x256"
     need, tiles = B.predict_workspace_bytes(desc), -(-T // 256)
     assert sum(batches) == L and batches[0] * tiles * 256 * (r * 2 + E * 4) == need
     g = torch.Generator(device="cuda").manual_seed(T + E)
@@ -708,7 +708,7 @@ def test_predict_runs_where_its_best_workspace_does_not_fit(monkeypatch):
     T, d, r, E, k, L = 1000, 64, 1024, 200, 3, 33
     desc = B.make_desc(T, d, r, E, k, L, B.BF16)
     least, best = B.predict_workspace_min_bytes(desc), B.predict_workspace_bytes(desc)
-    assert B.predict_plan(desc).tile == "256x256 two passes" and least < best
+    assert B.predict_plan(desc).tile == "two-pass 256x256" and least < best
     x, W1, W2, _, _ = _rand_layers(3, L=L, T=T, d=d, r=r, E=E, dtype="bf16")
     args = _dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k
     one = B.predict(*args, want_logits=True, workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
