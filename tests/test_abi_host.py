@@ -249,6 +249,8 @@ def test_plan_reports_the_family_and_the_tile_choice():
     (2048, 64, 1024, 200, 24, "none", True), (8192, 2048, 4096, 128, 16, "none", False),
     (8192, 2560, 4096, 128, 16, "none", True), (8192, 1024, 2048, 128, 16, "gelu", False),
     (8192, 1536, 2048, 128, 16, "gelu", True), (8192, 2048, 2048, 64, 16, "none", False),
+    (8192, 1984, 512, 100, 16, "silu", False), (8192, 2048, 512, 100, 16, "silu", True),
+    (8192, 2304, 2048, 100, 31, "none", False), (8192, 2304, 2048, 100, 32, "none", True),
 ])
 def test_two_passes_are_chosen_where_d_pays_for_h(T, d, r, E, L, act, two):
     """... and the workspace then holds the hidden vectors of a layer at least.  (With 128 experts and d = 256 two passes
