@@ -48,7 +48,7 @@ TRAFFIC_BYTES = {
                                       ("qwen3_30b_a3b", 8192): 1.43e+10,
                                       ("phi_mini_moe", 8192): 4.908e+09,
                                       ("stress", 32768): 6.887e+10},
-    ("decode", "ab79da61901cf2e7"): {("deepseek_v2_lite", 1): 2.257e+08,
+    ("decode", "c84ab1af92129c3a"): {("deepseek_v2_lite", 1): 2.257e+08,
                                      ("deepseek_v2_lite", 64): 2.587e+08},
 }
 

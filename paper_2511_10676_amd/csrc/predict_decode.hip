@@ -671,8 +671,9 @@ bool decode_supported(const PredictArgs& a)
 //               1024 17.2 / 17.7, 1536 20.3 / 19.0
 //   64 tokens   d = 512 15.3 / 17.0, 1024 18.7 / 18.6, 1536 22.6 / 19.7; 128 experts, 2 layers: 1536 23.6 / 24.6, 2048
 //               27.1 / 26.9; r = 4096: 2048 28.3 / 29.9
-// weights in the caches, row-split / 32 units, 1 token: 256 experts, r = 2048 x 4 layers, d = 1024 1.17 times as long, 2048
-// 0.98; r = 8192, d = 2048 1.21, 4096 1.05; 64 experts d = 768 1.02, 1024 0.94
+// weights in the caches, 32 units against row-split, 1 token: 256 experts, 1024 x 8 layers d = 1024 1.17 times as long, 2048
+// 0.98; 1 to 4 layers d = 768 0.98-1.06, 1024 0.89-1.01 (r = 1024 1.04-1.12); r = 8192 d = 2048 1.21, 4096 1.05; 64 experts d = 768 1.02,
+// 1024 0.94
 static int decode_thin_units(const PredictArgs& a)
 {
     if (a.r % RW_RS != 0) return 0;                           // the order of sums that it keeps is the row-split kernel's
@@ -687,8 +688,9 @@ static int decode_thin_units(const PredictArgs& a)
     if (long_sum && a.E > 128) return 0;
     int from = us == 32 || tb == 2 ? 1024 : tb == 1 ? 512 : 1536;
     if (long_sum) from += 512;
-    if (a.E > 64) from += us == 16 && tb == 1 ? 256 : 512;
-    if (a.E > 128) from += 512;
+    if (a.E > 64) from += us == 32 ? (long_sum || a.L > 4 ? 512 : 0) : tb == 1 ? 256 : 512;
+    // (32 to 63 slices are the most that one wave of the finalize kernel adds up by itself)
+    if (a.E > 128 && (a.L > 4 || (a.r / us >= 32 && a.r / us < 64))) from += 512;
     return a.d >= from ? us : 0;
 }
 

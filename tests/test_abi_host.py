@@ -132,7 +132,8 @@ def test_workspace_a_call_cannot_do_without():
     (1, 384, 2048, 64, 1, 64), (1, 512, 2048, 64, 1, 16), (1, 896, 4096, 64, 1, 64), (1, 1024, 4096, 64, 1, 16),
     (16, 640, 2048, 100, 2, 64), (16, 768, 2048, 100, 2, 16), (9, 896, 2048, 64, 4, 64), (9, 1024, 2048, 64, 4, 32),
     (32, 1024, 2048, 64, 1, 16), (32, 1536, 2048, 100, 2, 16), (64, 1536, 128, 64, 4, 16),
-    (16, 1920, 128, 256, 1, 64), (16, 2048, 128, 256, 1, 32), (1, 4096, 8192, 256, 1, 64),
+    (16, 896, 4096, 256, 1, 64), (16, 1024, 4096, 256, 1, 32), (16, 1920, 1024, 256, 8, 64), (16, 2048, 1024, 256, 8, 32),
+    (1, 4096, 8192, 256, 1, 64), (16, 1408, 1024, 200, 1, 64), (16, 1536, 1024, 200, 1, 32),
 ])
 def test_thin_slices_are_chosen_where_d_pays_for_them(T, d, r, E, L, units):
     """The workspace holds the scores of slices of 16, 32 or 64 units.  (64 tokens of a 512 x 512 layer: 13.7 us in slices of
