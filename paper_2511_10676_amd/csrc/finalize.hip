@@ -141,7 +141,7 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
     top.clear();
     constexpr bool SORTED = KMAX > 2 && NJ * 4 >= KMAX;   // whole lists of keys at a time
     constexpr int JB = SORTED ? KMAX / 4 : 1;
-    uint64_t more[JB * 4];
+    skey more[JB * 4];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int e = 4 * (j * G + g);
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_rows_kernel(
         }
         if constexpr (SORTED) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) more[(j % JB) * 4 + i] = (RAGGED ? e + i : e) < E ? make_key(z[j][i], e + i) : 0;
+            for (int i = 0; i < 4; ++i) more[(j % JB) * 4 + i] = (RAGGED ? e + i : e) < E ? make_key(z[j][i], e + i) : NO_KEY;
             if (j % JB == JB - 1) top.add(more, j < JB);
         }
     }

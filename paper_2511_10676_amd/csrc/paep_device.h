@@ -2,7 +2,7 @@
 //
 //  * bf16 <-> fp32 conversions on raw bit patterns,
 //  * order-preserving packing of (score, expert id) into one 64-bit key, so
-//    that an unsigned compare implements "higher score first, equal scores by
+//    that one compare implements "higher score first, equal scores by
 //    lower expert id" (the tie rule of the C header),
 //  * a sorted top-K list kept in registers, filled by streaming over a row of
 //    scores and merged across the lanes that share a row with wave shuffles,
@@ -111,54 +111,75 @@ __device__ __forceinline__ float unorderable(uint32_t o)
     return __uint_as_float(u);
 }
 
-__device__ __forceinline__ uint64_t make_key(float score, int e)
-{
-    return ((uint64_t)orderable(score) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)e);
-}
-__device__ __forceinline__ int key_expert(uint64_t key) { return (int)(0xFFFFFFFFu - (uint32_t)key); }
-__device__ __forceinline__ float key_score(uint64_t key) { return unorderable((uint32_t)(key >> 32)); }
+// The value a score takes part with: NaN for NaN, +0 for both zeros.
+__device__ __forceinline__ float ordered_value(float f) { return unorderable(orderable(f)); }
 
-// Sorted (descending) list of the KMAX best keys seen; 0 marks an empty slot
-// (every real key is > 0 because its low word is >= 0xFFFFFFFF - PAEP_MAX_E).
+// A key is a double: the ordered score above 30 bits that fall with the expert id, moved to where every pattern is a
+// positive normal number, so that the larger and the smaller of two keys are one full-rate instruction each (an unsigned
+// 64-bit compare and four selects otherwise).  NO_KEY is below every key.
+typedef double skey;
+static constexpr skey NO_KEY = 0.0;
+__device__ __forceinline__ skey make_key(float score, int e)
+{
+    const uint32_t o = orderable(score);
+    return __hiloint2double((int)((o >> 2) + 0x20000000u), (int)((o << 30) | (0x3FFFFFFFu - (uint32_t)e)));
+}
+__device__ __forceinline__ int key_expert(skey key) { return (int)(0x3FFFFFFFu - ((uint32_t)__double2loint(key) & 0x3FFFFFFFu)); }
+__device__ __forceinline__ float key_score(skey key)
+{
+    return unorderable((((uint32_t)__double2hiint(key) - 0x20000000u) << 2) | ((uint32_t)__double2loint(key) >> 30));
+}
+// (fmax and fmin would first make quiet NaNs of their operands' signalling ones, of which there are none)
+__device__ __forceinline__ skey key_max(skey a, skey b)
+{
+    skey r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ skey key_min(skey a, skey b)
+{
+    skey r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Sorted (descending) list of the KMAX best keys seen; NO_KEY marks an empty slot.
 template <int KMAX>
 struct TopList {
-    uint64_t key[KMAX];
+    skey key[KMAX];
 
+    static __device__ __forceinline__ void exchange(skey& a, skey& b)
+    {
+        const skey hi = key_max(a, b);
+        b = key_min(a, b);
+        a = hi;
+    }
     __device__ __forceinline__ void clear()
     {
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) key[j] = 0;
+        for (int j = 0; j < KMAX; ++j) key[j] = NO_KEY;
     }
-    __device__ __forceinline__ void insert(uint64_t c)
+    __device__ __forceinline__ void insert(skey c)
     {
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-            const bool gt = c > key[j];
-            const uint64_t hi = gt ? c : key[j];
-            c = gt ? key[j] : c;
-            key[j] = hi;
-        }
+        for (int j = 0; j < KMAX; ++j) exchange(key[j], c);
     }
     // The KMAX best of this list and another one (both sorted): max of the j-th best here and
     // the j-th worst there is a bitonic sequence of the KMAX best, which log2(KMAX) rounds of compare-exchanges
     // sort -- 8 + 12 exchanges for 8 keys where inserting one key after the other takes 64.
-    __device__ __forceinline__ void merge(const uint64_t (&other)[KMAX])
+    __device__ __forceinline__ void merge(const skey (&other)[KMAX])
     {
         static_assert((KMAX & (KMAX - 1)) == 0, "a power of two");
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) key[j] = other[KMAX - 1 - j] > key[j] ? other[KMAX - 1 - j] : key[j];
+        for (int j = 0; j < KMAX; ++j) key[j] = key_max(other[KMAX - 1 - j], key[j]);
 #pragma unroll
         for (int st = KMAX / 2; st > 0; st >>= 1)
 #pragma unroll
             for (int j = 0; j < KMAX; ++j)
-                if ((j & st) == 0) {
-                    const uint64_t a = key[j], b = key[j + st];
-                    key[j] = a > b ? a : b;
-                    key[j + st] = a > b ? b : a;
-                }
+                if ((j & st) == 0) exchange(key[j], key[j + st]);
     }
     // descending order of KMAX keys by Batcher's odd-even merge sort: 19 compare-exchanges for 8 keys, 63 for 16
-    static __device__ __forceinline__ void sort(uint64_t (&k)[KMAX])
+    static __device__ __forceinline__ void sort(skey (&k)[KMAX])
     {
 #pragma unroll
         for (int p = 1; p < KMAX; p <<= 1)
@@ -168,14 +189,10 @@ struct TopList {
                 for (int j = q % p; j + q < KMAX; j += 2 * q)
 #pragma unroll
                     for (int i = 0; i < q; ++i)
-                        if (i + j + q < KMAX && (i + j) / (2 * p) == (i + j + q) / (2 * p)) {
-                            const uint64_t a = k[i + j], b = k[i + j + q];
-                            k[i + j] = a > b ? a : b;
-                            k[i + j + q] = a > b ? b : a;
-                        }
+                        if (i + j + q < KMAX && (i + j) / (2 * p) == (i + j + q) / (2 * p)) exchange(k[i + j], k[i + j + q]);
     }
-    // KMAX more keys (0: none): sorted by themselves and merged, 39 compare-exchanges where inserting 8 takes 64
-    __device__ __forceinline__ void add(uint64_t (&more)[KMAX], bool first)
+    // KMAX more keys (NO_KEY: none): sorted by themselves and merged, 39 compare-exchanges where inserting 8 takes 64
+    __device__ __forceinline__ void add(skey (&more)[KMAX], bool first)
     {
         sort(more);
         if (first) {
@@ -190,9 +207,9 @@ struct TopList {
     {
 #pragma unroll
         for (int mask = 1; mask < G; mask <<= 1) {
-            uint64_t other[KMAX];
+            skey other[KMAX];
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j) other[j] = __shfl_xor((unsigned long long)key[j], mask, 64);
+            for (int j = 0; j < KMAX; ++j) other[j] = __shfl_xor(key[j], mask, 64);
             merge(other);
         }
     }
@@ -266,9 +283,9 @@ __device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k
     } else {
 #pragma unroll 1
         for (int e0 = g; e0 < E; e0 += G * KMAX) {
-            uint64_t more[KMAX];
+            skey more[KMAX];
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j) more[j] = e0 + G * j < E ? make_key(zrow[e0 + G * j], e0 + G * j) : 0;
+            for (int j = 0; j < KMAX; ++j) more[j] = e0 + G * j < E ? make_key(zrow[e0 + G * j], e0 + G * j) : NO_KEY;
             top.add(more, false);
         }
     }
@@ -293,28 +310,25 @@ template <int NV>
 __device__ __forceinline__ void wave_softmax_topk(const float (&z)[NV], int E, int k, int lane,
                                                   int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
-    uint64_t key[NV];
+    skey key[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int e = lane + 64 * v;
-        key[v] = (e < E) ? make_key(z[v], e) : 0ull;
+        key[v] = (e < E) ? make_key(z[v], e) : NO_KEY;
     }
-    uint64_t mine = 0ull;
+    skey mine = NO_KEY;
     const int rounds = k + ((o.margin_row && k < E) ? 1 : 0);
     for (int j = 0; j < rounds; ++j) {
-        uint64_t best = key[0];
+        skey best = key[0];
 #pragma unroll
-        for (int v = 1; v < NV; ++v) best = key[v] > best ? key[v] : best;
+        for (int v = 1; v < NV; ++v) best = key_max(key[v], best);
 #pragma unroll
-        for (int mask = 1; mask < 64; mask <<= 1) {
-            const uint64_t ot = __shfl_xor((unsigned long long)best, mask, 64);
-            best = ot > best ? ot : best;
-        }
+        for (int mask = 1; mask < 64; mask <<= 1) best = key_max(__shfl_xor(best, mask, 64), best);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) key[v] = (key[v] == best) ? 0ull : key[v];
+        for (int v = 0; v < NV; ++v) key[v] = (key[v] == best) ? NO_KEY : key[v];
         if (lane == j) mine = best;
     }
-    const float m = key_score(__shfl((unsigned long long)mine, 0, 64));     // row maximum
+    const float m = key_score(__shfl(mine, 0, 64));     // row maximum
     const float sc = key_score(mine);
     float s = 0.0f;
     if (o.prob_mode == 0) {
@@ -331,8 +345,8 @@ __device__ __forceinline__ void wave_softmax_topk(const float (&z)[NV], int E, i
         for (int mask = 1; mask < 64; mask <<= 1) s += __shfl_xor(s, mask, 64);
     }
     if (o.margin_row) {
-        const float last = key_score(__shfl((unsigned long long)mine, k - 1, 64));
-        const float next = key_score(__shfl((unsigned long long)mine, k < 64 ? k : 63, 64));
+        const float last = key_score(__shfl(mine, k - 1, 64));
+        const float next = key_score(__shfl(mine, k < 64 ? k : 63, 64));
         if (lane == 0) *o.margin_row = (k < E) ? last - next : __builtin_inff();
     }
     if (lane < k) {
@@ -351,14 +365,11 @@ __device__ __forceinline__ void wave_softmax_topk(const float (&z)[NV], int E, i
 __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, int lane,
                                                        int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
-    const uint64_t key = (lane < E) ? make_key(z, lane) : 0ull;
-    const uint32_t khi = (uint32_t)(key >> 32), klo = (uint32_t)key;
+    const skey key = (lane < E) ? make_key(z, lane) : NO_KEY;
+    const int khi = __double2hiint(key), klo = __double2loint(key);
     int rank = 0;
-    for (int j = 0; j < 64; ++j) {                             // uniform: lane j's key, broadcast
-        const uint32_t ohi = (uint32_t)__builtin_amdgcn_readlane((int)khi, j);
-        const uint32_t olo = (uint32_t)__builtin_amdgcn_readlane((int)klo, j);
-        rank += (ohi > khi || (ohi == khi && olo > klo)) ? 1 : 0;
-    }
+    for (int j = 0; j < 64; ++j)                               // uniform: lane j's key, broadcast
+        rank += __hiloint2double(__builtin_amdgcn_readlane(khi, j), __builtin_amdgcn_readlane(klo, j)) > key ? 1 : 0;
     // score of the key with a given rank, for every lane (rank < number of valid keys)
     auto score_of_rank = [&](int want) {
         float found = 0.0f;
@@ -368,8 +379,8 @@ __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, in
         return found + 0.0f;
     };
     // row maximum as the other routine takes it: the score of the best key (NaNs order last, -0 reads as +0)
-    const float m = key_score(((uint64_t)orderable(score_of_rank(0)) << 32));
-    const float sc = key_score(((uint64_t)khi << 32));
+    const float m = ordered_value(score_of_rank(0));
+    const float sc = ordered_value(z);
     float s = 0.0f;
     if (o.prob_mode == 0) {
         if (lane < E && z == z) s = __expf(z - m);
@@ -382,8 +393,7 @@ __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, in
     }
     if (o.margin_row) {
         float mg = __builtin_inff();
-        if (k < E) mg = key_score(((uint64_t)orderable(score_of_rank(k - 1)) << 32)) -
-                        key_score(((uint64_t)orderable(score_of_rank(k)) << 32));
+        if (k < E) mg = ordered_value(score_of_rank(k - 1)) - ordered_value(score_of_rank(k));
         if (lane == 0) *o.margin_row = mg;
     }
     if (lane < E && rank < k) {
