@@ -17,7 +17,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpaep.so")
 
 SOURCES = ["paep_api.cpp", "predict_simple.hip", "predict_f32.hip", "finalize.hip",
-           "predict_decode.hip", "predict_prefill.hip",
+           "predict_decode.hip", "predict_prefill.hip", "prefill256.hip",
            "group.hip", "score.hip", "profile.hip", "probe.hip", "fold.hip"]
 
 # The target feature switches the packed fp32 vector instructions (v_pk_add_f32, v_pk_mul_f32,

@@ -267,34 +267,57 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
     }
 }
 
-// Softmax + top-k of one row of E scores held in LDS, computed by G
+// Softmax + top-k of one row of E scores in LDS, z(e) being the e-th, computed by G
 // consecutive lanes (G a power of two, the group aligned to G).  Lane g of
 // the group scans e = g, g+G, ...; the per-lane lists are merged with
 // xor-shuffles so that every lane ends with the row's list.
-// SORTED: KMAX scores at a time, sorted and merged; else one inserted after the other (fewer registers).
-template <int KMAX, int G, bool SORTED>
-__device__ __forceinline__ void row_softmax_topk(const float* zrow, int E, int k, int g,
+// SORTED: KMAX scores at a time, sorted and merged, the next ones requested meanwhile; else one inserted after the
+// other (fewer registers).  Scores are read in batches: one by one, a lane waits for LDS E / G times.
+template <int KMAX, int G, bool SORTED, class Z>
+__device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
                                                  int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     TopList<KMAX> top;
     top.clear();
     if constexpr (!SORTED) {
-        for (int e = g; e < E; e += G) top.insert(make_key(zrow[e], e));
+        constexpr int NB = KMAX <= 8 ? 8 : 4;
+#pragma unroll 1
+        for (int e0 = g; e0 < E; e0 += G * NB) {
+            float v[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) v[j] = e0 + G * j < E ? z(e0 + G * j) : 0.0f;
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (e0 + G * j < E) top.insert(make_key(v[j], e0 + G * j));
+        }
     } else {
+        float v[KMAX];
+        auto request = [&](int e0) {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) v[j] = e0 + G * j < E ? z(e0 + G * j) : 0.0f;
+        };
+        request(g);
 #pragma unroll 1
         for (int e0 = g; e0 < E; e0 += G * KMAX) {
             skey more[KMAX];
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j) more[j] = e0 + G * j < E ? make_key(zrow[e0 + G * j], e0 + G * j) : NO_KEY;
+            for (int j = 0; j < KMAX; ++j) more[j] = e0 + G * j < E ? make_key(v[j], e0 + G * j) : NO_KEY;
+            request(e0 + G * KMAX);
             top.add(more, false);
         }
     }
     top.template merge_group<G>();
     write_selection<KMAX, G>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
+        constexpr int NB = SORTED || KMAX <= 8 ? 8 : 4;
         float s = 0.0f;
-        for (int e = g; e < E; e += G) {
-            const float v = zrow[e];
-            if (v == v) s += __expf(v - m);
+#pragma unroll 1
+        for (int e0 = g; e0 < E; e0 += G * NB) {
+            float v[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) v[j] = e0 + G * j < E ? z(e0 + G * j) : 0.0f;
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (e0 + G * j < E && v[j] == v[j]) s += __expf(v[j] - m);
         }
         return s;
     });
@@ -406,14 +429,14 @@ __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, in
 // row_softmax_topk with the smallest list length that holds k (and the runner-up, when the margin is wanted):
 // k <= 16, and k <= 15 when the margin is wanted and k < E.
 // LEAN: the caller's registers are full (lists of 16 by insertion).
-template <int G, bool LEAN>
-__device__ __forceinline__ void row_softmax_topk_upto16(const float* zrow, int E, int k, int g,
+template <int G, bool LEAN, class Z>
+__device__ __forceinline__ void row_softmax_topk_upto16(Z&& z, int E, int k, int g,
                                                         int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     const int need = k + ((o.margin_row && k < E) ? 1 : 0);
-    if (need <= 2)      row_softmax_topk<2, G, false>(zrow, E, k, g, idx_row, probs_row, o);
-    else if (need <= 8) row_softmax_topk<8, G, true>(zrow, E, k, g, idx_row, probs_row, o);
-    else                row_softmax_topk<16, G, !LEAN>(zrow, E, k, g, idx_row, probs_row, o);
+    if (need <= 2)      row_softmax_topk<2, G, false>(z, E, k, g, idx_row, probs_row, o);
+    else if (need <= 8) row_softmax_topk<8, G, true>(z, E, k, g, idx_row, probs_row, o);
+    else                row_softmax_topk<16, G, !LEAN>(z, E, k, g, idx_row, probs_row, o);
 }
 
 }  // namespace paep

@@ -24,26 +24,9 @@
 // token tile; their partial score tiles then meet in a workspace and the
 // finalize kernel adds them in a fixed order.  Long calls of many experts run
 // the first layer by itself and the scores as a second kernel (further down).
-#include <type_traits>
-
-#include "paep_device.h"
-#include "paep_internal.h"
+#include "prefill_common.h"
 
 namespace paep {
-
-// s_waitcnt immediate that waits for vmcnt <= n and nothing else (gfx9 encoding)
-#define PAEP_VMCNT(n) ((((n) & 0xF) | (((n) >> 4) << 14)) | 0x0F70)
-
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-template <int V> using IC = std::integral_constant<int, V>;
-template <int N, class F> __device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(IC<N - 1>{});
-    }
-}
 
 // Tile configuration.
 //   BM tokens x BN hidden units per workgroup and chunk, BK elements of d per
@@ -56,16 +39,15 @@ template <int N, class F> __device__ __forceinline__ void static_for(F&& f)
 // ds_read_b128 touch 64 distinct banks.  The swizzle is applied on the global
 // side of the copy (a lane picks which chunk it fetches), because the LDS side
 // of that instruction is fixed to lane * 16 bytes from a wave-uniform base.
-//   W2L: the chunk's slice of W2 (all experts x BN hidden units) is copied to LDS
+//   The chunk's slice of W2 (all experts x BN hidden units) is copied to LDS
 //   a chunk ahead, behind the stages, and the second layer reads its fragments
 //   from there.  Read straight from global memory, every fragment of the second
 //   layer is a load the next matrix instruction waits for (no registers are
-//   free to request them ahead): measured, the second layer then takes 16% of
-//   the loop with 64 experts and 36-39% with 128 and 256.
-template <int BM_, int BN_, int BK_, int NS_, int WR_, int WT_, int OCC_, bool W2L_ = true>
+//   free to request them ahead): measured, the second layer then takes 36-39%
+//   of the loop with 128 and 256 experts.
+template <int BM_, int BN_, int BK_, int NS_, int WR_, int WT_, int OCC_>
 struct PfCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_, WR = WR_, WT = WT_, OCC = OCC_;
-    static constexpr bool W2L = W2L_;
     static constexpr int CW = BN / 8;                       // 16-byte chunks per row of the W2 slice
     static constexpr int RPIW = 64 / CW;                    // slice rows moved by one copy instruction
     static constexpr int NW = WR * WT, THREADS = 64 * NW;
@@ -93,8 +75,6 @@ struct PfZRows {
 // one kernel for each, because the registers of a form that a call does not use are spilled by the one it does (22
 // spills with all forms in one kernel, none without: 26 layers 2048 x 2048, 4096 tokens 932 -> 899 us; 48 layers
 // 4096 x 2048, 256 experts 39.6 -> 36.1 ms, both with the late fragments below).
-// EB32 = 0: the first layer alone; h goes to memory (`hout`, bf16, laid out in fragments: block of 32 tokens, step of 16
-// units, then 16 bytes for every lane of the wave that will multiply it) and scores_of_h_kernel takes it from there.
 template <class C, int EB32, int MODE>
 __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     int T, int d, int r, int E, int k, int tiles_per_layer, int main_wgs, int main_groups, int tail_wgs,
@@ -104,7 +84,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     const uint16_t* __restrict__ b1, const uint16_t* __restrict__ b2,
     int32_t* __restrict__ idx, float* __restrict__ probs, float* __restrict__ logits,
     float* __restrict__ zpart, int32_t* __restrict__ counts,
-    int prob_mode, float* __restrict__ margin, u32x4* __restrict__ hout)
+    int prob_mode, float* __restrict__ margin)
 {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NS = C::NS, WR = C::WR, WT = C::WT;
     constexpr int WM = C::WM, WN = C::WN, MI = C::MI, NI = C::NI, CPR = C::CPR, RPI = C::RPI;
@@ -169,8 +149,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     const char* xtile = (const char*)(xl + (long long)t0 * d);
 
     f32x16 acc1[MI][NI];
-    constexpr int EBA = EB32 > 0 ? EB32 : 1;
-    f32x16 acc2[EBA][NI];
+    f32x16 acc2[EB32][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -236,21 +215,19 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     // chunks of 16 bytes, chunk c in slot c ^ (e % CW) (swizzled on the global side of the copy, like
     // the tiles).  Rows past E lie outside the buffer resource and arrive as zeros.
     constexpr int CW = C::CW, RPIW = C::RPIW, W2ROWS = EB32 * 32;
-    constexpr int W2J = C::W2L ? W2ROWS / RPIW / C::NW : 0;     // copy instructions per wave and slice
-    static_assert(!C::W2L || W2J * RPIW * C::NW == W2ROWS, "W2 slice copy split");
+    constexpr int W2J = W2ROWS / RPIW / C::NW;   // copy instructions per wave and slice
+    static_assert(W2J * RPIW * C::NW == W2ROWS, "W2 slice copy split");
     uint16_t* w2lds = tiles + NS * STAGE_ELEMS;
     const __amdgpu_buffer_rsrc_t rsrc_w2 =
         __builtin_amdgcn_make_buffer_rsrc((void*)W2l, 0, (int)((long long)E * r * 2), 0x00020000);
     auto issue_w2 = [&](int n) {
-        if constexpr (C::W2L) {
 #pragma unroll
-            for (int j = 0; j < W2J; ++j) {
-                const int row0 = (wave * W2J + j) * RPIW;
-                const int e = row0 + lane / CW;
-                const int chunk = (lane % CW) ^ (e % CW);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w2, (lptr_t)(w2lds + row0 * BN), 16,
-                                                         (int)((uint32_t)(e * r + chunk * 8) * 2u), n * BN * 2, 0, 0);
-            }
+        for (int j = 0; j < W2J; ++j) {
+            const int row0 = (wave * W2J + j) * RPIW;
+            const int e = row0 + lane / CW;
+            const int chunk = (lane % CW) ^ (e % CW);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w2, (lptr_t)(w2lds + row0 * BN), 16,
+                                                     (int)((uint32_t)(e * r + chunk * 8) * 2u), n * BN * 2, 0, 0);
         }
     };
 
@@ -356,28 +333,18 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                         hb[ni] = __builtin_bit_cast(bf16x8, pk);
                     }
                 }
-                if constexpr (EB32 == 0) {
-                    const long long steps = (long long)nchunks * (BN / 16);
-                    const int us = (n * BN + wr * WM + mi * 32 + 16 * s) / 16;
+                // fragments from LDS, the next one requested before the current one is multiplied
+                const int ubase = wr * WM + mi * 32 + 16 * s;
+                u32x4 cur = w2_fragment_lds(0, ubase);
 #pragma unroll
-                    for (int ni = 0; ni < NI; ++ni) {
-                        const long long blk = (long long)tile_id * (BM / 32) + wt * NI + ni;
-                        hout[(blk * steps + us) * 64 + lane] = __builtin_bit_cast(u32x4, hb[ni]);
-                    }
-                } else {
-                    // fragments from LDS, the next one requested before the current one is multiplied
-                    const int ubase = wr * WM + mi * 32 + 16 * s;
-                    u32x4 cur = w2_fragment_lds(0, ubase);
+                for (int eb = 0; eb < EB32; ++eb) {
+                    u32x4 nxt = cur;
+                    if (eb + 1 < EB32) nxt = w2_fragment_lds(eb + 1, ubase);
+                    const bf16x8 wa = __builtin_bit_cast(bf16x8, cur);
 #pragma unroll
-                    for (int eb = 0; eb < EB32; ++eb) {
-                        u32x4 nxt = cur;
-                        if (eb + 1 < EB32) nxt = w2_fragment_lds(eb + 1, ubase);
-                        const bf16x8 wa = __builtin_bit_cast(bf16x8, cur);
-#pragma unroll
-                        for (int ni = 0; ni < NI; ++ni)
-                            acc2[eb][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hb[ni], acc2[eb][ni], 0, 0, 0);
-                        cur = nxt;
-                    }
+                    for (int ni = 0; ni < NI; ++ni)
+                        acc2[eb][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hb[ni], acc2[eb][ni], 0, 0, 0);
+                    cur = nxt;
                 }
                 __builtin_amdgcn_sched_barrier(0);          // keep the W2 fetches of later steps from piling up in registers
             }
@@ -401,7 +368,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     constexpr bool DEFER = (NS >= 3) && (NP % 2 == 0) && (NP / 2 <= MI);
     constexpr int HALF = NP / 2;
     constexpr int PRO = LAG ? NS - 1 : NS;                        // tiles requested before the loop
-    constexpr int WAIT_LDS = 0xC07F;                              // lgkmcnt(0) only
+    constexpr int WAIT_LDS = PAEP_LGKM0;
     // next tile landed: the younger tiles that may still be in flight
     constexpr int WAIT_NEXT = LAG ? PAEP_VMCNT(NP * (NS - 3)) : (PAEP_VMCNT(NP * (NS - 2)) & WAIT_LDS);
 
@@ -464,7 +431,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
                     wg_barrier();
                     // Every wave is past the previous chunk's second layer here, so the slice in LDS may
                     // be replaced by this chunk's; it is read at the end of the chunk, NK - 1 tiles later.
-                    if (C::W2L && kt == 0 && n > n_begin) issue_w2(n);
+                    if (kt == 0 && n > n_begin) issue_w2(n);
                     if constexpr (!DEFER) issue_tile(free_slot);
                     // With 192 accumulators there is no room to carry the next tile's first fragments
                     // across the second layer: fetch them after it instead.
@@ -485,7 +452,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
             free_slot = LAG ? slot : nslot;
             slot = nslot;
         }
-        if (C::W2L && w2_sync) {
+        if (w2_sync) {
             // few tiles per chunk: the slice's copies may still be among the youngest in flight
             __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));
             wg_barrier();
@@ -497,10 +464,6 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
             read_b(stc, IC<0>{}, IC<(((KS - 1) & 1) ^ 1)>{});
         }
         __builtin_amdgcn_s_waitcnt(WAIT_LDS);                     // next tile's first fragments have landed
-    }
-    if constexpr (EB32 == 0) {
-        __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));         // the copies of the pipeline's end land in this workgroup's LDS
-        return;
     }
     // all tile reads done, and the copies of the pipeline's end landed, before LDS is reused
     __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));
@@ -572,7 +535,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
         if (tbase + tl < T) {
             const long long row = (long long)layer * T + tbase + tl;
             const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr, counts ? cnt_lds : nullptr};
-            row_softmax_topk_upto16<ZG, (EB32 > 2)>(zs + tl * ZP, E, k, gg, idx + row * k, probs + row * k, eo);
+            const float* zrow = zs + tl * ZP;
+            row_softmax_topk_upto16<ZG, (EB32 > 2)>([&](int e) { return zrow[e]; }, E, k, gg, idx + row * k, probs + row * k, eo);
         }
         __syncthreads();
     };
@@ -603,33 +567,20 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
     }
 }
 
-// Configurations (all 8 waves and one workgroup per CU except Small).  The 160 KB of
-// LDS hold the stages and, behind them, the chunk's W2 slice (E rounded up to 32 rows x
-// BN hidden units x 2 bytes):
-//   Big       256 x 256 tile, waves 2 x 4 (128 units x 64 tokens each: 0.75 LDS fragment reads per
-//             matrix instruction, the fewest bytes per flop through the CU's vector memory path),
-//             E <= 64; four 32-wide stages of 32 KB + 32 KB slice.
-//   BigDeep   the same tile in two 64-wide stages (64 KB each) + 32 KB slice: half as many barriers
-//             per flop, measured +3% at d = 4096 and no better at d = 2048.
-//   BigWide   the 256 x 256 tile with the 8 waves side by side along tokens (256 units x 32 tokens
-//             each: 128 + 64 accumulators per lane) for 64 < E <= 128; three 32-wide stages + 64 KB
-//             slice.  Measured on the Qwen3-30B-A3B shape: 934 TFLOP/s against 791 for Mid.
-//   Mid       256 tokens x 128 hidden units, waves 2 x 4 (64 units x 64 tokens each, 128 score
-//             accumulators per lane), 64 < E <= 128 when r is not a multiple of 256; five 32-wide
-//             stages of 24 KB + 32 KB slice.
-//   MidWide   the same tile with the waves side by side along tokens, which halves the score
-//             accumulators per lane (E up to 256) at 1.25 fragment reads per matrix instruction;
-//             four stages of 24 KB + 64 KB slice.
+// Configurations.  The LDS holds the stages and, behind them, the chunk's W2 slice (E rounded up to 32 rows x BN hidden
+// units x 2 bytes):
+//   256 x 256 (E <= 128, r a multiple of 256) and 256 tokens x 128 units (65 to 256 experts): prefill256.hip.
+//   Flat      256 x 256 for E <= 64 and d <= 128, 8 waves: a chunk is one or two of prefill256.hip's stages there, and its
+//             ends are what counts (16 layers of 8192 tokens, d = 64, 16 experts, r = 512 20.6 us, 23.9 there; d = 128,
+//             64 experts, r = 1024 68.6 and 71.1; d = 256 from then on no better).
 //   Small     128 x 128, 4 waves, two workgroups per CU (4 x 16 KB + 16 KB slice each): short inputs
 //             and any r that is a multiple of 128.  SmallWide: the same for E > 64 (64 KB slice).
 //   Tiny      64 x 64, 4 waves, four 64-wide stages, two workgroups per CU: calls whose 128 x 128 tiles would not reach
 //             every CU.  What bounds it is the chain of stages, 0.5 us each whatever is tried on it (eight stages, all
 //             of a stage's fragments read a stage ahead: no faster).
-typedef PfCfg<256, 256, 32, 4, 2, 4, 1> CfgBig;
-typedef PfCfg<256, 256, 64, 2, 2, 4, 1> CfgBigDeep;      // long rows (d >= 4096): half as many barriers per flop
-typedef PfCfg<256, 128, 32, 5, 2, 4, 1> CfgMid;
-typedef PfCfg<256, 256, 32, 3, 1, 8, 1> CfgBigWide;      // 64 < E <= 128, r a multiple of 256
-typedef PfCfg<256, 128, 32, 4, 1, 8, 1> CfgMidWide;
+typedef PfCfg<256, 256, 32, 4, 2, 4, 1> CfgFlat;
+struct Cfg256 { static constexpr int BM = 256, BN = 256; };
+struct Cfg256x128 { static constexpr int BM = 256, BN = 128; };
 typedef PfCfg<128, 128, 32, 4, 2, 2, 2> CfgSmall;
 typedef PfCfg<128, 128, 32, 4, 1, 4, 1> CfgSmallWide;
 typedef PfCfg<64, 64, 64, 4, 2, 2, 2> CfgTiny;
@@ -640,7 +591,7 @@ static size_t cfg_lds_bytes(int E)
     // score tile of the epilogue, then E activation counters
     const size_t z = sizeof(float) * (size_t)PfZRows<C, EB32>::value * (size_t)(E + 1) + sizeof(int32_t) * (size_t)E;
     // main loop: the stages, then the W2 slice (32 * EB32 rows of BN hidden units)
-    const size_t loop = (size_t)C::TILE_BYTES + (C::W2L ? (size_t)EB32 * 32 * C::BN * 2 : 0);
+    const size_t loop = (size_t)C::TILE_BYTES + (size_t)EB32 * 32 * C::BN * 2;
     return z > loop ? z : loop;
 }
 
@@ -753,8 +704,21 @@ static hipError_t launch_mode(const PredictArgs& a)
                        a.x_stride, a.w1_stride, a.w2_stride, (const uint16_t*)a.x,
                        (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
                        (const uint16_t*)a.b2, a.idx, a.probs, a.logits, zpart, a.counts, a.prob_mode,
-                       a.margin, nullptr);
+                       a.margin);
     err = hipGetLastError();
+    if (err != hipSuccess || f.split_tiles == 0) return err;
+    return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
+}
+
+template <class C>
+static hipError_t launch_cfg256(const PredictArgs& a)
+{
+    const int tiles = (a.T + C::BM - 1) / C::BM;
+    const PfLayout f = cfg_layout<C>(a);
+    float* zpart = (float*)a.workspace;
+    const PrefillGrid grid{tiles, f.main_tiles * f.main_groups, f.main_groups, f.tail_tiles * f.tail_groups, f.tail_groups,
+                           f.split_tile0, zpart};
+    const hipError_t err = launch_prefill256(a, grid, C::BN, nullptr);
     if (err != hipSuccess || f.split_tiles == 0) return err;
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
 }
@@ -773,25 +737,27 @@ static hipError_t launch_cfg(const PredictArgs& a)
 // Two passes for many experts.  The fused kernel keeps E scores per token in accumulators beside the chunk of h, and
 // with more than 64 experts that costs it the tile shape: 256 x 128 tiles (E up to 256) need half as many bytes again
 // per flop through the CU's copy path as 256 x 256 ones, which is what the loop waits for, and waves side by side along
-// tokens read 1.1-1.25 LDS fragments per matrix instruction instead of 0.75.  Here the first layer runs by itself in the
-// 2 x 4 layout with five stages, h takes a round trip through memory (2 r bytes per token each way, 0.1-0.2 of the
-// layer's bytes at 2048-wide rows), and a second kernel forms the scores.
+// tokens read 1.1-1.25 LDS fragments per matrix instruction.  Here the first layer runs by itself (prefill256.hip),
+// h takes a round trip through memory (2 r bytes per token each way, 0.1-0.2 of the layer's bytes at 2048-wide rows),
+// and a second kernel forms the scores.
 //
 // scores_of_h_kernel: a workgroup owns 256 tokens, eight waves with 32 tokens and all experts each.  h arrives in the
-// layout of the matrix instruction, straight into registers, two stages of 64 units ahead; W2's columns of a stage are
-// copied to LDS for all waves (swizzled like the slices above), a ring of three stages.  What bounds it is the reading
-// of h.  The scores go to memory as [tile][slice][256][E], finalize.hip does the rest.
+// layout of the matrix instruction, straight into registers, two stages of 64 units ahead, and takes its activation here:
+// beside the reading, which bounds this kernel, it costs little, while the first layer's waves have nothing to put beside
+// it.  W2's columns of a stage are copied to LDS for all waves (swizzled like the tiles of token rows above), a ring of
+// three stages.  The scores go to memory as [tile][slice][256][E], finalize.hip does the rest.
 // ---------------------------------------------------------------------------
 static constexpr int SH_BM = 256, SH_BN = 64, SH_NST = 3;
 
-template <int EB32>
-__global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
+// EB: blocks of 16 experts
+template <int EB, int ACT>
+__global__ __launch_bounds__(512, EB <= 8 ? 4 : 2) void scores_of_h_kernel(
     int T, int r, int E, int tiles_per_layer, int slices, long long w2s, const u32x4* __restrict__ h,
     const uint16_t* __restrict__ W2, float* __restrict__ zpart)
 {
-    constexpr int ROWS = EB32 * 32, STAGE_BYTES = ROWS * SH_BN * 2;
+    constexpr int ROWS = EB * 16, STAGE_BYTES = ROWS * SH_BN * 2;
     constexpr int W2J = ROWS / 8 / 8;                       // copy instructions per wave and stage, 8 rows each
-    constexpr int KS = SH_BN / 16;
+    constexpr int KS = SH_BN / 32, NB = SH_BM / 8 / 16;     // steps of 32 units; blocks of 16 tokens per wave
     static_assert(W2J * 64 == ROWS, "rows divide among the waves");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
@@ -799,10 +765,10 @@ __global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
     const int layer = tile_id / tiles_per_layer, t0 = (tile_id - layer * tiles_per_layer) * SH_BM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, g = lane >> 5;
+    const int l16 = lane & 15, g = lane >> 4;
     const int nst = r / SH_BN;
     const int s_begin = (int)((long long)slice * nst / slices), s_end = (int)((long long)(slice + 1) * nst / slices);
-    const u32x4* hw = h + ((long long)(tile_id * (SH_BM / 32) + wave) * (r / 16)) * 64 + lane;
+    const u32x4* hw = h + ((long long)(tile_id * (SH_BM / 16) + wave * NB) * (r / 32)) * 64 + lane;
 
     const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(W2 + (long long)layer * w2s), 0, (int)((long long)E * r * 2), 0x00020000);
@@ -810,7 +776,7 @@ __global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
 #pragma unroll
     for (int j = 0; j < W2J; ++j) {
         const int e = (wave * W2J + j) * 8 + (lane >> 3);
-        w2lane[j] = (uint32_t)(e * r + (((lane & 7) ^ (e & 7)) * 8)) * 2u;   // rows past E lie outside the resource: zeros
+        w2lane[j] = (uint32_t)(e * r + (((lane & 7) ^ ((e >> 1) & 7)) * 8)) * 2u;   // rows past E lie outside the resource: zeros
     }
     auto issue_w2 = [&](int st, int slot) {
 #pragma unroll
@@ -818,21 +784,23 @@ __global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w2, (lptr_t)(smem_raw + slot * STAGE_BYTES + (wave * W2J + j) * 1024),
                                                      16, (int)w2lane[j], st * SH_BN * 2, 0, 0);
     };
-    u32x4 hb[SH_NST][KS];
+    u32x4 hb[SH_NST][KS][NB];
     auto load_h = [&](auto buf_c, int st) {
         constexpr int buf = decltype(buf_c)::value;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) hb[buf][ks] = hw[(long long)(st * KS + ks) * 64];
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) hb[buf][ks][b] = hw[((long long)b * (r / 32) + st * KS + ks) * 64];
     };
-    f32x16 acc[EB32];
+    f32x4 acc[EB][NB];
 #pragma unroll
-    for (int eb = 0; eb < EB32; ++eb)
+    for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[eb][i] = 0.f;
+        for (int b = 0; b < NB; ++b) acc[eb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Stage s is requested two stages ahead, W2 first; past the end the last stage is requested again, into a slot
     // nobody reads any more, so that the count of requests in flight stays the same.
-    constexpr int WAIT_STAGE = PAEP_VMCNT((SH_NST - 2) * (W2J + KS));
+    constexpr int WAIT_STAGE = PAEP_VMCNT((SH_NST - 2) * (W2J + KS * NB));
     static_for<SH_NST - 1>([&](auto b_c) {
         constexpr int b = decltype(b_c)::value;
         const int st = s_begin + b < s_end ? s_begin + b : s_end - 1;
@@ -855,44 +823,50 @@ __global__ __launch_bounds__(512, EB32 <= 4 ? 4 : 2) void scores_of_h_kernel(
                 __builtin_amdgcn_sched_barrier(0);
                 load_h(IC<nb>{}, sn);
                 __builtin_amdgcn_sched_barrier(0);
-                const unsigned char* stage = smem_raw + b * STAGE_BYTES;
+                const uint16_t* stage = (const uint16_t*)(smem_raw + b * STAGE_BYTES);
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const bf16x8 hv = __builtin_bit_cast(bf16x8, hb[b][ks]);
+                    bf16x8 hv[NB];
+                    if constexpr (ACT > 0) __builtin_amdgcn_sched_barrier(0);    // one step's at a time: registers
 #pragma unroll
-                    for (int eb = 0; eb < EB32; ++eb) {
-                        const int e = eb * 32 + l32;
-                        const unsigned char* row = stage + e * (SH_BN * 2) + 8 * g;
-                        const u32x2 lo = *(const u32x2*)(row + (((2 * ks) ^ (l32 & 7)) << 4));
-                        const u32x2 hi = *(const u32x2*)(row + (((2 * ks + 1) ^ (l32 & 7)) << 4));
-                        const u32x4 w = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                        acc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), hv, acc[eb], 0, 0, 0);
+                    for (int n = 0; n < NB; ++n) {
+                        u32x4 v = hb[b][ks][n];
+                        if constexpr (ACT > 0)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                v[q] = pack_bf16x2(act_bf16<ACT>(__uint_as_float(v[q] << 16)), act_bf16<ACT>(__uint_as_float(v[q] & 0xFFFF0000u)));
+                        hv[n] = __builtin_bit_cast(bf16x8, v);
+                    }
+#pragma unroll
+                    for (int eb = 0; eb < EB; ++eb) {
+                        const int e = eb * 16 + l16;
+                        const bf16x8 w = __builtin_bit_cast(bf16x8, *(const u32x4*)(stage + e * SH_BN + (((4 * ks + g) ^ ((l16 >> 1) & 7)) * 8)));
+#pragma unroll
+                        for (int n = 0; n < NB; ++n) acc[eb][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hv[n], acc[eb][n], 0, 0, 0);
                     }
                 }
             }
         });
     }
     __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));              // no copy may land in this LDS once it belongs to another workgroup
-    const int tl = wave * 32 + l32;
-    if (t0 + tl < T) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int tl = (wave * NB + n) * 16 + l16;
+        if (t0 + tl >= T) continue;
         float* dst = zpart + (((long long)tile_id * slices + slice) * SH_BM + tl) * E;
 #pragma unroll
-        for (int eb = 0; eb < EB32; ++eb)
+        for (int eb = 0; eb < EB; ++eb) {
+            const int e = eb * 16 + 4 * g;
+            if (e + 3 < E) {
+                *(f32x4*)(dst + e) = acc[eb][n];
+            } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e = eb * 32 + 8 * q + 4 * g;
-                if (e + 3 < E) {
-                    *(f32x4*)(dst + e) = f32x4{acc[eb][4 * q], acc[eb][4 * q + 1], acc[eb][4 * q + 2], acc[eb][4 * q + 3]};
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (e + i < E) dst[e + i] = acc[eb][4 * q + i];
-                }
+                for (int i = 0; i < 4; ++i)
+                    if (e + i < E) dst[e + i] = acc[eb][n][i];
             }
+        }
     }
 }
-
-typedef PfCfg<256, 256, 32, 5, 2, 4, 1, false> CfgFirst;
 
 // Layers go through the two kernels in batches whose h takes up to TWO_PASS_BYTES: enough workgroups that the launches'
 // ends do not show, no more memory than that buys (48 layers 2048 x 2048, 128 experts, 6011 tokens, in batches of 150 /
@@ -904,7 +878,7 @@ static constexpr int TWO_PASS_GROUPS = 4;
 static int two_pass_groups(const PredictArgs& a)
 {
     int groups = TWO_PASS_GROUPS;
-    while ((a.r / CfgFirst::BN) % groups != 0) groups /= 2;
+    while ((a.r / Cfg256::BN) % groups != 0) groups /= 2;
     return groups;
 }
 
@@ -937,32 +911,16 @@ static TwoPass two_pass_layout(const PredictArgs& a)
 static bool two_pass_wanted(const PredictArgs& a)
 {
     const long long tiles = (long long)((a.T + 255) / 256) * a.L;
-    if (a.r % CfgFirst::BN != 0) return false;
+    if (a.r % Cfg256::BN != 0) return false;
     if (a.E > 128) return tiles >= 128 && (tiles < 256 || a.d >= (a.E < 192 ? 1024 : 768));
     return a.E > 64 && tiles >= 384 && a.d >= (a.act == 2 ? 1536 : a.r <= 512 ? 2048 : tiles >= 1024 ? 2304 : 2560);
 }
 
-template <int MODE>
-static hipError_t launch_first_layer(const PredictArgs& a, int tiles, int groups, u32x4* h)
-{
-    auto kern = prefill_kernel<CfgFirst, 0, MODE>;
-    const size_t lds = CfgFirst::TILE_BYTES;
-    static LdsLimit limit;
-    const hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kern, dim3(tiles * a.L * groups), dim3(CfgFirst::THREADS), lds, a.stream, a.T, a.d, a.r, a.E, a.k,
-                       tiles, tiles * a.L * groups, groups, 0, 1, 0, a.r / CfgFirst::BN, a.x_stride, a.w1_stride,
-                       a.w2_stride, (const uint16_t*)a.x, (const uint16_t*)a.W1, (const uint16_t*)a.W2,
-                       (const uint16_t*)a.b1, (const uint16_t*)nullptr, (int32_t*)nullptr, (float*)nullptr, (float*)nullptr,
-                       (float*)nullptr, (int32_t*)nullptr, 0, (float*)nullptr, h);
-    return hipGetLastError();
-}
-
-template <int EB32>
+template <int EB, int ACT>
 static hipError_t launch_scores_of_h(const PredictArgs& a, int tiles, int slices, const u32x4* h, float* z)
 {
-    auto kern = scores_of_h_kernel<EB32>;
-    const size_t lds = (size_t)SH_NST * EB32 * 32 * SH_BN * 2;
+    auto kern = scores_of_h_kernel<EB, ACT>;
+    const size_t lds = (size_t)SH_NST * EB * 16 * SH_BN * 2;
     static LdsLimit limit;
     const hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
     if (err != hipSuccess) return err;
@@ -991,14 +949,14 @@ static hipError_t launch_two_pass(const PredictArgs& a)
         if (a.logits) b.logits = a.logits + rows * a.E;
         if (a.margin) b.margin = a.margin + rows;
         if (a.counts) b.counts = a.counts + (long long)l0 * a.E;
-        hipError_t err;
-        switch (a.act) {
-        case 0: err = a.b1 ? launch_first_layer<1>(b, tiles, groups, h) : launch_first_layer<0>(b, tiles, groups, h); break;
-        case 1: err = launch_first_layer<2>(b, tiles, groups, h); break;
-        default: err = launch_first_layer<3>(b, tiles, groups, h); break;
-        }
+        const PrefillGrid grid{tiles, tiles * b.L * groups, groups, 0, 1, 0, nullptr};
+        hipError_t err = launch_prefill256(b, grid, Cfg256::BN, h);
         if (err != hipSuccess) return err;
-        err = a.E <= 128 ? launch_scores_of_h<4>(b, tiles, p.slices, h, z) : launch_scores_of_h<8>(b, tiles, p.slices, h, z);
+        switch (a.act) {
+        case 0: err = a.E <= 128 ? launch_scores_of_h<8, 0>(b, tiles, p.slices, h, z) : launch_scores_of_h<16, 0>(b, tiles, p.slices, h, z); break;
+        case 1: err = a.E <= 128 ? launch_scores_of_h<8, 1>(b, tiles, p.slices, h, z) : launch_scores_of_h<16, 1>(b, tiles, p.slices, h, z); break;
+        default: err = a.E <= 128 ? launch_scores_of_h<8, 2>(b, tiles, p.slices, h, z) : launch_scores_of_h<16, 2>(b, tiles, p.slices, h, z); break;
+        }
         if (err != hipSuccess) return err;
         err = launch_finalize(b, z, p.slices, tiles * b.L, SH_BM, 0, tiles);
         if (err != hipSuccess) return err;
@@ -1041,15 +999,15 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
     if (two_pass_wanted(a)) {
         *cfg = 6;
         *groups = two_pass_groups(a);
-        *chunks_per_group = a.r / CfgFirst::BN / *groups;
+        *chunks_per_group = a.r / Cfg256::BN / *groups;
         return;
     }
     *cfg = pick_cfg(a, true);
     switch (*cfg) {
     case 5: cfg_plan<CfgTiny>(a, groups, chunks_per_group); break;
-    case 2: cfg_plan<CfgBig>(a, groups, chunks_per_group); break;
-    case 3: cfg_plan<CfgMid>(a, groups, chunks_per_group); break;
-    case 4: cfg_plan<CfgBigWide>(a, groups, chunks_per_group); break;
+    case 2: cfg_plan<Cfg256>(a, groups, chunks_per_group); break;
+    case 3: cfg_plan<Cfg256x128>(a, groups, chunks_per_group); break;
+    case 4: cfg_plan<Cfg256>(a, groups, chunks_per_group); break;
     case 1: cfg_plan<CfgSmallWide>(a, groups, chunks_per_group); break;
     default: cfg_plan<CfgSmall>(a, groups, chunks_per_group); break;
     }
@@ -1058,9 +1016,9 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
 static size_t fused_workspace_bytes(const PredictArgs& a, bool roomy)
 {
     switch (pick_cfg(a, roomy)) {
-    case 2: return cfg_workspace_bytes<CfgBig>(a);
-    case 3: return cfg_workspace_bytes<CfgMid>(a);
-    case 4: return cfg_workspace_bytes<CfgBigWide>(a);
+    case 2: return cfg_workspace_bytes<Cfg256>(a);
+    case 3: return cfg_workspace_bytes<Cfg256x128>(a);
+    case 4: return cfg_workspace_bytes<Cfg256>(a);
     case 5: return cfg_workspace_bytes<CfgTiny>(a);
     case 1: return cfg_workspace_bytes<CfgSmallWide>(a);
     default: return cfg_workspace_bytes<CfgSmall>(a);
@@ -1091,10 +1049,10 @@ hipError_t launch_predict_prefill(const PredictArgs& a)
     case 5:
         return a.E <= 32 ? launch_cfg<CfgTiny, 1>(a) : a.E <= 64 ? launch_cfg<CfgTiny, 2>(a) : launch_cfg<CfgTiny, 4>(a);
     case 2:
-        if (a.d >= 4096 && a.d % 64 == 0) return a.E <= 32 ? launch_cfg<CfgBigDeep, 1>(a) : launch_cfg<CfgBigDeep, 2>(a);
-        return a.E <= 32 ? launch_cfg<CfgBig, 1>(a) : launch_cfg<CfgBig, 2>(a);
-    case 3: return a.E <= 128 ? launch_cfg<CfgMid, 4>(a) : launch_cfg<CfgMidWide, 8>(a);
-    case 4: return launch_cfg<CfgBigWide, 4>(a);
+        if (a.d <= 128) return a.E <= 32 ? launch_cfg<CfgFlat, 1>(a) : launch_cfg<CfgFlat, 2>(a);
+        return launch_cfg256<Cfg256>(a);
+    case 4: return launch_cfg256<Cfg256>(a);
+    case 3: return launch_cfg256<Cfg256x128>(a);
     case 1: return a.E <= 128 ? launch_cfg<CfgSmallWide, 4>(a) : launch_cfg<CfgSmallWide, 8>(a);
     default: return a.E <= 32 ? launch_cfg<CfgSmall, 1>(a) : launch_cfg<CfgSmall, 2>(a);
     }

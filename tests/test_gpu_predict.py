@@ -631,6 +631,45 @@ def test_biases_that_start_in_the_middle_of_a_word(T, d, r, E, L, act):
     assert torch.equal(a.logits, b.logits) and torch.equal(a.idx, b.idx) and torch.equal(a.probs, b.probs)
 
 
+@pytest.mark.parametrize("E,k,r,d,L,T,act", [
+    # r split (under 256 tiles) and not; one, two and three chunks; d of an odd multiple of 32: half a stage at the end
+    (16, 2, 256, 160, 8, 4100, "none"), (32, 8, 512, 288, 16, 4100, "silu"), (33, 6, 768, 192, 16, 4353, "gelu"),
+    (64, 12, 512, 1056, 8, 4099, "none"), (64, 16, 512, 320, 16, 4351, "silu"), (48, 5, 256, 224, 17, 4096, "gelu"),
+    (65, 8, 512, 160, 16, 4097, "silu"), (128, 16, 256, 32, 16, 4351, "gelu"), (70, 8, 384, 224, 16, 4100, "none"),
+    (129, 3, 640, 288, 16, 4100, "gelu"), (256, 16, 512, 32, 16, 4100, "silu"), (255, 8, 128, 160, 16, 4099, "none"),
+])
+def test_prefill_tiles_of_256_tokens(E, k, r, d, L, T, act):
+    """One- and two-half stages, ragged tiles, experts on either side of a block of 16 and of a shape's limit; both
+    biases; with the least workspace, so that the fused kernel runs.  Every seventh row and the last tile's.
+    (64 experts with SiLU at r = 512: at r = 256 a hidden unit of 4 to 8, ulp 2^-5, that falls on the other side of a rounding
+    boundary meets weights of up to 4.5 / 16 and moves a score by up to 4.4e-3, more than 2e-3 of a scale of 2 in one row of
+    14000, with this kernel and the eight-wave one before it alike; at 512 weights and chance are smaller.)"""
+    x, W1, W2, b1, b2 = _rand_layers(270 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    least = B.predict_workspace_min_bytes(B.make_desc(T, d, r, E, k, L, B.BF16, act=act))
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"256 tokens E={E} r={r} d={d} {act}",
+                             rows=np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 260, T)])),
+                             workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
+    assert out.path == "prefill"
+
+
+@pytest.mark.parametrize("L,T,d,r,E,k", [(1, 3, 128, 128, 60, 16), (1, 3, 128, 128, 200, 16), (1, 100, 64, 128, 60, 7),
+                                         (16, 4097, 160, 256, 60, 16), (16, 4097, 160, 256, 100, 2),
+                                         (16, 4097, 160, 256, 200, 7), (64, 64, 128, 128, 60, 8)])
+def test_selection_of_infinities_zeros_and_nan(L, T, d, r, E, k):
+    """Tokens of zeros leave the scores to b2: infinities, both zeros (a tie), NaN (below everything), the largest and the
+    smallest values, each of them several times.  Selection and order are the rule's on every row."""
+    vals = np.array([np.inf, -np.inf, 0.0, -0.0, np.nan, 3.0e38, -3.0e38, 1e-38, -1e-38, 1.0, -1.0], dtype=np.float32)
+    g = np.random.default_rng(E + k)
+    b2 = vals[g.integers(0, len(vals), (L, E))]
+    x = torch.zeros((L, T, d), dtype=torch.bfloat16, device="cuda")
+    w = lambda *s: torch.full(s, 0.5, dtype=torch.bfloat16, device="cuda")
+    out = B.predict(x, w(L, r, d), w(L, E, r), k, b2=_dev(b2, "bf16"))
+    torch.cuda.synchronize()
+    key = np.where(np.isnan(b2), -np.inf, b2 + 0.0)
+    want = np.stack([np.lexsort((np.arange(E), -key[l], np.isnan(b2[l])))[:k] for l in range(L)])
+    assert (out.idx.cpu().numpy() == want[:, None, :]).all()
+
+
 # ------------------------------------------------------------------ two passes for many experts
 @pytest.mark.parametrize("T,d,r,E,k,L,act,bias", [
     (4097, 64, 256, 129, 8, 8, "none", False),             # 17 tiles a layer, one row in the last; one chunk of r
