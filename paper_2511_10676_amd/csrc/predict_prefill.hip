@@ -710,15 +710,35 @@ static hipError_t launch_mode(const PredictArgs& a)
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
 }
 
+// Tiles of 224 tokens instead of 256 (E <= 64, whole-tile workgroups): where the last round of 256 workgroups is filled better by
+// them.  Time in units of a token of a full round; a partly filled round as in cfg_layout.  The same outputs to the bit.
+// Measured, 2048 x 2048, 64 experts, 256 / 224 tokens, us: 26 x 4096 tokens (416 tiles of 256, 494 of 224; 0.93 here)
+// 868 / 751-773, 26 x 3840 797 / 750, 25 x 4096 803 / 756, with GELU 950 / 905, d = 768, r = 512 106 / 98, 16 experts, d = 2080,
+// r = 1024 456 / 432; and where the rule keeps 256 (1.07 and more): 32 x 4096 935 / 1076, 27 x 4096 843 / 1022, 48 x 4096
+// 1381 / 1472, 44 x 4096, d = 1024 663 / 757.
+static bool tiles_of_224_wanted(const PredictArgs& a)
+{
+    if (a.E > 64) return false;
+    auto time = [&](int tokens) {
+        const int tiles = ((a.T + tokens - 1) / tokens) * a.L, rounds = tiles / 256, tail = tiles % 256;
+        return tokens * (rounds + (tail ? 0.55 + 0.40 * tail / 256 : 0.0));
+    };
+    return time(224) < 0.97 * time(256);
+}
+
 template <class C>
 static hipError_t launch_cfg256(const PredictArgs& a)
 {
-    const int tiles = (a.T + C::BM - 1) / C::BM;
     const PfLayout f = cfg_layout<C>(a);
+    if (C::BN == 256 && f.split_tiles == 0 && tiles_of_224_wanted(a)) {
+        const int tiles = (a.T + 223) / 224;
+        return launch_prefill256(a, PrefillGrid{tiles, tiles * a.L, 1, 0, 1, 0, nullptr}, 224, C::BN, nullptr);
+    }
+    const int tiles = (a.T + C::BM - 1) / C::BM;
     float* zpart = (float*)a.workspace;
     const PrefillGrid grid{tiles, f.main_tiles * f.main_groups, f.main_groups, f.tail_tiles * f.tail_groups, f.tail_groups,
                            f.split_tile0, zpart};
-    const hipError_t err = launch_prefill256(a, grid, C::BN, nullptr);
+    const hipError_t err = launch_prefill256(a, grid, C::BM, C::BN, nullptr);
     if (err != hipSuccess || f.split_tiles == 0) return err;
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
 }
@@ -950,7 +970,7 @@ static hipError_t launch_two_pass(const PredictArgs& a)
         if (a.margin) b.margin = a.margin + rows;
         if (a.counts) b.counts = a.counts + (long long)l0 * a.E;
         const PrefillGrid grid{tiles, tiles * b.L * groups, groups, 0, 1, 0, nullptr};
-        hipError_t err = launch_prefill256(b, grid, Cfg256::BN, h);
+        hipError_t err = launch_prefill256(b, grid, Cfg256::BM, Cfg256::BN, h);
         if (err != hipSuccess) return err;
         switch (a.act) {
         case 0: err = a.E <= 128 ? launch_scores_of_h<8, 0>(b, tiles, p.slices, h, z) : launch_scores_of_h<16, 0>(b, tiles, p.slices, h, z); break;

@@ -1,4 +1,4 @@
-// Prefill in tiles of 256 tokens x 256 hidden units: the kernel of long calls, fused with the scores for up to 64
+// Prefill in tiles of 256 (or 224) tokens x 256 hidden units: the kernel of long calls, fused with the scores for up to 64
 // experts, the first layer alone for more (predict_prefill.hip chooses).
 //
 // Four waves, one per SIMD, own 128 hidden units x 128 tokens of the tile each, as 8 x 8 blocks of
@@ -24,11 +24,13 @@ namespace paep {
 
 namespace {
 
-constexpr int BM = 256, BK = 64;
+constexpr int BK = 64;
 
 // A wave's part of the tile in 16 x 16 blocks, MI of hidden units by NI of tokens; WR waves along the units, 4 / WR along
 // the tokens; two stages in LDS.
 //   Square: 2 x 2 waves of 128 x 128, tiles of 256 x 256: the fewest fragment reads; the first layer alone and E <= 64.
+//   Square224: 128 x 112 each, tiles of 256 x 224, for calls whose last round of workgroups is a badly filled one otherwise
+//           (predict_prefill.hip): a ninth more bytes per flop, and full rounds run at 0.97 of Square's rate (48 x 16 tiles).
 //   Long:   256 units x 64 tokens each, the same tile: a wave has the chunk's whole contribution to its tokens' scores,
 //           which for 65 to 128 experts fit in the registers only so.
 //   Short:  128 units x 64 tokens each, tiles of 256 x 128: E up to 256, and r that is no multiple of 256.
@@ -36,13 +38,14 @@ constexpr int BM = 256, BK = 64;
 // first stage; Long, whose slice does not fit, reads its fragments of W2 from memory: 7 % of the time at 128 experts,
 // 2048 x 2048.  (Short from memory too: 256 experts, d = 512 604 us, 178 of them for W2.)
 template <int MI_, int NI_, int WR_, bool W2L_> struct Shape {
-    static constexpr int MI = MI_, NI = NI_, WR = WR_, WT = 4 / WR_, BN = 16 * MI * WR;
+    static constexpr int MI = MI_, NI = NI_, WR = WR_, WT = 4 / WR_, BN = 16 * MI * WR, BM = 16 * NI * WT;
     static constexpr bool W2L = W2L_;
     static constexpr int STAGE = (BN + BM) * BK;                     // elements: W1 rows, then token rows
     static constexpr int JA = BN / 32, JB = BM / 32, COPIES = JA + JB;   // copy instructions per wave and stage, 8 rows each
-    static_assert(16 * NI * WT == BM && MI % 2 == 0 && NI % 2 == 0, "wave tile");
+    static_assert(MI % 2 == 0, "wave tile");
 };
 typedef Shape<8, 8, 2, true> Square;
+typedef Shape<8, 7, 2, true> Square224;
 typedef Shape<16, 4, 1, false> Long;
 typedef Shape<8, 4, 1, true> Short;
 
@@ -61,18 +64,18 @@ struct Args {
 // A stage is multiplied while the next one lies in LDS and the one after is copied into its place as soon as all its
 // fragments are in registers (slot FREE, a barrier); at slot LANDED (a barrier) the next stage's copies have landed
 // and its first fragments are read.  Where few accumulators leave room for both k-steps' fragments (ROOM), that frees the
-// stage earliest.  Else blocks are walked in two halves of the tokens, so that fragments retire early and the next
+// stage earliest.  Else blocks are walked in two halves of the tokens (4 and 3 blocks of 7), so that fragments retire early and the next
 // k-step's move into their registers, half a k-step before they are needed; what no longer fits behind FREE and LANDED
 // goes to the front of the next stage.  Short's stages are half as long: it has room for eight fragments more (SOME).
 template <class C, int EB> struct Slots {
-    static constexpr int MI = C::MI, NI = C::NI, K = MI * NI, F = MI + NI, H = NI / 2, N = 2 * K;
+    static constexpr int MI = C::MI, NI = C::NI, K = MI * NI, F = MI + NI, H = (NI + 1) / 2, K1 = MI * H, N = 2 * K;
     static constexpr bool ROOM = C::WR == 2 && EB <= 2, SOME = K == 32;
-    static constexpr int mi(int i) { return ROOM ? i / NI : (i % (K / 2)) / H; }
-    static constexpr int ni(int i) { return ROOM ? i % NI : i / (K / 2) * H + i % H; }
+    static constexpr int mi(int i) { return ROOM ? i / NI : i < K1 ? i / H : (i - K1) / (NI - H); }
+    static constexpr int ni(int i) { return ROOM ? i % NI : i < K1 ? i % H : H + (i - K1) % (NI - H); }
     // the q-th fragment to be read: token block 0 .. NI - 1, or NI + unit block
-    static constexpr int frag(int q) { return ROOM || q < H ? q : q < H + MI ? q + H : q - MI; }
+    static constexpr int frag(int q) { return ROOM || q < H ? q : q < H + MI ? q - H + NI : q - MI; }
     // slot of the q-th read of the second k-step's fragments, and of the next stage's first
-    static constexpr int half(int q) { return q < H ? K / 2 + 1 + 2 * q : q < H + MI ? K / 2 + H + 2 + H * (q - H) : K + 4 + 2 * (q - H - MI); }
+    static constexpr int half(int q) { return q < H ? K1 + 1 + 2 * q : q < H + MI ? K1 + 2 + NI % 2 + (NI - H) * (q - H + 1) : K + 4 + 2 * (q - H - MI); }
     static constexpr int second(int q) { return ROOM || (SOME && q < 8) ? 2 * q : SOME ? 2 * q + 1 : half(q); }
     static constexpr int FREE = ROOM ? 34 : second(F - 1) + 10, LANDED = ROOM ? 94 : K + K / 2, STEP = ROOM ? 6 : SOME ? 3 : 4;
     static constexpr int next(int q) { return ROOM ? LANDED + 2 * q : SOME ? LANDED + 1 + q : K + half(q); }
@@ -87,6 +90,13 @@ template <class C, int EB> struct Slots {
     // the slice of W2, in a chunk's first stage, from LANDED on: landed with the next stage's copies
     static constexpr int W2COPIES = C::W2L ? EB * 16 * C::BN * 2 / 1024 / 4 : 0, W2STEP = W2COPIES == 0 ? 1 : (N - LANDED) / W2COPIES;
     static constexpr int w2_copy(int m) { return m >= LANDED && (m - LANDED) % W2STEP == 0 && (m - LANDED) / W2STEP < W2COPIES ? (m - LANDED) / W2STEP : -1; }
+    static constexpr bool each_read()                    // no two reads of a kind in one slot
+    {
+        for (int q = 0; q < F; ++q)
+            if (read_second(second(q)) != q || read_next(next(q)) != q) return false;
+        return true;
+    }
+    static_assert(each_read(), "one slot each");
     static_assert(next(0) >= LANDED && second(F - 1) < FREE && FREE < LANDED && (C::COPIES - 1) * STEP < N, "one stage's events");
     static_assert(next(F - 1) - N < K / 2 && FREE + (C::COPIES - 1) * STEP - N < LANDED - 16, "in time");
     static_assert(W2STEP > 0, "the slice within the stage");
@@ -94,14 +104,14 @@ template <class C, int EB> struct Slots {
 
 constexpr int pitch(int eb) { return eb * 16 + 1; }      // floats per token of the score tile
 // tokens whose scores, of all WR parts, are in LDS at once
-template <class C, int EB> constexpr int score_rows() { return C::WR * BM * pitch(EB) * 4 > 150 * 1024 ? BM / 2 : BM; }
+template <class C, int EB> constexpr int score_rows() { return C::WR * C::BM * pitch(EB) * 4 > 150 * 1024 ? C::BM / 2 : C::BM; }
 
 // EB: blocks of 16 experts, 0: the first layer alone.  MODE: 0 neither bias b1 nor activation, else act + 1, b1 optional.
 template <class C, int EB, int MODE>
 __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
 {
     typedef Slots<C, EB> S;
-    constexpr int MI = C::MI, NI = C::NI, WR = C::WR, WT = C::WT, BN = C::BN, STAGE = C::STAGE, COPIES = C::COPIES;
+    constexpr int MI = C::MI, NI = C::NI, WR = C::WR, WT = C::WT, BN = C::BN, BM = C::BM, STAGE = C::STAGE, COPIES = C::COPIES;
     constexpr int RA = BN / 4, RB = BM / 4;              // rows that a wave copies
     constexpr bool LOW1 = EB > 8;                        // acc1 in the lower half of the register file, acc2 in the upper
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -170,7 +180,8 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
         }
     };
     // The last stage of a chunk where d is an odd multiple of 32: the upper four chunks of every row are moved out of the
-    // resources and arrive as zeros.  (Bit 2 of a lane's chunk is bit 2 of the lane, flipped by bit 2 of s.)
+    // resources and arrive as zeros.  (Bit 2 of a lane's chunk is bit 2 of the lane, flipped by bit 2 of s, which for tokens
+    // is bit 3 of the row.)
     auto mask_tail = [&]() {
         const uint32_t beyond = (d & 32) && iss_kt == NK - 1 ? 0x80000000u : 0u;
 #pragma unroll
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
             lane_a[j] = (lane_a[j] & 0x7FFFFFFFu) | ((((uint32_t)lane << 29) ^ ((uint32_t)(j >> 1) << 31)) & beyond);
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            lane_b[j] = (lane_b[j] & 0x7FFFFFFFu) | ((((uint32_t)lane << 29) ^ ((uint32_t)j << 31)) & beyond);
+            lane_b[j] = (lane_b[j] & 0x7FFFFFFFu) | ((((uint32_t)lane << 29) ^ ((uint32_t)(wave * (RB / 8) + j) << 31)) & beyond);
     };
     // past the end the last stage is copied again, to where nobody looks any more: the count in flight stays the same
     auto copy_advance = [&]() {
@@ -195,7 +206,7 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
     auto read = [&](const uint16_t* st, auto ks_c, auto f_c) {
         constexpr int ks = decltype(ks_c)::value, f = decltype(f_c)::value;
         if constexpr (f < NI) fb[ks][f] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + ((boff ^ (ks * 32)) + f * 16 * BK)));
-        else fa[ks][f - NI] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + ((aoff ^ (ks * 32)) + ((f - NI) / 2 * 32 + (f & 1) * 4) * BK)));
+        else fa[ks][f - NI] = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + ((aoff ^ (ks * 32)) + ((f - NI) / 2 * 32 + ((f - NI) & 1) * 4) * BK)));
     };
     auto barrier = [&]() {
         asm volatile("" ::: "memory");
@@ -407,7 +418,7 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
                 }
             }
             const int tl = tid / G;
-            if (!split && t0 + r0 + tl < T) {             // the lanes of a row together
+            if (!split && tl < ROWS && t0 + r0 + tl < T) {             // the lanes of a row together
                 const long long row = (long long)layer * T + t0 + r0 + tl;
                 const EpilogueOut eo{p.prob_mode, p.margin ? p.margin + row : nullptr, p.counts ? cnt_lds : nullptr};
                 row_softmax_topk_upto16<G, false>([&](int e) { return score(tl, e); }, E, k, tid % G, p.idx + row * k,
@@ -447,12 +458,14 @@ hipError_t launch_experts(const Args& p, int act, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_prefill256(const PredictArgs& a, const PrefillGrid& grid, int units, u32x4* h)
+hipError_t launch_prefill256(const PredictArgs& a, const PrefillGrid& grid, int tokens, int units, u32x4* h)
 {
     const Args p{a.T, a.d, a.r, a.E, a.k, a.prob_mode, grid, a.x_stride, a.w1_stride, a.w2_stride,
                  (const uint16_t*)a.x, (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
                  (const uint16_t*)a.b2, a.idx, a.probs, a.logits, a.margin, a.counts, h};
     if (h) return a.b1 ? launch_mode<Square, 0, 1>(p, a.stream) : launch_mode<Square, 0, 0>(p, a.stream);
+    if (tokens == 224)
+        return a.E <= 32 ? launch_experts<Square224, 2>(p, a.act, a.stream) : launch_experts<Square224, 4>(p, a.act, a.stream);
     if (units == 256)
         return a.E <= 32 ? launch_experts<Square, 2>(p, a.act, a.stream)
              : a.E <= 64 ? launch_experts<Square, 4>(p, a.act, a.stream) : launch_experts<Long, 8>(p, a.act, a.stream);

@@ -32,6 +32,6 @@ struct PrefillGrid {
 
 // prefill256.hip: tiles of 256 tokens x `units` hidden units, 256 (E <= 128) or 128 (64 < E <= 256).  h: the first layer alone,
 // 256 units, hidden vectors (before the activation) to memory, laid out in fragments for scores_of_h; null: everything.
-hipError_t launch_prefill256(const PredictArgs& a, const PrefillGrid& grid, int units, u32x4* h);
+hipError_t launch_prefill256(const PredictArgs& a, const PrefillGrid& grid, int tokens, int units, u32x4* h);
 
 }  // namespace paep

@@ -652,6 +652,21 @@ def test_prefill_tiles_of_256_tokens(E, k, r, d, L, T, act):
     assert out.path == "prefill"
 
 
+@pytest.mark.parametrize("E,k,r,d,L,T,act,bias", [
+    # one, two and four chunks of r; d of an odd multiple of 32; 14 blocks of 16 tokens, the last tile of 1, 64 and 223 rows;
+    # experts on either side of a block of 16 and of 32
+    (64, 6, 512, 192, 26, 4096, "none", False), (33, 16, 512, 160, 26, 4033, "gelu", True),
+    (16, 2, 256, 1056, 26, 4033, "none", True), (32, 8, 1024, 224, 25, 4255, "silu", True),
+    (5, 5, 512, 288, 25, 4096, "none", False), (64, 16, 1024, 160, 25, 4255, "none", True),
+])
+def test_prefill_tiles_of_224_tokens(E, k, r, d, L, T, act, bias):
+    """Calls of 400 to 442 tiles of 256 tokens, 475 to 494 of 224, take the latter.  Every ninth row and the last tile's."""
+    x, W1, W2, b1, b2 = _rand_layers(370 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"224 tokens E={E} r={r} d={d} {act}",
+                             rows=np.unique(np.concatenate([np.arange(0, T, 9), np.arange(T - 224, T)])))
+    assert out.path == "prefill"
+
+
 @pytest.mark.parametrize("L,T,d,r,E,k", [(1, 3, 128, 128, 60, 16), (1, 3, 128, 128, 200, 16), (1, 100, 64, 128, 60, 7),
                                          (16, 4097, 160, 256, 60, 16), (16, 4097, 160, 256, 100, 2),
                                          (16, 4097, 160, 256, 200, 7), (64, 64, 128, 128, 60, 8)])
