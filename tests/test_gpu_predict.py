@@ -667,6 +667,14 @@ def test_prefill_tiles_of_224_tokens(E, k, r, d, L, T, act, bias):
     assert out.path == "prefill"
 
 
+@pytest.mark.parametrize("T,r,E,L", [(300, 1024, 20, 3), (300, 1024, 200, 3), (130, 384, 100, 5), (65, 512, 64, 1), (513, 1024, 16, 2)])
+def test_prefill_few_tiles_of_several_layers(T, r, E, L):
+    """Shares of the chip's eight parts that end within a layer, token tiles fastest in them; every row."""
+    x, W1, W2, b1, b2 = _rand_layers(470 + E, L=L, T=T, d=192, r=r, E=E, dtype="bf16", bias=True)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, 6, "bf16", what=f"few tiles T={T} r={r} E={E} L={L}")
+    assert out.path == "prefill"
+
+
 @pytest.mark.parametrize("L,T,d,r,E,k", [(1, 3, 128, 128, 60, 16), (1, 3, 128, 128, 200, 16), (1, 100, 64, 128, 60, 7),
                                          (16, 4097, 160, 256, 60, 16), (16, 4097, 160, 256, 100, 2),
                                          (16, 4097, 160, 256, 200, 7), (64, 64, 128, 128, 60, 8)])
