@@ -782,34 +782,40 @@ static hipError_t launch_cfg(const PredictArgs& a)
 // h takes a round trip through memory (2 r bytes per token each way, 0.1-0.2 of the layer's bytes at 2048-wide rows),
 // and a second kernel forms the scores.
 //
-// scores_of_h_kernel: a workgroup owns 256 tokens, eight waves with 32 tokens and all experts each.  h arrives in the
+// scores_of_h_kernel: a workgroup owns 128 (E <= 128) or 256 tokens, a wave 32 of them and all experts.  h arrives in the
 // layout of the matrix instruction, straight into registers, two stages of 64 units ahead, and takes its activation here:
 // beside the reading, which bounds this kernel, it costs little, while the first layer's waves have nothing to put beside
 // it.  W2's columns of a stage are copied to LDS for all waves (swizzled like the tiles of token rows above), a ring of
 // three stages.  The scores go to memory as [tile][slice][256][E], finalize.hip does the rest.
+// Up to 128 experts three workgroups of four waves fit a CU (48 KB of stages each).  Eight waves and two workgroups left half of
+// the CUs with one of a batch's 384: 16 layers of 6011 tokens, 2048 x 2048, 128 experts, GELU 860 -> 832 us (both kernels),
+// 48 layers 2460 -> 2368; 8 x 20000, d = 3072, r = 512, SiLU 510 -> 488; 32 x 4000, d = 2560, r = 1024 623 -> 615.
 // ---------------------------------------------------------------------------
 static constexpr int SH_BM = 256, SH_BN = 64, SH_NST = 3;
 
 // EB: blocks of 16 experts
+template <int EB> constexpr int sh_waves() { return EB <= 8 ? 4 : 8; }
 template <int EB, int ACT>
-__global__ __launch_bounds__(512, EB <= 8 ? 4 : 2) void scores_of_h_kernel(
+__global__ __launch_bounds__(sh_waves<EB>() * 64, EB <= 8 ? 3 : 2) void scores_of_h_kernel(
     int T, int r, int E, int tiles_per_layer, int slices, long long w2s, const u32x4* __restrict__ h,
     const uint16_t* __restrict__ W2, float* __restrict__ zpart)
 {
     constexpr int ROWS = EB * 16, STAGE_BYTES = ROWS * SH_BN * 2;
-    constexpr int W2J = ROWS / 8 / 8;                       // copy instructions per wave and stage, 8 rows each
+    constexpr int WAVES = sh_waves<EB>(), PARTS = 8 / WAVES; // workgroups per tile of 256 tokens
+    constexpr int W2J = ROWS / 8 / WAVES;                   // copy instructions per wave and stage, 8 rows each
     constexpr int KS = SH_BN / 32, NB = SH_BM / 8 / 16;     // steps of 32 units; blocks of 16 tokens per wave
-    static_assert(W2J * 64 == ROWS, "rows divide among the waves");
+    static_assert(W2J * 8 * WAVES == ROWS, "rows divide among the waves");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
-    const int slice = blockIdx.x % slices, tile_id = blockIdx.x / slices;
+    const int slice = blockIdx.x % slices, tile_id = blockIdx.x / slices / PARTS, part = blockIdx.x / slices % PARTS;
     const int layer = tile_id / tiles_per_layer, t0 = (tile_id - layer * tiles_per_layer) * SH_BM;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int nst = r / SH_BN;
     const int s_begin = (int)((long long)slice * nst / slices), s_end = (int)((long long)(slice + 1) * nst / slices);
-    const u32x4* hw = h + ((long long)(tile_id * (SH_BM / 16) + wave * NB) * (r / 32)) * 64 + lane;
+    const int first = (part * WAVES + wave) * NB * 16;      // token in the tile
+    const u32x4* hw = h + ((long long)(tile_id * (SH_BM / 16) + first / 16) * (r / 32)) * 64 + lane;
 
     const __amdgpu_buffer_rsrc_t rsrc_w2 = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(W2 + (long long)layer * w2s), 0, (int)((long long)E * r * 2), 0x00020000);
@@ -892,7 +898,7 @@ __global__ __launch_bounds__(512, EB <= 8 ? 4 : 2) void scores_of_h_kernel(
     __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));              // no copy may land in this LDS once it belongs to another workgroup
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        const int tl = (wave * NB + n) * 16 + l16;
+        const int tl = first + n * 16 + l16;
         if (t0 + tl >= T) continue;
         float* dst = zpart + (((long long)tile_id * slices + slice) * SH_BM + tl) * E;
 #pragma unroll
@@ -965,7 +971,7 @@ static hipError_t launch_scores_of_h(const PredictArgs& a, int tiles, int slices
     static LdsLimit limit;
     const hipError_t err = ensure_lds_limit(limit, (const void*)kern, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kern, dim3(tiles * a.L * slices), dim3(512), lds, a.stream, a.T, a.r, a.E, tiles, slices,
+    hipLaunchKernelGGL(kern, dim3(tiles * a.L * slices * (8 / sh_waves<EB>())), dim3(64 * sh_waves<EB>()), lds, a.stream, a.T, a.r, a.E, tiles, slices,
                        a.w2_stride, h, (const uint16_t*)a.W2, z);
     return hipGetLastError();
 }
