@@ -59,7 +59,8 @@ def _code_hash(path):
     import hashlib
     import re
     m = hashlib.sha256()
-    for f in ("predict_%s.hip" % path, "finalize.hip", "paep_device.h"):
+    more = ("prefill256.hip", "prefill_common.h") if path == "prefill" else ()
+    for f in ("predict_%s.hip" % path, *more, "finalize.hip", "paep_device.h"):
         try:
             with open(os.path.join(ROOT, "paper_2511_10676_amd", "csrc", f), "r") as fh:
                 text = fh.read()
