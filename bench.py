@@ -44,11 +44,10 @@ MALL_BYTES = 256 << 20
 # once a kernel's code changes, the figure no longer describes it and the
 # report says null.
 TRAFFIC_BYTES = {
-    ("prefill", "c7de2a5d3054ef1f"): {("deepseek_v2_lite", 4096): 3.838e+09,
-                                      ("qwen3_30b_a3b", 8192): 1.43e+10,
-                                      ("phi_mini_moe", 8192): 4.908e+09,
-                                      ("stress", 32768): 6.887e+10},
-    ("decode", "c84ab1af92129c3a"): {("deepseek_v2_lite", 1): 2.257e+08,
+    ("prefill", "b6b85f0a56bd8c5c"): {("deepseek_v2_lite", 4096): 3.844e+09,
+                                      ("qwen3_30b_a3b", 8192): 1.334e+10,
+                                      ("phi_mini_moe", 8192): 4.906e+09},
+    ("decode", "60f217f8fd35c9ac"): {("deepseek_v2_lite", 1): 2.258e+08,
                                      ("deepseek_v2_lite", 64): 2.587e+08},
 }
 

@@ -219,7 +219,8 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  *   plan[1] tile configuration of the prefill family (0 otherwise):
  *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
  *           5 64x64, 6 256x256 for the first layer and the scores as a second
- *           kernel (5 and 6 given the workspace that
+ *           kernel (2: 224x256 where that fills the last round of workgroups
+ *           better; 5 and 6 given the workspace that
  *           paep_predict_workspace_bytes names; with less, one of the others)
  *   plan[2] workgroups that share one token tile (the inner width r split
  *           between them; 1 = no split, and but for tile 6 no workspace)
