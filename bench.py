@@ -140,6 +140,7 @@ class Runner:
         desc = B.make_desc(T, w.d, w.r, w.E, kp, L, B.BF16)
         self.path = B.resolve_path(desc)
         self.plan = B.predict_plan(desc)
+        self.kernel = B.predict_kernel(desc)
         ws = B.predict_workspace_bytes(desc)
         self.ws = torch.empty(max(ws, 16), dtype=torch.uint8, device=dev)
         # Pipelined mode: two sets of result buffers and two streams, predict of step i+1 (stream A)
@@ -221,8 +222,8 @@ class Runner:
             ach = flops * w.L / (predict_ms * 1e-3) / 1e12
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": measured_traffic("prefill", w.name, T),
-                    "kernel": ("prefill_kernel+scores_of_h_kernel+finalize" if self.plan.tile.startswith("two-pass")
-                               else "prefill_kernel"), "kernel_ms": round(predict_ms, 4)}
+                    "kernel": self.kernel + (" + finalize" if self.plan.groups > 1 else ""),
+                    "kernel_ms": round(predict_ms, 4)}
         else:
             ach = nbytes * w.L / (predict_ms * 1e-3) / 1e9
             roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -236,7 +237,7 @@ class Runner:
         self.torch.cuda.synchronize()
         self.entropy0 = round(float(prof.entropy[0]), 4)
         return {"T": T, "k_pred": self.k_pred, "path": self.path,
-                "launch": (f"{self.plan.tile} tiles, {self.plan.groups} workgroup(s) per token tile"
+                "launch": (f"{self.kernel.split()[1]} tiles, {self.plan.groups} workgroup(s) per token tile"
                            if self.path == "prefill" else
                            f"r in slices of {128 if w.r % 128 == 0 else 64} per workgroup + finalize"),
                 "ms_per_step": round(ms_step, 4),

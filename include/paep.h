@@ -220,7 +220,7 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
  *           5 64x64, 6 256x256 for the first layer and the scores as a second
  *           kernel (2: 224x256 where that fills the last round of workgroups
- *           better; 5 and 6 given the workspace that
+ *           better, see paep_predict_kernel; 5 and 6 given the workspace that
  *           paep_predict_workspace_bytes names; with less, one of the others)
  *   plan[2] workgroups that share one token tile (the inner width r split
  *           between them; 1 = no split, and but for tile 6 no workspace)
@@ -228,6 +228,16 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  * Returns PAEP_OK, or the status paep_predict would give for the descriptor.
  */
 paep_status paep_predict_plan(const paep_predict_desc *desc, int32_t want_margin, int32_t plan[4]);
+
+/*
+ * The kernel that the same call runs in a workspace of `workspace_bytes`, in
+ * words: of the prefill family its name, its tile (tokens x hidden units: here
+ * 224 and 256 tokens differ, and the two kernels of 256x256 tiles) and " tiles
+ * first" where token tiles are the grid's fastest index; "decode", "simple" or
+ * (T = 0) "none" otherwise.  NULL where the call would be refused.  Host only;
+ * for tests and reports, the wording may change.
+ */
+const char *paep_predict_kernel(const paep_predict_desc *desc, int32_t want_margin, size_t workspace_bytes);
 
 /*
  * Architecture 1 of section 4.3 puts BatchNorm between the first linear layer

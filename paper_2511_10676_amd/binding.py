@@ -32,7 +32,8 @@ STATUS_NAMES = ["PAEP_OK", "PAEP_ERR_NULL", "PAEP_ERR_SHAPE", "PAEP_ERR_K", "PAE
 
 STATIC_SCRATCH_BYTES = 16 << 20
 
-EXPORTS = ["paep_predict_workspace_bytes", "paep_predict_workspace_min_bytes", "paep_predict_resolve_path", "paep_predict_plan", "paep_predict",
+EXPORTS = ["paep_predict_workspace_bytes", "paep_predict_workspace_min_bytes", "paep_predict_resolve_path", "paep_predict_plan",
+           "paep_predict_kernel", "paep_predict",
            "paep_static_init", "paep_predict_static",
            "paep_predict_counted", "paep_predict_confidence", "paep_fold_batchnorm",
            "paep_group_workspace_bytes", "paep_group_by_expert", "paep_score",
@@ -92,6 +93,8 @@ def lib() -> ctypes.CDLL:
         L.paep_static_init.restype = ctypes.c_int
         L.paep_predict_plan.argtypes = [dp, i32, ctypes.POINTER(ctypes.c_int32 * 4)]
         L.paep_predict_plan.restype = ctypes.c_int
+        L.paep_predict_kernel.argtypes = [dp, i32, sz]
+        L.paep_predict_kernel.restype = ctypes.c_char_p
         L.paep_fold_batchnorm.argtypes = [vp] * 6 + [ctypes.c_float] + [i32] * 4 + [vp] * 3
         L.paep_fold_batchnorm.restype = ctypes.c_int
         L.paep_group_workspace_bytes.argtypes = [i32] * 4
@@ -210,6 +213,15 @@ def predict_plan(desc: PredictDesc, want_margin: bool = False) -> Plan:
         raise PaepError(st, "paep_predict_plan")
     path = PATH_NAME.get(out[0], "invalid")
     return Plan(path, TILE_CFG.get(out[1], "?") if path == "prefill" else "", int(out[2]), int(out[3]))
+
+
+def predict_kernel(desc: PredictDesc, want_margin: bool = False, workspace_bytes: Optional[int] = None) -> str:
+    """The kernel that the call runs in a workspace of that size (default: predict_workspace_bytes), in words;
+    "" where it would be refused."""
+    if workspace_bytes is None:
+        workspace_bytes = predict_workspace_bytes(desc)
+    name = lib().paep_predict_kernel(ctypes.byref(desc), int(bool(want_margin)), workspace_bytes)
+    return name.decode() if name else ""
 
 
 def _check_predict_inputs(x, W1, W2, k, b1, b2, act, path, prob):

@@ -262,6 +262,23 @@ paep_status paep_predict_plan(const paep_predict_desc* desc, int32_t want_margin
     return PAEP_OK;
 }
 
+const char* paep_predict_kernel(const paep_predict_desc* desc, int32_t want_margin, size_t workspace_bytes)
+{
+    if (check_desc(desc) != PAEP_OK) return nullptr;
+    paep::PredictArgs a = to_args(desc);
+    static float margin_wanted;                              // only its address matters, as above
+    a.margin = want_margin ? &margin_wanted : nullptr;
+    const int path = resolve(desc, a);
+    if (!path || workspace_bytes < path_workspace_min(path, a)) return nullptr;
+    if (a.T == 0) return "none";
+    a.workspace_bytes = workspace_bytes;
+    switch (path) {
+    case PAEP_PATH_PREFILL: return paep::prefill_kernel_name(a);
+    case PAEP_PATH_DECODE: return "decode";
+    default: return "simple";
+    }
+}
+
 paep_status paep_fold_batchnorm(const void* W1_dev, const void* b1_dev, const float* gamma_dev,
                                 const float* beta_dev, const float* mean_dev, const float* var_dev, float eps,
                                 int32_t L, int32_t r, int32_t d, int32_t dtype, void* W1_out_dev,

@@ -75,6 +75,8 @@ hipError_t launch_predict_prefill(const PredictArgs& a);
 // tile configuration id, workgroups per token tile, chunks of r per workgroup (what the launcher will use, given the
 // workspace of prefill_workspace_bytes)
 void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_group);
+// what the launcher runs in a workspace of a.workspace_bytes: kernel, token x hidden-unit tile, order of the grid
+const char* prefill_kernel_name(const PredictArgs& a);
 
 size_t group_workspace_bytes(int L, int T, int k, int E);
 hipError_t launch_group(const int32_t* idx, int L, int T, int k, int E,

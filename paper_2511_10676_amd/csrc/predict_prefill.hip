@@ -747,14 +747,16 @@ static bool tiles_of_224_wanted(const PredictArgs& a)
     return time(224) < 0.97 * time(256);
 }
 
+static hipError_t launch_tiles_of_224(const PredictArgs& a)
+{
+    const int tiles = (a.T + 223) / 224;
+    return launch_prefill256(a, PrefillGrid{tiles, tiles * a.L, 1, 0, 1, 0, nullptr}, 224, Cfg256::BN, nullptr);
+}
+
 template <class C>
 static hipError_t launch_cfg256(const PredictArgs& a)
 {
     const PfLayout f = cfg_layout<C>(a);
-    if (C::BN == 256 && f.split_tiles == 0 && tiles_of_224_wanted(a)) {
-        const int tiles = (a.T + 223) / 224;
-        return launch_prefill256(a, PrefillGrid{tiles, tiles * a.L, 1, 0, 1, 0, nullptr}, 224, C::BN, nullptr);
-    }
     const int tiles = (a.T + C::BM - 1) / C::BM;
     float* zpart = (float*)a.workspace;
     const PrefillGrid grid{tiles, f.main_tiles * f.main_groups, f.main_groups, f.tail_tiles * f.tail_groups, f.tail_groups,
@@ -1089,18 +1091,57 @@ size_t prefill_workspace_bytes(const PredictArgs& a)
     return best > need ? best : need;
 }
 
+// The kernel of a call in the workspace it was given: one choice for the launch and for those who ask.
+enum class Route { Small, SmallWide, Tiny, Flat, Square, Square224, Long, Short, TwoPass };
+static Route route_of(const PredictArgs& a)
+{
+    if (two_pass_wanted(a) && a.workspace_bytes >= two_pass_bytes(a)) return Route::TwoPass;
+    switch (pick_cfg(a, a.workspace_bytes >= fused_workspace_bytes(a, true))) {
+    case 5: return Route::Tiny;
+    case 4: return Route::Long;
+    case 3: return Route::Short;
+    case 2:
+        if (a.d <= 128) return Route::Flat;
+        return cfg_layout<Cfg256>(a).split_tiles == 0 && tiles_of_224_wanted(a) ? Route::Square224 : Route::Square;
+    case 1: return Route::SmallWide;
+    default: return Route::Small;
+    }
+}
+
+template <class C>
+static const char* name_with_order(const PredictArgs& a, const char* groups_first, const char* tiles_first)
+{
+    return tile_fastest<C>(a, cfg_layout<C>(a)) ? tiles_first : groups_first;
+}
+
+const char* prefill_kernel_name(const PredictArgs& a)
+{
+    switch (route_of(a)) {
+    case Route::TwoPass: return "prefill256_kernel 256x256 + scores_of_h_kernel";
+    case Route::Square: return "prefill256_kernel 256x256";
+    case Route::Square224: return "prefill256_kernel 224x256";
+    case Route::Long: return "prefill256_kernel 256x256 wide";
+    case Route::Short: return "prefill256_kernel 256x128";
+    case Route::Flat: return name_with_order<CfgFlat>(a, "prefill_kernel 256x256", "prefill_kernel 256x256 tiles first");
+    case Route::Tiny: return name_with_order<CfgTiny>(a, "prefill_kernel 64x64", "prefill_kernel 64x64 tiles first");
+    case Route::SmallWide:
+        return name_with_order<CfgSmallWide>(a, "prefill_kernel 128x128 wide", "prefill_kernel 128x128 wide tiles first");
+    default: return name_with_order<CfgSmall>(a, "prefill_kernel 128x128", "prefill_kernel 128x128 tiles first");
+    }
+}
+
 hipError_t launch_predict_prefill(const PredictArgs& a)
 {
-    if (two_pass_wanted(a) && a.workspace_bytes >= two_pass_bytes(a)) return launch_two_pass(a);
-    switch (pick_cfg(a, a.workspace_bytes >= fused_workspace_bytes(a, true))) {
-    case 5:
+    switch (route_of(a)) {
+    case Route::TwoPass: return launch_two_pass(a);
+    case Route::Tiny:
         return a.E <= 32 ? launch_cfg<CfgTiny, 1>(a) : a.E <= 64 ? launch_cfg<CfgTiny, 2>(a) : launch_cfg<CfgTiny, 4>(a);
-    case 2:
-        if (a.d <= 128) return a.E <= 32 ? launch_cfg<CfgFlat, 1>(a) : launch_cfg<CfgFlat, 2>(a);
-        return launch_cfg256<Cfg256>(a);
-    case 4: return launch_cfg256<Cfg256>(a);
-    case 3: return launch_cfg256<Cfg256x128>(a);
-    case 1: return a.E <= 128 ? launch_cfg<CfgSmallWide, 4>(a) : launch_cfg<CfgSmallWide, 8>(a);
+    case Route::Flat: return a.E <= 32 ? launch_cfg<CfgFlat, 1>(a) : launch_cfg<CfgFlat, 2>(a);
+    case Route::Square224: return launch_tiles_of_224(a);
+    case Route::Square:
+    case Route::Long: return launch_cfg256<Cfg256>(a);
+    case Route::Short: return launch_cfg256<Cfg256x128>(a);
+    case Route::SmallWide: return a.E <= 128 ? launch_cfg<CfgSmallWide, 4>(a) : launch_cfg<CfgSmallWide, 8>(a);
     default: return a.E <= 32 ? launch_cfg<CfgSmall, 1>(a) : launch_cfg<CfgSmall, 2>(a);
     }
 }

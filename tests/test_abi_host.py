@@ -244,6 +244,43 @@ def test_plan_reports_the_family_and_the_tile_choice():
     assert B.lib().paep_predict_plan(ctypes.byref(d16), 0, None) == E_NULL
 
 
+@pytest.mark.parametrize("T,d,r,E,L,act,kernel", [
+    (4096, 2048, 2048, 64, 26, "none", "prefill256_kernel 224x256"),       # 416 tiles of 256 are two rounds, 494 of 224 too
+    (4096, 2048, 2048, 64, 32, "none", "prefill256_kernel 256x256"),       # whole rounds of 256
+    (4096, 2048, 2048, 64, 12, "gelu", "prefill256_kernel 256x256"),       # r is split
+    (8192, 4096, 1024, 16, 32, "none", "prefill256_kernel 256x256"),
+    (8192, 64, 512, 16, 16, "none", "prefill_kernel 256x256"),             # short rows
+    (8192, 128, 1024, 64, 16, "silu", "prefill_kernel 256x256"),
+    (8192, 2048, 2048, 128, 48, "none", "prefill256_kernel 256x256 wide"),
+    (8192, 2048, 2048, 128, 48, "gelu", "prefill256_kernel 256x256 + scores_of_h_kernel"),
+    (32768, 2048, 4096, 256, 48, "none", "prefill256_kernel 256x256 + scores_of_h_kernel"),
+    (8192, 512, 4096, 256, 16, "none", "prefill256_kernel 256x128"),
+    (8192, 2048, 640, 64, 16, "none", "prefill_kernel 128x128"),           # r no multiple of 256
+    (301, 2048, 2048, 64, 26, "none", "prefill_kernel 128x128"),
+    (301, 2048, 2048, 200, 26, "none", "prefill_kernel 128x128 wide"),
+    (64, 2048, 2048, 64, 26, "none", "decode"), (0, 2048, 2048, 64, 26, "none", "none"),
+    (512, 2040, 2048, 64, 26, "none", "simple"),
+])
+def test_the_kernel_of_a_call_is_named(T, d, r, E, L, act, kernel):
+    """What the launch dispatch itself picks, tiles of 224 tokens and the two kernels of 256 x 256 tiles apart; with the
+    least workspace a call of two passes or 64 x 64 tiles names the kernel that it then runs."""
+    desc = B.make_desc(T, d, r, E, 4, L, B.BF16, act=act)
+    assert B.predict_kernel(desc) == kernel
+    least = B.predict_kernel(desc, workspace_bytes=B.predict_workspace_min_bytes(desc))
+    assert least and "scores_of_h" not in least and "64x64" not in least
+
+
+def test_no_kernel_is_named_for_a_call_that_is_refused():
+    desc = B.make_desc(512, 2048, 2048, 64, 6, 1, B.BF16)
+    assert B.predict_kernel(desc).startswith("prefill_kernel 64x64")
+    least = B.predict_workspace_min_bytes(desc)
+    assert B.predict_kernel(desc, workspace_bytes=least).startswith("prefill_kernel 128x128")
+    assert B.predict_kernel(desc, workspace_bytes=least - 1) == ""
+    assert B.predict_kernel(B.make_desc(512, 2048, 2048, 64, 0, 1, B.BF16)) == ""
+    wide = B.make_desc(4096, 2048, 2048, 64, 16, 32, B.BF16)               # a margin asks for a 17th candidate
+    assert B.predict_kernel(wide) == "prefill256_kernel 256x256" and B.predict_kernel(wide, want_margin=True) == "simple"
+
+
 @pytest.mark.parametrize("T,d,r,E,L,act,two", [
     (8192, 512, 4096, 256, 16, "none", False), (8192, 768, 4096, 256, 16, "none", True),
     (8192, 768, 2048, 140, 16, "none", False), (8192, 1024, 2048, 140, 16, "none", True),
