@@ -230,14 +230,14 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
 paep_status paep_predict_plan(const paep_predict_desc *desc, int32_t want_margin, int32_t plan[4]);
 
 /*
- * The kernel that the same call runs in a workspace of `workspace_bytes`, in
- * words: of the prefill family its name, its tile (tokens x hidden units: here
+ * The kernel that the same call, with or without a bias b1, runs in a workspace
+ * of `workspace_bytes`, in words: of the prefill family its name, its tile (tokens x hidden units: here
  * 224 and 256 tokens differ, and the two kernels of 256x256 tiles) and " tiles
  * first" where token tiles are the grid's fastest index; "decode", "simple" or
  * (T = 0) "none" otherwise.  NULL where the call would be refused.  Host only;
  * for tests and reports, the wording may change.
  */
-const char *paep_predict_kernel(const paep_predict_desc *desc, int32_t want_margin, size_t workspace_bytes);
+const char *paep_predict_kernel(const paep_predict_desc *desc, int32_t want_margin, int32_t with_b1, size_t workspace_bytes);
 
 /*
  * Architecture 1 of section 4.3 puts BatchNorm between the first linear layer

@@ -93,7 +93,7 @@ def lib() -> ctypes.CDLL:
         L.paep_static_init.restype = ctypes.c_int
         L.paep_predict_plan.argtypes = [dp, i32, ctypes.POINTER(ctypes.c_int32 * 4)]
         L.paep_predict_plan.restype = ctypes.c_int
-        L.paep_predict_kernel.argtypes = [dp, i32, sz]
+        L.paep_predict_kernel.argtypes = [dp, i32, i32, sz]
         L.paep_predict_kernel.restype = ctypes.c_char_p
         L.paep_fold_batchnorm.argtypes = [vp] * 6 + [ctypes.c_float] + [i32] * 4 + [vp] * 3
         L.paep_fold_batchnorm.restype = ctypes.c_int
@@ -215,12 +215,13 @@ def predict_plan(desc: PredictDesc, want_margin: bool = False) -> Plan:
     return Plan(path, TILE_CFG.get(out[1], "?") if path == "prefill" else "", int(out[2]), int(out[3]))
 
 
-def predict_kernel(desc: PredictDesc, want_margin: bool = False, workspace_bytes: Optional[int] = None) -> str:
-    """The kernel that the call runs in a workspace of that size (default: predict_workspace_bytes), in words;
+def predict_kernel(desc: PredictDesc, want_margin: bool = False, workspace_bytes: Optional[int] = None,
+                   with_b1: bool = False) -> str:
+    """The kernel that the call, with or without b1, runs in a workspace of that size (default: predict_workspace_bytes), in words;
     "" where it would be refused."""
     if workspace_bytes is None:
         workspace_bytes = predict_workspace_bytes(desc)
-    name = lib().paep_predict_kernel(ctypes.byref(desc), int(bool(want_margin)), workspace_bytes)
+    name = lib().paep_predict_kernel(ctypes.byref(desc), int(bool(want_margin)), int(bool(with_b1)), workspace_bytes)
     return name.decode() if name else ""
 
 

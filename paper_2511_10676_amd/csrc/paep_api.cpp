@@ -262,12 +262,13 @@ paep_status paep_predict_plan(const paep_predict_desc* desc, int32_t want_margin
     return PAEP_OK;
 }
 
-const char* paep_predict_kernel(const paep_predict_desc* desc, int32_t want_margin, size_t workspace_bytes)
+const char* paep_predict_kernel(const paep_predict_desc* desc, int32_t want_margin, int32_t with_b1, size_t workspace_bytes)
 {
     if (check_desc(desc) != PAEP_OK) return nullptr;
     paep::PredictArgs a = to_args(desc);
-    static float margin_wanted;                              // only its address matters, as above
-    a.margin = want_margin ? &margin_wanted : nullptr;
+    static float present;                                    // only its address matters, as above
+    a.margin = want_margin ? &present : nullptr;
+    a.b1 = with_b1 ? &present : nullptr;
     const int path = resolve(desc, a);
     if (!path || workspace_bytes < path_workspace_min(path, a)) return nullptr;
     if (a.T == 0) return "none";

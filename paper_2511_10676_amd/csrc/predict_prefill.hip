@@ -574,9 +574,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
 // Configurations.  The LDS holds the stages and, behind them, the chunk's W2 slice (E rounded up to 32 rows x BN hidden
 // units x 2 bytes):
 //   256 x 256 (E <= 128, r a multiple of 256) and 256 tokens x 128 units (65 to 256 experts): prefill256.hip.
-//   Flat      256 x 256 for E <= 64 and d <= 128, 8 waves: a chunk is one or two of prefill256.hip's stages there, and its
-//             ends are what counts (16 layers of 8192 tokens, d = 64, 16 experts, r = 512 20.6 us, 23.9 there; d = 128,
-//             64 experts, r = 1024 68.6 and 71.1; d = 256 from then on no better).
+//   Flat      256 x 256 for E <= 64 and short rows (flat_wanted), 8 waves: a chunk is a few of prefill256.hip's stages there,
+//             and its ends are what counts.
 //   Small     128 x 128, 4 waves, two workgroups per CU (4 x 16 KB + 16 KB slice each): short inputs
 //             and any r that is a multiple of 128.  SmallWide: the same for E > 64 (64 KB slice).
 //   Tiny      64 x 64, 4 waves, four 64-wide stages, two workgroups per CU: calls whose 128 x 128 tiles would not reach
@@ -745,6 +744,21 @@ static bool tiles_of_224_wanted(const PredictArgs& a)
         return tokens * (rounds + (tail ? 0.55 + 0.40 * tail / 256 : 0.0));
     };
     return time(224) < 0.97 * time(256);
+}
+
+// Flat or prefill256.hip for E <= 64: the latter's stages are 64 columns wide, so that an odd multiple of 32 costs 32 columns
+// more, and the ends of a chunk are bare under its one wave per SIMD.  Biases b1 and activations, whose Flat forms spill,
+// turn that round.  Flat / prefill256, us: 16 layers of 8192 tokens, d = 64, 16 experts, r = 512 20.6 / 23.9; 32 x 4096 tokens, r = 2048, 64 experts,
+// d = 160 120 / 143, 224 143 / 166, 256 155 / 166, 320 183 / 191, 416 222 / 248, 608 307 / 318, with SiLU, r = 1024, d = 160
+// 154 / 134, with b1 alone 120 / 99; from d = 384 (an odd multiple of 32: 640) on prefill256 is level or faster.  Split calls of more than 32 experts with one
+// or two chunks a workgroup wait for their score tiles, which prefill256 writes faster: 4 x 9000 tokens, r = 1024, 64 experts,
+// d = 160 64 / 54, 608 92 / 80.
+static bool flat_wanted(const PredictArgs& a)
+{
+    if (a.d <= 128) return true;
+    if (a.act != 0 || a.b1 || a.d > (a.d % 64 != 0 ? 608 : 320)) return false;
+    const int groups = prefill_groups<Cfg256>(a);
+    return a.E <= 32 || groups == 1 || a.r / Cfg256::BN / groups > 2;
 }
 
 static hipError_t launch_tiles_of_224(const PredictArgs& a)
@@ -1101,7 +1115,7 @@ static Route route_of(const PredictArgs& a)
     case 4: return Route::Long;
     case 3: return Route::Short;
     case 2:
-        if (a.d <= 128) return Route::Flat;
+        if (flat_wanted(a)) return Route::Flat;
         return cfg_layout<Cfg256>(a).split_tiles == 0 && tiles_of_224_wanted(a) ? Route::Square224 : Route::Square;
     case 1: return Route::SmallWide;
     default: return Route::Small;

@@ -270,6 +270,23 @@ def test_the_kernel_of_a_call_is_named(T, d, r, E, L, act, kernel):
     assert least and "scores_of_h" not in least and "64x64" not in least
 
 
+@pytest.mark.parametrize("d,r,E,L,T,act,b1,short", [
+    (160, 2048, 64, 32, 4096, "none", False, True), (608, 2048, 16, 48, 4096, "none", False, True),
+    (672, 2048, 16, 48, 4096, "none", False, False),
+    (256, 1024, 64, 32, 4096, "none", False, True), (320, 256, 64, 26, 4096, "none", False, True),
+    (384, 1024, 64, 32, 4096, "none", False, False),
+    (160, 2048, 64, 32, 4096, "none", True, False), (160, 2048, 64, 32, 4096, "gelu", False, False),
+    (128, 2048, 64, 32, 4096, "gelu", True, True),
+    (160, 2048, 64, 16, 3000, "none", False, True), (160, 1024, 64, 16, 3000, "none", False, False),   # r split: 4, 2 chunks each
+    (160, 1024, 32, 16, 3000, "none", False, True),
+])
+def test_short_rows_of_few_experts_keep_the_eight_wave_kernel(d, r, E, L, T, act, b1, short):
+    """prefill256_kernel takes up to 17 % longer there: its stages are 64 columns wide and nothing runs beside a chunk's ends.
+    With b1 or an activation, whose forms of the other kernel spill, and in split calls with little work each, it is faster."""
+    name = B.predict_kernel(B.make_desc(T, d, r, E, 6, L, B.BF16, act=act), with_b1=b1)
+    assert name.startswith("prefill_kernel 256x256" if short else "prefill256_kernel "), name
+
+
 def test_no_kernel_is_named_for_a_call_that_is_refused():
     desc = B.make_desc(512, 2048, 2048, 64, 6, 1, B.BF16)
     assert B.predict_kernel(desc).startswith("prefill_kernel 64x64")
