@@ -695,6 +695,10 @@ static size_t cfg_workspace_bytes(const PredictArgs& a)
 // the order of groups / of tiles, us, 2048 x 2048, 64 experts: one layer of 1024 tokens 28.9 / 27.4, 2000 tokens 40.4 / 37.4
 // (equally many rows; 256 experts 63.6 / 60.7), r = 4096, d = 1024, 512 tokens 26.4 / 24.4, r = 1024, d = 4096 25.4 / 24.5, 300
 // and 512 tokens the same; where the rule keeps groups 4000 tokens 60.6 / 61.7, 20000 tokens 229 / 245.
+// Only where the rows that the order of groups touches do not fit the 4 MB of that L2: below 3 MB nothing is gained and up to a
+// tenth lost (256 experts, d = 4096, r = 512, 384 tokens 59.4 / 65.5); with more than 64 experts in 64 x 64 tiles, whose score
+// tiles are as large as their operands, below 7 MB (128 experts, 4 layers of 512 tokens, 1024 x 1024 30.6 / 34.8; 3 of 256,
+// r = 2048 29.0 / 32.2; 2048 x 2048, one of 301 27.4 / 28.4; but one of 700 34.1 / 32.2).
 template <class C>
 static bool tile_fastest(const PredictArgs& a, const PfLayout& f)
 {
@@ -704,7 +708,9 @@ static bool tile_fastest(const PredictArgs& a, const PfLayout& f)
     auto rows = [&](int n, int size, int other) {              // n side by side, of `size` rows each
         return (n < share ? n : share) * size + (share + n - 1) / n * other;
     };
-    return rows(tiles, C::BM, chunk_rows) <= rows(groups, chunk_rows, C::BM);
+    const int by_groups = rows(groups, chunk_rows, C::BM);
+    const long long mb = C::BM == 64 && a.E > 64 ? 7 : 3;
+    return rows(tiles, C::BM, chunk_rows) <= by_groups && 2ll * a.d * by_groups >= mb << 20;
 }
 
 template <class C, int EB32, int MODE>

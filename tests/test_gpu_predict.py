@@ -667,11 +667,18 @@ def test_prefill_tiles_of_224_tokens(E, k, r, d, L, T, act, bias):
     assert out.path == "prefill"
 
 
-@pytest.mark.parametrize("T,r,E,L", [(300, 1024, 20, 3), (300, 1024, 200, 3), (130, 384, 100, 5), (65, 512, 64, 1), (513, 1024, 16, 2)])
-def test_prefill_few_tiles_of_several_layers(T, r, E, L):
-    """Shares of the chip's eight parts that end within a layer, token tiles fastest in them; every row."""
-    x, W1, W2, b1, b2 = _rand_layers(470 + E, L=L, T=T, d=192, r=r, E=E, dtype="bf16", bias=True)
-    out, *_ = _run_and_check(x, W1, W2, b1, b2, 6, "bf16", what=f"few tiles T={T} r={r} E={E} L={L}")
+@pytest.mark.parametrize("T,r,E,L,d", [(300, 1024, 20, 3, 192), (300, 1024, 200, 3, 192), (130, 384, 100, 5, 192), (65, 512, 64, 1, 192),
+                                       (513, 1024, 16, 2, 192),
+                                       (65, 1024, 16, 3, 2048), (130, 1024, 16, 5, 2048), (300, 640, 200, 3, 4096),
+                                       (257, 1024, 20, 5, 2048), (1000, 1024, 20, 3, 2048)])
+def test_prefill_few_tiles_of_several_layers(T, r, E, L, d):
+    """Shares of the chip's eight parts that end within a layer, groups of hidden units fastest in them or, with long rows,
+    token tiles, in tiles of 64 x 64, 128 x 128 and those of many experts; every row (of more than 600, every fourth)."""
+    name = B.predict_kernel(B.make_desc(T, d, r, E, 6, L, B.BF16), with_b1=True)
+    assert name.startswith("prefill_kernel ") and name.endswith("tiles first") == (d >= 2048), name
+    x, W1, W2, b1, b2 = _rand_layers(470 + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, 6, "bf16", what=f"few tiles T={T} r={r} E={E} L={L} d={d} {name}",
+                             rows=np.unique(np.concatenate([np.arange(0, T, 4), np.arange(max(0, T - 70), T)])) if T > 600 else None)
     assert out.path == "prefill"
 
 
