@@ -698,19 +698,20 @@ static size_t cfg_workspace_bytes(const PredictArgs& a)
 // Only where the rows that the order of groups touches do not fit the 4 MB of that L2: below 3 MB nothing is gained and up to a
 // tenth lost (256 experts, d = 4096, r = 512, 384 tokens 59.4 / 65.5); with more than 64 experts in 64 x 64 tiles, whose score
 // tiles are as large as their operands, below 7 MB (128 experts, 4 layers of 512 tokens, 1024 x 1024 30.6 / 34.8; 3 of 256,
-// r = 2048 29.0 / 32.2; 2048 x 2048, one of 301 27.4 / 28.4; but one of 700 34.1 / 32.2).
+// r = 2048 29.0 / 32.2; 2048 x 2048, one of 301 27.4 / 28.4; but one of 700 34.1 / 32.2).  Of hidden units a chunk's rows
+// count, not a workgroup's: token rows are read again for every chunk (4 layers of 2310 tokens, 3456 x 4096 in 9 groups of three
+// chunks 365 / 441).
 template <class C>
 static bool tile_fastest(const PredictArgs& a, const PfLayout& f)
 {
     const int tiles = (a.T + C::BM - 1) / C::BM, groups = f.main_groups, share = tiles * a.L * groups / 8;
     if (f.tail_tiles > 0 || share == 0 || share >= tiles * groups) return false;
-    const int chunk_rows = a.r / groups;
     auto rows = [&](int n, int size, int other) {              // n side by side, of `size` rows each
         return (n < share ? n : share) * size + (share + n - 1) / n * other;
     };
-    const int by_groups = rows(groups, chunk_rows, C::BM);
+    const int by_groups = rows(groups, C::BN, C::BM);
     const long long mb = C::BM == 64 && a.E > 64 ? 7 : 3;
-    return rows(tiles, C::BM, chunk_rows) <= by_groups && 2ll * a.d * by_groups >= mb << 20;
+    return rows(tiles, C::BM, C::BN) <= by_groups && 2ll * a.d * by_groups >= mb << 20;
 }
 
 template <class C, int EB32, int MODE>
