@@ -631,40 +631,84 @@ def test_biases_that_start_in_the_middle_of_a_word(T, d, r, E, L, act):
     assert torch.equal(a.logits, b.logits) and torch.equal(a.idx, b.idx) and torch.equal(a.probs, b.probs)
 
 
-@pytest.mark.parametrize("E,k,r,d,L,T,act", [
-    # r split (under 256 tiles) and not; one, two and three chunks; d of an odd multiple of 32: half a stage at the end
-    (16, 2, 256, 160, 8, 4100, "none"), (32, 8, 512, 288, 16, 4100, "silu"), (33, 6, 768, 192, 16, 4353, "gelu"),
-    (64, 12, 512, 1056, 8, 4099, "none"), (64, 16, 512, 320, 16, 4351, "silu"), (48, 5, 256, 224, 17, 4096, "gelu"),
-    (65, 8, 512, 160, 16, 4097, "silu"), (128, 16, 256, 32, 16, 4351, "gelu"), (70, 8, 384, 224, 16, 4100, "none"),
-    (129, 3, 640, 288, 16, 4100, "gelu"), (256, 16, 512, 32, 16, 4100, "silu"), (255, 8, 128, 160, 16, 4099, "none"),
+def _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out, workspace=None):
+    """The call again with counts and margin: the same outputs, counts added to what is there, the margin of the scores."""
+    L, E = W2.shape[:2]
+    dev = lambda v: None if v is None else _dev(v, "bf16")
+    counts = torch.full((L, E), 3, dtype=torch.int32, device="cuda")
+    o = B.predict(dev(x), dev(W1), dev(W2), k, b1=dev(b1), b2=dev(b2), act=act, counts=counts, want_margin=k < 16,
+                  workspace=workspace)
+    torch.cuda.synchronize()
+    assert torch.equal(o.idx, out.idx) and torch.equal(o.probs, out.probs)
+    ref = torch.stack([torch.bincount(o.idx[l].flatten().long(), minlength=E) for l in range(L)])
+    assert torch.equal(counts.long() - 3, ref)
+    if k < 16:
+        srt = torch.sort(out.logits, dim=2, descending=True).values
+        assert torch.equal(o.margin, srt[:, :, k - 1] - srt[:, :, k] if k < E else torch.full_like(o.margin, float("inf")))
+
+
+@pytest.mark.parametrize("E,k,r,d,L,T,act,bias,kernel", [
+    # 256 tiles of 256 tokens: whole rounds, no tiles of 224, r not split; one to three chunks of r; d of an odd multiple of
+    # 32: half a stage at the end; the last tile of 1 to 255 rows; up to 32 and up to 64 experts
+    (16, 2, 256, 160, 16, 3841, "none", True, "256x256"), (8, 3, 512, 448, 16, 4090, "none", False, "256x256"),
+    (32, 8, 512, 288, 16, 4000, "silu", True, "256x256"), (20, 5, 256, 224, 16, 4095, "gelu", True, "256x256"),
+    (64, 12, 512, 1056, 16, 3900, "none", True, "256x256"), (48, 5, 256, 384, 16, 4096, "none", False, "256x256"),
+    (64, 16, 256, 320, 16, 4095, "silu", True, "256x256"), (33, 6, 768, 192, 16, 4095, "gelu", True, "256x256"),
+    # r split over two and three workgroups; 256 + 41 tiles, of which the 41 are
+    (64, 12, 512, 1056, 8, 4099, "none", True, "256x256"), (24, 6, 768, 160, 5, 8229, "silu", True, "256x256"),
+    (64, 6, 1024, 192, 9, 8229, "none", True, "256x256"), (30, 6, 1024, 160, 9, 8229, "gelu", True, "256x256"),
+    # more experts
+    (65, 8, 512, 160, 16, 4097, "silu", True, "256x256 wide"), (128, 16, 256, 32, 16, 4351, "gelu", True, "256x256 wide"),
+    (100, 15, 512, 192, 16, 4095, "silu", True, "256x256 wide"), (128, 7, 768, 96, 16, 4000, "none", False, "256x256 wide"),
+    (128, 8, 512, 288, 8, 4100, "none", True, "256x256 wide"),
+    (70, 8, 384, 224, 16, 4100, "none", True, "256x128"), (90, 7, 384, 160, 16, 4000, "gelu", True, "256x128"),
+    (129, 3, 640, 288, 16, 4100, "gelu", True, "256x128"), (256, 16, 512, 32, 16, 4100, "silu", True, "256x128"),
+    (255, 8, 128, 160, 16, 4099, "none", True, "256x128"), (256, 15, 384, 96, 16, 4095, "none", False, "256x128"),
 ])
-def test_prefill_tiles_of_256_tokens(E, k, r, d, L, T, act):
-    """One- and two-half stages, ragged tiles, experts on either side of a block of 16 and of a shape's limit; both
-    biases; with the least workspace, so that the fused kernel runs.  Every seventh row and the last tile's.
-    (64 experts with SiLU at r = 512: at r = 256 a hidden unit of 4 to 8, ulp 2^-5, that falls on the other side of a rounding
-    boundary meets weights of up to 4.5 / 16 and moves a score by up to 4.4e-3, more than 2e-3 of a scale of 2 in one row of
-    14000, with this kernel and the eight-wave one before it alike; at 512 weights and chance are smaller.)"""
-    x, W1, W2, b1, b2 = _rand_layers(270 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
-    least = B.predict_workspace_min_bytes(B.make_desc(T, d, r, E, k, L, B.BF16, act=act))
+def test_prefill_tiles_of_256_tokens(E, k, r, d, L, T, act, bias, kernel):
+    """One- and two-half stages, ragged tiles, experts on either side of a block of 16 and of a shape's limit; with the
+    least workspace, so that the fused kernel runs.  Every seventh row and the last tile's; counts and margin."""
+    x, W1, W2, b1, b2 = _rand_layers(270 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
+    ws = torch.empty(max(B.predict_workspace_min_bytes(desc), 16), dtype=torch.uint8, device="cuda")
+    assert B.predict_kernel(desc, workspace_bytes=ws.numel(), with_b1=bias) == "prefill256_kernel " + kernel
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"256 tokens E={E} r={r} d={d} {act}",
-                             rows=np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 260, T)])),
-                             workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
+                             rows=np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 260, T)])), workspace=ws)
     assert out.path == "prefill"
+    _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out, ws)
 
 
 @pytest.mark.parametrize("E,k,r,d,L,T,act,bias", [
     # one, two and four chunks of r; d of an odd multiple of 32; 14 blocks of 16 tokens, the last tile of 1, 64 and 223 rows;
     # experts on either side of a block of 16 and of 32
-    (64, 6, 512, 192, 26, 4096, "none", False), (33, 16, 512, 160, 26, 4033, "gelu", True),
+    (64, 6, 512, 640, 26, 4096, "none", False), (33, 16, 512, 160, 26, 4033, "gelu", True),
     (16, 2, 256, 1056, 26, 4033, "none", True), (32, 8, 1024, 224, 25, 4255, "silu", True),
-    (5, 5, 512, 288, 25, 4096, "none", False), (64, 16, 1024, 160, 25, 4255, "none", True),
+    (5, 5, 512, 672, 25, 4096, "none", False), (64, 15, 1024, 160, 25, 4255, "none", True),
 ])
 def test_prefill_tiles_of_224_tokens(E, k, r, d, L, T, act, bias):
-    """Calls of 400 to 442 tiles of 256 tokens, 475 to 494 of 224, take the latter.  Every ninth row and the last tile's."""
+    """Calls of 400 to 442 tiles of 256 tokens, 475 to 494 of 224, take the latter.  Every ninth row and the last tile's; counts
+    and margin."""
+    assert B.predict_kernel(B.make_desc(T, d, r, E, k, L, B.BF16, act=act), with_b1=bias) == "prefill256_kernel 224x256"
     x, W1, W2, b1, b2 = _rand_layers(370 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"224 tokens E={E} r={r} d={d} {act}",
                              rows=np.unique(np.concatenate([np.arange(0, T, 9), np.arange(T - 224, T)])))
     assert out.path == "prefill"
+    _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out)
+
+
+@pytest.mark.parametrize("E,k,r,d,L,T,act,bias", [
+    # 256 x 256 tiles in eight waves: short rows, d = 32 to 608; r split into four and whole, the last 41 of 297 tiles cut
+    (64, 6, 512, 64, 8, 8229, "gelu", True), (20, 15, 256, 128, 16, 4095, "silu", True), (33, 8, 512, 160, 16, 4095, "none", False),
+    (16, 2, 1024, 608, 9, 8229, "none", False), (64, 12, 1024, 96, 4, 8229, "none", True), (64, 8, 2048, 224, 16, 3000, "none", False),
+])
+def test_prefill_short_rows_of_few_experts(E, k, r, d, L, T, act, bias):
+    """Every seventh row and the last tile's; counts and margin."""
+    assert B.predict_kernel(B.make_desc(T, d, r, E, k, L, B.BF16, act=act), with_b1=bias).startswith("prefill_kernel 256x256")
+    x, W1, W2, b1, b2 = _rand_layers(420 + E + d, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"short rows E={E} r={r} d={d} {act}",
+                             rows=np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 260, T)])))
+    assert out.path == "prefill"
+    _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out)
 
 
 @pytest.mark.parametrize("T,r,E,L,d", [(300, 1024, 20, 3, 192), (300, 1024, 200, 3, 192), (130, 384, 100, 5, 192), (65, 512, 64, 1, 192),

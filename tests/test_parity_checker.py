@@ -3,6 +3,8 @@ selections and the checker must refuse each of them (and accept the correct ones
 import numpy as np
 import pytest
 
+from paper_2511_10676_amd import datagen
+
 import oracle
 import parity
 
@@ -72,6 +74,51 @@ def test_sloppy_softmax_is_refused_by_the_own_score_check():
     parity.compare_rows(z, idx, P, idx, sloppy, None, 4, 2e-2, "wide bound passes")
     with pytest.raises(AssertionError, match="softmax of the kernel's own"):
         parity.compare_rows(z, idx, P, idx, sloppy, z.astype(np.float32).astype(np.float64), 4, 2e-2, "planted")
+
+
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_only_a_unit_at_a_rounding_boundary_may_be_rounded_the_other_way(act):
+    """32 tokens, 16 hidden units with weights of up to 1: one that is moved to its bf16 neighbour passes the 2e-3 bar where
+    its sum stands at the boundary, and is refused where it does not, or where it moves by two steps."""
+    g = np.random.default_rng(act)
+    d, r, E, k = 64, 16, 12, 3
+    x = datagen.round_to_storage(g.standard_normal((32, d)).astype(np.float32), "bf16")
+    W1 = datagen.round_to_storage((g.standard_normal((r, d)) / 8).astype(np.float32), "bf16")
+    W2 = datagen.round_to_storage(g.uniform(-1, 1, (E, r)).astype(np.float32), "bf16")
+    # unit 0 is worth 5.015625, halfway between two neighbours, whatever the token (its first weight and x[:, 0] alone)
+    x[:, 0] = 1.0
+    W1[0] = 0.0
+    W1[0, 0], W1[0, 1], x[:, 1] = 5.0, 2.0 ** -6, 1.0
+    # unit 1 holds a value whose activation stands within 1e-6 of a boundary
+    W1[1], W1[1, 0] = 0.0, (0.0, 5.9375, -0.3359375)[act]
+    _, _, z = oracle.predict(x, W1, W2, k, act=act, round_h=True)
+    u = x.astype(np.float64) @ W1.astype(np.float64).T
+    h, step = parity._bf16(u), 2.0 ** -5
+    assert (h[:, 0] == 5.0).all() and (u[:, 0] == 5.0 + step / 2).all()
+
+    def check(unit, steps):
+        moved = h[7, unit] + steps * np.ldexp(1.0, np.frexp(h[7, unit])[1] - 8)
+        zg = z.copy()
+        zg[7] += (parity._bf16(parity._act(moved, act)) - parity._bf16(parity._act(h[7, unit], act))) * W2[:, unit].astype(np.float64)
+        zg = zg.astype(np.float32)
+        idx = parity.topk_rule(zg, k)
+        probs = np.take_along_axis(parity.softmax64(zg.astype(np.float64)), idx.astype(np.int64), axis=1).astype(np.float32)
+        return parity.check_layer(x, W1, W2, None, None, act, k, "bf16", idx, probs, zg, what="planted")
+
+    _, rep = check(0, 1)
+    assert rep.rows == 32 and rep.max_logit_err < 1e-5
+    with pytest.raises(AssertionError, match="scores off by more than 0.002"):
+        check(0, 3)
+    if act:
+        value, other = parity._neighbour(parity._act(h[7], act))
+        z_other = z[7] + (other[1] - value[1]) * W2[:, 1]
+        found = parity.rounded_the_other_way(x[7], W1, W2, None, act, z[7], z_other)
+        assert np.abs(found - z_other).max() < 1e-12
+    far = 2 + int(u[7, 2:].argmax())                             # a unit on the grid's own side, moved by 4e-3 of the scale
+    ulp = np.ldexp(1.0, np.frexp(h[7, far])[1] - 8)
+    assert abs(u[7, far] - h[7, far]) < 0.49 * ulp
+    with pytest.raises(AssertionError, match="scores off by more than 0.002"):
+        check(far, int(np.ceil(4e-3 * np.abs(z[7]).max() / (ulp * np.abs(W2[:, far]).max()))))
 
 
 def test_strict_row_mismatch_duplicate_and_out_of_range_are_refused():
