@@ -617,8 +617,10 @@ bool prefill_supported(const PredictArgs& a)
 //    (measured: 3.3x fewer bytes fetched past L2 at 8 groups), but every extra
 //    group costs a pipeline fill and a score tile written and re-read.  Two
 //    groups where the token tile is large (d >= 4096: 2 MB per tile; one / two /
-//    four groups on 32 layers 1024 x 4096, 8192 tokens 2070 / 1865 / 1818 us); at
-//    d = 2048 the gain is of the order of the differences between sizes.
+//    four groups, 8192 tokens, us: 32 layers 1024 x 4096, 16 experts 1658 / 1559 / 1598; 2048 x 4096,
+//    64 experts 3635 / 3297 / 3245); at d = 2048 there is nothing to gain (1658 / 1669 / 1742; 48 layers,
+//    128 experts 2708 / 2698 / 2907).  The line is the former kernels': d = 3072 would take two
+//    (1489 / 1300 / 1378), d = 5120 four (26 layers of 4096 tokens 2145 / 2037 / 1804).
 template <class C>
 static int prefill_groups(const PredictArgs& a)
 {
@@ -637,8 +639,9 @@ static int prefill_groups(const PredictArgs& a)
 // `tail_tiles` with `tail_groups` each.  With whole-tile workgroups (main_groups = 1) the tiles beyond the
 // last full round of 256 would keep a fraction of the CUs busy for a whole tile's duration; where it pays
 // they are cut along r into pieces short enough to fill every CU evenly, at the price of the score-tile
-// exchange (measured, 2048 x 2048 layers of 16 tiles: 20 layers 842 -> 985 TFLOP/s, 24 layers 934 -> 1015;
-// with 26 layers the tail of 160 tiles is too long for any cut to win and stays whole).
+// exchange.  2048 x 2048 layers of 16 tiles, 64 experts, whole / in 2 / 4 / 8 pieces, us: 17 layers (a tail of 16) 730 / 569 /
+// 493 / 474, 20 (64) 764 / 604 / 561 / 560, 24 (128) 795 / 650 / 662 / 678, 26 (160) 811 / 792 / 734 / 730, 28 (192) 837 / 840 /
+// 770 / 800, 30 (224) 884 / 842 / 858 / 856; 128 experts 26 layers 864 / 876 / 795 / 800.
 struct PfLayout {
     int main_tiles, main_groups, tail_tiles, tail_groups;
     int split_tile0, split_tiles, split_groups;              // the tiles that go through the workspace
@@ -657,12 +660,10 @@ static PfLayout cfg_layout(const PredictArgs& a)
     constexpr int CUS = 256;
     const int tail = tiles % CUS;
     if (tiles < CUS || tail == 0) return f;
-    // Time of the tail in units of one whole-tile workgroup on a full chip, from measurements on 2048 x 2048
-    // layers: uncut, the tail's workgroups run faster than on a full chip (the clock rises when CUs idle:
-    // 0.62 for 64 tiles, 0.76 for 128, 0.92 for 160); cut g ways they take 1/g plus about 0.08 each (pipeline
-    // fill, the score-tile exchange, and the XCD's workgroups no longer walking the same chunk of W1).  The exchange was then
-    // part of this kernel; with the finalize kernels a cut pays from longer tails on than this still leaves whole (28
-    // layers, a tail of 192 tiles: whole 924-942, in four pieces 895 us).
+    // Time of the tail in units of one whole-tile workgroup on a full chip: uncut, the tail's workgroups run faster than on
+    // a full chip (the clock rises when CUs idle); cut g ways they take 1/g plus about 0.08 each (pipeline fill, the
+    // score-tile exchange, and the XCD's workgroups no longer walking the same chunk of W1).  The constants are those of the
+    // eight-wave kernels, whose exchange was dearer: tails of 160 to 224 tiles stay whole although cuts in four win above.
     int best = 1;
     double best_t = 0.55 + 0.40 * tail / CUS;
     for (int g = 2; g <= 8 && g <= NC; g *= 2) {
@@ -739,10 +740,10 @@ static hipError_t launch_mode(const PredictArgs& a)
 
 // Tiles of 224 tokens instead of 256 (E <= 64, whole-tile workgroups): where the last round of 256 workgroups is filled better by
 // them.  Time in units of a token of a full round; a partly filled round as in cfg_layout.  The same outputs to the bit.
-// Measured, 2048 x 2048, 64 experts, 256 / 224 tokens, us: 26 x 4096 tokens (416 tiles of 256, 494 of 224; 0.93 here)
-// 868 / 751-773, 26 x 3840 797 / 750, 25 x 4096 803 / 756, with GELU 950 / 905, d = 768, r = 512 106 / 98, 16 experts, d = 2080,
-// r = 1024 456 / 432; and where the rule keeps 256 (1.07 and more): 32 x 4096 935 / 1076, 27 x 4096 843 / 1022, 48 x 4096
-// 1381 / 1472, 44 x 4096, d = 1024 663 / 757.
+// The same kernel, whole tiles, one box, 2048 x 2048, 64 experts, 256 / 224 tokens, us: 26 x 4096 tokens (416 tiles of 256, 494 of
+// 224; 0.93 here) 828 / 759, 26 x 3840 792 / 733, 25 x 4096 786 / 741, with GELU 935 / 879, 26 x 4096, d = 768, r = 512 98 / 92,
+// 16 experts, d = 2080, r = 1024 451 / 428; and where the rule keeps 256 (1.07 and more): 32 x 4096 896 / 1134, 27 x 4096 837 / 1061,
+// 48 x 4096 1300 / 1516, 44 x 4096, d = 1024 646 / 767.
 static bool tiles_of_224_wanted(const PredictArgs& a)
 {
     if (a.E > 64) return false;
@@ -939,11 +940,13 @@ __global__ __launch_bounds__(sh_waves<EB>() * 64, EB <= 8 ? 3 : 2) void scores_o
 }
 
 // Layers go through the two kernels in batches whose h takes up to TWO_PASS_BYTES: enough workgroups that the launches'
-// ends do not show, no more memory than that buys (48 layers 2048 x 2048, 128 experts, 6011 tokens, in batches of 150 /
-// 300 / 600 / 1300 MB 3.33 / 3.13 / 3.04 / 2.95 ms; 4096 x 2048, 256 experts, 32768 tokens 300 / 600 / 1300 MB 27.9 / 27.1 / 27.9).
+// ends do not show, no more memory than that buys (batches of 150 / 300 / 600 / 1300 MB, ms: 48 layers 2048 x 2048, 128 experts,
+// GELU, 6011 tokens 2.68 / 2.56 / 2.36 / 2.33; 256 experts, 8192 tokens 3.17 / 3.04 / 2.99 / 3.04; 4096 x 2048, 256 experts, 32768
+// tokens 23.0 / 23.0 / 22.6 / 22.8).
 static constexpr long long TWO_PASS_BYTES = 600ll * 1000 * 1000;
 // Workgroups per token tile of the first kernel, each with its share of r: 4 of them and 8 tiles run on an XCD together and
-// share their rows of W1 and x through its L2 (2 / 4 / 8: 28.1 / 27.1 / 27.4 ms on the larger shape).
+// share their rows of W1 and x through its L2 (1 / 2 / 4 / 8 on the same three: 2.86 / 2.31 / 2.30 / 2.40, 3.61 / 3.10 / 2.98 / 3.07,
+// 28.2 / 23.7 / 22.6 / 22.9 ms).
 static constexpr int TWO_PASS_GROUPS = 4;
 static int two_pass_groups(const PredictArgs& a)
 {
@@ -969,15 +972,16 @@ static TwoPass two_pass_layout(const PredictArgs& a)
 }
 
 // Where the fused kernel is the slower one.  What two passes cost goes with r (h written and read again), what they save
-// with d, more of it where the fused kernel has to be 128 units wide (E > 128) and where GELU meets 192 accumulators in
-// it (64 < E <= 128).  Two passes / fused:
-//   256 experts  d = 512 0.94-1.18, 768 0.82-1.03, 1024 0.80-0.99, 2048 0.74-0.89, 4096 0.66-0.77 (from 256 tiles on, 320 to
-//                640 of them, r = 1024 to 4096); 192 tiles: 0.91 or less at any d
-//   130 experts  d = 768 0.84-1.11, 1024 0.81-1.01, 2048 0.75-0.90
-//   128 experts  d = 1024 1.06-1.29, 1536 1.01-1.22, 2048 0.96-1.08 (r = 512 0.91-0.97), 2304 0.95-1.03 (from 1024 tiles on
-//                0.91-1.03), 2560 0.89-1.02, 4096 0.92-1.04 (384 to 1568 tiles); with SiLU 2048 0.97-1.06, 2560 0.88-1.00; with GELU 1024 0.91-1.07, 1536 0.86-1.03,
-//                2048 0.82-0.92
-//   64 experts   slower: 2048 x 2048, 32 layers x 4096 tokens 1030 / 1101 us, 26 x 8192 1621 / 1850 us
+// with d, more of it where the fused kernel has to be 128 units wide (E > 128).  Two passes / fused, prefill256.hip on either
+// side, r = 512 to 4096, 320 to 1024 tiles unless said:
+//   256 experts  d = 256 1.05-1.67, 512 1.00-1.31, 768 0.96-1.17 (r = 4096 1.00-1.17), 1024 0.88-0.96 (1.08 at 320 tiles, r = 4096),
+//                2048 0.75-0.91, 4096 0.67-0.80; SiLU and GELU 512 0.90-1.00, 768 0.87-0.94; 192 tiles 0.61-0.98 at any d and r but
+//                r = 4096 with d = 256 (1.14)
+//   160 experts  d = 768 0.99-1.18, 1024 0.90-1.07, 1536 0.80-0.98, 2048 0.76-0.91
+//   128 experts  d = 512 1.02-1.40, 1024 1.06-1.26, 1536 1.02-1.24, 2048 0.97-1.17 (r = 512 0.89-1.00), 2304 0.91-1.10 (1024 tiles
+//                0.95-0.98), 2560 0.90-1.06, 4096 0.84-1.04; SiLU 1536 0.99-1.08, 2048 0.92-1.04, 2560 0.86-0.97; GELU 1024
+//                0.95-1.06, 1536 0.93-1.00, 2048 0.89-0.99, 2560 0.84-0.95
+//   64 experts   slower: with the eight-wave kernels 2048 x 2048, 32 layers x 4096 tokens 1030 / 1101 us fused / two passes
 static bool two_pass_wanted(const PredictArgs& a)
 {
     const long long tiles = (long long)((a.T + 255) / 256) * a.L;

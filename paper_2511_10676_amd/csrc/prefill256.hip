@@ -4,14 +4,14 @@
 // Four waves, one per SIMD, own 128 hidden units x 128 tokens of the tile each, as 8 x 8 blocks of
 // v_mfma_f32_16x16x32_bf16: W1 rows are the A operand, token rows the B operand, so a lane's accumulators are
 // hidden units of one token.  What bounds it is power, then the way from L2 to LDS:
-//  * 16x16x32 rather than 32x32x16: registers alone, random operands, all CUs: 2.03 against 1.82 PFLOP/s (the clock
-//    gives way under both).
+//  * 16x16x32 rather than 32x32x16: registers alone, random operands, all CUs: 2.03 against 1.82 PFLOP/s in a probe (the
+//    clock gives way under both).
 //  * 128 x 128 per wave: 0.25 fragment reads of 1 KB per matrix instruction of 16384 products-and-sums, a third
 //    fewer than 128 x 64 in eight waves.
 //  * stages of 64 columns: a copy instruction fetches whole 128-byte lines; stages of 32 columns ask L2 for every line
-//    twice (200 M requests against 100 M on 98304 x 4096 x 2048).
+//    twice (65536 tokens, 2048 x 4096, first layer alone: 144 M requests with the eight waves, 77 M here).
 //  * one copy per six matrix instructions.  The copies of a stage in one burst hold the wave at the address unit
-//    (57 % of the cycles in matrix instructions, 1100 TFLOP/s), two per six reach 1290, one 1390 (one box).
+//    (57 % of the cycles in matrix instructions, 1100 TFLOP/s), two per six reach 1290, one 1390 (variants on one box).
 // First layer alone, 3 layers of 32768 tokens, 2048 x 4096: 1387 us with eight waves of 32x32x16 and five stages of
 // 32 columns, 1187 us now; 26 layers of 4096 tokens, 2048 x 2048, 829 -> 707 us (same box).
 //
@@ -30,13 +30,15 @@ constexpr int BK = 64;
 // the tokens; two stages in LDS.
 //   Square: 2 x 2 waves of 128 x 128, tiles of 256 x 256: the fewest fragment reads; the first layer alone and E <= 64.
 //   Square224: 128 x 112 each, tiles of 256 x 224, for calls whose last round of workgroups is a badly filled one otherwise
-//           (predict_prefill.hip): a ninth more bytes per flop, and full rounds run at 0.97 of Square's rate (48 x 16 tiles).
+//           (predict_prefill.hip): a fourteenth more bytes per flop, and full rounds run at 0.97 of Square's rate (48 x 16 tiles).
 //   Long:   256 units x 64 tokens each, the same tile: a wave has the chunk's whole contribution to its tokens' scores,
 //           which for 65 to 128 experts fit in the registers only so.
 //   Short:  128 units x 64 tokens each, tiles of 256 x 128: E up to 256, and r that is no multiple of 256.
 // Square and Short keep the chunk's slice of W2 (all experts x BN units) in LDS behind the stages, copied during the chunk's
 // first stage; Long, whose slice does not fit, reads its fragments of W2 from memory: 7 % of the time at 128 experts,
-// 2048 x 2048.  (Short from memory too: 256 experts, d = 512 604 us, 178 of them for W2.)
+// 2048 x 2048.  On short rows, where a chunk's 64 KB weigh most, the kernel still beats the eight-wave one that had the slice in
+// LDS: 32 layers of 4096 tokens, r = 2048, d = 64 181 -> 176 us, 256 268 -> 242, 768 515 -> 436; only d = 32, half of whose
+// stage is padding, does not (170 -> 176).  (Short from memory too: 256 experts, d = 512 604 us, 178 of them for W2.)
 template <int MI_, int NI_, int WR_, bool W2L_> struct Shape {
     static constexpr int MI = MI_, NI = NI_, WR = WR_, WT = 4 / WR_, BN = 16 * MI * WR, BM = 16 * NI * WT;
     static constexpr bool W2L = W2L_;
