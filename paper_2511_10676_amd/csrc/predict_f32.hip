@@ -7,12 +7,16 @@
 // only twice as wide, so small tiles are enough to keep it fed -- a 64 x 64
 // tile asks LDS for 16 bytes per clock of the 128 it can deliver -- and the
 // tiles are kept small so that a few hundred tokens of one layer already
-// spread over every CU.
+// spread over every CU.  Vector instructions do not run beside it: a stage of 1024 clocks of products
+// took 1030 with nothing else in the loop, 1190 with the LDS reads and their addresses, 1370 with the
+// copies, 1500 with the sums in double.  So the loop goes through the ring's stages unrolled (no address
+// arithmetic), a chain starts from a zero operand instead of cleared registers and only the last stage's
+// copies look for the end of d: 33 tokens of 2048 x 2048, whole call, 53.3 -> 48.9 us, 512 tokens of d = 4096 95.4 -> 85.9.
 //
 // A workgroup owns BM tokens of one layer and a range of chunks of BN
 // hidden units.  Per chunk it forms h^T[BN, BM] = W1[chunk, :] . x^T over stages of
 // 32 columns, which travel global -> LDS by direct copies through a ring of NS
-// stages (row of 128 bytes = 8 chunks of 16 bytes, chunk c in slot c ^ (row % 8),
+// stages (row of 128 bytes = 8 chunks of 16 bytes, chunk c in slot c ^ (row / 2 % 8),
 // chosen on the global side; rows past T, r and columns past d lie outside the
 // buffer resource and arrive as zeros).  A lane takes its fragment as one
 // ds_read_b128, four k-steps of the instruction: the order in which k is walked is
@@ -29,12 +33,16 @@
 // added up in double, sums over r chains of 8 units added up per chunk; with that the scores are no further from
 // float64 than those of a lane-split dot product with a butterfly (relative error of the scores, that / chains of 128
 // and 64 / here: 512 tokens 2048 x 2048 1.76e-7 / 2.85e-7 / 1.72e-7, 4 x 8192 tokens 1.77e-7 / 8.4e-7 / 1.72e-7, 256 x 64
-// 1.06e-7 / 2.9e-7 / 1.05e-7).  A chain is folded behind the next stage's LDS reads, when its last product is through the
-// pipe (the first of these in one run: 61.2 us, folded at the end of its own stage 64.5; the long chains 57.9).
+// 1.06e-7 / 2.9e-7 / 1.05e-7).
 // Few token tiles: r is cut over several workgroups per tile, their scores meet in the
-// workspace and finalize_kernel adds them; otherwise softmax and top-k follow here.
+// workspace and finalize_kernel adds them; otherwise softmax and top-k follow here, 8 or 16 lanes to a row (a wave
+// per row, one after the other: 4 x 1024 tokens of 256 x 64, 16 experts 36.7 us, 22.1 here).
+// More than 128 experts: one workgroup per CU, whose waves keep their scores in registers (two spilled them: 4 x 1024 tokens of
+// 2048 x 2048, 256 experts 413 -> 379 us, 2 x 1024 of 1024 x 1024, 200 experts 121 -> 100).
 // Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for a kernel of vector
-// instructions (a wave per hidden unit), 55 us here.
+// instructions (a wave per hidden unit), 52 us here.
+#include <type_traits>
+
 #include "paep_device.h"
 #include "paep_internal.h"
 
@@ -53,10 +61,19 @@ __device__ __forceinline__ f32x16 zero16()
     return v;
 }
 #define PAEP_F32_VMCNT(n) ((((n) & 0xF) | (((n) >> 4) << 14)) | 0x0F70)
+template <int V> using F32IC = std::integral_constant<int, V>;
+template <int N, class F> __device__ __forceinline__ void f32_static_for(F&& f)
+{
+    if constexpr (N > 0) {
+        f32_static_for<N - 1>(f);
+        f(F32IC<N - 1>{});
+    }
+}
+static constexpr int PAEP_F32_LGKM0 = 0xC07F;              // lgkmcnt(0) and nothing else
 
-// EBW: 32 x 32 score blocks per wave
-template <int B_, int NS, int EBW>
-__global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predict_f32_kernel(
+// EBW: 32 x 32 score blocks per wave.  CHAIN: columns of d summed in fp32 before the sum is added up in double.
+template <int B_, int NS, int EBW, int CHAIN>
+__global__ __launch_bounds__(B_ == 64 ? 512 : 256, B_ == 32 || EBW >= 4 ? 2 : 4) void predict_f32_kernel(
     int T, int d, int r, int E, int k, int act, int tiles_per_layer, int groups, int nchunks,
     long long xs, long long w1s, long long w2s, const float* __restrict__ x, const float* __restrict__ W1,
     const float* __restrict__ W2, const float* __restrict__ b1, const float* __restrict__ b2,
@@ -96,13 +113,11 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const int row = ((wave % (WAVES / 2)) * NP + j) * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ (row & 7);
+        const int c = (lane & 7) ^ ((row >> 1) & 7);
         src_off[j] = (uint32_t)(row * d + c * 4) * 4u;
         lcol[j] = c * 4;
     }
     const int NKT = (d + F32_BK - 1) / F32_BK;
-    const int chain = d < 768 ? 8 : d < 2048 ? 16 : 32;    // columns; shorter ones where d leaves fewer roundings to hide among
-    const int fold_every = chain > 8 * QPW ? chain / (8 * QPW) : 1;      // stages
 
     f32x16 zacc[EBW];
 #pragma unroll
@@ -117,54 +132,92 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
         const int wrows = r - u0 < BN ? r - u0 : BN;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(moves_w ? W1l + (long long)u0 * d : xl), 0, (moves_w ? wrows : xrows) * d * 4, 0x00020000);
-        auto issue = [&](int kt, int slot) {
+        auto issue_piece = [&](int kt, int slot, int j) {
             if (kt >= NKT) kt = NKT - 1;                   // past the end: the last stage again, into a slot nobody reads
-            const int left = d - kt * F32_BK;              // columns past d: an offset outside the resource
-#pragma unroll
-            for (int j = 0; j < NP; ++j)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rsrc, (f32_lds_ptr_t)(fsmem + slot * STAGE + (wave * NP + j) * 1024), 16,
-                    (int)(lcol[j] < left ? src_off[j] : 0x70000000u), kt * (F32_BK * 4), 0, 0);
+            const int left = d - kt * F32_BK;
+            const f32_lds_ptr_t to = (f32_lds_ptr_t)(fsmem + slot * STAGE + (wave * NP + j) * 1024);
+            if (left >= F32_BK)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, to, 16, (int)src_off[j], kt * (F32_BK * 4), 0, 0);
+            else                                           // columns past d: an offset outside the resource
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, to, 16, (int)(lcol[j] < left ? src_off[j] : 0x70000000u),
+                                                         kt * (F32_BK * 4), 0, 0);
         };
         const int blk = wave % NBLK, kpart = wave / NBLK;  // block of h: units (blk / TBN) * 32.., tokens (blk % TBN) * 32..
         f32x16 acc = zero16();
-        int fold_in = fold_every + 1;                      // stages until the chain is as long as it may get
         double tot[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) tot[i] = 0.0;             // 29 more bits: the order of these sums no longer matters
         auto fold = [&]() {
 #pragma unroll
             for (int i = 0; i < 16; ++i) tot[i] += (double)acc[i];
-            acc = zero16();
         };
         const int arow = (blk / TBN) * 32 + l32;
         const int brow = BN + (blk % TBN) * 32 + l32;
-        for (int s = 0; s < NS - 1; ++s) issue(s, s);
-        int slot = 0;
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) issue_piece(s, s, j);
+        // Fragments of the stage being multiplied, replaced one by one by the next stage's (QPW = 1: two, in turn).
+        constexpr int NF = 2;
+        static_assert(QPW <= NF && NP == 2, "fragments, copies");
+        f32x4 fa[NF], fb[NF];
+        auto read = [&](auto slot_c, auto q_c, auto buf_c) {
+            constexpr int q = decltype(q_c)::value, buf = decltype(buf_c)::value;
+            const float* st = (const float*)(fsmem + decltype(slot_c)::value * STAGE);
+            const int c = ((2 * (kpart * QPW + q) + g) ^ ((l32 >> 1) & 7)) * 4;
+            fa[buf] = *(const f32x4*)(st + arow * F32_BK + c);
+            fb[buf] = *(const f32x4*)(st + brow * F32_BK + c);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // Step s (8 columns) of the unrolled loop; a chain's first product takes no earlier sum.  COPY: stage kt's copies,
+        // into `slot`, between the products.
+        auto multiply = [&](auto s_c, auto buf_c, auto copy_c, int kt, int slot) {
+            constexpr int buf = decltype(buf_c)::value;
+            constexpr bool FIRST = decltype(s_c)::value % (CHAIN / 8) == 0, COPY = decltype(copy_c)::value;
+            if constexpr (FIRST) fold();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][i], fb[buf][i], FIRST && i == 0 ? zero16() : acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (COPY)
+                    if (i % 2 == 0) issue_piece(kt, slot, i / 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // from here on the next stage is read and this one's place is copied into: this wave's part of the one has landed,
+        // its fragments of the other are in registers; everyone's
+        auto hand_over = [&]() {
+            __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(NP * (NS - 2)) & PAEP_F32_LGKM0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(NP * (NS - 1)));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read(F32IC<0>{}, F32IC<0>{}, F32IC<0>{});
+        if constexpr (QPW == 2) read(F32IC<0>{}, F32IC<1>{}, F32IC<1>{});
+        static_assert(NS % 2 == 0 && NS * QPW % (CHAIN / 8) == 0, "a chain ends with the unrolled loop");
 #pragma unroll 1
-        for (int kt = 0; kt < NKT; ++kt) {
-            __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(NP * (NS - 2)));   // this wave's part of stage kt has landed
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();                  // everyone's has, and everyone is done with stage kt - 1
-            asm volatile("" ::: "memory");
-            issue(kt + NS - 1, slot == 0 ? NS - 1 : slot - 1);
-            const float* st = (const float*)(fsmem + slot * STAGE);
-            f32x4 fa[QPW], fb[QPW];
-#pragma unroll
-            for (int q = 0; q < QPW; ++q) {
-                const int c = ((2 * (kpart * QPW + q) + g) ^ (l32 & 7)) * 4;
-                fa[q] = *(const f32x4*)(st + arow * F32_BK + c);
-                fb[q] = *(const f32x4*)(st + brow * F32_BK + c);
-            }
-            if (--fold_in == 0) { fold(); fold_in = fold_every; }
-#pragma unroll
-            for (int q = 0; q < QPW; ++q) {
-                if (q > 0 && chain == 8) fold();
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q][i], fb[q][i], acc, 0, 0, 0);
-            }
-            slot = slot + 1 == NS ? 0 : slot + 1;
-        }
+        for (int k0 = 0; k0 < NKT; k0 += NS)
+            f32_static_for<NS>([&](auto u_c) {
+                constexpr int u = decltype(u_c)::value;
+                constexpr F32IC<(u + 1) % NS> next{};
+                const int kt = k0 + u;
+                if (kt < NKT) {
+                    if constexpr (QPW == 1) {
+                        hand_over();
+                        read(next, F32IC<0>{}, F32IC<(u + 1) % 2>{});
+                        multiply(F32IC<u>{}, F32IC<u % 2>{}, std::true_type{}, kt + NS, u);
+                    } else {
+                        multiply(F32IC<2 * u>{}, F32IC<0>{}, std::false_type{}, 0, 0);
+                        hand_over();
+                        read(next, F32IC<0>{}, F32IC<0>{});
+                        multiply(F32IC<2 * u + 1>{}, F32IC<1>{}, std::true_type{}, kt + NS, u);
+                        read(next, F32IC<1>{}, F32IC<1>{});
+                    }
+                }
+            });
         fold();
         __builtin_amdgcn_s_waitcnt(PAEP_F32_VMCNT(0));     // no copy may land in the ring once it holds h
         __syncthreads();
@@ -260,21 +313,37 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, EBW >= 8 ? 2 : 4) void predic
                 }
         }
         __syncthreads();
-        for (int rr = wave; rr < 32; rr += WAVES) {            // one wave per row
-            const int t = t0 + tb * 32 + rr;
+        if (logits)
+            for (int i = tid; i < 32 * E; i += THREADS) {
+                const int rr = i / E, e = i - rr * E;
+                if (t0 + tb * 32 + rr < T) logits[((long long)layer * T + t0 + tb * 32 + rr) * E + e] = zs[rr * ZP + e];
+            }
+        if (k + (margin && k < E ? 1 : 0) <= 16) {             // G lanes per row, all rows at once
+            constexpr int G = THREADS / 32;
+            const int rr = tid / G, t = t0 + tb * 32 + rr;
             if (t < T) {
-                constexpr int NV = EBW * WAVES / TBN / 2;      // experts per lane
                 const long long row = (long long)layer * T + t;
-                float z[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const int e = lane + 64 * v;
-                    z[v] = e < E ? zs[rr * ZP + e] : 0.0f;
-                    if (logits && e < E) logits[row * E + e] = z[v];
-                }
+                const float* zrow = zs + rr * ZP;
                 const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr,
                                      counts ? counts + (long long)layer * E : nullptr};
-                wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
+                row_softmax_topk_upto16<G, true>([&](int e) { return zrow[e]; }, E, k, tid % G, idx + row * k, probs + row * k, eo);
+            }
+        } else {
+            for (int rr = wave; rr < 32; rr += WAVES) {        // longer lists: one wave per row
+                const int t = t0 + tb * 32 + rr;
+                if (t < T) {
+                    constexpr int NV = EBW * WAVES / TBN / 2;  // experts per lane
+                    const long long row = (long long)layer * T + t;
+                    float z[NV];
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        const int e = lane + 64 * v;
+                        z[v] = e < E ? zs[rr * ZP + e] : 0.0f;
+                    }
+                    const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr,
+                                         counts ? counts + (long long)layer * E : nullptr};
+                    wave_softmax_topk<NV>(z, E, k, lane, idx + row * k, probs + row * k, eo);
+                }
             }
         }
         __syncthreads();
@@ -320,10 +389,10 @@ hipError_t launch_predict_f32(const PredictArgs& a)
     const int eblocks = (a.E + 31) / 32, waves = B == 64 ? 8 : 4,
               ebw = (eblocks * (B / 32) + waves - 1) / waves;
     hipError_t err;
-#define PAEP_LAUNCH_F32(BV, NSV, EBV)                                                                              \
+#define PAEP_LAUNCH_F32_C(BV, NSV, EBV, CV)                                                                        \
     do {                                                                                                           \
         const size_t ring = (size_t)NSV * 2 * BV * F32_BK * 4, lds = ring > epilogue ? ring : epilogue;            \
-        auto kern = predict_f32_kernel<BV, NSV, EBV>;                                                              \
+        auto kern = predict_f32_kernel<BV, NSV, EBV, CV>;                                                            \
         static LdsLimit limit;                                                                                     \
         err = ensure_lds_limit(limit, (const void*)kern, lds);                                                     \
         if (err != hipSuccess) return err;                                                                         \
@@ -332,6 +401,13 @@ hipError_t launch_predict_f32(const PredictArgs& a)
                            (const float*)a.x, (const float*)a.W1, (const float*)a.W2, (const float*)a.b1,          \
                            (const float*)a.b2, a.idx, a.probs, a.logits, a.counts, a.prob_mode, a.margin,          \
                            (float*)a.workspace);                                                                   \
+    } while (0)
+    // columns in a chain: fewer where d leaves fewer roundings to hide among
+#define PAEP_LAUNCH_F32(BV, NSV, EBV)                                                                              \
+    do {                                                                                                           \
+        if (a.d < 768)       PAEP_LAUNCH_F32_C(BV, NSV, EBV, 8);                                                   \
+        else if (a.d < 2048) PAEP_LAUNCH_F32_C(BV, NSV, EBV, 16);                                                  \
+        else                 PAEP_LAUNCH_F32_C(BV, NSV, EBV, 32);                                                  \
     } while (0)
     // score blocks per wave the kernel is compiled for
     if (B == 64) {
@@ -345,6 +421,7 @@ hipError_t launch_predict_f32(const PredictArgs& a)
         else               PAEP_LAUNCH_F32(32, 8, 8);
     }
 #undef PAEP_LAUNCH_F32
+#undef PAEP_LAUNCH_F32_C
     err = hipGetLastError();
     if (err != hipSuccess || groups == 1) return err;
     return launch_finalize(a, (const float*)a.workspace, groups, a.L, a.T, 0, 1);

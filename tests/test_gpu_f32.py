@@ -99,3 +99,24 @@ def test_f32_infinite_token_does_not_meet_the_padding_of_r(T, r):
     assert bool((z[0, 1] == float("inf")).all())
     keep = torch.arange(T, device="cuda") != 1
     assert torch.equal(z[0, keep], plain[0, keep])
+
+
+@pytest.mark.parametrize("T,E,k", [(70, 16, 15), (70, 40, 16), (31, 17, 16), (33, 200, 1), (100, 64, 7)])
+@pytest.mark.parametrize("prob", ["softmax", "softmax_topk", "sigmoid"])
+def test_f32_rows_finished_in_the_kernel(T, E, k, prob):
+    """One chunk of r, so softmax and top-k run there: lists of up to 16 keys (the margin needs one more) by several lanes per
+    row, longer ones by a wave.  Against the definition in float64 on the kernel's own scores; probabilities to 2e-5 of their value,
+    the bound of tests/parity.py for the same comparison."""
+    import torch
+    from paper_2511_10676_amd import binding as B
+    from test_gpu_predict import _dev
+    x, W1, W2, b1, b2 = _rand_layers(T + E, L=2, T=T, d=72, r=32, E=E, dtype="f32", bias=True)
+    o = B.predict(_dev(x, "f32"), _dev(W1, "f32"), _dev(W2, "f32"), k, b1=_dev(b1, "f32"), b2=_dev(b2, "f32"), act="silu",
+                  prob=prob, want_logits=True, want_margin=True)
+    srt, order = torch.sort(o.logits, dim=2, descending=True, stable=True)
+    assert torch.equal(o.idx.long(), order[:, :, :k])
+    assert torch.equal(o.margin, srt[:, :, k - 1] - srt[:, :, k])
+    z = srt.double()
+    want = torch.sigmoid(z) if prob == "sigmoid" else torch.softmax(z[:, :, :k] if prob == "softmax_topk" else z, dim=2)
+    want = want[:, :, :k]
+    assert ((o.probs.double() - want).abs() <= 2e-5 * want).all()
