@@ -202,11 +202,11 @@ struct TopList {
             merge(more);
         }
     }
-    // every lane of an aligned group of G ends with the group's list
-    template <int G> __device__ __forceinline__ void merge_group()
+    // every lane of a group of G, STRIDE lanes apart, ends with the group's list
+    template <int G, int STRIDE = 1> __device__ __forceinline__ void merge_group()
     {
 #pragma unroll
-        for (int mask = 1; mask < G; mask <<= 1) {
+        for (int mask = STRIDE; mask < G * STRIDE; mask <<= 1) {
             skey other[KMAX];
 #pragma unroll
             for (int j = 0; j < KMAX; ++j) other[j] = __shfl_xor(key[j], mask, 64);
@@ -232,8 +232,8 @@ __device__ __forceinline__ float sigmoidf_(float v) { return 1.0f / (1.0f + __ex
 
 // The outputs of one row from its merged list `top`, by the G lanes that share it: lane g writes outputs
 // j = g, g + G, ... < k.  KMAX >= k, and >= k + 1 when the margin is wanted and k < E.  exp_sum(m) is this lane's
-// share of sum(exp(z - m)) over the row's scores.
-template <int KMAX, int G, class F>
+// share of sum(exp(z - m)) over the row's scores.  STRIDE: how far apart the row's lanes are.
+template <int KMAX, int G, int STRIDE = 1, class F>
 __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E, int k, int g, int32_t* idx_row,
                                                 float* probs_row, const EpilogueOut& o, F&& exp_sum)
 {
@@ -242,7 +242,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
     if (o.prob_mode == 0) {
         s = exp_sum(m);
 #pragma unroll
-        for (int mask = 1; mask < G; mask <<= 1) s += __shfl_xor(s, mask, 64);
+        for (int mask = STRIDE; mask < G * STRIDE; mask <<= 1) s += __shfl_xor(s, mask, 64);
     } else if (o.prob_mode == 1) {
 #pragma unroll
         for (int j = 0; j < KMAX; ++j)           // every lane holds the whole list: same sum, same order

@@ -776,6 +776,27 @@ def test_two_passes_and_one(T, d, r, E, k, L, act, bias):
     assert torch.equal(counts.long(), ref)
 
 
+@pytest.mark.parametrize("E,k,margin", [(129, 1, True), (144, 2, False), (200, 2, True), (130, 7, True), (255, 8, False),
+                                        (256, 15, True), (256, 16, False)])
+@pytest.mark.parametrize("prob", ["softmax", "softmax_topk", "sigmoid"])
+def test_two_passes_finish_their_rows(E, k, margin, prob):
+    """Whole r in one slice: the scores kernel selects by itself, with lists of 2, 8 and 16 keys.  Against the definition in
+    float64 on its own scores; probabilities to 2e-5 of their value, the bound of tests/parity.py for the same comparison."""
+    T, d, r, L = 4097, 64, 256, 12
+    assert _plan(T, d, r, E, k, L).tile == "two-pass 256x256"
+    x, W1, W2, _, b2 = _rand_layers(E + k, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    o = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, b2=_dev(b2, "bf16"), prob=prob, want_logits=True,
+                  want_margin=margin)
+    srt, order = torch.sort(o.logits, dim=2, descending=True, stable=True)
+    assert torch.equal(o.idx.long(), order[:, :, :k])
+    if margin:
+        assert torch.equal(o.margin, srt[:, :, k - 1] - srt[:, :, k])
+    z = srt.double()
+    want = torch.sigmoid(z) if prob == "sigmoid" else torch.softmax(z[:, :, :k] if prob == "softmax_topk" else z, dim=2)
+    want = want[:, :, :k]
+    assert ((o.probs.double() - want).abs() <= 2e-5 * want).all()
+
+
 @pytest.mark.parametrize("T,d,r,E,k,L,act,shared,batches", [
     (5000, 768, 4096, 200, 8, 32, "none", False, (11, 11, 10)),
     (5000, 768, 4096, 256, 15, 32, "silu", True, (11, 11, 10)),
