@@ -821,11 +821,6 @@ static constexpr int SH_BM = 256, SH_BN = 64, SH_NST = 3;
 
 // EB: blocks of 16 experts
 template <int EB> constexpr int sh_waves() { return EB <= 8 ? 4 : 8; }
-template <int EB, int ACT>
-__global__ __launch_bounds__(sh_waves<EB>() * 64, EB <= 8 ? 3 : 2) void scores_of_h_kernel(
-    int T, int r, int E, int tiles_per_layer, int slices, long long w2s, const u32x4* __restrict__ h,
-    const uint16_t* __restrict__ W2, float* __restrict__ zpart, RowOutputs out)
-{
 
 // what a call writes
 struct RowOutputs {
@@ -873,6 +868,11 @@ __device__ __forceinline__ void finish_token(const f32x4 (&z)[EB], int E, int g,
     });
 }
 
+template <int EB, int ACT>
+__global__ __launch_bounds__(sh_waves<EB>() * 64, EB <= 8 ? 3 : 2) void scores_of_h_kernel(
+    int T, int r, int E, int tiles_per_layer, int slices, long long w2s, const u32x4* __restrict__ h,
+    const uint16_t* __restrict__ W2, float* __restrict__ zpart, RowOutputs out)
+{
     constexpr int ROWS = EB * 16, STAGE_BYTES = ROWS * SH_BN * 2;
     constexpr int WAVES = sh_waves<EB>(), PARTS = 8 / WAVES; // workgroups per tile of 256 tokens
     constexpr int W2J = ROWS / 8 / WAVES;                   // copy instructions per wave and stage, 8 rows each
@@ -969,11 +969,6 @@ __device__ __forceinline__ void finish_token(const f32x4 (&z)[EB], int E, int g,
         });
     }
     __builtin_amdgcn_s_waitcnt(PAEP_VMCNT(0));              // no copy may land in this LDS once it belongs to another workgroup
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int tl = first + n * 16 + l16;
-        if (t0 + tl >= T) continue;
-        float* dst = zpart + (((long long)tile_id * slices + slice) * SH_BM + tl) * E;
     if (slices == 1) {
         int32_t* cnt_lds = (int32_t*)smem_raw;              // counted per workgroup, flushed once
         if (out.counts) {
@@ -1020,6 +1015,11 @@ __device__ __forceinline__ void finish_token(const f32x4 (&z)[EB], int E, int g,
         return;
     }
 #pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int tl = first + n * 16 + l16;
+        if (t0 + tl >= T) continue;
+        float* dst = zpart + (((long long)tile_id * slices + slice) * SH_BM + tl) * E;
+#pragma unroll
         for (int eb = 0; eb < EB; ++eb) {
             const int e = eb * 16 + 4 * g;
             if (e + 3 < E) {
@@ -1061,12 +1061,12 @@ static TwoPass two_pass_layout(const PredictArgs& a)
     batch = (a.L + (a.L + batch - 1) / batch - 1) / ((a.L + batch - 1) / batch);      // batches of even size
     TwoPass p{(int)batch, 1, (size_t)(batch * per_layer), 0};
     while (tiles * batch * p.slices < 192 && p.slices < 4) p.slices *= 2;
+    // (one slice needs none: callers know this size)
     p.z_bytes = (size_t)(batch * tiles) * p.slices * SH_BM * a.E * sizeof(float);
     return p;
 }
 
 // Where the fused kernel is the slower one.  What two passes cost goes with r (h written and read again), what they save
-    // (one slice needs none: callers know this size)
 // with d, more of it where the fused kernel has to be 128 units wide (E > 128).  Two passes / fused, prefill256.hip on either
 // side, r = 512 to 4096, 320 to 1024 tiles unless said:
 //   256 experts  d = 256 1.05-1.67, 512 1.00-1.31, 768 0.96-1.17 (r = 4096 1.00-1.17), 1024 0.88-0.96 (1.08 at 320 tiles, r = 4096),
