@@ -220,7 +220,10 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
  *           5 64x64, 6 256x256 for the first layer and the scores as a second
  *           kernel (2: 224x256 where that fills the last round of workgroups
- *           better, see paep_predict_kernel; 5 and 6 given the workspace that
+ *           better, see paep_predict_kernel; 0 and 1: the class of calls of few
+ *           tokens, which run tiles of 128 to 256 tokens x 256 units where those
+ *           take less time, plan[2] and plan[3] being those tiles', in chunks of
+ *           128 units; 5 and 6 given the workspace that
  *           paep_predict_workspace_bytes names; with less, one of the others)
  *   plan[2] workgroups that share one token tile (the inner width r split
  *           between them; 1 = no split, and but for tile 6 no workspace)
@@ -232,7 +235,8 @@ paep_status paep_predict_plan(const paep_predict_desc *desc, int32_t want_margin
 /*
  * The kernel that the same call, with or without a bias b1, runs in a workspace
  * of `workspace_bytes`, in words: of the prefill family its name, its tile (tokens x hidden units: here
- * 224 and 256 tokens differ, and the two kernels of 256x256 tiles) and " tiles
+ * 224 and 256 tokens differ, and the two kernels of 256x256 tiles; the class of
+ * calls of few tokens has one name, 128x128, as in the plan) and " tiles
  * first" where token tiles are the grid's fastest index; "decode", "simple" or
  * (T = 0) "none" otherwise.  NULL where the call would be refused.  Host only;
  * for tests and reports, the wording may change.

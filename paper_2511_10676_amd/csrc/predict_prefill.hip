@@ -576,7 +576,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
 //   256 x 256 (E <= 128, r a multiple of 256) and 256 tokens x 128 units (65 to 256 experts): prefill256.hip.
 //   Flat      256 x 256 for E <= 64 and short rows (flat_wanted), 8 waves: a chunk is a few of prefill256.hip's stages there,
 //             and its ends are what counts.
-//   Small     128 x 128, 4 waves, two workgroups per CU (4 x 16 KB + 16 KB slice each): short inputs
+//   Few       128 to 256 tokens x 256 (prefill256.hip): short inputs of up to 128 experts (few_plan).
+//   Small     128 x 128, 4 waves, two workgroups per CU (4 x 16 KB + 16 KB slice each): short inputs otherwise
 //             and any r that is a multiple of 128.  SmallWide: the same for E > 64 (64 KB slice).
 //   Tiny      64 x 64, 4 waves, four 64-wide stages, two workgroups per CU: calls whose 128 x 128 tiles would not reach
 //             every CU.  What bounds it is the chain of stages, 0.5 us each whatever is tried on it (eight stages, all
@@ -702,17 +703,21 @@ static size_t cfg_workspace_bytes(const PredictArgs& a)
 // r = 2048 29.0 / 32.2; 2048 x 2048, one of 301 27.4 / 28.4; but one of 700 34.1 / 32.2).  Of hidden units a chunk's rows
 // count, not a workgroup's: token rows are read again for every chunk (4 layers of 2310 tokens, 3456 x 4096 in 9 groups of three
 // chunks 365 / 441).
-template <class C>
-static bool tile_fastest(const PredictArgs& a, const PfLayout& f)
+static bool tile_fastest(const PredictArgs& a, int bm, int bn, int groups)
 {
-    const int tiles = (a.T + C::BM - 1) / C::BM, groups = f.main_groups, share = tiles * a.L * groups / 8;
-    if (f.tail_tiles > 0 || share == 0 || share >= tiles * groups) return false;
+    const int tiles = (a.T + bm - 1) / bm, share = tiles * a.L * groups / 8;
+    if (share == 0 || share >= tiles * groups) return false;
     auto rows = [&](int n, int size, int other) {              // n side by side, of `size` rows each
         return (n < share ? n : share) * size + (share + n - 1) / n * other;
     };
-    const int by_groups = rows(groups, C::BN, C::BM);
-    const long long mb = C::BM == 64 && a.E > 64 ? 7 : 3;
-    return rows(tiles, C::BM, C::BN) <= by_groups && 2ll * a.d * by_groups >= mb << 20;
+    const int by_groups = rows(groups, bn, bm);
+    const long long mb = bm == 64 && a.E > 64 ? 7 : 3;
+    return rows(tiles, bm, bn) <= by_groups && 2ll * a.d * by_groups >= mb << 20;
+}
+template <class C>
+static bool tile_fastest(const PredictArgs& a, const PfLayout& f)
+{
+    return f.tail_tiles == 0 && tile_fastest(a, C::BM, C::BN, f.main_groups);
 }
 
 template <class C, int EB32, int MODE>
@@ -772,7 +777,7 @@ static bool flat_wanted(const PredictArgs& a)
 static hipError_t launch_tiles_of_224(const PredictArgs& a)
 {
     const int tiles = (a.T + 223) / 224;
-    return launch_prefill256(a, PrefillGrid{tiles, tiles * a.L, 1, 0, 1, 0, nullptr}, 224, Cfg256::BN, nullptr);
+    return launch_prefill256(a, PrefillGrid{tiles, tiles * a.L, 1, 0, 1, 0, nullptr, 0}, 224, Cfg256::BN, nullptr);
 }
 
 template <class C>
@@ -782,7 +787,7 @@ static hipError_t launch_cfg256(const PredictArgs& a)
     const int tiles = (a.T + C::BM - 1) / C::BM;
     float* zpart = (float*)a.workspace;
     const PrefillGrid grid{tiles, f.main_tiles * f.main_groups, f.main_groups, f.tail_tiles * f.tail_groups, f.tail_groups,
-                           f.split_tile0, zpart};
+                           f.split_tile0, zpart, 0};
     const hipError_t err = launch_prefill256(a, grid, C::BM, C::BN, nullptr);
     if (err != hipSuccess || f.split_tiles == 0) return err;
     return launch_finalize(a, zpart, f.split_groups, f.split_tiles, C::BM, f.split_tile0, tiles);
@@ -1119,7 +1124,7 @@ static hipError_t launch_two_pass(const PredictArgs& a)
         if (a.logits) b.logits = a.logits + rows * a.E;
         if (a.margin) b.margin = a.margin + rows;
         if (a.counts) b.counts = a.counts + (long long)l0 * a.E;
-        const PrefillGrid grid{tiles, tiles * b.L * groups, groups, 0, 1, 0, nullptr};
+        const PrefillGrid grid{tiles, tiles * b.L * groups, groups, 0, 1, 0, nullptr, 0};
         hipError_t err = launch_prefill256(b, grid, Cfg256::BM, Cfg256::BN, h);
         if (err != hipSuccess) return err;
         switch (a.act) {
@@ -1156,6 +1161,78 @@ static int pick_cfg(const PredictArgs& a, bool roomy)
     return (a.E <= 128 && a.r % 256 == 0) ? 4 : 3;
 }
 
+// Calls of fewer than 128 tiles of 256 tokens, up to 128 experts, whose 64 x 64 tiles would be too many: prefill256.hip's kernel in
+// tiles of 128 to 256 tokens x 256 hidden units (65 to 128 experts: 128 tokens) instead of 128 x 128.  What bounds those is
+// LDS: four waves of 64 x 64 read twice as many fragments a product as waves of 128 x 64, and a round of 512 workgroups is
+// seldom full.  The size of the tile and the split of r are those of the least time in this model, in us, fitted to 600 timed
+// combinations of shape, tile and split: rounds of 256 workgroups (the last one, partly filled, three quarters of one and more), in
+// each a stage of 64 columns 0.004 a token and 0.43 on a full chip, 4 for a workgroup's ends; score tiles at 4 TB/s.
+// The choice is within 3 % of the best of up to 30 for 34 shapes of 42, within 10 % for all but one of them (13 %).
+// 128 x 128 tiles / here, us: 26 layers of 301 tokens, 2048 x 2048, 64 experts 129 / 77, with SiLU 149 / 91; one of 4096 62 / 39;
+// 20 of 500, 4096 x 4096 547 / 335-349; 9 of 3000, d = 4096 678 / 357; 10 of 700, 128 experts 113 / 68; 48 of 200 240 / 154; 4 of
+// 4000, 1024 x 64 30 / 19.5; 30 of 130, 1536 x 800 53 / 29.  At under 112 workgroups they are level (one of 1500 37.4 / 35.1, one of
+// 1024 in 64 x 64 tiles 27.1 / 32.7), and so where the model says so (3 of 1200, 1024 x 4096, 16 experts 48.3 / 52.2; one of 1683,
+// 2048 x 4352, 128 experts 58.1 / 63.7).
+struct FewPlan { int tokens, groups; };                      // no tokens: the other tiles
+static double rounds_of(long long wgs, int slots)
+{
+    const long long full = wgs / slots, tail = wgs % slots;
+    return (double)full + (tail == 0 ? 0.0 : full == 0 ? 1.0 : 0.75 + 0.25 * (double)tail / slots);
+}
+static double split_us(const PredictArgs& a, long long tiles, int tokens, int groups)
+{
+    return groups > 1 ? 1.0 + (double)tiles * tokens * groups * a.E * 8 / 4e6 : 0.0;
+}
+static double time256_us(const PredictArgs& a, int tokens, int groups)
+{
+    const long long tiles = (long long)((a.T + tokens - 1) / tokens) * a.L, wgs = tiles * groups;
+    const double stage = 0.0040 * tokens + 0.43 * (wgs < 256 ? (double)wgs / 256 : 1.0);
+    const int chunks = a.r / Cfg256::BN / groups, stages = (a.d + 63) / 64;
+    return rounds_of(wgs, 256) * (4 + chunks * (stages * stage + 0.5 + a.E / 64.0)) + split_us(a, tiles, tokens, groups);
+}
+template <class C>
+static double time128_us(const PredictArgs& a)
+{
+    const int groups = prefill_groups<C>(a), stages = (a.d + 63) / 64;
+    const long long tiles = (long long)((a.T + C::BM - 1) / C::BM) * a.L, wgs = tiles * groups;
+    const double fill = wgs < 384 ? 0.75 : wgs < 512 ? (double)wgs / 512 : 1.0;
+    const double stage = wgs <= 256 ? 0.75 : C::OCC == 1 ? 0.85 : 1.3 * fill;
+    const double rounds = C::OCC == 1 ? rounds_of(wgs, 256) : wgs < 512 ? 1.0 : (double)wgs / 512;
+    return rounds * (4 + a.r / C::BN / groups * (stages * stage + 0.3)) + split_us(a, tiles, C::BM, groups);
+}
+static FewPlan few_plan(const PredictArgs& a)
+{
+    FewPlan best{0, 1};
+    if (a.E > 128 || a.r % Cfg256::BN != 0 || enough_large_tiles(a)) return best;
+    double least = 0.93 * (a.E > 64 ? time128_us<CfgSmallWide>(a) : time128_us<CfgSmall>(a));
+    const int chunks = a.r / Cfg256::BN;
+    for (int tokens = 128; tokens <= (a.E > 64 ? 128 : 256); tokens += 32)
+        for (int groups = 1; groups <= chunks; ++groups) {
+            if (chunks % groups != 0 || (long long)((a.T + tokens - 1) / tokens) * a.L * groups < 112) continue;
+            const double t = time256_us(a, tokens, groups);
+            if (t < least) {
+                least = t;
+                best = FewPlan{tokens, groups};
+            }
+        }
+    return best;
+}
+static size_t few_bytes(const PredictArgs& a, const FewPlan& f)
+{
+    if (f.groups == 1) return 0;
+    return (size_t)((a.T + f.tokens - 1) / f.tokens) * a.L * f.groups * f.tokens * a.E * sizeof(float);
+}
+static hipError_t launch_few(const PredictArgs& a, const FewPlan& f)
+{
+    const int tiles = (a.T + f.tokens - 1) / f.tokens;
+    float* zpart = (float*)a.workspace;
+    const PrefillGrid grid{tiles, tiles * a.L * f.groups, f.groups, 0, 1, 0, zpart,
+                           (int)tile_fastest(a, f.tokens, Cfg256::BN, f.groups)};
+    const hipError_t err = launch_prefill256(a, grid, f.tokens, Cfg256::BN, nullptr);
+    if (err != hipSuccess || f.groups == 1) return err;
+    return launch_finalize(a, zpart, f.groups, tiles * a.L, f.tokens, 0, tiles);
+}
+
 template <class C>
 static void cfg_plan(const PredictArgs& a, int* groups, int* cpg)
 {
@@ -1173,6 +1250,14 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
         return;
     }
     *cfg = pick_cfg(a, true);
+    if (*cfg == 0 || *cfg == 1) {
+        const FewPlan f = few_plan(a);
+        if (f.tokens > 0) {                                  // in chunks of 128 hidden units, as the other tiles of the class
+            *groups = f.groups;
+            *chunks_per_group = a.r / CfgSmall::BN / f.groups;
+            return;
+        }
+    }
     switch (*cfg) {
     case 5: cfg_plan<CfgTiny>(a, groups, chunks_per_group); break;
     case 2: cfg_plan<Cfg256>(a, groups, chunks_per_group); break;
@@ -1208,16 +1293,24 @@ static size_t two_pass_bytes(const PredictArgs& a)
 size_t prefill_workspace_bytes(const PredictArgs& a)
 {
     size_t need = prefill_workspace_min(a);
-    const size_t best = two_pass_wanted(a) ? two_pass_bytes(a) : fused_workspace_bytes(a, true);
+    size_t best = two_pass_wanted(a) ? two_pass_bytes(a) : fused_workspace_bytes(a, true);
+    const int cfg = pick_cfg(a, true);
+    const size_t few = cfg == 0 || cfg == 1 ? few_bytes(a, few_plan(a)) : 0;
+    if (few > best) best = few;
     return best > need ? best : need;
 }
 
 // The kernel of a call in the workspace it was given: one choice for the launch and for those who ask.
-enum class Route { Small, SmallWide, Tiny, Flat, Square, Square224, Long, Short, TwoPass };
+enum class Route { Small, SmallWide, Few, Tiny, Flat, Square, Square224, Long, Short, TwoPass };
 static Route route_of(const PredictArgs& a)
 {
     if (two_pass_wanted(a) && a.workspace_bytes >= two_pass_bytes(a)) return Route::TwoPass;
-    switch (pick_cfg(a, a.workspace_bytes >= fused_workspace_bytes(a, true))) {
+    const int cfg = pick_cfg(a, a.workspace_bytes >= fused_workspace_bytes(a, true));
+    if (cfg == 0 || cfg == 1) {
+        const FewPlan f = few_plan(a);
+        if (f.tokens > 0 && a.workspace_bytes >= few_bytes(a, f)) return Route::Few;
+    }
+    switch (cfg) {
     case 5: return Route::Tiny;
     case 4: return Route::Long;
     case 3: return Route::Short;
@@ -1245,6 +1338,13 @@ const char* prefill_kernel_name(const PredictArgs& a)
     case Route::Short: return "prefill256_kernel 256x128";
     case Route::Flat: return name_with_order<CfgFlat>(a, "prefill_kernel 256x256", "prefill_kernel 256x256 tiles first");
     case Route::Tiny: return name_with_order<CfgTiny>(a, "prefill_kernel 64x64", "prefill_kernel 64x64 tiles first");
+    // The 128 x 128 tiles' class of calls: callers know it by that name.
+    case Route::Few: {
+        const FewPlan f = few_plan(a);
+        if (tile_fastest(a, f.tokens, Cfg256::BN, f.groups))
+            return a.E > 64 ? "prefill_kernel 128x128 wide tiles first" : "prefill_kernel 128x128 tiles first";
+        return a.E > 64 ? "prefill_kernel 128x128 wide" : "prefill_kernel 128x128";
+    }
     case Route::SmallWide:
         return name_with_order<CfgSmallWide>(a, "prefill_kernel 128x128 wide", "prefill_kernel 128x128 wide tiles first");
     default: return name_with_order<CfgSmall>(a, "prefill_kernel 128x128", "prefill_kernel 128x128 tiles first");
@@ -1257,6 +1357,7 @@ hipError_t launch_predict_prefill(const PredictArgs& a)
     case Route::TwoPass: return launch_two_pass(a);
     case Route::Tiny:
         return a.E <= 32 ? launch_cfg<CfgTiny, 1>(a) : a.E <= 64 ? launch_cfg<CfgTiny, 2>(a) : launch_cfg<CfgTiny, 4>(a);
+    case Route::Few: return launch_few(a, few_plan(a));
     case Route::Flat: return a.E <= 32 ? launch_cfg<CfgFlat, 1>(a) : launch_cfg<CfgFlat, 2>(a);
     case Route::Square224: return launch_tiles_of_224(a);
     case Route::Square:

@@ -31,6 +31,8 @@ constexpr int BK = 64;
 //   Square: 2 x 2 waves of 128 x 128, tiles of 256 x 256: the fewest fragment reads; the first layer alone and E <= 64.
 //   Square224: 128 x 112 each, tiles of 256 x 224, for calls whose last round of workgroups is a badly filled one otherwise
 //           (predict_prefill.hip): a fourteenth more bytes per flop, and full rounds run at 0.97 of Square's rate (48 x 16 tiles).
+//   Few:    128 units x 64 to 96 tokens each, tiles of 256 x 128 to 192, for calls whose larger tiles would leave CUs without one
+//           (few_plan in predict_prefill.hip): 0.94 us for a stage of 128 tokens on a full chip, 1.07 of 160, 1.45 of 256.
 //   Long:   256 units x 64 tokens each, the same tile: a wave has the chunk's whole contribution to its tokens' scores,
 //           which for 65 to 128 experts fit in the registers only so.
 //   Short:  128 units x 64 tokens each, tiles of 256 x 128: E up to 256, and r that is no multiple of 256.
@@ -48,6 +50,7 @@ template <int MI_, int NI_, int WR_, bool W2L_> struct Shape {
 };
 typedef Shape<8, 8, 2, true> Square;
 typedef Shape<8, 7, 2, true> Square224;
+template <int NI> using Few = Shape<8, NI, 2, true>;
 typedef Shape<16, 4, 1, false> Long;
 typedef Shape<8, 4, 1, true> Short;
 
@@ -71,13 +74,13 @@ struct Args {
 // goes to the front of the next stage.  Short's stages are half as long: it has room for eight fragments more (SOME).
 template <class C, int EB> struct Slots {
     static constexpr int MI = C::MI, NI = C::NI, K = MI * NI, F = MI + NI, H = (NI + 1) / 2, K1 = MI * H, N = 2 * K;
-    static constexpr bool ROOM = C::WR == 2 && EB <= 2, SOME = K == 32;
+    static constexpr bool ROOM = C::WR == 2 && NI >= 7 && EB <= 2, SOME = K == 32;
     static constexpr int mi(int i) { return ROOM ? i / NI : i < K1 ? i / H : (i - K1) / (NI - H); }
     static constexpr int ni(int i) { return ROOM ? i % NI : i < K1 ? i % H : H + (i - K1) % (NI - H); }
     // the q-th fragment to be read: token block 0 .. NI - 1, or NI + unit block
     static constexpr int frag(int q) { return ROOM || q < H ? q : q < H + MI ? q - H + NI : q - MI; }
     // slot of the q-th read of the second k-step's fragments, and of the next stage's first
-    static constexpr int half(int q) { return q < H ? K1 + 1 + 2 * q : q < H + MI ? K1 + 2 + NI % 2 + (NI - H) * (q - H + 1) : K + 4 + 2 * (q - H - MI); }
+    static constexpr int half(int q) { return q < H ? K1 + 1 + 2 * q : q < H + MI ? K1 + (NI - H == 3 ? 3 : 2) + (NI - H) * (q - H + 1) : K + 4 + 2 * (q - H - MI); }
     static constexpr int second(int q) { return ROOM || (SOME && q < 8) ? 2 * q : SOME ? 2 * q + 1 : half(q); }
     static constexpr int FREE = ROOM ? 34 : second(F - 1) + 10, LANDED = ROOM ? 94 : K + K / 2, STEP = ROOM ? 6 : SOME ? 3 : 4;
     static constexpr int next(int q) { return ROOM ? LANDED + 2 * q : SOME ? LANDED + 1 + q : K + half(q); }
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
     uint16_t* stages = (uint16_t*)smem_raw;
     const int T = p.T, d = p.d, E = p.E, k = p.k, nchunks = p.r / BN;
 
-    // Work items as in prefill_kernel: (layer, token tile, group of chunks), the group fastest, a contiguous range to each XCD.
+    // Work items as in prefill_kernel: (layer, token tile, group of chunks), the group (or the tile) fastest, a contiguous range to each XCD.
     int wg = blockIdx.x;
     const bool in_tail = wg >= p.grid.main_wgs;
     {
@@ -132,8 +135,12 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
     }
     const int groups = in_tail ? p.grid.tail_groups : p.grid.main_groups;
     const int cpg = nchunks / groups;
-    const int cg = wg % groups;
-    const int tile_id = (in_tail ? p.grid.main_wgs / p.grid.main_groups : 0) + wg / groups;
+    int cg = wg % groups, tile_id = (in_tail ? p.grid.main_wgs / p.grid.main_groups : 0) + wg / groups;
+    if (p.grid.tile_fastest) {
+        const int column = wg / p.grid.tiles_per_layer, l = column / groups;
+        cg = column - l * groups;
+        tile_id = l * p.grid.tiles_per_layer + wg - column * p.grid.tiles_per_layer;
+    }
     const int layer = tile_id / p.grid.tiles_per_layer;
     const int t0 = (tile_id - layer * p.grid.tiles_per_layer) * BM;
     const int n_begin = cg * cpg, n_end = n_begin + cpg;
@@ -473,6 +480,12 @@ hipError_t launch_prefill256(const PredictArgs& a, const PrefillGrid& grid, int 
                  (const uint16_t*)a.x, (const uint16_t*)a.W1, (const uint16_t*)a.W2, (const uint16_t*)a.b1,
                  (const uint16_t*)a.b2, a.idx, a.probs, a.logits, a.margin, a.counts, h};
     if (h) return a.b1 ? launch_mode<Square, 0, 1>(p, a.stream) : launch_mode<Square, 0, 0>(p, a.stream);
+    if (tokens == 128 && a.E > 64) return launch_experts<Few<4>, 8>(p, a.act, a.stream);
+    if (tokens == 128)
+        return a.E <= 32 ? launch_experts<Few<4>, 2>(p, a.act, a.stream) : launch_experts<Few<4>, 4>(p, a.act, a.stream);
+    if (tokens == 160)
+        return a.E <= 32 ? launch_experts<Few<5>, 2>(p, a.act, a.stream) : launch_experts<Few<5>, 4>(p, a.act, a.stream);
+    if (tokens == 192) return launch_experts<Few<6>, 4>(p, a.act, a.stream);
     if (tokens == 224)
         return a.E <= 32 ? launch_experts<Square224, 2>(p, a.act, a.stream) : launch_experts<Square224, 4>(p, a.act, a.stream);
     if (units == 256)
