@@ -1222,15 +1222,50 @@ static size_t few_bytes(const PredictArgs& a, const FewPlan& f)
     if (f.groups == 1) return 0;
     return (size_t)((a.T + f.tokens - 1) / f.tokens) * a.L * f.groups * f.tokens * a.E * sizeof(float);
 }
-static hipError_t launch_few(const PredictArgs& a, const FewPlan& f)
+static hipError_t launch_few(const PredictArgs& a, const FewPlan& f, bool tiles_first)
 {
     const int tiles = (a.T + f.tokens - 1) / f.tokens;
     float* zpart = (float*)a.workspace;
-    const PrefillGrid grid{tiles, tiles * a.L * f.groups, f.groups, 0, 1, 0, zpart,
-                           (int)tile_fastest(a, f.tokens, Cfg256::BN, f.groups)};
+    const PrefillGrid grid{tiles, tiles * a.L * f.groups, f.groups, 0, 1, 0, zpart, (int)tiles_first};
     const hipError_t err = launch_prefill256(a, grid, f.tokens, Cfg256::BN, nullptr);
     if (err != hipSuccess || f.groups == 1) return err;
     return launch_finalize(a, zpart, f.groups, tiles * a.L, f.tokens, 0, tiles);
+}
+
+// Calls of 128 to 255 tiles of 256 tokens, and with long rows up to 511: every tile's r split evenly, in tiles of 160 to 256
+// tokens (65 to 128 experts: 256), where that beats the split that cfg_layout makes for them by a twentieth in this model of
+// the time in us, fitted to 13 shapes of up to 30 (tile, split) each: of them its choice was the best nine times, within
+// 4 % else.  A stage costs 0.004 a token, 0.55, and from d = 1024 on what the token tile, which does not stay in L2, costs workgroups
+// that do not share it; the last round, partly filled, half of one and more.
+// cfg_layout / here, us: 16 layers of 1800 tokens, 1536 x 960, 60 experts 115 / 80; 12 of 4096, 2048 x 2048, 64 experts 366 / 316; 20 of
+// 3500, d = 3072 820 / 701; 24 of 2000, 3072 x 3584 933 / 806; 48 of 600, d = 4096 549 / 482; 26 of 2600, 1024 x 4096, 16 experts,
+// GELU 573 / 503; 12 of 4000, 2048 x 1024, 100 experts 227 / 197.  Beyond those tiles the rounds are many and even by themselves.
+static double even_us(const PredictArgs& a, int tokens, int groups)
+{
+    const long long tiles = (long long)((a.T + tokens - 1) / tokens) * a.L, wgs = tiles * groups, full = wgs / 256, tail = wgs % 256;
+    const double rounds = (double)full + (tail == 0 ? 0.0 : full == 0 ? 1.0 : 0.5 + 0.5 * (double)tail / 256);
+    const double shared = a.d > 1024 ? 0.15 * (a.d - 1024) / 1024 / groups * tokens / 256 : 0.0;
+    const int chunks = a.r / Cfg256::BN / groups, stages = (a.d + 63) / 64;
+    return rounds * (4 + chunks * (stages * (0.0040 * tokens + 0.55 + shared) + 0.5 + a.E / 64.0)) + split_us(a, tiles, tokens, groups);
+}
+static FewPlan even_plan(const PredictArgs& a)
+{
+    FewPlan best{0, 1};
+    const long long tiles256 = (long long)((a.T + 255) / 256) * a.L;
+    if (a.E > 128 || a.r % Cfg256::BN != 0 || tiles256 < 128 || tiles256 >= (a.d >= 3072 ? 512 : 256) || (a.E <= 64 && flat_wanted(a)))
+        return best;
+    double least = 0.95 * even_us(a, 256, prefill_groups<Cfg256>(a));
+    const int chunks = a.r / Cfg256::BN;
+    for (int tokens = a.E > 64 ? 256 : 160; tokens <= 256; tokens += 32)
+        for (int groups = 1; groups <= chunks && groups <= 8; ++groups) {
+            if (chunks % groups != 0) continue;
+            const double t = even_us(a, tokens, groups);
+            if (t < least) {
+                least = t;
+                best = FewPlan{tokens, groups};
+            }
+        }
+    return best;
 }
 
 template <class C>
@@ -1255,6 +1290,14 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
         if (f.tokens > 0) {                                  // in chunks of 128 hidden units, as the other tiles of the class
             *groups = f.groups;
             *chunks_per_group = a.r / CfgSmall::BN / f.groups;
+            return;
+        }
+    }
+    if (*cfg == 2 || *cfg == 4) {
+        const FewPlan f = even_plan(a);
+        if (f.tokens > 0) {
+            *groups = f.groups;
+            *chunks_per_group = a.r / Cfg256::BN / f.groups;
             return;
         }
     }
@@ -1289,19 +1332,26 @@ static size_t two_pass_bytes(const PredictArgs& a)
     return p.h_bytes + p.z_bytes;
 }
 
+// The even split asks for more than the least, so that with the least a call runs the layout that this is the size of.
+static size_t even_bytes(const PredictArgs& a, const FewPlan& f)
+{
+    const size_t more = prefill_workspace_min(a) + 16, scores = few_bytes(a, f);
+    return f.tokens == 0 ? 0 : scores > more ? scores : more;
+}
+
 // what it runs fastest with; calls with less, down to the above, run without what the rest is for
 size_t prefill_workspace_bytes(const PredictArgs& a)
 {
     size_t need = prefill_workspace_min(a);
     size_t best = two_pass_wanted(a) ? two_pass_bytes(a) : fused_workspace_bytes(a, true);
     const int cfg = pick_cfg(a, true);
-    const size_t few = cfg == 0 || cfg == 1 ? few_bytes(a, few_plan(a)) : 0;
+    const size_t few = cfg == 0 || cfg == 1 ? few_bytes(a, few_plan(a)) : cfg == 2 || cfg == 4 ? even_bytes(a, even_plan(a)) : 0;
     if (few > best) best = few;
     return best > need ? best : need;
 }
 
 // The kernel of a call in the workspace it was given: one choice for the launch and for those who ask.
-enum class Route { Small, SmallWide, Few, Tiny, Flat, Square, Square224, Long, Short, TwoPass };
+enum class Route { Small, SmallWide, Few, Even, Tiny, Flat, Square, Square224, Long, Short, TwoPass };
 static Route route_of(const PredictArgs& a)
 {
     if (two_pass_wanted(a) && a.workspace_bytes >= two_pass_bytes(a)) return Route::TwoPass;
@@ -1309,6 +1359,10 @@ static Route route_of(const PredictArgs& a)
     if (cfg == 0 || cfg == 1) {
         const FewPlan f = few_plan(a);
         if (f.tokens > 0 && a.workspace_bytes >= few_bytes(a, f)) return Route::Few;
+    }
+    if (cfg == 2 || cfg == 4) {
+        const FewPlan f = even_plan(a);
+        if (f.tokens > 0 && a.workspace_bytes >= even_bytes(a, f)) return Route::Even;
     }
     switch (cfg) {
     case 5: return Route::Tiny;
@@ -1345,6 +1399,13 @@ const char* prefill_kernel_name(const PredictArgs& a)
             return a.E > 64 ? "prefill_kernel 128x128 wide tiles first" : "prefill_kernel 128x128 tiles first";
         return a.E > 64 ? "prefill_kernel 128x128 wide" : "prefill_kernel 128x128";
     }
+    case Route::Even:
+        switch (even_plan(a).tokens) {
+        case 160: return "prefill256_kernel 160x256";
+        case 192: return "prefill256_kernel 192x256";
+        case 224: return "prefill256_kernel 224x256";
+        default: return a.E > 64 ? "prefill256_kernel 256x256 wide" : "prefill256_kernel 256x256";
+        }
     case Route::SmallWide:
         return name_with_order<CfgSmallWide>(a, "prefill_kernel 128x128 wide", "prefill_kernel 128x128 wide tiles first");
     default: return name_with_order<CfgSmall>(a, "prefill_kernel 128x128", "prefill_kernel 128x128 tiles first");
@@ -1357,7 +1418,11 @@ hipError_t launch_predict_prefill(const PredictArgs& a)
     case Route::TwoPass: return launch_two_pass(a);
     case Route::Tiny:
         return a.E <= 32 ? launch_cfg<CfgTiny, 1>(a) : a.E <= 64 ? launch_cfg<CfgTiny, 2>(a) : launch_cfg<CfgTiny, 4>(a);
-    case Route::Few: return launch_few(a, few_plan(a));
+    case Route::Few: {
+        const FewPlan f = few_plan(a);
+        return launch_few(a, f, tile_fastest(a, f.tokens, Cfg256::BN, f.groups));
+    }
+    case Route::Even: return launch_few(a, even_plan(a), false);
     case Route::Flat: return a.E <= 32 ? launch_cfg<CfgFlat, 1>(a) : launch_cfg<CfgFlat, 2>(a);
     case Route::Square224: return launch_tiles_of_224(a);
     case Route::Square:

@@ -938,3 +938,30 @@ def test_prefill_few_tokens(L, T, d, r, E, k, act, bias, groups):
     torch.cuda.synchronize()
     scale = one.logits.abs().amax(dim=2, keepdim=True)
     assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+
+
+# ------------------------------------------------------------------ 128 to 511 tiles: r split evenly
+@pytest.mark.parametrize("L,T,d,r,E,k,act,kernel,groups", [
+    (64, 300, 192, 256, 40, 6, "silu", "160x256", 1), (64, 300, 192, 512, 16, 3, "silu", "160x256", 2),
+    (40, 1000, 192, 256, 16, 2, "silu", "192x256", 1), (33, 1500, 192, 256, 64, 8, "silu", "224x256", 1),
+    (16, 1800, 288, 512, 16, 4, "silu", "256x256", 2), (33, 1000, 416, 768, 60, 6, "gelu", "160x256", 1),
+    (64, 300, 416, 512, 100, 6, "silu", "256x256 wide", 2), (16, 1800, 640, 768, 128, 12, "none", "256x256 wide", 3),
+])
+def test_prefill_even_splits(L, T, d, r, E, k, act, kernel, groups):
+    """Against the oracle; and against the layout that runs with the least workspace: the same hidden vector, scores of other
+    slices of r (2e-6 of the row's scale, as for the two passes); with counts and margin."""
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
+    assert B.predict_kernel(desc, with_b1=True) == "prefill256_kernel " + kernel
+    x, W1, W2, b1, b2 = _rand_layers(1100 + T + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    rows = np.unique(np.concatenate([np.arange(0, T, 29), np.arange(T - 20, T)]))
+    out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"even splits {L} x {T} d={d} r={r} E={E}", rows=rows)
+    _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out)
+    least = B.predict_workspace_min_bytes(desc)
+    one = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, act=act, want_logits=True, b1=_dev(b1, "bf16"),
+                    b2=_dev(b2, "bf16"), workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    scale = one.logits.abs().amax(dim=2, keepdim=True)
+    assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+    if groups > 1:                                         # score tiles of all of them, tokens of the tile x experts
+        tokens = int(kernel.split("x")[0])
+        assert B.predict_workspace_bytes(desc) >= -(-T // tokens) * L * groups * tokens * E * 4
