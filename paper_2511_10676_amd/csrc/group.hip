@@ -29,6 +29,7 @@ namespace paep {
 
 static constexpr int PART_WAVES = 16;                   // waves per workgroup on layers that take the workspace
 static constexpr int PART_SUB = 512;                    // positions per wave of a part (doubled while parts > SCAN_PARTS)
+static constexpr int PART_REGS = 12;                    // ... of parts grown for whole rounds: positions per lane
 static constexpr int SCAN_PARTS = 64;                   // more parts than this: columns are scanned by a launch of their own
 
 // counts of one part: hist[layer][part][0..E], 1024 threads, grid (P, L)
@@ -121,7 +122,7 @@ __device__ __forceinline__ uint64_t lanes_with_same_id(int32_t e, bool valid, in
 }
 
 template <int WAVES, bool PRE, int REGS>
-__global__ __launch_bounds__(WAVES * 64, (WAVES == 16 && REGS <= 8) ? 8 : WAVES / 4) void group_fused_kernel(
+__global__ __launch_bounds__(WAVES * 64, (WAVES == 16 && REGS <= PART_REGS) ? 8 : WAVES / 4) void group_fused_kernel(
     const int32_t* __restrict__ idx, int n, int E, int nbits, int P, int sub,
     const int32_t* __restrict__ part_hist, int scanned, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ token_pos,
     int32_t* __restrict__ active, int32_t* __restrict__ n_active, int32_t* __restrict__ n_invalid)
@@ -335,7 +336,7 @@ static size_t fused_lds(int hists, int waves, int E, int sub)
 {
     return sizeof(int32_t) * ((size_t)hists * waves * (size_t)(E + 1) + (size_t)E + (size_t)sub * waves);
 }
-static FusedPlan fused_plan(long long n, int E)
+static FusedPlan fused_plan(int L, long long n, int E)
 {
     FusedPlan f{false, false, 16, 1, 64, 0};
     if (n <= FUSED_MAX_ITEMS) {
@@ -368,6 +369,17 @@ static FusedPlan fused_plan(long long n, int E)
         f.sub *= 2;
     }
     f.scan = f.P > SCAN_PARTS;
+    // Two workgroups of up to 12 positions a lane share a compute unit, so 512 of them run at a time, and they take equally
+    // long: somewhat longer parts where that saves a round (48 layers of 98304 selections: 576 parts of 8192 25.2 us, 480 of
+    // 10240 20 us, both launches 31.6 -> 26.5).  A part's time goes with its positions and a half of PART_SUB's on top (loads, barriers, scans).
+    auto rounds_time = [&](int sub) {
+        const long long parts = (n + (long long)sub * f.waves - 1) / ((long long)sub * f.waves);
+        return (parts * L + 511) / 512 * (sub + PART_SUB / 2);
+    };
+    if (!f.scan && f.sub == PART_SUB)
+        for (int sub = PART_SUB + 64; sub <= 64 * PART_REGS; sub += 64)
+            if (2 * (fused_lds(1, f.waves, E, sub) + 8 * COLSUM_INTS + 512) <= 160 * 1024 && rounds_time(sub) < rounds_time(f.sub)) f.sub = sub;
+    f.P = (int)((n + (long long)f.sub * f.waves - 1) / ((long long)f.sub * f.waves));
     f.lds = fused_lds(1, f.waves, E, f.sub);
     return f;
 }
@@ -375,7 +387,7 @@ static FusedPlan fused_plan(long long n, int E)
 size_t group_workspace_bytes(int L, int T, int k, int E)
 {
     const long long n = (long long)T * k;
-    const FusedPlan f = fused_plan(n, E);
+    const FusedPlan f = fused_plan(L, n, E);
     if (!f.pre) return 0;
     return sizeof(int32_t) * (size_t)L * (size_t)(f.P + 1) * (size_t)(E + 1);
 }
@@ -394,7 +406,7 @@ static hipError_t launch_fused_regs(const FusedPlan& f, const int32_t* idx, int 
     return hipGetLastError();
 }
 
-// compiled for 8 positions per lane (short sub-spans: two workgroups of 16 waves share a compute unit) and for 32
+// compiled for 8 and 12 positions per lane (short sub-spans: two workgroups of 16 waves share a compute unit) and for 32
 template <int WAVES, bool PRE>
 static hipError_t launch_fused(const FusedPlan& f, const int32_t* idx, int L, int n, int E, int nbits,
                                const int32_t* hist, int32_t* counts, int32_t* offsets, int32_t* token_pos,
@@ -403,6 +415,10 @@ static hipError_t launch_fused(const FusedPlan& f, const int32_t* idx, int L, in
     if (f.sub <= 64 * 8)
         return launch_fused_regs<WAVES, PRE, 8>(f, idx, L, n, E, nbits, hist, counts, offsets, token_pos, active,
                                                 n_active, n_invalid, stream);
+    if constexpr (WAVES == 16 && PRE)
+        if (f.sub <= 64 * PART_REGS)
+            return launch_fused_regs<WAVES, PRE, PART_REGS>(f, idx, L, n, E, nbits, hist, counts, offsets, token_pos, active,
+                                                     n_active, n_invalid, stream);
     if constexpr (WAVES == 16)
         return launch_fused_regs<WAVES, PRE, FUSED_REGS>(f, idx, L, n, E, nbits, hist, counts, offsets, token_pos,
                                                          active, n_active, n_invalid, stream);
@@ -417,7 +433,7 @@ hipError_t launch_group(const int32_t* idx, int L, int T, int k, int E,
     const int n = T * k;
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
-    const FusedPlan f = fused_plan(n, E);
+    const FusedPlan f = fused_plan(L, n, E);
     if (!f.pre) {
         if (f.waves == 4)
             return launch_fused<4, false>(f, idx, L, n, E, nbits, nullptr, counts, offsets, token_pos, active,
