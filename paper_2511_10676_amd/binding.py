@@ -8,6 +8,7 @@ been built (``python -m paper_2511_10676_amd.build``), loading raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import NamedTuple, Optional
@@ -134,7 +135,6 @@ def _on(stream):
     """Context in which torch allocates on `stream` (its caching allocator ties a block to the stream that
     was current when it was handed out): temporaries made for a call must belong to the stream the call's
     kernels are enqueued on, or the allocator may hand them to someone else while those kernels still run."""
-    import contextlib
     return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
 
 
@@ -371,10 +371,11 @@ def group_workspace_bytes(L: int, T: int, k: int, E: int) -> int:
 
 
 def alloc_grouping(L: int, T: int, k: int, E: int, device) -> Grouping:
+    # empty_like costs half of empty's argument parsing, and calls of short kernels wait for the host
     i32 = dict(dtype=torch.int32, device=device)
-    return Grouping(torch.empty((L, E), **i32), torch.empty((L, E + 1), **i32),
-                    torch.empty((L, T * k), **i32), torch.empty((L, E), **i32),
-                    torch.empty((L,), **i32), torch.empty((L,), **i32))
+    counts, n_active = torch.empty((L, E), **i32), torch.empty((L,), **i32)
+    return Grouping(counts, torch.empty((L, E + 1), **i32), torch.empty((L, T * k), **i32), torch.empty_like(counts),
+                    n_active, torch.empty_like(n_active))
 
 
 def prepare_group_by_expert(idx: torch.Tensor, E: int, *, out: Optional[Grouping] = None,
@@ -481,7 +482,7 @@ def activation_profile(counts: torch.Tensor, stream=None) -> ActivationProfile:
         raise TypeError("counts must be contiguous int32")
     L, E = counts.shape
     with _on(stream):
-        out = ActivationProfile(torch.empty((L, E), dtype=torch.int32, device=counts.device),
+        out = ActivationProfile(torch.empty_like(counts),
                                 torch.empty((L,), dtype=torch.int32, device=counts.device),
                                 torch.empty((L,), dtype=torch.float64, device=counts.device))
     st = lib().paep_activation_profile(_ptr(counts), L, E, _ptr(out.order), _ptr(out.n_active), _ptr(out.entropy),
