@@ -620,8 +620,8 @@ bool prefill_supported(const PredictArgs& a)
 //    groups where the token tile is large (d >= 4096: 2 MB per tile; one / two /
 //    four groups, 8192 tokens, us: 32 layers 1024 x 4096, 16 experts 1658 / 1559 / 1598; 2048 x 4096,
 //    64 experts 3635 / 3297 / 3245); at d = 2048 there is nothing to gain (1658 / 1669 / 1742; 48 layers,
-//    128 experts 2708 / 2698 / 2907).  The line is the former kernels': d = 3072 would take two
-//    (1489 / 1300 / 1378), d = 5120 four (26 layers of 4096 tokens 2145 / 2037 / 1804).
+//    128 experts 2708 / 2698 / 2907).  With more than the least
+//    workspace d = 3072 takes two as well (1489 / 1300 / 1378) and d = 5120 four (even_plan).
 template <class C>
 static int prefill_groups(const PredictArgs& a)
 {
@@ -1239,7 +1239,9 @@ static hipError_t launch_few(const PredictArgs& a, const FewPlan& f, bool tiles_
 // that do not share it; the last round, partly filled, half of one and more.
 // cfg_layout / here, us: 16 layers of 1800 tokens, 1536 x 960, 60 experts 115 / 80; 12 of 4096, 2048 x 2048, 64 experts 366 / 316; 20 of
 // 3500, d = 3072 820 / 701; 24 of 2000, 3072 x 3584 933 / 806; 48 of 600, d = 4096 549 / 482; 26 of 2600, 1024 x 4096, 16 experts,
-// GELU 573 / 503; 12 of 4000, 2048 x 1024, 100 experts 227 / 197.  Beyond those tiles the rounds are many and even by themselves.
+// GELU 573 / 503; 12 of 4000, 2048 x 1024, 100 experts 227 / 197.  Beyond those tiles the rounds are many and even by themselves;
+// there long rows take two workgroups to a tile, or four, up to 64 experts (16 layers of 8192 tokens,
+// 1024 x 3584 833 / 730; 26 of 5120, 2048 x 3072 1561 / 1504, x 5120 in two / in four 2625 / 2334, 20 of 8000, 1024 x 5120 1311 / 1249).
 static double even_us(const PredictArgs& a, int tokens, int groups)
 {
     const long long tiles = (long long)((a.T + tokens - 1) / tokens) * a.L, wgs = tiles * groups, full = wgs / 256, tail = wgs % 256;
@@ -1252,8 +1254,12 @@ static FewPlan even_plan(const PredictArgs& a)
 {
     FewPlan best{0, 1};
     const long long tiles256 = (long long)((a.T + 255) / 256) * a.L;
-    if (a.E > 128 || a.r % Cfg256::BN != 0 || tiles256 < 128 || tiles256 >= (a.d >= 3072 ? 512 : 256) || (a.E <= 64 && flat_wanted(a)))
-        return best;
+    if (a.E > 128 || a.r % Cfg256::BN != 0 || tiles256 < 128 || (a.E <= 64 && flat_wanted(a))) return best;
+    if (tiles256 >= 512 && a.E <= 64 && a.d >= 3072) {
+        const int groups = a.d >= 5120 ? 4 : 2;
+        return a.r / Cfg256::BN % groups == 0 && groups != prefill_groups<Cfg256>(a) ? FewPlan{256, groups} : best;
+    }
+    if (tiles256 >= (a.d >= 3072 ? 512 : 256)) return best;
     double least = 0.95 * even_us(a, 256, prefill_groups<Cfg256>(a));
     const int chunks = a.r / Cfg256::BN;
     for (int tokens = a.E > 64 ? 256 : 160; tokens <= 256; tokens += 32)

@@ -965,3 +965,33 @@ def test_prefill_even_splits(L, T, d, r, E, k, act, kernel, groups):
     if groups > 1:                                         # score tiles of all of them, tokens of the tile x experts
         tokens = int(kernel.split("x")[0])
         assert B.predict_workspace_bytes(desc) >= -(-T // tokens) * L * groups * tokens * E * 4
+
+
+@pytest.mark.parametrize("d,r,E,act,groups", [(3072, 512, 16, "none", 2), (3616, 768, 64, "silu", 1), (4064, 1024, 40, "gelu", 2),
+                                              (5120, 1024, 64, "none", 4)])
+def test_prefill_long_rows_of_many_tiles(d, r, E, act, groups):
+    """512 tiles and more: two workgroups to a tile from d = 3072 (where the chunks of r divide), four from 5120; layers that
+    share their tokens.  Every row against the layout of the least workspace (2e-6 of the row's scale, as above), some against the oracle."""
+    T, L, k = 2041, 64, 6
+    desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
+    assert _plan(T, d, r, E, k, L).groups == groups
+    g = torch.Generator(device="cuda").manual_seed(d)
+    rnd = lambda *s: torch.randn(s, device="cuda", generator=g)
+    x = rnd(1, T, d).to(torch.bfloat16)
+    W1 = torch.stack([(rnd(r, d) / d ** 0.5).to(torch.bfloat16) for _ in range(L)])
+    W2 = (rnd(L, E, r) / r ** 0.5).to(torch.bfloat16)
+    b1, b2 = (0.3 * rnd(L, r)).to(torch.bfloat16), (0.5 * rnd(L, E)).to(torch.bfloat16)
+    opts = dict(b1=b1, b2=b2, act=act, want_logits=True)
+    out = B.predict(x, W1, W2, k, **opts)
+    least = B.predict_workspace_min_bytes(desc)
+    one = B.predict(x, W1, W2, k, workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"), **opts)
+    torch.cuda.synchronize()
+    scale = one.logits.abs().amax(dim=2, keepdim=True)
+    assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+    assert torch.equal(out.idx.long(), torch.sort(out.logits, dim=2, descending=True, stable=True).indices[:, :, :k])
+    rows = np.array([0, 255, 256, 1791, T - 1])
+    cpu = lambda t: t.float().cpu().numpy()
+    for l in (0, 31, L - 1):
+        parity.check_layer(cpu(x[0][rows]), cpu(W1[l]), cpu(W2[l]), cpu(b1[l]), cpu(b2[l]), ACT_ID[act], k, "bf16",
+                           out.idx[l].cpu().numpy()[rows], out.probs[l].cpu().numpy()[rows], out.logits[l].cpu().numpy()[rows],
+                           what=f"long rows layer {l}")
