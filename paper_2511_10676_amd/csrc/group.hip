@@ -371,7 +371,7 @@ static FusedPlan fused_plan(int L, long long n, int E)
     f.scan = f.P > SCAN_PARTS;
     // Two workgroups of up to 12 positions a lane share a compute unit, so 512 of them run at a time, and they take equally
     // long: somewhat longer parts where that saves a round (48 layers of 98304 selections: 576 parts of 8192 25.2 us, 480 of
-    // 10240 20 us, both launches 31.6 -> 26.5).  A part's time goes with its positions and a half of PART_SUB's on top (loads, barriers, scans).
+    // 10240 22.1 us, both launches 31.6 -> 26.5).  A part's time goes with its positions and a half of PART_SUB's on top (loads, barriers, scans).
     auto rounds_time = [&](int sub) {
         const long long parts = (n + (long long)sub * f.waves - 1) / ((long long)sub * f.waves);
         return (parts * L + 511) / 512 * (sub + PART_SUB / 2);
