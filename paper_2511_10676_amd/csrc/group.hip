@@ -331,6 +331,7 @@ struct FusedPlan {
     bool pre, scan;
     int waves, P, sub;
     size_t lds;
+    int P_asked;                                            // parts that the workspace is asked for, P or more
 };
 static size_t fused_lds(int hists, int waves, int E, int sub)
 {
@@ -338,7 +339,7 @@ static size_t fused_lds(int hists, int waves, int E, int sub)
 }
 static FusedPlan fused_plan(int L, long long n, int E)
 {
-    FusedPlan f{false, false, 16, 1, 64, 0};
+    FusedPlan f{false, false, 16, 1, 64, 0, 1};
     if (n <= FUSED_MAX_ITEMS) {
         // short layers: a small workgroup (the per-expert loops over waves are what a short layer pays for)
         f.waves = (n <= 2048 && E <= 256) ? 4 : 16;
@@ -369,6 +370,7 @@ static FusedPlan fused_plan(int L, long long n, int E)
         f.sub *= 2;
     }
     f.scan = f.P > SCAN_PARTS;
+    f.P_asked = f.P;                                        // not the fewer of grown parts: a workspace of a longer layer serves
     // Two workgroups of up to 12 positions a lane share a compute unit, so 512 of them run at a time, and they take equally
     // long: somewhat longer parts where that saves a round (48 layers of 98304 selections: 576 parts of 8192 25.2 us, 480 of
     // 10240 22.1 us, both launches 31.6 -> 26.5).  A part's time goes with its positions and a half of PART_SUB's on top (loads, barriers, scans).
@@ -389,7 +391,7 @@ size_t group_workspace_bytes(int L, int T, int k, int E)
     const long long n = (long long)T * k;
     const FusedPlan f = fused_plan(L, n, E);
     if (!f.pre) return 0;
-    return sizeof(int32_t) * (size_t)L * (size_t)(f.P + 1) * (size_t)(E + 1);
+    return sizeof(int32_t) * (size_t)L * (size_t)(f.P_asked + 1) * (size_t)(E + 1);
 }
 
 template <int WAVES, bool PRE, int REGS>

@@ -167,6 +167,10 @@ def test_group_rejects_bad_arguments():
     assert B.group_workspace_bytes(1, 70000, 8, 64) == 4 * 36 * 65              # 35 parts of 16384
     assert B.group_workspace_bytes(1, 262200, 8, 64) == 4 * 66 * 65             # 65 parts of 32768
     assert B.group_workspace_bytes(2, 66000, 16, 1024) == 2 * 4 * 66 * 1025     # 1024 experts: parts of 16384 at most
+    # parts grown for whole rounds of workgroups leave the size alone: a longer layer's workspace serves a shorter one
+    assert B.group_workspace_bytes(24, 21504, 8, 64) == 24 * 4 * 22 * 65        # 21 parts of 8192
+    assert B.group_workspace_bytes(24, 21505, 8, 64) == 24 * 4 * 23 * 65        # 22, run as 19 of 9216
+    assert B.group_workspace_bytes(256, 24576, 2, 7) == 256 * 4 * 7 * 8         # 6, run as 4 of 12288
     # shorter layers run in one launch out of LDS and need none (a NULL workspace is then accepted:
     # checked with real buffers in the GPU tests, since every valid call launches)
     assert B.group_workspace_bytes(1, 4096, 8, 256) == 0
