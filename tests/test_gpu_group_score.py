@@ -61,6 +61,9 @@ def test_group_matches_oracle(T, k, E, L):
     (70000, 8, 64, 1, 0), (258000, 8, 256, 1, 0), (262144, 8, 128, 1, -1),
     # more than 64 parts of the longest kind LDS allows: the columns get a launch of their own
     (262200, 8, 64, 2, -1), (66000, 16, 1024, 1, 0), (300000, 9, 300, 1, -3),
+    # many layers: parts of 8192 would take a round of workgroups more than longer ones (9216 positions, the last part ragged;
+    # 12288, the longest, whole and one position short)
+    (21505, 8, 64, 24, -2), (24576, 2, 7, 256, 0), (49151, 1, 200, 256, -1),
 ])
 def test_group_long_layers(T, k, E, L, lo):
     g = np.random.default_rng(T + k + E)
@@ -127,6 +130,27 @@ def test_score_matches_oracle(T, kp, kr, E, L):
     for l in range(L):
         want = oracle.score(idx[l], ref[l], E)
         assert got[l].tolist() == want.tolist(), f"layer {l}"
+
+
+@pytest.mark.parametrize("off_p,off_r", [(0, 0), (4, 0), (1, 0), (0, 3), (2, 2)])
+@pytest.mark.parametrize("kp,kr", [(4, 4), (8, 4), (12, 8), (8, 6), (16, 5)])
+def test_score_rows_at_any_address(kp, kr, off_p, off_r):
+    """Rows of whole 16-byte pieces are loaded as such only where the arrays begin at a multiple of 16 bytes."""
+    L, T, E = 2, 4097, 64
+    g = np.random.default_rng(kp * 16 + kr + off_p + off_r)
+    ref = _skewed_idx(g, L, T, kr, E)
+    idx = _skewed_idx(g, L, T, kp, E)
+    n = min(kp, kr)
+    idx[:, ::3, :n] = ref[:, ::3, :n]
+    idx[:, 5, kp - 1] = E                                           # a row that adds nothing
+
+    def at(a, off):
+        buf = torch.zeros(a.size + off, dtype=torch.int32, device="cuda")
+        buf[off:] = torch.from_numpy(a).cuda().reshape(-1)
+        return buf[off:].view(a.shape)
+    got = B.score(at(idx, off_p), at(ref, off_r), E).cpu().numpy()
+    for l in range(L):
+        assert got[l].tolist() == oracle.score(idx[l], ref[l], E).tolist()
 
 
 def test_score_hand_cases_and_invalid_rows():
