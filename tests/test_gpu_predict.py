@@ -957,6 +957,22 @@ def test_prefill_few_tokens(L, T, d, r, E, k, act, bias, groups):
     assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
 
 
+@pytest.mark.parametrize("L,T,d,r,E", [(60, 130, 64, 256, 64), (60, 200, 32, 256, 128), (12, 4096, 512, 512, 64),
+                                       (12, 4096, 512, 256, 128)])
+def test_probabilities_are_sums_of_short_chains(L, T, d, r, E):
+    """The first probability of calls that finish their rows in prefill256_kernel, as in the test of two passes: one or two lanes
+    a row with 8 chains each, of up to 16 terms, 5.0e-8 (5.1 to 5.5 seen); one chain a lane, of 32 to 128 terms, gives 7.5e-8 to
+    1.7e-7 (both seen)."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, W1, W2 = rnd(L, T, d), rnd(L, r, d) / d ** 0.5, rnd(L, E, r) / r ** 0.5
+    assert _plan(T, d, r, E, 8, L).groups == 1
+    o = B.predict(x.to(torch.bfloat16), W1.to(torch.bfloat16), W2.to(torch.bfloat16), 8, want_logits=True)
+    z = o.logits.double()
+    want = 1 / torch.exp(z - z.amax(dim=2, keepdim=True)).sum(dim=2)
+    assert float(((o.probs[..., 0].double() - want) / want).square().mean().sqrt()) <= 6.2e-8
+
+
 # ------------------------------------------------------------------ 128 to 511 tiles: r split evenly
 @pytest.mark.parametrize("L,T,d,r,E,k,act,kernel,groups", [
     (64, 300, 192, 256, 40, 6, "silu", "160x256", 1), (64, 300, 192, 512, 16, 3, "silu", "160x256", 2),
