@@ -242,7 +242,8 @@ template <int N> __device__ __forceinline__ float sum_in_pairs(float (&t)[N])
 // The outputs of one row from its merged list `top`, by the G lanes that share it: lane g writes outputs
 // j = g, g + G, ... < k.  KMAX >= k, and >= k + 1 when the margin is wanted and k < E.  exp_sum(m) is this lane's
 // share of sum(exp(z - m)) over the row's scores.  STRIDE: how far apart the row's lanes are.
-template <int KMAX, int G, int STRIDE = 1, class F>
+// FINE: a sum in pairs and a division, as wave_softmax_topk rounds them, for rows of fp32 calls.
+template <int KMAX, int G, int STRIDE = 1, bool FINE = false, class F>
 __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E, int k, int g, int32_t* idx_row,
                                                 float* probs_row, const EpilogueOut& o, F&& exp_sum)
 {
@@ -252,10 +253,17 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
         s = exp_sum(m);
 #pragma unroll
         for (int mask = STRIDE; mask < G * STRIDE; mask <<= 1) s += __shfl_xor(s, mask, 64);
-    } else if (o.prob_mode == 1) {
+    } else if (o.prob_mode == 1) {               // every lane holds the whole list: same sum, same order
+        if constexpr (FINE) {
+            float t[KMAX];
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j)           // every lane holds the whole list: same sum, same order
-            if (j < k) s += __expf(key_score(top.key[j]) - m);
+            for (int j = 0; j < KMAX; ++j) t[j] = j < k ? __expf(key_score(top.key[j]) - m) : 0.0f;
+            s = sum_in_pairs(t);
+        } else {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j)
+                if (j < k) s += __expf(key_score(top.key[j]) - m);
+        }
     }
     const float inv = 1.0f / s;
 #pragma unroll
@@ -263,7 +271,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
         if (j < k && (j % G) == g) {
             const float sc = key_score(top.key[j]);
             idx_row[j] = key_expert(top.key[j]);
-            probs_row[j] = (o.prob_mode == 2) ? sigmoidf_(sc) : __expf(sc - m) * inv;
+            probs_row[j] = (o.prob_mode == 2) ? sigmoidf_(sc) : FINE ? __expf(sc - m) / s : __expf(sc - m) * inv;
             if (o.counts_row) atomicAdd(&o.counts_row[key_expert(top.key[j])], 1);   // activation counts (exact: integers)
         }
     }
@@ -282,7 +290,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
 // xor-shuffles so that every lane ends with the row's list.
 // SORTED: KMAX scores at a time, sorted and merged, the next ones requested meanwhile; else one inserted after the
 // other (fewer registers).  Scores are read in batches: one by one, a lane waits for LDS E / G times.
-template <int KMAX, int G, bool SORTED, class Z>
+template <int KMAX, int G, bool SORTED, bool FINE = false, class Z>
 __device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
                                                  int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
@@ -316,7 +324,7 @@ __device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
         }
     }
     top.template merge_group<G>();
-    write_selection<KMAX, G>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
+    write_selection<KMAX, G, 1, FINE>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
         // NB chains, added in pairs: where a row has one lane, a single chain of its E terms rounds more than the lanes of
         // finalize_rows_kernel, 16 terms each (64 experts, the first probability against float64, rms: 1.2e-7, here and there 5.7e-8)
         constexpr int NB = SORTED || KMAX <= 8 ? 8 : 4;
@@ -439,15 +447,15 @@ __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, in
 
 // row_softmax_topk with the smallest list length that holds k (and the runner-up, when the margin is wanted):
 // k <= 16, and k <= 15 when the margin is wanted and k < E.
-// LEAN: the caller's registers are full (lists of 16 by insertion).
-template <int G, bool LEAN, class Z>
+// LEAN: the caller's registers are full (lists of 16 by insertion).  FINE: as in write_selection.
+template <int G, bool LEAN, bool FINE = false, class Z>
 __device__ __forceinline__ void row_softmax_topk_upto16(Z&& z, int E, int k, int g,
                                                         int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     const int need = k + ((o.margin_row && k < E) ? 1 : 0);
-    if (need <= 2)      row_softmax_topk<2, G, false>(z, E, k, g, idx_row, probs_row, o);
-    else if (need <= 8) row_softmax_topk<8, G, true>(z, E, k, g, idx_row, probs_row, o);
-    else                row_softmax_topk<16, G, !LEAN>(z, E, k, g, idx_row, probs_row, o);
+    if (need <= 2)      row_softmax_topk<2, G, false, FINE>(z, E, k, g, idx_row, probs_row, o);
+    else if (need <= 8) row_softmax_topk<8, G, true, FINE>(z, E, k, g, idx_row, probs_row, o);
+    else                row_softmax_topk<16, G, !LEAN, FINE>(z, E, k, g, idx_row, probs_row, o);
 }
 
 }  // namespace paep
