@@ -242,7 +242,7 @@ template <int N> __device__ __forceinline__ float sum_in_pairs(float (&t)[N])
 // The outputs of one row from its merged list `top`, by the G lanes that share it: lane g writes outputs
 // j = g, g + G, ... < k.  KMAX >= k, and >= k + 1 when the margin is wanted and k < E.  exp_sum(m) is this lane's
 // share of sum(exp(z - m)) over the row's scores.  STRIDE: how far apart the row's lanes are.
-// FINE: a sum in pairs and a division, as wave_softmax_topk rounds them, for rows of fp32 calls.
+// FINE: a sum in pairs and quotients, as wave_softmax_topk rounds them, for rows of fp32 calls.
 template <int KMAX, int G, int STRIDE = 1, bool FINE = false, class F>
 __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E, int k, int g, int32_t* idx_row,
                                                 float* probs_row, const EpilogueOut& o, F&& exp_sum)
@@ -271,7 +271,9 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
         if (j < k && (j % G) == g) {
             const float sc = key_score(top.key[j]);
             idx_row[j] = key_expert(top.key[j]);
-            probs_row[j] = (o.prob_mode == 2) ? sigmoidf_(sc) : FINE ? __expf(sc - m) / s : __expf(sc - m) * inv;
+            float q = __expf(sc - m) * inv;
+            if constexpr (FINE) q = fmaf(fmaf(-q, s, __expf(sc - m)), inv, q);      // a division takes 3 % longer (4 layers of 1024 tokens, 256 x 64, 16 experts, k = 12 25.9 us, 25.3 here)
+            probs_row[j] = (o.prob_mode == 2) ? sigmoidf_(sc) : q;
             if (o.counts_row) atomicAdd(&o.counts_row[key_expert(top.key[j])], 1);   // activation counts (exact: integers)
         }
     }
