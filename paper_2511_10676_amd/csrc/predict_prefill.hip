@@ -1353,8 +1353,14 @@ size_t prefill_workspace_bytes(const PredictArgs& a)
     size_t need = prefill_workspace_min(a);
     size_t best = two_pass_wanted(a) ? two_pass_bytes(a) : fused_workspace_bytes(a, true);
     const int cfg = pick_cfg(a, true);
-    const size_t few = cfg == 0 || cfg == 1 ? few_bytes(a, few_plan(a)) : cfg == 2 || cfg == 4 ? even_bytes(a, even_plan(a)) : 0;
-    if (few > best) best = few;
+    auto ask = [&](size_t bytes) { if (bytes > best) best = bytes; };
+    if (cfg == 0 || cfg == 1) ask(few_bytes(a, few_plan(a)));
+    if (cfg == 2 || cfg == 4)
+        for (const void* b1 : {(const void*)nullptr, (const void*)&a}) {     // a call may have one: of flat_wanted it matters whether
+            PredictArgs b = a;
+            b.b1 = b1;
+            ask(even_bytes(b, even_plan(b)));
+        }
     return best > need ? best : need;
 }
 

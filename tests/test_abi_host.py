@@ -304,6 +304,19 @@ def test_token_tiles_come_first_where_the_other_order_overflows_a_cache(T, d, r,
     assert B.predict_kernel(B.make_desc(T, d, r, E, 6, L, B.BF16)) == f"prefill_kernel {kernel}" + (" tiles first" if first else "")
 
 
+@pytest.mark.parametrize("E", [16, 40, 64, 100, 128, 200])
+@pytest.mark.parametrize("act", ["none", "silu", "gelu"])
+def test_the_size_asked_for_is_enough_for_the_fastest_kernel(E, act):
+    """With b1, which the size is not told of, and without: a larger workspace runs no other kernel."""
+    sizes = [(L, T, d, r) for L, T in ((40, 1000), (16, 1800), (64, 300), (33, 1500), (26, 301), (12, 4096), (1, 2000), (4, 512))
+             for d in (96, 160, 192, 288, 320, 416, 640, 2048, 3072, 4096) for r in (256, 768, 1024, 2048)]
+    for L, T, d, r in sizes:
+        desc = B.make_desc(T, d, r, E, 6, L, B.BF16, act=act)
+        for b1 in (False, True):
+            asked, more = (B.predict_kernel(desc, workspace_bytes=n, with_b1=b1) for n in (B.predict_workspace_bytes(desc), 8 << 30))
+            assert asked == more, (L, T, d, r, E, act, b1)
+
+
 def test_no_kernel_is_named_for_a_call_that_is_refused():
     desc = B.make_desc(512, 2048, 2048, 64, 6, 1, B.BF16)
     assert B.predict_kernel(desc).startswith("prefill_kernel 64x64")
