@@ -222,7 +222,7 @@ class Runner:
             ach = flops * w.L / (predict_ms * 1e-3) / 1e12
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": measured_traffic("prefill", w.name, T),
-                    "kernel": self.kernel + (" + finalize" if self.plan.groups > 1 else ""),
+                    "kernel": self.kernel + (" + finalize" if self.plan.groups > 1 and "scores_of_h" not in self.kernel else ""),
                     "kernel_ms": round(predict_ms, 4)}
         else:
             ach = nbytes * w.L / (predict_ms * 1e-3) / 1e9

@@ -219,15 +219,17 @@ paep_status paep_predict_static(const paep_predict_desc *desc,
  *   plan[1] tile configuration of the prefill family (0 otherwise):
  *           0 128x128, 1 128x128 wide, 2 256x256, 3 256x128, 4 256x256 wide,
  *           5 64x64, 6 256x256 for the first layer and the scores as a second
- *           kernel (2: 224x256 where that fills the last round of workgroups
- *           better, see paep_predict_kernel; 0 and 1: the class of calls of few
- *           tokens, which run tiles of 128 to 256 tokens x 256 units where those
- *           take less time, plan[2] and plan[3] being those tiles', in chunks of
- *           128 units; 5 and 6 given the workspace that
- *           paep_predict_workspace_bytes names; with less, one of the others)
+ *           kernel, 7 128 to 256 tokens x 256 hidden units, for calls of few
+ *           tokens (2: 160x256 to 224x256 where those fill the rounds of
+ *           workgroups better; paep_predict_kernel names the tile of 2 and 7.
+ *           All given the workspace that paep_predict_workspace_bytes names;
+ *           with less, others may run)
  *   plan[2] workgroups that share one token tile (the inner width r split
- *           between them; 1 = no split, and but for tile 6 no workspace)
+ *           between them; 1 = no split, and but for tile 6 no score tiles in
+ *           the workspace)
  *   plan[3] chunks of r each of them walks
+ * This is the plan of a call without b1; with one, short rows of few experts may
+ * take other tiles, which paep_predict_kernel names.
  * Returns PAEP_OK, or the status paep_predict would give for the descriptor.
  */
 paep_status paep_predict_plan(const paep_predict_desc *desc, int32_t want_margin, int32_t plan[4]);
@@ -235,8 +237,7 @@ paep_status paep_predict_plan(const paep_predict_desc *desc, int32_t want_margin
 /*
  * The kernel that the same call, with or without a bias b1, runs in a workspace
  * of `workspace_bytes`, in words: of the prefill family its name, its tile (tokens x hidden units: here
- * 224 and 256 tokens differ, and the two kernels of 256x256 tiles; the class of
- * calls of few tokens has one name, 128x128, as in the plan) and " tiles
+ * 160, 192, 224 and 256 tokens differ, and the two kernels of 256x256 tiles) and " tiles
  * first" where token tiles are the grid's fastest index; "decode", "simple" or
  * (T = 0) "none" otherwise.  NULL where the call would be refused.  Host only;
  * for tests and reports, the wording may change.

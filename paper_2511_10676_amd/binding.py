@@ -25,7 +25,7 @@ PATH = {"auto": 0, "simple": 1, "decode": 2, "prefill": 3}
 PATH_NAME = {v: k for k, v in PATH.items()}
 PROB = {"softmax": 0, "softmax_topk": 1, "sigmoid": 2}
 TILE_CFG = {0: "128x128", 1: "128x128 wide", 2: "256x256", 3: "256x128", 4: "256x256 wide", 5: "64x64",
-            6: "two-pass 256x256"}
+            6: "two-pass 256x256", 7: "128-256x256"}
 MAX_K, MAX_E = 32, 1024
 
 STATUS_NAMES = ["PAEP_OK", "PAEP_ERR_NULL", "PAEP_ERR_SHAPE", "PAEP_ERR_K", "PAEP_ERR_DTYPE",

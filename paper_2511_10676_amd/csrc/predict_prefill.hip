@@ -1295,9 +1295,10 @@ void prefill_plan(const PredictArgs& a, int* cfg, int* groups, int* chunks_per_g
     *cfg = pick_cfg(a, true);
     if (*cfg == 0 || *cfg == 1) {
         const FewPlan f = few_plan(a);
-        if (f.tokens > 0) {                                  // in chunks of 128 hidden units, as the other tiles of the class
+        if (f.tokens > 0) {
+            *cfg = 7;
             *groups = f.groups;
-            *chunks_per_group = a.r / CfgSmall::BN / f.groups;
+            *chunks_per_group = a.r / Cfg256::BN / f.groups;
             return;
         }
     }
@@ -1396,6 +1397,18 @@ static const char* name_with_order(const PredictArgs& a, const char* groups_firs
     return tile_fastest<C>(a, cfg_layout<C>(a)) ? tiles_first : groups_first;
 }
 
+static const char* plan_name(const PredictArgs& a, const FewPlan& f, bool tiles_first)
+{
+    switch (f.tokens) {
+    case 128: return tiles_first ? "prefill256_kernel 128x256 tiles first" : "prefill256_kernel 128x256";
+    case 160: return tiles_first ? "prefill256_kernel 160x256 tiles first" : "prefill256_kernel 160x256";
+    case 192: return tiles_first ? "prefill256_kernel 192x256 tiles first" : "prefill256_kernel 192x256";
+    case 224: return tiles_first ? "prefill256_kernel 224x256 tiles first" : "prefill256_kernel 224x256";
+    default:
+        return tiles_first ? "prefill256_kernel 256x256 tiles first" : a.E > 64 ? "prefill256_kernel 256x256 wide" : "prefill256_kernel 256x256";
+    }
+}
+
 const char* prefill_kernel_name(const PredictArgs& a)
 {
     switch (route_of(a)) {
@@ -1406,20 +1419,11 @@ const char* prefill_kernel_name(const PredictArgs& a)
     case Route::Short: return "prefill256_kernel 256x128";
     case Route::Flat: return name_with_order<CfgFlat>(a, "prefill_kernel 256x256", "prefill_kernel 256x256 tiles first");
     case Route::Tiny: return name_with_order<CfgTiny>(a, "prefill_kernel 64x64", "prefill_kernel 64x64 tiles first");
-    // The 128 x 128 tiles' class of calls: callers know it by that name.
     case Route::Few: {
         const FewPlan f = few_plan(a);
-        if (tile_fastest(a, f.tokens, Cfg256::BN, f.groups))
-            return a.E > 64 ? "prefill_kernel 128x128 wide tiles first" : "prefill_kernel 128x128 tiles first";
-        return a.E > 64 ? "prefill_kernel 128x128 wide" : "prefill_kernel 128x128";
+        return plan_name(a, f, tile_fastest(a, f.tokens, Cfg256::BN, f.groups));
     }
-    case Route::Even:
-        switch (even_plan(a).tokens) {
-        case 160: return "prefill256_kernel 160x256";
-        case 192: return "prefill256_kernel 192x256";
-        case 224: return "prefill256_kernel 224x256";
-        default: return a.E > 64 ? "prefill256_kernel 256x256 wide" : "prefill256_kernel 256x256";
-        }
+    case Route::Even: return plan_name(a, even_plan(a), false);
     case Route::SmallWide:
         return name_with_order<CfgSmallWide>(a, "prefill_kernel 128x128 wide", "prefill_kernel 128x128 wide tiles first");
     default: return name_with_order<CfgSmall>(a, "prefill_kernel 128x128", "prefill_kernel 128x128 tiles first");

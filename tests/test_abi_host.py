@@ -228,7 +228,7 @@ def test_plan_reports_the_family_and_the_tile_choice():
     assert p == B.Plan("prefill", "256x256", 1, 8)
     # a single layer of the same: too few tiles, r is split over workgroups that meet in the workspace
     p1 = B.predict_plan(B.make_desc(4096, 2048, 2048, 64, 6, 1, B.BF16))
-    assert p1.path == "prefill" and p1.groups > 1 and p1.groups * p1.chunks_per_group * 128 in (2048, 4096)
+    assert p1 == B.Plan("prefill", "128-256x256", 8, 1)
     assert B.predict_plan(B.make_desc(8, 2048, 2048, 64, 6, 26, B.BF16)).path == "decode"
     assert B.predict_plan(B.make_desc(512, 256, 64, 16, 2, 1, B.F32)) == B.Plan("simple", "", 1, 0)
     # many experts and wide tokens: the first layer in 256 x 256 tiles, four workgroups to each, the scores by a second
@@ -260,7 +260,10 @@ def test_plan_reports_the_family_and_the_tile_choice():
     (32768, 2048, 4096, 256, 48, "none", "prefill256_kernel 256x256 + scores_of_h_kernel"),
     (8192, 512, 4096, 256, 16, "none", "prefill256_kernel 256x128"),
     (8192, 2048, 640, 64, 16, "none", "prefill_kernel 128x128"),           # r no multiple of 256
-    (301, 2048, 2048, 64, 26, "none", "prefill_kernel 128x128"),
+    (301, 2048, 2048, 64, 26, "none", "prefill256_kernel 160x256"),        # few tokens
+    (500, 4096, 4096, 64, 20, "none", "prefill256_kernel 256x256"), (130, 64, 768, 64, 26, "none", "prefill256_kernel 128x256"),
+    (200, 2048, 2048, 128, 48, "none", "prefill256_kernel 128x256"),
+    (1800, 1536, 1024, 60, 16, "silu", "prefill256_kernel 256x256"), (600, 512, 256, 64, 60, "none", "prefill256_kernel 160x256"),
     (301, 2048, 2048, 200, 26, "none", "prefill_kernel 128x128 wide"),
     (64, 2048, 2048, 64, 26, "none", "decode"), (0, 2048, 2048, 64, 26, "none", "none"),
     (512, 2040, 2048, 64, 26, "none", "simple"),
@@ -294,14 +297,16 @@ def test_short_rows_of_few_experts_keep_the_eight_wave_kernel(d, r, E, L, T, act
 @pytest.mark.parametrize("T,d,r,E,L,kernel,first", [
     (512, 1024, 1024, 128, 4, "64x64", False), (512, 2048, 2048, 64, 1, "64x64", True),
     (301, 2048, 2048, 128, 1, "64x64", False), (301, 2048, 2048, 128, 2, "64x64", True),
-    (384, 4096, 512, 256, 1, "128x128 wide", False), (700, 2048, 2048, 128, 4, "128x128 wide", True),
-    (1500, 2048, 2048, 64, 1, "128x128", True), (2310, 4096, 3456, 64, 4, "128x128", False), (4000, 2048, 2048, 64, 1, "128x128", False),
+    (384, 4096, 512, 256, 1, "128x128 wide", False), (700, 2048, 2048, 128, 4, "prefill256_kernel 128x256", True),
+    (1500, 2048, 2048, 64, 1, "128x128", True), (2310, 4096, 3456, 64, 4, "128x128", False),
+    (4000, 2048, 2048, 64, 1, "prefill256_kernel 128x256", False),
 ])
 def test_token_tiles_come_first_where_the_other_order_overflows_a_cache(T, d, r, E, L, kernel, first):
     """Either side of the rule, whose measurements stand beside it: 4 layers of 512 tokens with 128 experts were 14 % slower
     with token tiles first, 4 of 700, 2048 x 2048, are 10 % faster; with three chunks a workgroup 2310 tokens were 21 %
     slower."""
-    assert B.predict_kernel(B.make_desc(T, d, r, E, 6, L, B.BF16)) == f"prefill_kernel {kernel}" + (" tiles first" if first else "")
+    name = kernel if kernel.startswith("prefill") else f"prefill_kernel {kernel}"
+    assert B.predict_kernel(B.make_desc(T, d, r, E, 6, L, B.BF16)) == name + (" tiles first" if first else "")
 
 
 @pytest.mark.parametrize("E", [16, 40, 64, 100, 128, 200])

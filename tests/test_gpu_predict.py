@@ -926,35 +926,47 @@ def test_prefill_64x64_tiles(T, d, r, E, k, L, act, bias):
 
 
 # ------------------------------------------------------------------ few tokens: 128 to 256 tokens x 256 hidden units
-@pytest.mark.parametrize("L,T,d,r,E,k,act,bias,groups", [
-    (60, 130, 96, 256, 33, 6, "none", False, 1),           # tiles of 128 tokens, two rows in the second; a stage and a half
-    (26, 130, 64, 768, 64, 12, "none", True, 3),           # ... r in three, one stage per chunk
-    (127, 130, 32, 256, 16, 2, "silu", True, 1),           # of 160, half a stage
-    (40, 159, 448, 768, 64, 6, "gelu", False, 3),          # of 160, seven stages
-    (40, 161, 192, 768, 64, 8, "gelu", True, 3),           # of 192
-    (40, 161, 32, 768, 20, 3, "none", False, 3),           # ... few experts
-    (40, 223, 320, 768, 16, 2, "none", True, 3),           # of 224, one row short of full
-    (40, 480, 256, 768, 33, 6, "silu", False, 3),          # of 256
-    (13, 900, 64, 512, 100, 12, "silu", True, 2),          # of 128, up to 128 experts; a ragged last tile
-    (60, 200, 32, 256, 128, 15, "none", True, 1),          # ... one stage in all
+@pytest.mark.parametrize("L,T,d,r,E,k,act,bias,kernel,groups", [
+    (60, 130, 96, 256, 33, 6, "none", False, "128x256", 1),            # two rows in the second tile; a stage and a half
+    (26, 130, 64, 768, 64, 12, "none", True, "128x256", 3),            # r in three, one stage per chunk
+    (40, 223, 320, 768, 16, 2, "none", True, "128x256", 3),
+    (13, 900, 64, 512, 100, 12, "silu", True, "128x256", 2),           # up to 128 experts; a ragged last tile
+    (60, 200, 32, 256, 128, 15, "none", True, "128x256", 1),           # ... one stage in all
+    (127, 130, 32, 256, 16, 2, "silu", True, "160x256", 1),            # half a stage
+    (40, 159, 448, 768, 64, 6, "gelu", False, "160x256", 3),           # seven stages
+    (40, 161, 192, 768, 64, 8, "gelu", True, "192x256", 3),
+    (40, 161, 32, 768, 20, 3, "none", False, "192x256", 3),            # ... few experts
+    (30, 210, 32, 1024, 33, 6, "none", True, "224x256", 4),            # ragged, r split
+    (33, 208, 32, 1024, 16, 2, "gelu", False, "224x256", 4),           # ... few experts
+    (40, 480, 256, 768, 33, 6, "silu", False, "256x256", 3),
+    (43, 225, 32, 768, 20, 12, "silu", True, "256x256", 3),            # ... few experts
+    # token tiles fastest in an XCD's share of the grid, which ends within a layer (of 7 layers one share is 17 or 18 of 20
+    # workgroups a layer); r whole and in five, last tiles of 3 to 222 rows
+    (5, 3003, 736, 256, 16, 2, "none", True, "128x256 tiles first", 1),
+    (7, 387, 960, 1280, 33, 6, "silu", True, "128x256 tiles first", 5),
+    (6, 387, 992, 1280, 128, 7, "gelu", True, "128x256 tiles first", 5),
+    (6, 2387, 768, 256, 100, 6, "none", False, "128x256 tiles first", 1),
+    (6, 1076, 896, 1280, 33, 6, "none", True, "160x256 tiles first", 5),
+    (6, 1323, 736, 1280, 20, 3, "silu", False, "192x256 tiles first", 5),
+    (6, 1566, 1248, 1280, 40, 9, "none", True, "224x256 tiles first", 5),
 ])
-def test_prefill_few_tokens(L, T, d, r, E, k, act, bias, groups):
-    """Against the oracle, and the 128 x 128 tiles that run with the least workspace where r is split: the same hidden vector,
-    scores of other slices of r (2e-6 of the row's scale, as for the two passes); with counts and margin."""
+def test_prefill_few_tokens(L, T, d, r, E, k, act, bias, kernel, groups):
+    """Against the oracle; and, every row of three layers, against calls of those layers alone, which run another kernel's tiles of
+    64 x 64 or 128 x 128: the same hidden vector, scores of other slices of r (2e-6 of the row's scale, as for the two passes);
+    with counts and margin."""
     desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
-    plan = B.predict_plan(desc)
-    assert plan.tile.startswith("128x128") and (plan.groups, plan.chunks_per_group) == (groups, r // 128 // groups), plan
+    assert B.predict_kernel(desc, with_b1=bias) == "prefill256_kernel " + kernel
+    assert B.predict_plan(desc) == B.Plan("prefill", "128-256x256", groups, r // 256 // groups)
+    assert B.predict_kernel(B.make_desc(T, d, r, E, k, 1, B.BF16, act=act), with_b1=bias).startswith("prefill_kernel ")
     x, W1, W2, b1, b2 = _rand_layers(1000 + T + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
-    rows = np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 40, T)]))
+    rows = np.unique(np.concatenate([np.arange(0, T, 7 if T < 1000 else 41), np.arange(T - 40, T)]))
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"few tokens {L} x {T} d={d} r={r} E={E}", rows=rows)
     _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out)
-    need = B.predict_workspace_min_bytes(desc)
-    one = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, act=act, want_logits=True,
-                    b1=None if b1 is None else _dev(b1, "bf16"), b2=None if b2 is None else _dev(b2, "bf16"),
-                    workspace=torch.empty(max(need, 16), dtype=torch.uint8, device="cuda"))
-    torch.cuda.synchronize()
-    scale = one.logits.abs().amax(dim=2, keepdim=True)
-    assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+    for l in (0, L // 2, L - 1):
+        one = B.predict(_dev(x[l], "bf16"), _dev(W1[l], "bf16"), _dev(W2[l], "bf16"), k, act=act, want_logits=True,
+                        b1=None if b1 is None else _dev(b1[l], "bf16"), b2=None if b2 is None else _dev(b2[l], "bf16"))
+        scale = one.logits.abs().amax(dim=2, keepdim=True)
+        assert ((out.logits[l] - one.logits).abs() <= 2e-6 * scale).all()
 
 
 @pytest.mark.parametrize("L,T,d,r,E", [(60, 130, 64, 256, 64), (60, 200, 32, 256, 128), (12, 4096, 512, 512, 64),
