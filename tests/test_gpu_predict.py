@@ -986,37 +986,49 @@ def test_probabilities_are_sums_of_short_chains(L, T, d, r, E):
 
 
 # ------------------------------------------------------------------ 128 to 511 tiles: r split evenly
-@pytest.mark.parametrize("L,T,d,r,E,k,act,kernel,groups", [
-    (64, 300, 192, 256, 40, 6, "silu", "160x256", 1), (64, 300, 192, 512, 16, 3, "silu", "160x256", 2),
-    (40, 1000, 192, 256, 16, 2, "silu", "192x256", 1), (33, 1500, 192, 256, 64, 8, "silu", "224x256", 1),
-    (16, 1800, 288, 512, 16, 4, "silu", "256x256", 2), (33, 1000, 416, 768, 60, 6, "gelu", "160x256", 1),
-    (64, 300, 416, 512, 100, 6, "silu", "256x256 wide", 2), (16, 1800, 640, 768, 128, 12, "none", "256x256 wide", 3),
+@pytest.mark.parametrize("L,T,d,r,E,k,act,bias,kernel,groups", [
+    (64, 300, 192, 256, 40, 6, "silu", True, "160x256", 1), (64, 300, 192, 512, 16, 3, "silu", True, "160x256", 2),
+    (64, 265, 160, 512, 33, 6, "none", False, "160x256", 2), (33, 1000, 416, 768, 60, 6, "gelu", True, "160x256", 1),
+    (40, 1000, 192, 256, 16, 2, "silu", True, "192x256", 1), (64, 357, 288, 512, 40, 6, "none", False, "192x256", 2),
+    (40, 1000, 192, 1024, 16, 3, "none", True, "192x256", 2),          # an even split for b1's sake
+    (30, 1569, 160, 512, 33, 8, "silu", True, "224x256", 1),
+    (43, 589, 384, 768, 16, 4, "none", False, "224x256", 3), (64, 422, 320, 512, 33, 6, "gelu", True, "224x256", 2),
+    (16, 1929, 192, 1024, 33, 12, "gelu", True, "256x256", 2),
+    (64, 339, 256, 1024, 100, 6, "silu", True, "256x256 wide", 2), (16, 1800, 640, 768, 128, 12, "none", False, "256x256 wide", 1),
 ])
-def test_prefill_even_splits(L, T, d, r, E, k, act, kernel, groups):
-    """Against the oracle; and against the layout that runs with the least workspace: the same hidden vector, scores of other
-    slices of r (2e-6 of the row's scale, as for the two passes); with counts and margin."""
+def test_prefill_even_splits(L, T, d, r, E, k, act, bias, kernel, groups):
+    """Against the oracle; and against the layout that runs with the least workspace, which splits r otherwise or has other
+    tiles: the same hidden vector, scores of other slices of r (2e-6 of the row's scale, as for the two passes); with counts
+    and margin."""
     desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
-    assert B.predict_kernel(desc, with_b1=True) == "prefill256_kernel " + kernel
-    x, W1, W2, b1, b2 = _rand_layers(1100 + T + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=True)
+    least, asked = B.predict_workspace_min_bytes(desc), B.predict_workspace_bytes(desc)
+    assert B.predict_kernel(desc, with_b1=bias) == "prefill256_kernel " + kernel and asked > least
+    if not bias or act != "none":                          # else the plan, which knows of no b1, is another
+        assert B.predict_plan(desc).groups == groups
+    x, W1, W2, b1, b2 = _rand_layers(1100 + T + E, L=L, T=T, d=d, r=r, E=E, dtype="bf16", bias=bias)
     rows = np.unique(np.concatenate([np.arange(0, T, 29), np.arange(T - 20, T)]))
     out, *_ = _run_and_check(x, W1, W2, b1, b2, k, "bf16", act=act, what=f"even splits {L} x {T} d={d} r={r} E={E}", rows=rows)
     _same_with_counts_and_margin(x, W1, W2, b1, b2, k, act, out)
-    least = B.predict_workspace_min_bytes(desc)
-    one = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, act=act, want_logits=True, b1=_dev(b1, "bf16"),
-                    b2=_dev(b2, "bf16"), workspace=torch.empty(max(least, 16), dtype=torch.uint8, device="cuda"))
+    one = B.predict(_dev(x, "bf16"), _dev(W1, "bf16"), _dev(W2, "bf16"), k, act=act, want_logits=True,
+                    b1=None if b1 is None else _dev(b1, "bf16"), b2=None if b2 is None else _dev(b2, "bf16"),
+                    workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
     torch.cuda.synchronize()
+    other = B.predict_kernel(desc, workspace_bytes=least, with_b1=bias)
+    # tiles of another size are seen in the name; workgroups of another number by the order of the scores' sums
+    assert other != "prefill256_kernel " + kernel or not torch.equal(out.logits, one.logits)
     scale = one.logits.abs().amax(dim=2, keepdim=True)
     assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
     if groups > 1:                                         # score tiles of all of them, tokens of the tile x experts
         tokens = int(kernel.split("x")[0])
-        assert B.predict_workspace_bytes(desc) >= -(-T // tokens) * L * groups * tokens * E * 4
+        assert asked >= -(-T // tokens) * L * groups * tokens * E * 4
 
 
 @pytest.mark.parametrize("d,r,E,act,groups", [(3072, 512, 16, "none", 2), (3616, 768, 64, "silu", 1), (4064, 1024, 40, "gelu", 2),
                                               (5120, 1024, 64, "none", 4)])
 def test_prefill_long_rows_of_many_tiles(d, r, E, act, groups):
     """512 tiles and more: two workgroups to a tile from d = 3072 (where the chunks of r divide), four from 5120; layers that
-    share their tokens.  Every row against the layout of the least workspace (2e-6 of the row's scale, as above), some against the oracle."""
+    share their tokens.  Every row against the layout of the least workspace (2e-6 of the row's scale, as above; the same one
+    where the chunks do not divide), some against the oracle."""
     T, L, k = 2041, 64, 6
     desc = B.make_desc(T, d, r, E, k, L, B.BF16, act=act)
     assert _plan(T, d, r, E, k, L).groups == groups
@@ -1033,6 +1045,7 @@ def test_prefill_long_rows_of_many_tiles(d, r, E, act, groups):
     torch.cuda.synchronize()
     scale = one.logits.abs().amax(dim=2, keepdim=True)
     assert ((out.logits - one.logits).abs() <= 2e-6 * scale).all()
+    assert torch.equal(out.logits, one.logits) == (groups == 1)        # another order of the scores' sums: not the same call twice
     assert torch.equal(out.idx.long(), torch.sort(out.logits, dim=2, descending=True, stable=True).indices[:, :, :k])
     rows = np.array([0, 255, 256, 1791, T - 1])
     cpu = lambda t: t.float().cpu().numpy()
