@@ -103,7 +103,10 @@ typedef struct {
  * possible).  Calls with less run on where the work can be laid out without it
  * (large bf16 calls of more than 64 experts: the hidden vectors then stay on
  * chip; T <= 64 with few layers: wider slices of r, L * (r / 64) * T * E * 4
- * bytes; fp32), else they return PAEP_ERR_WORKSPACE.  Returns 0 for an invalid
+ * bytes; fp32; bf16 calls whose token tiles' r is split, which ask for
+ * plan[2] * L * T * E * 4 bytes, T rounded up to tiles: with less, another split
+ * or none), else they return PAEP_ERR_WORKSPACE.  A call with b1 and one without
+ * are asked for the same.  Returns 0 for an invalid
  * descriptor; paep_predict reports the reason. */
 size_t paep_predict_workspace_bytes(const paep_predict_desc *desc);
 

@@ -36,11 +36,14 @@
 // 1.06e-7 / 2.9e-7 / 1.05e-7).
 // Few token tiles: r is cut over several workgroups per tile, their scores meet in the
 // workspace and finalize_kernel adds them; otherwise softmax and top-k follow here, 8 or 16 lanes to a row (a wave
-// per row, one after the other: 4 x 1024 tokens of 256 x 64, 16 experts 36.7 us, 22.1 here).
-// More than 128 experts: one workgroup per CU, whose waves keep their scores in registers (two spilled them: 4 x 1024 tokens of
-// 2048 x 2048, 256 experts 413 -> 379 us, 2 x 1024 of 1024 x 1024, 200 experts 121 -> 100).
+// per row, one after the other: 4 x 1024 tokens of 256 x 64, 16 experts 36.7 us, 22.1 here).  That part costs the 64 x 64 tiles
+// registers, also where r is cut: 5 vector registers spilled up to 128 experts at d >= 2048, outside the loop.
+// 64 x 64 tiles run two workgroups to a CU up to 256 experts although 129 and more spill 63 to 88 registers (250 bytes a lane),
+// and one from 257 on (16 spilled, from 513 on 200).  Two / one, us: 4 x 1024 tokens of 2048 x 2048, 256 experts 401 / 372, 200
+// experts 571 / 589; 2 x 1024 of 1024 x 1024, 200 experts 120 / 100, of 512 x 1024, 160 experts 71 / 77; 3 x 1024 of 4096 x 1024, 130
+// experts 328 / 331.
 // Measured, 512 tokens x (2048 x 2048, 64 experts), whole call: 5200 us for a kernel of vector
-// instructions (a wave per hidden unit), 52 us here.
+// instructions (a wave per hidden unit), 50 us here.
 #include <type_traits>
 
 #include "paep_device.h"

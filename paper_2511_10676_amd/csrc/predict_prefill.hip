@@ -581,7 +581,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void prefill_kernel(
 //             and any r that is a multiple of 128.  SmallWide: the same for E > 64 (64 KB slice).
 //   Tiny      64 x 64, 4 waves, four 64-wide stages, two workgroups per CU: calls whose 128 x 128 tiles would not reach
 //             every CU.  What bounds it is the chain of stages, 0.5 us each whatever is tried on it (eight stages, all
-//             of a stage's fragments read a stage ahead: no faster).
+//             of a stage's fragments read a stage ahead: no faster); what the half microsecond consists of is not known.
 typedef PfCfg<256, 256, 32, 4, 2, 4, 1> CfgFlat;
 struct Cfg256 { static constexpr int BM = 256, BN = 256; };
 struct Cfg256x128 { static constexpr int BM = 256, BN = 128; };
@@ -1219,6 +1219,9 @@ static FewPlan few_plan(const PredictArgs& a)
         }
     return best;
 }
+// Score tiles: the size of the call's scores (tokens rounded up to tiles) times the workgroups that share a tile.  Nothing bounds them
+// but that: 48 layers of 32768 tokens, d = 3072, 64 experts ask for 0.8 GB (beside 9.7 GB of token rows); with less a call runs the
+// layout of the least workspace.
 static size_t few_bytes(const PredictArgs& a, const FewPlan& f)
 {
     if (f.groups == 1) return 0;
@@ -1237,7 +1240,8 @@ static hipError_t launch_few(const PredictArgs& a, const FewPlan& f, bool tiles_
 // Calls of 128 to 255 tiles of 256 tokens, and with long rows up to 511: every tile's r split evenly, in tiles of 160 to 256
 // tokens (65 to 128 experts: 256), where that beats the split that cfg_layout makes for them by a twentieth in this model of
 // the time in us, fitted to 13 shapes of up to 30 (tile, split) each: of them its choice was the best nine times, within
-// 4 % else.  A stage costs 0.004 a token, 0.55, and from d = 1024 on what the token tile, which does not stay in L2, costs workgroups
+// 4 % else.  (time256_us has other constants for the same kernel below 128 tiles: each is a fit to its own calls, one for both has
+// not been tried.)  A stage costs 0.004 a token, 0.55, and from d = 1024 on what the token tile, which does not stay in L2, costs workgroups
 // that do not share it; the last round, partly filled, half of one and more.
 // cfg_layout / here, us: 16 layers of 1800 tokens, 1536 x 960, 60 experts 115 / 80; 12 of 4096, 2048 x 2048, 64 experts 366 / 316; 20 of
 // 3500, d = 3072 820 / 701; 24 of 2000, 3072 x 3584 933 / 806; 48 of 600, d = 4096 549 / 482; 26 of 2600, 1024 x 4096, 16 experts,
