@@ -230,6 +230,16 @@ struct EpilogueOut {
 
 __device__ __forceinline__ float sigmoidf_(float v) { return 1.0f / (1.0f + __expf(-v)); }
 
+// How a row's lanes sum their exponentials.
+//   Chain   one after the other
+//   Chains  in 4 or 8 chains that are then added in pairs: where a row has one lane, a single chain of its E terms rounds more than
+//           the lanes of finalize_rows_kernel, 16 terms each (64 experts, the first probability against float64, rms: 1.2e-7, in
+//           chains 5.2e-8, there 5.7e-8).  prefill_kernel keeps the one: its loops, which split calls run alone, are compiled slower
+//           beside the others (9 layers of 285 tokens, 896 x 1024, 76 experts 26.3 -> 28.2 us)
+//   Fine    ... and of the selected scores in pairs, and quotients instead of products with a reciprocal, as wave_softmax_topk
+//           rounds them, for rows of fp32 calls
+enum class Sums { Chain, Chains, Fine };
+
 template <int N> __device__ __forceinline__ float sum_in_pairs(float (&t)[N])
 {
 #pragma unroll
@@ -242,8 +252,7 @@ template <int N> __device__ __forceinline__ float sum_in_pairs(float (&t)[N])
 // The outputs of one row from its merged list `top`, by the G lanes that share it: lane g writes outputs
 // j = g, g + G, ... < k.  KMAX >= k, and >= k + 1 when the margin is wanted and k < E.  exp_sum(m) is this lane's
 // share of sum(exp(z - m)) over the row's scores.  STRIDE: how far apart the row's lanes are.
-// FINE: a sum in pairs and quotients, as wave_softmax_topk rounds them, for rows of fp32 calls.
-template <int KMAX, int G, int STRIDE = 1, bool FINE = false, class F>
+template <int KMAX, int G, int STRIDE = 1, Sums SUMS = Sums::Chain, class F>
 __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E, int k, int g, int32_t* idx_row,
                                                 float* probs_row, const EpilogueOut& o, F&& exp_sum)
 {
@@ -254,7 +263,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
 #pragma unroll
         for (int mask = STRIDE; mask < G * STRIDE; mask <<= 1) s += __shfl_xor(s, mask, 64);
     } else if (o.prob_mode == 1) {               // every lane holds the whole list: same sum, same order
-        if constexpr (FINE) {
+        if constexpr (SUMS == Sums::Fine) {
             float t[KMAX];
 #pragma unroll
             for (int j = 0; j < KMAX; ++j) t[j] = j < k ? __expf(key_score(top.key[j]) - m) : 0.0f;
@@ -272,7 +281,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
             const float sc = key_score(top.key[j]);
             idx_row[j] = key_expert(top.key[j]);
             float q = __expf(sc - m) * inv;
-            if constexpr (FINE) q = fmaf(fmaf(-q, s, __expf(sc - m)), inv, q);      // a division takes 3 % longer (4 layers of 1024 tokens, 256 x 64, 16 experts, k = 12 25.9 us, 25.3 here)
+            if constexpr (SUMS == Sums::Fine) q = fmaf(fmaf(-q, s, __expf(sc - m)), inv, q);      // a division takes 3 % longer (4 layers of 1024 tokens, 256 x 64, 16 experts, k = 12 25.9 us, 25.3 here)
             probs_row[j] = (o.prob_mode == 2) ? sigmoidf_(sc) : q;
             if (o.counts_row) atomicAdd(&o.counts_row[key_expert(top.key[j])], 1);   // activation counts (exact: integers)
         }
@@ -292,7 +301,7 @@ __device__ __forceinline__ void write_selection(const TopList<KMAX>& top, int E,
 // xor-shuffles so that every lane ends with the row's list.
 // SORTED: KMAX scores at a time, sorted and merged, the next ones requested meanwhile; else one inserted after the
 // other (fewer registers).  Scores are read in batches: one by one, a lane waits for LDS E / G times.
-template <int KMAX, int G, bool SORTED, bool FINE = false, class Z>
+template <int KMAX, int G, bool SORTED, Sums SUMS = Sums::Chain, class Z>
 __device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
                                                  int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
@@ -326,11 +335,9 @@ __device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
         }
     }
     top.template merge_group<G>();
-    write_selection<KMAX, G, 1, FINE>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
-        // NB chains, added in pairs: where a row has one lane, a single chain of its E terms rounds more than the lanes of
-        // finalize_rows_kernel, 16 terms each (64 experts, the first probability against float64, rms: 1.2e-7, here and there 5.7e-8)
-        constexpr int NB = SORTED || KMAX <= 8 ? 8 : 4;
-        float s[NB] = {};
+    write_selection<KMAX, G, 1, SUMS>(top, E, k, g, idx_row, probs_row, o, [&](float m) {
+        constexpr int NB = SORTED || KMAX <= 8 ? 8 : 4, CHAINS = SUMS == Sums::Chain ? 1 : NB;
+        float s[CHAINS] = {};
 #pragma unroll 1
         for (int e0 = g; e0 < E; e0 += G * NB) {
             float v[NB];
@@ -338,7 +345,7 @@ __device__ __forceinline__ void row_softmax_topk(Z&& z, int E, int k, int g,
             for (int j = 0; j < NB; ++j) v[j] = e0 + G * j < E ? z(e0 + G * j) : 0.0f;
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-                if (e0 + G * j < E && v[j] == v[j]) s[j] += __expf(v[j] - m);
+                if (e0 + G * j < E && v[j] == v[j]) s[j % CHAINS] += __expf(v[j] - m);
         }
         return sum_in_pairs(s);
     });
@@ -449,15 +456,15 @@ __device__ __forceinline__ void wave_softmax_topk_rank(float z, int E, int k, in
 
 // row_softmax_topk with the smallest list length that holds k (and the runner-up, when the margin is wanted):
 // k <= 16, and k <= 15 when the margin is wanted and k < E.
-// LEAN: the caller's registers are full (lists of 16 by insertion).  FINE: as in write_selection.
-template <int G, bool LEAN, bool FINE = false, class Z>
+// LEAN: the caller's registers are full (lists of 16 by insertion).
+template <int G, bool LEAN, Sums SUMS = Sums::Chain, class Z>
 __device__ __forceinline__ void row_softmax_topk_upto16(Z&& z, int E, int k, int g,
                                                         int32_t* idx_row, float* probs_row, const EpilogueOut& o)
 {
     const int need = k + ((o.margin_row && k < E) ? 1 : 0);
-    if (need <= 2)      row_softmax_topk<2, G, false, FINE>(z, E, k, g, idx_row, probs_row, o);
-    else if (need <= 8) row_softmax_topk<8, G, true, FINE>(z, E, k, g, idx_row, probs_row, o);
-    else                row_softmax_topk<16, G, !LEAN, FINE>(z, E, k, g, idx_row, probs_row, o);
+    if (need <= 2)      row_softmax_topk<2, G, false, SUMS>(z, E, k, g, idx_row, probs_row, o);
+    else if (need <= 8) row_softmax_topk<8, G, true, SUMS>(z, E, k, g, idx_row, probs_row, o);
+    else                row_softmax_topk<16, G, !LEAN, SUMS>(z, E, k, g, idx_row, probs_row, o);
 }
 
 }  // namespace paep

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(B_ == 64 ? 512 : 256, B_ == 32 || EBW >= 4 ? 2 : 4)
                 const float* zrow = zs + rr * ZP;
                 const EpilogueOut eo{prob_mode, margin ? margin + row : nullptr,
                                      counts ? counts + (long long)layer * E : nullptr};
-                row_softmax_topk_upto16<G, true, true>([&](int e) { return zrow[e]; }, E, k, tid % G, idx + row * k, probs + row * k, eo);
+                row_softmax_topk_upto16<G, true, Sums::Fine>([&](int e) { return zrow[e]; }, E, k, tid % G, idx + row * k, probs + row * k, eo);
             }
         } else {
             for (int rr = wave; rr < 32; rr += WAVES) {        // longer lists: one wave per row

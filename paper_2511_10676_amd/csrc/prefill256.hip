@@ -437,7 +437,7 @@ __global__ __launch_bounds__(256, 1) void prefill256_kernel(Args p)
             if (!split && tl < ROWS && t0 + r0 + tl < T) {             // the lanes of a row together
                 const long long row = (long long)layer * T + t0 + r0 + tl;
                 const EpilogueOut eo{p.prob_mode, p.margin ? p.margin + row : nullptr, p.counts ? cnt_lds : nullptr};
-                row_softmax_topk_upto16<G, false>([&](int e) { return score(tl, e); }, E, k, tid % G, p.idx + row * k,
+                row_softmax_topk_upto16<G, false, Sums::Chains>([&](int e) { return score(tl, e); }, E, k, tid % G, p.idx + row * k,
                                                   p.probs + row * k, eo);
             }
             __syncthreads();
