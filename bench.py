@@ -44,11 +44,11 @@ MALL_BYTES = 256 << 20
 # once a kernel's code changes, the figure no longer describes it and the
 # report says null.
 TRAFFIC_BYTES = {
-    ("prefill", "a48a1566240fd105"): {("deepseek_v2_lite", 4096): 3.844e+09,
+    ("prefill", "689019a7b786398c"): {("deepseek_v2_lite", 4096): 3.843e+09,
                                       ("qwen3_30b_a3b", 8192): 1.334e+10,
                                       ("phi_mini_moe", 8192): 4.906e+09},
-    ("decode", "60f217f8fd35c9ac"): {("deepseek_v2_lite", 1): 2.258e+08,
-                                     ("deepseek_v2_lite", 64): 2.587e+08},
+    ("decode", "6adb532e644729f3"): {("deepseek_v2_lite", 1): 2.258e+08,
+                                     ("deepseek_v2_lite", 64): 2.588e+08},
 }
 
 
